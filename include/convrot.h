@@ -112,9 +112,10 @@ const char *convrot_build_info(void);
  */
 int convrot_init(void);
 
-/* Host.  X rows per block tile that both GEMM kernels use for an [M, N] output: 192 (tile 192 x 192) or
- * 256 (tile 256 x 128); 0 when M or N < 0.  The result of the GEMM does not depend on it; the query
- * exists so that tests and tuning runs can tell which kernel configuration a shape exercises. */
+/* Host.  X rows of the large block tile that suits an [M, N] output: 192 (tile 192 x 192) or 256 (tile
+ * 256 x 128); 0 when M or N < 0.  Products too small to fill the device with such tiles take smaller ones.  The
+ * result of the GEMM does not depend on the tile; the query exists so that tests and tuning runs can tell which
+ * kernel configuration a large shape exercises. */
 int convrot_gemm_tile_rows(int64_t M, int64_t N);
 
 /* Host.  Bytes of a 4-bit code matrix with `rows` rows of K codes in the layout above

@@ -59,6 +59,11 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b)
     return *reinterpret_cast<uint32_t *>(&r);
 }
 
+// Eight (four) bf16 of a row of Y.  A row starts at any multiple of two bytes when N is odd; the memory path takes
+// such addresses in one store, and the compiler is told no more than that.
+typedef uint32_t u32x4_row __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x2_row __attribute__((ext_vector_type(2), aligned(2)));
+
 // Tile order: blocks are dealt round-robin to the 8 XCDs by the hardware, each XCD has its own
 // L2.  Give every XCD one contiguous range of logical tile ids, and walk that range in bands of
 // `GM` tile rows (a template parameter: 6 suits 256 x 128 tiles, 8 square ones) so that tiles that run together share X and W panels.  `bid` may run past the
@@ -79,6 +84,19 @@ __device__ __forceinline__ bool tile_of_block(int bid, int tiles_m, int tiles_n,
     tn = local / rows_in_band;
     return true;
 }
+
+// One product, as the launchers pass it on: the arguments of launch_gemm_w4a4 / launch_gemm_w8a8.
+struct Operands {
+    const void *Xq;
+    const float *x_scale;
+    const void *Wq;
+    const float *w_scale;
+    const void *bias;
+    int M, N, K;
+    void *Y;          // bf16 output, or
+    int32_t *acc;     // raw accumulators
+    hipStream_t stream;
+};
 
 }  // namespace gemm
 

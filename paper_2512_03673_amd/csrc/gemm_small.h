@@ -1,0 +1,144 @@
+// The GEMM of libconvrot for products that the tiles of gemm_tiled.h cannot fill the chip with: few tokens, narrow
+// layers.  Same operands, same exact accumulation, same dequantisation.
+//
+// Such a product is bound by latency: the tiled kernel's blocks walk K one stage at a time (0.15-0.6 us each) and only a
+// few of the 256 compute units have a block.  Here a block owns one small tile (16 XF x 16 WF) of the output and its
+// S wavefronts split K between them: wavefront w takes stages w, w + S, ... of the whole tile, straight from memory
+// into registers in the MFMA's operand shape (no LDS, no barrier, PD stages requested ahead), so that the tile's
+// operand bytes are in flight at once and the serial chain is K / S long.  The S partial tiles meet in LDS once, at the
+// end: sums of integers, exact in any order.  Measured against the 256 x 128 tile, us, 4 / 8 bits: M1 x N9216 x K3072
+// 14.1 -> 4.9 / 19.3 -> 6.3; M256 x N1024 x K1024 8.2 -> 3.6 / 9.7 -> 4.0; M32 x N3072 x K15360 71 -> 10 / 124 -> 13.
+// An operand byte is loaded once per tile that needs it and shared by nobody (18 TB/s over the chip, whatever the
+// tile), so past a few tiles per compute unit the LDS-sharing tiles of gemm_tiled.h move less and win (gemm_plan.h).
+//
+// `C` (Small4 / Small8) says what a lane holds of 16 rows x one K stage: lane l has row l % 16 and quarter l / 16 of the
+// stage, so that the lanes of a load cover whole contiguous lines; one MFMA per 16 x 16 tile and stage.
+#pragma once
+#include "gemm_common.h"
+
+namespace convrot {
+namespace gemm {
+
+constexpr int kSlabBytes = 16 * 16 + 16;     // four consecutive n of 16 rows, padded so that a row's quads lie in different banks
+
+template <class C, bool RAW, int XF, int WF, int S, int PD>
+__global__ __launch_bounds__(64 * S) void gemm_small_kernel(const uint8_t *__restrict__ Xq, const float *__restrict__ x_scale,
+                                                            const uint8_t *__restrict__ Wq, const float *__restrict__ w_scale,
+                                                            const uint16_t *__restrict__ bias, int M, int N, int K,
+                                                            uint16_t *__restrict__ Y, int32_t *__restrict__ acc_out, int tiles_m,
+                                                            int tiles_n)
+{
+    constexpr int TM = 16 * XF, TN = 16 * WF, kThreads = 64 * S;
+    constexpr int kTileBytes = 4 * kSlabBytes;                      // one 16 x 16 partial tile
+    __shared__ __attribute__((aligned(16))) uint8_t part[S * XF * WF * kTileBytes];
+
+    int tm, tn;
+    if (!tile_of_block<8>(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
+    const int m0 = tm * TM, n0 = tn * TN;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int KS = C::stages(K);
+
+    C x[XF], w[WF];
+#pragma unroll
+    for (int i = 0; i < XF; ++i) x[i].init(Xq, tm * XF + i, M, KS, lane);
+#pragma unroll
+    for (int j = 0; j < WF; ++j) w[j].init(Wq, tn * WF + j, N, KS, lane);
+
+    typename C::Acc acc[XF][WF];
+#pragma unroll
+    for (int i = 0; i < XF; ++i)
+#pragma unroll
+        for (int j = 0; j < WF; ++j) acc[i][j] = {0, 0, 0, 0};
+
+    typename C::Frag fx[PD][XF], fw[PD][WF];
+    auto fetch = [&](int b, int s) {
+#pragma unroll
+        for (int j = 0; j < WF; ++j) fw[b][j] = w[j].load(s);
+#pragma unroll
+        for (int i = 0; i < XF; ++i) fx[b][i] = x[i].load(s);
+    };
+    auto multiply = [&](int b) {
+#pragma unroll
+        for (int i = 0; i < XF; ++i)
+#pragma unroll
+            for (int j = 0; j < WF; ++j) C::mma(acc[i][j], fw[b][j], fx[b][i]);
+    };
+#pragma unroll
+    for (int p = 0; p < PD; ++p)
+        if (wave + p * S < KS) fetch(p, wave + p * S);
+    for (int s = wave; s < KS; s += PD * S) {
+#pragma unroll
+        for (int p = 0; p < PD; ++p) {
+            if (s + p * S < KS) {
+                multiply(p);
+                if (s + (p + PD) * S < KS) fetch(p, s + (p + PD) * S);
+            }
+        }
+    }
+
+    // ---- lane l, register r of a 16 x 16 tile: m = l % 16, n = 4 (l / 16) + r: a slab is four consecutive n of the 16 rows
+#pragma unroll
+    for (int i = 0; i < XF; ++i)
+#pragma unroll
+        for (int j = 0; j < WF; ++j)
+            *reinterpret_cast<typename C::Acc *>(part + ((wave * XF + i) * WF + j) * kTileBytes + (lane >> 4) * kSlabBytes + (lane & 15) * 16) = acc[i][j];
+    __syncthreads();
+    constexpr int kQuads = TM * TN / 4;
+#pragma unroll
+    for (int it = 0; it < (kQuads + kThreads - 1) / kThreads; ++it) {
+        const int u = it * kThreads + tid;
+        if (u >= kQuads) break;
+        const int ml = u / (TN / 4), q = u % (TN / 4);
+        const int m = m0 + ml, n = n0 + 4 * q;
+        if (m >= M || n >= N) continue;
+        const uint8_t *p = part + ((ml / 16) * WF + q / 4) * kTileBytes + (q % 4) * kSlabBytes + (ml % 16) * 16;
+        typename C::Acc v = *reinterpret_cast<const typename C::Acc *>(p);
+#pragma unroll
+        for (int s = 1; s < S; ++s) v += *reinterpret_cast<const typename C::Acc *>(p + s * (XF * WF * kTileBytes));
+        if constexpr (RAW) {
+            int32_t *dst = acc_out + (int64_t)m * N + n;
+            if ((N & 3) == 0) {
+                *reinterpret_cast<int4 *>(dst) = make_int4((int)v[0], (int)v[1], (int)v[2], (int)v[3]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (n + e < N) dst[e] = (int)v[e];
+            }
+        } else {
+            const float sx = x_scale[m];
+            float y[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int nn = min(n + e, N - 1);
+                const float t = (float)v[e] * sx;
+                y[e] = bias ? fmaf(t, w_scale[nn], bf16_to_f32(bias[nn])) : t * w_scale[nn];
+            }
+            const uint32_t lo = pack_bf16x2(y[0], y[1]), hi = pack_bf16x2(y[2], y[3]);
+            uint16_t *dst = Y + (int64_t)m * N + n;
+            if (n + 4 <= N) {
+                *reinterpret_cast<u32x2_row *>(dst) = u32x2_row{lo, hi};
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (n + e < N) dst[e] = (uint16_t)((e < 2 ? lo : hi) >> (16 * (e & 1)));
+            }
+        }
+    }
+}
+
+template <class C, int XF, int WF, int S, int PD>
+hipError_t launch_small(const Operands &o)
+{
+    const int tiles_m = (o.M + 16 * XF - 1) / (16 * XF), tiles_n = (o.N + 16 * WF - 1) / (16 * WF);
+    if ((int64_t)tiles_m * tiles_n > (1 << 30)) return hipErrorInvalidValue;   // the kernel counts tiles in 32 bits
+    const int ntiles = tiles_m * tiles_n, grid = (ntiles + kNumXcd - 1) / kNumXcd * kNumXcd;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * S), 0, o.stream, (const uint8_t *)o.Xq, o.x_scale, (const uint8_t *)o.Wq,
+                           o.w_scale, (const uint16_t *)o.bias, o.M, o.N, o.K, (uint16_t *)o.Y, o.acc, tiles_m, tiles_n);
+        return hipGetLastError();
+    };
+    return o.acc ? go(gemm_small_kernel<C, true, XF, WF, S, PD>) : go(gemm_small_kernel<C, false, XF, WF, S, PD>);
+}
+
+}  // namespace gemm
+}  // namespace convrot

@@ -1,0 +1,362 @@
+// The tiled GEMM kernel of libconvrot, shared by the 4-bit and the 8-bit layer (gemm_w4a4.hip, gemm_w8a8.hip).
+//
+//   acc[m,n] = sum_k q_x[m,k] q_w[n,k]        exact
+//   Y[m,n]   = bf16( float(acc) * s_x[m] * s_w[n] + bias[n] )
+//
+// `C` (Codes4 / Codes8) says what a stage of the operands looks like in memory and how a fragment is read from LDS and
+// multiplied; `T` (Tile) is the block's share of the output.
+//
+// Data movement.  A block of WGM x WGN wavefronts owns a TM x TN tile of the output.  A K stage of the tile's operand
+// rows is kPieces contiguous kilobytes in memory, copied by LDS-direct loads (dealt round-robin to the wavefronts)
+// into a ring of NS stage buffers.  A stage is two K steps; a wavefront reads the fragments of a step (32 rows each)
+// one step ahead, into the other half of a double-buffered register set, so that no MFMA waits for LDS.
+//
+// The block meets once per stage, between its two steps: by then every wavefront has read the whole of stage s into
+// registers, so the buffer can take stage s + NS, and everybody's share of stage s + 1 has landed.  With NS = 2 the
+// refill has to be issued at once, in the second step of stage s; with more stages half of it waits for the first
+// step of stage s + 1, so that the load path has work in both halves of the stage (it would otherwise idle in one and
+// hold up the MFMAs in the other: 256 x 128 tiles, eight wavefronts, M512 x N12288 x K3072, 17.2 -> 16.4 us).
+//
+// A wavefront issues in order, so every memory instruction gets an MFMA slot of its own (scheduling barriers pin the
+// order) instead of queueing up in a burst.
+//
+// The MFMA's row operand is the W tile and its column operand the X tile, so that a lane ends up with four
+// consecutive n for one m; the epilogue scales, rounds to bf16, transposes through LDS and writes 16 bytes per lane,
+// whole contiguous rows of the wavefront's tile.
+#pragma once
+#include "gemm_common.h"
+
+namespace convrot {
+namespace gemm {
+
+// WGM x WGN wavefronts of XF x WF accumulator tiles (32 x 32) each, NS stage buffers, OCC wavefronts per SIMD that the
+// registers have to leave room for, BAND tile rows per band of the XCD-aware tile order.
+template <int WGM_, int WGN_, int XF_, int WF_, int NS_, int OCC_, int BAND_>
+struct Tile {
+    static constexpr int WGM = WGM_, WGN = WGN_, XF = XF_, WF = WF_, NS = NS_, OCC = OCC_, kBandRows = BAND_;
+    static constexpr int NW = WGM * WGN, kThreads = 64 * NW;
+    static constexpr int WM = XF * 32, WN = WF * 32;          // wavefront tile
+    static constexpr int TM = WGM * WM, TN = WGN * WN, kRows = TM + TN;
+    static constexpr int NF = XF + WF;                        // fragments per wavefront and step
+    static constexpr int kMfmas = XF * WF;                    // slots of a step
+    static constexpr int kEpiPitch = WN * 2 + 16;             // bf16 row of the wavefront tile + pad
+    static constexpr int kEpiBytes = NW * 32 * kEpiPitch;
+};
+
+template <class C, class T>
+struct Stage {
+    static constexpr int kBytes = T::kRows * C::kRowBytes;    // a K stage of the tile's operand rows, X rows first
+    static constexpr int kPieces = kBytes / 1024;
+    static constexpr int kLoads = kPieces / T::NW;            // loads per wavefront and stage ...
+    static constexpr int kExtra = kPieces % T::NW;            // ... and one more for this many wavefronts
+    static constexpr int kMaxLoads = kLoads + (kExtra != 0);
+    static constexpr int kRing = T::NS * kBytes;
+    static constexpr int kScales = kRing > T::kEpiBytes ? kRing : T::kEpiBytes;     // scales and bias, past the ring
+    static constexpr int kLds = kScales + (T::TM + 2 * T::TN) * 4;
+    static_assert(kPieces * 1024 == kBytes && T::NW % 2 == 0, "stage must split into kilobytes");
+    static_assert(T::NS >= 2 && T::NS <= 4 && T::kRows % 64 == 0, "ring");
+    static_assert(kLds * (T::OCC * 4 / T::NW) <= 160 * 1024, "blocks per compute unit");
+};
+
+template <class C, bool RAW, class T>
+__global__ __launch_bounds__(T::kThreads, T::OCC) void gemm_tiled_kernel(
+    const uint8_t *__restrict__ Xq, const float *__restrict__ x_scale, const uint8_t *__restrict__ Wq,
+    const float *__restrict__ w_scale, const uint16_t *__restrict__ bias, int M, int N, int K,
+    uint16_t *__restrict__ Y, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n)
+{
+    using St = Stage<C, T>;
+    constexpr int TM = T::TM, TN = T::TN, WM = T::WM, WN = T::WN, XF = T::XF, WF = T::WF, NF = T::NF, NW = T::NW, NS = T::NS;
+    constexpr int kMfmas = T::kMfmas, kEpiPitch = T::kEpiPitch, kLoads = St::kLoads, kMaxLoads = St::kMaxLoads;
+    constexpr bool kUneven = St::kExtra != 0;
+    // Statically sized: above 64 KB a dynamic allocation would need a per-device function attribute set
+    // from the host before the first launch, i.e. hidden library state; a static one needs nothing.
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[St::kLds];
+
+    int tm, tn;
+    if (!tile_of_block<T::kBandRows>(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
+    const int m0 = tm * TM, n0 = tn * TN;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm0 = (wave % T::WGM) * WM, wn0 = (wave / T::WGM) * WN;
+    const int KS = C::stages(K);   // the last one is zero-padded
+
+    // ---- dequantisation scales of the tile's rows and columns: thread t fetches x_scale[m0 + t] and
+    // w_scale[n0 + t] now, so that the latency hides under the main loop, and parks them in LDS (past
+    // the ring) once the loop is over.
+    static_assert(TM <= T::kThreads && TN <= T::kThreads, "one scale per thread");
+    float my_sx = 0.0f, my_sw = 0.0f, my_b = 0.0f;
+    if constexpr (!RAW) {
+        if (tid < TM && m0 + tid < M) my_sx = x_scale[m0 + tid];
+        if (tid < TN && n0 + tid < N) {
+            my_sw = w_scale[n0 + tid];
+            if (bias) my_b = bf16_to_f32(bias[n0 + tid]);
+        }
+    }
+
+    // ---- global -> LDS (direct).  Load j of a stage copies the j-th kilobyte of the tile's operand rows (C::piece:
+    // where it lies in memory and in a stage buffer); wavefront w issues loads w, w + NW, ...  Rows past the
+    // operand's last block (edge tiles) re-read that block, whose results are never stored.
+    const uint8_t *src[kMaxLoads];   // stage 0 source of each of this wavefront's loads (wavefront-uniform)
+    uint32_t dst[kMaxLoads];         // its place in a stage buffer
+    const int swave = __builtin_amdgcn_readfirstlane(wave);
+#pragma unroll
+    for (int i = 0; i < kMaxLoads; ++i) {
+        const int j = kUneven ? min(swave + NW * i, St::kPieces - 1) : swave + NW * i;
+        C::template piece<TM, T::kRows>(j, Xq, Wq, m0, n0, M, N, KS, src[i], dst[i]);
+    }
+    const bool extra = kUneven && swave < St::kExtra;    // this wavefront has kMaxLoads loads
+    // LDS-direct loads are issued from inline assembly so that the compiler does not serialise every
+    // later LDS read behind them; completion is tracked by hand with vmcnt.
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds;
+    const uint32_t lane_off = C::lane_offset(lane, wave);
+    auto load_piece = [&](auto IC, int s, uint32_t buf) {   // load i of this wavefront's share of stage s
+        constexpr int i = decltype(IC)::value;
+        if constexpr (i < kMaxLoads)
+            if (i < kLoads || extra) lds_dma16(src[i], lane_off + (uint32_t)s * C::kStageStride, lds_base + buf + dst[i]);
+    };
+    auto load_stage = [&](int s, uint32_t buf) {
+#define CONVROT_L(i) load_piece(std::integral_constant<int, i>{}, s, buf);
+        CONVROT_L(0) CONVROT_L(1) CONVROT_L(2) CONVROT_L(3) CONVROT_L(4) CONVROT_L(5) CONVROT_L(6) CONVROT_L(7) CONVROT_L(8)
+#undef CONVROT_L
+        static_assert(kMaxLoads <= 9, "loads of a stage");
+    };
+    // all of this wavefront's loads but those of the `n` youngest stages have landed; its LDS reads have returned
+    auto wait_loads = [&](auto NI) {
+        constexpr int n = decltype(NI)::value;
+        if constexpr (kUneven) {
+            if (extra) wait_vmcnt_lgkm0<n * kMaxLoads>();
+            else wait_vmcnt_lgkm0<n * kLoads>();
+        } else {
+            wait_vmcnt_lgkm0<n * kLoads>();
+        }
+    };
+    auto wait_loads_upto = [&](int n) {      // the same for a count known at run time (the last stages)
+        if (NS > 3 && n >= 3) wait_loads(std::integral_constant<int, 3>{});
+        else if (NS > 2 && n == 2) wait_loads(std::integral_constant<int, 2>{});
+        else if (n == 1) wait_loads(std::integral_constant<int, 1>{});
+        else wait_loads(std::integral_constant<int, 0>{});
+    };
+
+    // ---- LDS -> registers
+    typename C::Reader reader(lane, T::kRows);
+    typename C::Op op[2][NF];   // [step parity][fragment]: 0..XF-1 X rows 32 f .., then W rows 32 (f - XF) ..
+    auto read_frag = [&](uint32_t buf, auto KSI, auto F) {
+        constexpr int ks = decltype(KSI)::value, f = decltype(F)::value;
+        if constexpr (f < NF) op[ks][f] = reader.template read<ks>(lds + buf, f < XF ? wm0 + f * 32 : TM + wn0 + (f - XF) * 32);
+    };
+
+    typename C::Acc acc[XF][WF];
+#pragma unroll
+    for (int i = 0; i < XF; ++i)
+#pragma unroll
+        for (int j = 0; j < WF; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+
+    // One step, slot by slot, in issue order.  Slot m: MFMA (i = m / WF, j = m % WF: the X fragment stays for WF MFMAs,
+    // measured 1 % faster than the W fragment staying); with REFILL this slot's share of the LDS-direct loads of
+    // stage rs into buffer rbuf; a fragment of the next step (the other step parity; stage buffer nbuf) in each of the first
+    // slots, or two if there are more fragments than slots.
+    auto slot = [&](auto MI, auto KSI, auto REFILL, uint32_t nbuf, int rs, uint32_t rbuf) {
+        constexpr int m = decltype(MI)::value, ks = decltype(KSI)::value, i = m / WF, j = m % WF;
+        if constexpr (m < kMfmas) {
+            C::mma(acc[i][j], op[ks][XF + j], op[ks][i]);
+            if constexpr (decltype(REFILL)::value) {
+                // NS = 2: everything in the second step; otherwise its second half in the first step of the next stage
+                constexpr int half = NS > 2 ? kMaxLoads / 2 : kMaxLoads;
+                constexpr int first = ks == 1 ? 0 : half, count = ks == 1 ? half : kMaxLoads - half;
+                constexpr int l0 = first + m * count / kMfmas, l1 = first + (m + 1) * count / kMfmas;
+                static_assert(l1 - l0 <= 3, "loads per slot");
+                if constexpr (l0 < l1) load_piece(std::integral_constant<int, l0>{}, rs, rbuf);
+                if constexpr (l0 + 1 < l1) load_piece(std::integral_constant<int, l0 + 1>{}, rs, rbuf);
+                if constexpr (l0 + 2 < l1) load_piece(std::integral_constant<int, l0 + 2>{}, rs, rbuf);
+            }
+            constexpr int f0 = kMfmas >= NF ? m : m * NF / kMfmas, f1 = kMfmas >= NF ? m + 1 : (m + 1) * NF / kMfmas;
+            static_assert(f1 - f0 <= 2, "fragments per slot");
+            read_frag(nbuf, std::integral_constant<int, 1 - ks>{}, std::integral_constant<int, f0>{});
+            if constexpr (f0 + 1 < f1) read_frag(nbuf, std::integral_constant<int, 1 - ks>{}, std::integral_constant<int, f0 + 1>{});
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto step = [&](auto KSI, auto REFILL, uint32_t nbuf, int rs, uint32_t rbuf) {
+        __builtin_amdgcn_sched_barrier(0);
+#define CONVROT_SLOT(m) slot(std::integral_constant<int, m>{}, KSI, REFILL, nbuf, rs, rbuf);
+        CONVROT_SLOT(0) CONVROT_SLOT(1) CONVROT_SLOT(2) CONVROT_SLOT(3) CONVROT_SLOT(4) CONVROT_SLOT(5) CONVROT_SLOT(6) CONVROT_SLOT(7)
+        CONVROT_SLOT(8)
+#undef CONVROT_SLOT
+        static_assert(kMfmas <= 9, "slots of a step");
+    };
+
+    // ---- pipeline
+    using K0 = std::integral_constant<int, 0>;
+    using K1 = std::integral_constant<int, 1>;
+    using No = std::false_type;
+    using Yes = std::true_type;
+    using Rest = std::integral_constant<bool, (NS > 2)>;      // the part of a refill that waits for the next stage's first step
+    load_stage(0, 0);
+#pragma unroll
+    for (int p = 1; p < NS; ++p)
+        if (p < KS) load_stage(p, p * St::kBytes);
+    wait_loads_upto(min(KS, NS) - 1);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+#define CONVROT_F(f) read_frag(0, K0{}, std::integral_constant<int, f>{});
+    CONVROT_F(0) CONVROT_F(1) CONVROT_F(2) CONVROT_F(3) CONVROT_F(4) CONVROT_F(5)
+#undef CONVROT_F
+    static_assert(NF <= 6, "fragments of a step");
+
+    int s = 0;
+    uint32_t buf = 0;      // stage s's buffer
+    auto stage = [&](auto REST, auto REFILL, auto WAIT) {
+        const uint32_t next = buf + St::kBytes == St::kRing ? 0 : buf + St::kBytes;
+        const uint32_t prev = buf == 0 ? St::kRing - St::kBytes : buf - St::kBytes;
+        step(K0{}, REST, buf, s - 1 + NS, prev);      // fetches the fragments of the second step
+        __builtin_amdgcn_sched_barrier(0);
+        WAIT();
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        step(K1{}, REFILL, next, s + NS, buf);        // fetches the first fragments of stage s + 1
+        buf = next;
+        ++s;
+    };
+    auto steady = [&]() { wait_loads(std::integral_constant<int, NS - 2>{}); };
+    auto drain = [&]() { wait_loads_upto(max(min(KS - 2 - s, NS - 2), 0)); };
+    if constexpr (NS == 2) {
+        while (s < KS - NS) stage(No{}, Yes{}, steady);
+    } else if (KS > NS) {
+        stage(No{}, Yes{}, steady);
+        while (s < KS - NS) stage(Rest{}, Yes{}, steady);
+        stage(Rest{}, No{}, steady);
+    }
+    while (s < KS) stage(No{}, No{}, drain);          // (what the very last step fetches is unused)
+
+    // ---- epilogue.  Lane l, register r of a 32x32 accumulator tile: m = l % 32, n = 8 (r/4) + 4 (l/32) + r % 4.
+    if constexpr (RAW) {
+        const bool vec_ok = (N & 3) == 0;
+#pragma unroll
+        for (int i = 0; i < XF; ++i) {
+            const int m = m0 + wm0 + i * 32 + (lane & 31);
+            if (m >= M) continue;
+#pragma unroll
+            for (int j = 0; j < WF; ++j) {
+#pragma unroll
+                for (int rb = 0; rb < 4; ++rb) {
+                    const int n = n0 + wn0 + j * 32 + rb * 8 + (lane >> 5) * 4;
+                    if (n >= N) continue;
+                    int32_t o[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = (int32_t)acc[i][j][rb * 4 + e];   // exact: a float holds an integer below 2^24
+                    int32_t *out = acc_out + (int64_t)m * N + n;
+                    if (vec_ok) {
+                        *reinterpret_cast<int4 *>(out) = make_int4(o[0], o[1], o[2], o[3]);
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (n + e < N) out[e] = o[e];
+                    }
+                }
+            }
+        }
+    } else {
+        float *sx_lds = reinterpret_cast<float *>(lds + St::kScales), *sw_lds = sx_lds + TM;
+        if (tid < TM) sx_lds[tid] = my_sx;
+        if (tid < TN) {
+            sw_lds[tid] = my_sw;
+            sw_lds[TN + tid] = my_b;
+        }
+        __syncthreads();     // every wavefront has finished reading the ring; the scales are visible
+        float sxm[XF];
+#pragma unroll
+        for (int i = 0; i < XF; ++i) sxm[i] = sx_lds[wm0 + i * 32 + (lane & 31)];
+        uint8_t *stage_lds = lds + wave * (32 * kEpiPitch);      // this wavefront's 32 x WN bf16 staging tile
+        // read-back: the 32 rows of WN bf16 are 32 * WN / 8 pieces of 16 bytes, dealt to the 64 lanes in order
+        // (piece p = 64 pass + lane: row p / (WN / 8), columns 8 (p % (WN / 8)) ...), so every pass has all
+        // lanes at work and stores whole rows of the wavefront tile back to back
+        constexpr int kRowPieces = WN / 8, kRbPasses = 32 * kRowPieces / 64;
+        static_assert(kRbPasses * 64 == 32 * kRowPieces, "read-back passes");
+        const int rb_row0 = lane / kRowPieces, rb_piece0 = lane % kRowPieces;   // pass 0; 64 more pieces per pass
+        // the column scales of the lane's accumulator registers, fetched once for all XF row blocks
+        float4 swv[WF][4];
+#pragma unroll
+        for (int j = 0; j < WF; ++j)
+#pragma unroll
+            for (int rb = 0; rb < 4; ++rb)
+                swv[j][rb] = *reinterpret_cast<const float4 *>(sw_lds + wn0 + j * 32 + rb * 8 + (lane >> 5) * 4);
+        auto body = [&](auto EDGE, auto BIAS) {
+#pragma unroll
+            for (int i = 0; i < XF; ++i) {
+                const int mrow = m0 + wm0 + i * 32;
+#pragma unroll
+                for (int j = 0; j < WF; ++j)
+#pragma unroll
+                    for (int rb = 0; rb < 4; ++rb) {
+                        const int col = j * 32 + rb * 8 + (lane >> 5) * 4;
+                        const float4 sw = swv[j][rb];
+                        const float t[4] = {(float)acc[i][j][rb * 4 + 0] * sxm[i], (float)acc[i][j][rb * 4 + 1] * sxm[i],
+                                            (float)acc[i][j][rb * 4 + 2] * sxm[i], (float)acc[i][j][rb * 4 + 3] * sxm[i]};
+                        float y[4];
+                        if constexpr (decltype(BIAS)::value) {   // explicitly fused, so that every tile shape rounds alike
+                            const float4 b = *reinterpret_cast<const float4 *>(sw_lds + TN + wn0 + col);
+                            y[0] = fmaf(t[0], sw.x, b.x); y[1] = fmaf(t[1], sw.y, b.y); y[2] = fmaf(t[2], sw.z, b.z); y[3] = fmaf(t[3], sw.w, b.w);
+                        } else {
+                            y[0] = t[0] * sw.x; y[1] = t[1] * sw.y; y[2] = t[2] * sw.z; y[3] = t[3] * sw.w;
+                        }
+                        *reinterpret_cast<uint2 *>(stage_lds + (lane & 31) * kEpiPitch + col * 2) =
+                            make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
+                    }
+                // the same wavefront reads back row-contiguous
+#pragma unroll
+                for (int it = 0; it < kRbPasses; ++it) {
+                    int piece = rb_piece0 + (it * 64) % kRowPieces, r = rb_row0 + (it * 64) / kRowPieces;
+                    if ((it * 64) % kRowPieces != 0 && piece >= kRowPieces) { piece -= kRowPieces; ++r; }
+                    const v4i v = *reinterpret_cast<const v4i *>(stage_lds + r * kEpiPitch + piece * 16);
+                    const int mo = mrow + r, ncol = n0 + wn0 + piece * 8;
+                    uint16_t *out = Y + (int64_t)mo * N + ncol;
+                    if constexpr (decltype(EDGE)::value == 0) {
+                        *reinterpret_cast<u32x4_row *>(out) = __builtin_bit_cast(u32x4_row, v);
+                    } else if constexpr (decltype(EDGE)::value == 1) {
+                        if (mo < M && ncol < N) *reinterpret_cast<u32x4_row *>(out) = __builtin_bit_cast(u32x4_row, v);
+                    } else {
+                        if (mo < M && ncol + 8 <= N) {
+                            *reinterpret_cast<u32x4_row *>(out) = __builtin_bit_cast(u32x4_row, v);
+                        } else if (mo < M) {
+#pragma unroll
+                            for (int e = 0; e < 8; ++e)
+                                if (ncol + e < N) out[e] = (uint16_t)((uint32_t)v[e >> 1] >> (16 * (e & 1)));
+                        }
+                    }
+                }
+            }
+        };
+        // Bounds checks only where the tile crosses the edge of Y, and element stores only where it ends inside a
+        // 16-byte piece (uniform over the block; the edge bodies add a bias of zero where there is none).
+        using Edge0 = std::integral_constant<int, 0>;
+        using Edge1 = std::integral_constant<int, 1>;
+        using Edge2 = std::integral_constant<int, 2>;
+        if (m0 + TM <= M && n0 + TN <= N) {
+            if (bias) body(Edge0{}, std::true_type{});
+            else body(Edge0{}, std::false_type{});
+        } else if ((N & 7) == 0 || n0 + TN <= N) {
+            body(Edge1{}, std::true_type{});
+        } else {
+            body(Edge2{}, std::true_type{});
+        }
+    }
+}
+
+template <class C, class T>
+hipError_t launch_tiled(const Operands &o)
+{
+    const int tiles_m = (o.M + T::TM - 1) / T::TM, tiles_n = (o.N + T::TN - 1) / T::TN;
+    if ((int64_t)tiles_m * tiles_n > (1 << 30)) return hipErrorInvalidValue;   // the kernel counts tiles in 32 bits
+    const int ntiles = tiles_m * tiles_n;
+    const int grid = ((ntiles + kNumXcd - 1) / kNumXcd) * kNumXcd;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(T::kThreads), 0, o.stream, (const uint8_t *)o.Xq, o.x_scale, (const uint8_t *)o.Wq,
+                           o.w_scale, (const uint16_t *)o.bias, o.M, o.N, o.K, (uint16_t *)o.Y, o.acc, tiles_m, tiles_n);
+        return hipGetLastError();
+    };
+    return o.acc ? go(gemm_tiled_kernel<C, true, T>) : go(gemm_tiled_kernel<C, false, T>);
+}
+
+}  // namespace gemm
+}  // namespace convrot

@@ -1,0 +1,90 @@
+"""Every tile the GEMMs are compiled with, at the sizes where each can go wrong: one row, one column, one stage of K, ragged
+edges in both directions, a K whose stages do not divide among the wavefronts that share it, the steady-state loop
+of each ring.  Which tile a shape takes is a host function (csrc/gemm_plan.h), compiled and asked here on the CPU, so
+that the list keeps naming the tiles it means to."""
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import bf16_to_host_bits, bf16_ulp_diff, bits_to_f64, check_output, codes4_to_dev, codes8_to_dev, to_dev_bf16
+from paper_2512_03673_amd import workloads as wl
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2512_03673_amd", "csrc")
+PLANS = ("192x192", "256x128", "256x128w8", "128x128", "64x64", "split32x64", "split32x32", "split16x32", "split16x16")
+
+# (M, N, K): the tile of the 4-bit layer, of the 8-bit one
+SHAPES = {
+    (1, 1, 32): ("split16x32", "split16x32"), (16, 33, 64): ("split16x32", "split16x32"), (5, 4100, 2048): ("split16x32", "split16x32"),
+    (17, 31, 4128): ("split16x16", "split16x16"), (1, 96, 65536): ("split16x16", "split16x16"),
+    (33, 4095, 96): ("split32x32", "split32x32"), (300, 520, 96): ("split32x32", "split32x32"), (40, 3000, 7264): ("split32x32", "split32x32"),
+    (1, 9216, 3072): ("split32x64", "split16x32"), (65, 4095, 1056): ("split32x64", "split32x64"),
+    (65, 4097, 160): ("64x64", "split32x64"), (191, 2050, 32): ("64x64", "64x64"), (1024, 1025, 1056): ("64x64", "64x64"),
+    (511, 4097, 96): ("64x64", "64x64"), (1023, 3070, 512): ("64x64", "128x128"), (513, 6100, 1056): ("128x128", "128x128"),
+    (513, 6100, 3072): ("128x128", "128x128"), (511, 12281, 544): ("256x128w8", "256x128"), (2300, 2300, 352): ("256x128w8", "256x128"),
+    (1537, 3070, 672): ("256x128w8", "256x128"), (4608, 3072, 128): ("256x128", "256x128"), (4601, 3068, 480): ("256x128", "256x128"),
+    (3001, 3070, 160): ("192x192", "192x192"), (2050, 4090, 1056): ("192x192", "192x192"),
+}
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not installed")
+def test_shapes_take_the_tiles_they_are_meant_for(tmp_path):
+    src = tmp_path / "plan.cpp"
+    src.write_text('#include "gemm_plan.h"\n#include <cstdio>\n#include <cstdlib>\nint main(int n, char **v) {\n'
+                   '  for (int i = 1; i + 2 < n; i += 3)\n    std::printf("%d %d\\n", (int)convrot::gemm::choose<4>(atol(v[i]), atol(v[i + 1]), '
+                   'atol(v[i + 2])), (int)convrot::gemm::choose<8>(atol(v[i]), atol(v[i + 1]), atol(v[i + 2])));\n}\n')
+    exe = str(tmp_path / "plan")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, "-o", exe, str(src)], check=True)
+    # the benchmark's layers and the extremes of the argument range stay on the large tiles
+    large = {(4608, 3072 * 4, 3072): "192x192", (4608, 9216, 3072): "192x192", (16896, 3072, 12288): "192x192", (4608, 3072, 12288): "256x128",
+             (4608, 3072, 15360): "256x128", (2 ** 31 - 1, 2 ** 31 - 1, 65536): "256x128"}
+    shapes = list(SHAPES) + list(large)
+    out = subprocess.run([exe] + [str(d) for s in shapes for d in s], check=True, capture_output=True, text=True).stdout.split()
+    got = {s: (PLANS[int(out[2 * i])], PLANS[int(out[2 * i + 1])]) for i, s in enumerate(shapes)}
+    for s, (p4, p8) in SHAPES.items():
+        assert got[s] == (p4, p8), s
+    for s, p in large.items():
+        assert got[s] == (p, p), s
+    assert {p for p, _ in SHAPES.values()} == set(PLANS) and {p for _, p in SHAPES.values()} == set(PLANS) - {"256x128w8"}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bits", (4, 8))
+@pytest.mark.parametrize("M,N,K", list(SHAPES))
+def test_every_tile_against_the_oracle(M, N, K, bits):
+    from paper_2512_03673_amd import binding as cr
+    q = 7 if bits == 4 else 127
+    rng = np.random.default_rng(M * 7 + N * 3 + K)
+    qx = rng.integers(-q, q + 1, size=(M, K)).astype(np.int8)
+    qw = rng.integers(-q, q + 1, size=(N, K)).astype(np.int8)
+    qx[0, :] = q
+    qw[0, :] = -q             # reaches the accumulator bound
+    to_dev, raw, dequant = ((codes4_to_dev, cr.convrot_w4a4_gemm_i32, cr.convrot_w4a4_gemm_dequant) if bits == 4 else
+                            (codes8_to_dev, cr.convrot_w8a8_gemm_i32, cr.convrot_w8a8_gemm_dequant))
+    xq, wq = to_dev(qx), to_dev(qw)
+    ref = oracle.int_gemm(qx, qw)
+    # one row more than the result has, to see that nothing is written past it
+    acc = torch.full((M + 1, N), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    raw(xq, wq, M, N, K, acc=acc)
+    torch.cuda.synchronize()
+    assert np.array_equal(acc[:M].cpu().numpy(), ref) and (acc[M] == 0x5A5A5A5A).all()
+    sx = np.exp(rng.uniform(-6, 2, M)).astype(np.float32)
+    sw = np.exp(rng.uniform(-9, -4, N)).astype(np.float32)
+    bias = wl.f32_to_bf16_bits((rng.standard_normal(N) * 0.5).astype(np.float32))
+    for b in (None, bias):
+        y = torch.full((M + 1, N), 3.0, dtype=torch.bfloat16, device="cuda")
+        dequant(xq, torch.from_numpy(sx).cuda(), wq, torch.from_numpy(sw).cuda(), K, Y=y, bias=None if b is None else to_dev_bf16(b))
+        torch.cuda.synchronize()
+        assert (y[M] == 3.0).all()
+        yb, yo = bf16_to_host_bits(y[:M]), oracle.dequant(ref, sx, sw, b)
+        if b is None:         # fp32 (acc*sx)*sw then one rounding vs the double product: at most one bf16 step
+            d = bf16_ulp_diff(yb, yo)
+            assert d.max() <= 1 and (d == 0).mean() >= 0.999
+        else:                 # ... relative to the larger of the output and the bias where the two cancel
+            mag = np.maximum(np.abs(bits_to_f64(yo)), np.abs(bits_to_f64(b))[None, :])
+            assert (np.abs(bits_to_f64(yb) - bits_to_f64(yo)) <= mag * 2.0 ** -7).all()
+        check_output(yb, yo, f"{bits} bits")
