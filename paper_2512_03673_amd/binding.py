@@ -1,8 +1,12 @@
-"""ctypes binding of libconvrot: same names as the C ABI, argument marshalling only.
+"""Binding of libconvrot: same names as the C ABI, argument marshalling only.
 
 Tensors are torch tensors on the GPU (torch is used for device memory and streams, nothing
 else); every step of the path runs inside the library's kernels.  There is no fallback: if the
 shared library has not been built, loading raises.
+
+The calls that a model makes for every layer go through a small extension module (csrc/torch_calls.cpp), because
+taking tensors apart in Python and passing twelve arguments through ctypes takes longer than a small layer's
+kernels run; everything else is ctypes.
 """
 from __future__ import annotations
 
@@ -29,6 +33,7 @@ EXPORTS = ("convrot_status_string", "convrot_version", "convrot_packed_bytes", "
 NOALLOC_WORKSPACE_BYTES = 64 << 20
 
 _lib = None
+_calls = None
 
 
 class ConvRotError(RuntimeError):
@@ -87,6 +92,26 @@ def load() -> ctypes.CDLL:
     return lib
 
 
+def _load_calls():
+    """The extension module with the per-layer calls, built together with the library."""
+    global _calls
+    load()
+    try:
+        from . import _torch_calls
+    except ImportError as e:
+        raise ImportError("the extension module _torch_calls is not built (or built for another torch); "
+                          "run `python -m paper_2512_03673_amd.build`") from e
+    _calls = _torch_calls
+    return _calls
+
+
+def _done(result, what: str):
+    """The result of a call of the extension module: an output, or an error status to raise."""
+    if result.__class__ is int:
+        raise ConvRotError(result, what)
+    return result
+
+
 def status_string(status: int) -> str:
     return load().convrot_status_string(int(status)).decode()
 
@@ -143,13 +168,6 @@ def _dev(t: torch.Tensor, dtype: torch.dtype, name: str) -> None:
         raise TypeError(f"{name}: need a contiguous {dtype} tensor on the GPU")
 
 
-def _bias(b: Optional[torch.Tensor], N: int) -> None:
-    if b is not None:
-        _dev(b, torch.bfloat16, "bias")
-        if b.shape != (N,):
-            raise ValueError("bias: need shape [N]")
-
-
 def _codes(t: torch.Tensor, nbytes: int, name: str) -> None:
     """A code matrix is an opaque uint8 buffer in the library's panel layout."""
     _dev(t, torch.uint8, name)
@@ -157,34 +175,16 @@ def _codes(t: torch.Tensor, nbytes: int, name: str) -> None:
         raise ValueError(f"{name}: need {nbytes} bytes (convrot_packed_bytes), got {t.numel()}")
 
 
-def _new_codes(nbytes: int, device) -> torch.Tensor:
-    return torch.empty((nbytes,), dtype=torch.uint8, device=device)
-
-
 def convrot_prepare_weight(W: torch.Tensor, group: int, Wq: Optional[torch.Tensor] = None,
                            w_scale: Optional[torch.Tensor] = None, stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
     """W bf16 [N, K] -> (Wq uint8 [packed_bytes(N, K)], w_scale f32 [N])."""
-    _dev(W, torch.bfloat16, "W")
-    N, K = W.shape
-    Wq = _new_codes(packed_bytes(N, K), W.device) if Wq is None else Wq
-    _codes(Wq, packed_bytes(N, K), "Wq")
-    w_scale = torch.empty((N,), dtype=torch.float32, device=W.device) if w_scale is None else w_scale
-    _check(load().convrot_prepare_weight(_ptr(W), N, K, group, _ptr(Wq), _ptr(w_scale), _stream(stream)),
-           "convrot_prepare_weight")
-    return Wq, w_scale
+    return _done((_calls or _load_calls()).rotquant4(W, group, Wq, w_scale, stream, "W", "Wq"), "convrot_prepare_weight")
 
 
 def convrot_rotquant_act(X: torch.Tensor, group: int, Xq: Optional[torch.Tensor] = None,
                          x_scale: Optional[torch.Tensor] = None, stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
     """X bf16 [M, K] -> (Xq uint8 [packed_bytes(M, K)], x_scale f32 [M])."""
-    _dev(X, torch.bfloat16, "X")
-    M, K = X.shape
-    Xq = _new_codes(packed_bytes(M, K), X.device) if Xq is None else Xq
-    _codes(Xq, packed_bytes(M, K), "Xq")
-    x_scale = torch.empty((M,), dtype=torch.float32, device=X.device) if x_scale is None else x_scale
-    _check(load().convrot_rotquant_act(_ptr(X), M, K, group, _ptr(Xq), _ptr(x_scale), _stream(stream)),
-           "convrot_rotquant_act")
-    return Xq, x_scale
+    return _done((_calls or _load_calls()).rotquant4(X, group, Xq, x_scale, stream, "X", "Xq"), "convrot_rotquant_act")
 
 
 def convrot_unpack_codes(Xq: torch.Tensor, rows: int, K: int, codes: Optional[torch.Tensor] = None,
@@ -200,14 +200,7 @@ def convrot_w4a4_gemm_dequant(Xq: torch.Tensor, x_scale: torch.Tensor, Wq: torch
                               K: int, Y: Optional[torch.Tensor] = None, bias: Optional[torch.Tensor] = None,
                               stream=None) -> torch.Tensor:
     """Code matrices + scales f32 [M], [N] (+ bias bf16 [N]) -> Y bf16 [M, N]."""
-    _dev(x_scale, torch.float32, "x_scale"); _dev(w_scale, torch.float32, "w_scale")
-    M, N = x_scale.shape[0], w_scale.shape[0]
-    _codes(Xq, packed_bytes(M, K), "Xq"); _codes(Wq, packed_bytes(N, K), "Wq")
-    Y = torch.empty((M, N), dtype=torch.bfloat16, device=Xq.device) if Y is None else Y
-    _bias(bias, N)
-    _check(load().convrot_w4a4_gemm_dequant(_ptr(Xq), _ptr(x_scale), _ptr(Wq), _ptr(w_scale), _ptr(bias), M, N,
-                                            K, _ptr(Y), _stream(stream)), "convrot_w4a4_gemm_dequant")
-    return Y
+    return _done((_calls or _load_calls()).gemm_dequant4(Xq, x_scale, Wq, w_scale, K, Y, bias, stream), "convrot_w4a4_gemm_dequant")
 
 
 def convrot_w4a4_gemm_i32(Xq: torch.Tensor, Wq: torch.Tensor, M: int, N: int, K: int,
@@ -224,33 +217,13 @@ def convlinear4bit_forward(X: torch.Tensor, Wq: torch.Tensor, w_scale: torch.Ten
                            Y: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,
                            bias: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """X bf16 [M, K], prepared weight -> Y bf16 [M, N]; `workspace` is a uint8 tensor of workspace_bytes(M, K)."""
-    _dev(X, torch.bfloat16, "X"); _dev(w_scale, torch.float32, "w_scale")
-    M, K = X.shape
-    N = w_scale.shape[0]
-    _codes(Wq, packed_bytes(N, K), "Wq")
-    Y = torch.empty((M, N), dtype=torch.bfloat16, device=X.device) if Y is None else Y
-    if workspace is None:
-        workspace = torch.empty((max(workspace_bytes(M, K), 256),), dtype=torch.uint8, device=X.device)
-    _bias(bias, N)
-    _check(load().convlinear4bit_forward(_ptr(X), _ptr(Wq), _ptr(w_scale), _ptr(bias), M, N, K, group, _ptr(Y),
-                                         _ptr(workspace), workspace.numel(), _stream(stream)),
-           "convlinear4bit_forward")
-    return Y
+    return _done((_calls or _load_calls()).forward4(X, Wq, w_scale, group, Y, workspace, bias, stream), "convlinear4bit_forward")
 
 
 def convlinear4bit_forward_noalloc(X: torch.Tensor, Wq: torch.Tensor, w_scale: torch.Tensor, group: int,
                                    Y: torch.Tensor, bias: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """As convlinear4bit_forward, the activation codes in the library's static device array; `Y` is the caller's."""
-    _dev(X, torch.bfloat16, "X"); _dev(w_scale, torch.float32, "w_scale"); _dev(Y, torch.bfloat16, "Y")
-    M, K = X.shape
-    N = w_scale.shape[0]
-    if Y.shape != (M, N):
-        raise ValueError("Y: need shape [M, N]")
-    _codes(Wq, packed_bytes(N, K), "Wq")
-    _bias(bias, N)
-    _check(load().convlinear4bit_forward_noalloc(_ptr(X), _ptr(Wq), _ptr(w_scale), _ptr(bias), M, N, K, group,
-                                                 _ptr(Y), _stream(stream)), "convlinear4bit_forward_noalloc")
-    return Y
+    return _done((_calls or _load_calls()).forward4_noalloc(X, Wq, w_scale, group, Y, bias, stream), "convlinear4bit_forward_noalloc")
 
 
 ROT_NONE, ROT_REGULAR, ROT_SYLVESTER = 0, 1, 2
@@ -268,40 +241,23 @@ def convrot_rotated_absmax(X: torch.Tensor, group: int, kind: int, out: Optional
 
 
 # ---------------------------------------------------------------------------- W8A8 variant
-def _rotquant8(fn_name: str, X: torch.Tensor, group: int, Xq, x_scale, stream):
-    _dev(X, torch.bfloat16, "input")
-    rows, K = X.shape
-    Xq = _new_codes(packed_bytes8(rows, K), X.device) if Xq is None else Xq
-    _codes(Xq, packed_bytes8(rows, K), "codes")
-    x_scale = torch.empty((rows,), dtype=torch.float32, device=X.device) if x_scale is None else x_scale
-    _check(getattr(load(), fn_name)(_ptr(X), rows, K, group, _ptr(Xq), _ptr(x_scale), _stream(stream)), fn_name)
-    return Xq, x_scale
-
-
 def convrot_prepare_weight8(W: torch.Tensor, group: int, Wq: Optional[torch.Tensor] = None,
                             w_scale: Optional[torch.Tensor] = None, stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
     """W bf16 [N, K] -> (Wq uint8 [packed_bytes8(N, K)], w_scale f32 [N])."""
-    return _rotquant8("convrot_prepare_weight8", W, group, Wq, w_scale, stream)
+    return _done((_calls or _load_calls()).rotquant8(W, group, Wq, w_scale, stream, "W", "Wq"), "convrot_prepare_weight8")
 
 
 def convrot_rotquant_act8(X: torch.Tensor, group: int, Xq: Optional[torch.Tensor] = None,
                           x_scale: Optional[torch.Tensor] = None, stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
     """X bf16 [M, K] -> (Xq uint8 [packed_bytes8(M, K)], x_scale f32 [M])."""
-    return _rotquant8("convrot_rotquant_act8", X, group, Xq, x_scale, stream)
+    return _done((_calls or _load_calls()).rotquant8(X, group, Xq, x_scale, stream, "X", "Xq"), "convrot_rotquant_act8")
 
 
 def convrot_w8a8_gemm_dequant(Xq: torch.Tensor, x_scale: torch.Tensor, Wq: torch.Tensor, w_scale: torch.Tensor,
                               K: int, Y: Optional[torch.Tensor] = None, bias: Optional[torch.Tensor] = None,
                               stream=None) -> torch.Tensor:
     """8-bit code matrices + scales f32 [M], [N] (+ bias bf16 [N]) -> Y bf16 [M, N]."""
-    _dev(x_scale, torch.float32, "x_scale"); _dev(w_scale, torch.float32, "w_scale")
-    M, N = x_scale.shape[0], w_scale.shape[0]
-    _codes(Xq, packed_bytes8(M, K), "Xq"); _codes(Wq, packed_bytes8(N, K), "Wq")
-    Y = torch.empty((M, N), dtype=torch.bfloat16, device=Xq.device) if Y is None else Y
-    _bias(bias, N)
-    _check(load().convrot_w8a8_gemm_dequant(_ptr(Xq), _ptr(x_scale), _ptr(Wq), _ptr(w_scale), _ptr(bias), M, N, K,
-                                            _ptr(Y), _stream(stream)), "convrot_w8a8_gemm_dequant")
-    return Y
+    return _done((_calls or _load_calls()).gemm_dequant8(Xq, x_scale, Wq, w_scale, K, Y, bias, stream), "convrot_w8a8_gemm_dequant")
 
 
 def convrot_w8a8_gemm_i32(Xq: torch.Tensor, Wq: torch.Tensor, M: int, N: int, K: int,
@@ -318,15 +274,4 @@ def convlinear8bit_forward(X: torch.Tensor, Wq: torch.Tensor, w_scale: torch.Ten
                            Y: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,
                            bias: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """X bf16 [M, K], prepared 8-bit weight -> Y bf16 [M, N]; `workspace`: uint8 tensor of workspace_bytes8(M, K)."""
-    _dev(X, torch.bfloat16, "X"); _dev(w_scale, torch.float32, "w_scale")
-    M, K = X.shape
-    N = w_scale.shape[0]
-    _codes(Wq, packed_bytes8(N, K), "Wq")
-    Y = torch.empty((M, N), dtype=torch.bfloat16, device=X.device) if Y is None else Y
-    if workspace is None:
-        workspace = torch.empty((max(workspace_bytes8(M, K), 256),), dtype=torch.uint8, device=X.device)
-    _bias(bias, N)
-    _check(load().convlinear8bit_forward(_ptr(X), _ptr(Wq), _ptr(w_scale), _ptr(bias), M, N, K, group, _ptr(Y),
-                                         _ptr(workspace), workspace.numel(), _stream(stream)),
-           "convlinear8bit_forward")
-    return Y
+    return _done((_calls or _load_calls()).forward8(X, Wq, w_scale, group, Y, workspace, bias, stream), "convlinear8bit_forward")

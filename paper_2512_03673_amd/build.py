@@ -1,15 +1,17 @@
-"""Build libconvrot.so in-tree with hipcc for gfx950.  Run as ``python -m paper_2512_03673_amd.build``."""
+"""Build libconvrot.so and the extension module _torch_calls.so in-tree with hipcc for gfx950.  Run as ``python -m paper_2512_03673_amd.build``."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libconvrot.so")
+CALLS = os.path.join(HERE, "_torch_calls.so")
 SOURCES = ("convrot_api.hip", "rotquant.hip", "gemm_w4a4.hip", "gemm_w8a8.hip")
 
 FLAGS = [
@@ -39,6 +41,26 @@ def build(verbose: bool = True, extra_flags=(), out: str = LIB) -> str:
         objs = list(ex.map(compile_one, SOURCES))
     tmp = out + f".tmp{os.getpid()}"
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, out)
+    if out == LIB:
+        build_calls(verbose)
+    return out
+
+
+def build_calls(verbose: bool = True, out: str = CALLS) -> str:
+    """Compile the extension module (host code only; it calls the library next to it through the C ABI)."""
+    import torch    # headers and libraries; neither torch nor a GPU is used
+    root = os.path.dirname(torch.__file__)
+    lib = os.path.join(root, "lib")
+    tmp = out + f".tmp{os.getpid()}"
+    cmd = ["hipcc", "--offload-arch=gfx950", "--offload-host-only", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", os.path.join(ROOT, "include"),
+           "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_path("include"), "-o", tmp, os.path.join(CSRC, "torch_calls.cpp"), "-L", lib, "-ltorch_python",
+           "-ltorch_cpu", "-lc10", "-lc10_hip", "-L", HERE, "-lconvrot", "-Wl,-rpath,$ORIGIN"]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)

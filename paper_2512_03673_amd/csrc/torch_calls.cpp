@@ -1,0 +1,264 @@
+// The calls a model makes for every layer, as a CPython extension: torch tensors in, one C ABI call, torch tensor out.
+// binding.py holds the public functions (names, defaults, documentation) and hands their arguments on in order.
+//
+// A small layer's kernels take less time than the interpreter needs to take five tensors apart: through ctypes one
+// forward cost 14 us of host time, of which the two launches are 7 (MI355X host, M1 x N256 x K3072); here tensors are
+// read as the C++ objects they are.
+#include <Python.h>
+
+#include <ATen/ops/empty.h>
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include "convrot.h"
+
+namespace {
+
+struct Failed {};   // a Python error is set
+
+[[noreturn]] void fail(PyObject *type, const char *format, const char *a, long long b = 0, long long c = 0)
+{
+    PyErr_Format(type, format, a, b, c);
+    throw Failed{};
+}
+
+const at::Tensor &tensor(PyObject *o, const char *name)
+{
+    if (!THPVariable_Check(o)) fail(PyExc_TypeError, "%s: need a torch tensor", name);
+    return THPVariable_Unpack(o);
+}
+
+const at::Tensor &device_tensor(PyObject *o, at::ScalarType type, const char *type_name, const char *name)
+{
+    const at::Tensor &t = tensor(o, name);
+    if (!(t.is_cuda() && t.scalar_type() == type && t.is_contiguous())) {
+        PyErr_Format(PyExc_TypeError, "%s: need a contiguous %s tensor on the GPU", name, type_name);
+        throw Failed{};
+    }
+    return t;
+}
+
+const at::Tensor &bf16(PyObject *o, const char *name) { return device_tensor(o, at::kBFloat16, "torch.bfloat16", name); }
+const at::Tensor &f32(PyObject *o, const char *name) { return device_tensor(o, at::kFloat, "torch.float32", name); }
+
+// A code matrix: an opaque uint8 buffer of at least `bytes` bytes.
+const at::Tensor &codes(PyObject *o, size_t bytes, const char *name)
+{
+    const at::Tensor &t = device_tensor(o, at::kByte, "torch.uint8", name);
+    if ((size_t)t.numel() < bytes)
+        fail(PyExc_ValueError, "%s: need %lld bytes (convrot_packed_bytes), got %lld", name, (long long)bytes, (long long)t.numel());
+    return t;
+}
+
+const void *bias_of(PyObject *o, int64_t N)
+{
+    if (o == Py_None) return nullptr;
+    const at::Tensor &b = bf16(o, "bias");
+    if (b.dim() != 1 || b.size(0) != N) fail(PyExc_ValueError, "%s: need shape [N]", "bias");
+    return b.data_ptr();
+}
+
+void matrix(const at::Tensor &t, const char *name, int64_t &rows, int64_t &cols)
+{
+    if (t.dim() != 2) fail(PyExc_ValueError, "%s: need a matrix, got %lld dimensions", name, (long long)t.dim());
+    rows = t.size(0);
+    cols = t.size(1);
+}
+
+int64_t length(const at::Tensor &t, const char *name)
+{
+    if (t.dim() < 1) fail(PyExc_ValueError, "%s: need a vector, got %lld dimensions", name, (long long)t.dim());
+    return t.size(0);
+}
+
+long long integer(PyObject *o)
+{
+    const long long v = PyLong_AsLongLong(o);
+    if (v == -1 && PyErr_Occurred()) throw Failed{};
+    return v;
+}
+
+void *stream_of(PyObject *o)
+{
+    if (o == Py_None) return c10::hip::getCurrentHIPStream().stream();
+    PyObject *s = PyObject_GetAttrString(o, "cuda_stream");
+    if (!s) throw Failed{};
+    void *p = PyLong_AsVoidPtr(s);
+    Py_DECREF(s);
+    if (!p && PyErr_Occurred()) throw Failed{};
+    return p;
+}
+
+at::Tensor new_on(const at::Tensor &like, at::IntArrayRef shape, at::ScalarType type)
+{
+    return at::empty(shape, at::TensorOptions().dtype(type).device(like.device()));
+}
+
+// An output: the caller's tensor, or a new one.
+struct Out {
+    PyObject *given;
+    at::Tensor made;
+    void *ptr;
+    Out(PyObject *o, const char *name) : given(o), ptr(o == Py_None ? nullptr : tensor(o, name).data_ptr()) {}
+    void make(const at::Tensor &like, at::IntArrayRef shape, at::ScalarType type)
+    {
+        made = new_on(like, shape, type);
+        ptr = made.data_ptr();
+    }
+    PyObject *release()
+    {
+        if (given != Py_None) {
+            Py_INCREF(given);
+            return given;
+        }
+        return THPVariable_Wrap(std::move(made));
+    }
+};
+
+// Runs the call without the interpreter lock; an error status goes back as an int for binding.py to raise.
+template <class F>
+int call(F f)
+{
+    int status;
+    Py_BEGIN_ALLOW_THREADS
+    status = f();
+    Py_END_ALLOW_THREADS
+    return status;
+}
+
+template <class F>
+PyObject *guarded(Py_ssize_t n, Py_ssize_t expected, F f)
+{
+    if (n != expected) {
+        PyErr_Format(PyExc_TypeError, "need %zd arguments, got %zd", expected, n);
+        return nullptr;
+    }
+    try {
+        return f();
+    } catch (const Failed &) {
+    } catch (const std::exception &e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what());
+    }
+    return nullptr;
+}
+
+// (X, Wq, w_scale, group, Y, workspace, bias, stream) -> Y
+template <int BITS>
+PyObject *forward(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    return guarded(n, 8, [&]() -> PyObject * {
+        const at::Tensor &X = bf16(a[0], "X"), &ws = f32(a[2], "w_scale");
+        int64_t M, K;
+        matrix(X, "X", M, K);
+        const int64_t N = length(ws, "w_scale");
+        const at::Tensor &Wq = codes(a[1], BITS == 4 ? convrot_packed_bytes(N, K) : convrot_packed_bytes8(N, K), "Wq");
+        Out Y(a[4], "Y");
+        if (a[4] == Py_None) Y.make(X, {M, N}, at::kBFloat16);
+        at::Tensor own;
+        const at::Tensor *workspace = &own;
+        if (a[5] == Py_None) {
+            const int64_t bytes = BITS == 4 ? convrot_workspace_bytes(M, K) : convrot_workspace_bytes8(M, K);
+            own = new_on(X, {std::max<int64_t>(bytes, 256)}, at::kByte);
+        } else {
+            workspace = &tensor(a[5], "workspace");
+        }
+        const void *bias = bias_of(a[6], N), *x = X.data_ptr(), *w = Wq.data_ptr();
+        const float *s = (const float *)ws.data_ptr();
+        const int group = (int)integer(a[3]);
+        void *stream = stream_of(a[7]), *wp = workspace->data_ptr();
+        const size_t wn = workspace->numel();
+        const int status = call([&] {
+            return BITS == 4 ? convlinear4bit_forward(x, w, s, bias, M, N, K, group, Y.ptr, wp, wn, stream)
+                             : convlinear8bit_forward(x, w, s, bias, M, N, K, group, Y.ptr, wp, wn, stream);
+        });
+        return status ? PyLong_FromLong(status) : Y.release();
+    });
+}
+
+// (X, Wq, w_scale, group, Y, bias, stream) -> Y
+PyObject *forward_noalloc(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    return guarded(n, 7, [&]() -> PyObject * {
+        const at::Tensor &X = bf16(a[0], "X"), &ws = f32(a[2], "w_scale"), &Y = bf16(a[4], "Y");
+        int64_t M, K;
+        matrix(X, "X", M, K);
+        const int64_t N = length(ws, "w_scale");
+        if (Y.dim() != 2 || Y.size(0) != M || Y.size(1) != N) fail(PyExc_ValueError, "%s: need shape [M, N]", "Y");
+        const at::Tensor &Wq = codes(a[1], convrot_packed_bytes(N, K), "Wq");
+        const void *bias = bias_of(a[5], N), *x = X.data_ptr(), *w = Wq.data_ptr();
+        const float *s = (const float *)ws.data_ptr();
+        void *y = Y.data_ptr(), *stream = stream_of(a[6]);
+        const int group = (int)integer(a[3]);
+        const int status = call([&] { return convlinear4bit_forward_noalloc(x, w, s, bias, M, N, K, group, y, stream); });
+        if (status) return PyLong_FromLong(status);
+        Py_INCREF(a[4]);
+        return a[4];
+    });
+}
+
+// (Xq, x_scale, Wq, w_scale, K, Y, bias, stream) -> Y
+template <int BITS>
+PyObject *gemm_dequant(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    return guarded(n, 8, [&]() -> PyObject * {
+        const at::Tensor &xs = f32(a[1], "x_scale"), &ws = f32(a[3], "w_scale");
+        const int64_t M = length(xs, "x_scale"), N = length(ws, "w_scale"), K = integer(a[4]);
+        auto bytes = BITS == 4 ? convrot_packed_bytes : convrot_packed_bytes8;
+        const at::Tensor &Xq = codes(a[0], bytes(M, K), "Xq"), &Wq = codes(a[2], bytes(N, K), "Wq");
+        Out Y(a[5], "Y");
+        if (a[5] == Py_None) Y.make(Xq, {M, N}, at::kBFloat16);
+        const void *bias = bias_of(a[6], N), *x = Xq.data_ptr(), *w = Wq.data_ptr();
+        const float *sx = (const float *)xs.data_ptr(), *sw = (const float *)ws.data_ptr();
+        void *stream = stream_of(a[7]);
+        const int status = call([&] {
+            return (BITS == 4 ? convrot_w4a4_gemm_dequant : convrot_w8a8_gemm_dequant)(x, sx, w, sw, bias, M, N, K, Y.ptr, stream);
+        });
+        return status ? PyLong_FromLong(status) : Y.release();
+    });
+}
+
+// (X, group, Xq, x_scale, stream, name of X, name of Xq) -> (Xq, x_scale).  Activations and weights run through the same kernel.
+template <int BITS>
+PyObject *rotquant(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    return guarded(n, 7, [&]() -> PyObject * {
+        const char *in_name = PyUnicode_AsUTF8(a[5]), *out_name = PyUnicode_AsUTF8(a[6]);
+        if (!in_name || !out_name) throw Failed{};
+        const at::Tensor &X = bf16(a[0], in_name);
+        int64_t rows, K;
+        matrix(X, in_name, rows, K);
+        const size_t bytes = BITS == 4 ? convrot_packed_bytes(rows, K) : convrot_packed_bytes8(rows, K);
+        Out Xq(a[2], out_name), scale(a[3], "scale");
+        if (a[2] == Py_None) Xq.make(X, {(int64_t)bytes}, at::kByte);
+        else codes(a[2], bytes, out_name);
+        if (a[3] == Py_None) scale.make(X, {rows}, at::kFloat);
+        const void *x = X.data_ptr();
+        const int group = (int)integer(a[1]);
+        void *stream = stream_of(a[4]);
+        const int status = call([&] {
+            return (BITS == 4 ? convrot_rotquant_act : convrot_rotquant_act8)(x, rows, K, group, Xq.ptr, (float *)scale.ptr, stream);
+        });
+        if (status) return PyLong_FromLong(status);
+        PyObject *q = Xq.release(), *s = scale.release(), *pair = PyTuple_Pack(2, q, s);
+        Py_XDECREF(q);
+        Py_XDECREF(s);
+        return pair;
+    });
+}
+
+PyMethodDef methods[] = {
+    {"forward4", (PyCFunction)(void (*)(void))forward<4>, METH_FASTCALL, nullptr},
+    {"forward8", (PyCFunction)(void (*)(void))forward<8>, METH_FASTCALL, nullptr},
+    {"forward4_noalloc", (PyCFunction)(void (*)(void))forward_noalloc, METH_FASTCALL, nullptr},
+    {"gemm_dequant4", (PyCFunction)(void (*)(void))gemm_dequant<4>, METH_FASTCALL, nullptr},
+    {"gemm_dequant8", (PyCFunction)(void (*)(void))gemm_dequant<8>, METH_FASTCALL, nullptr},
+    {"rotquant4", (PyCFunction)(void (*)(void))rotquant<4>, METH_FASTCALL, nullptr},
+    {"rotquant8", (PyCFunction)(void (*)(void))rotquant<8>, METH_FASTCALL, nullptr},
+    {nullptr, nullptr, 0, nullptr},
+};
+
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_torch_calls", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__torch_calls() { return PyModule_Create(&module); }
