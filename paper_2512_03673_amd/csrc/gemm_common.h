@@ -64,6 +64,16 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b)
 typedef uint32_t u32x4_row __attribute__((ext_vector_type(4), aligned(2)));
 typedef uint32_t u32x2_row __attribute__((ext_vector_type(2), aligned(2)));
 
+// The same, written through the L2.  Blocks that have a compute unit to themselves end their tiles together: 128 KB of Y from
+// each of an XCD's 32 units, as much as its L2 holds.  Written through, the lines are on their way to memory at once instead of
+// when the next tiles' lines push them out (256 x 256 tiles: M4608 x N12288 x K3072 90.1 -> 86.2 us, N3072 24.0 -> 23.4; two blocks
+// a unit: no difference).  The wait state is the one that a store of more than 64 bits needs before its data registers
+// are written again, which the compiler cannot see here.
+__device__ __forceinline__ void store_through(uint16_t *out, const v4i &v)
+{
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" :: "v"(out), "v"(v) : "memory");
+}
+
 // Tile order: blocks are dealt round-robin to the 8 XCDs by the hardware, each XCD has its own
 // L2.  Give every XCD one contiguous range of logical tile ids, and walk that range in bands of
 // `GM` tile rows (a template parameter: 6 suits 256 x 128 tiles, 8 square ones) so that tiles that run together share X and W panels.  `bid` may run past the

@@ -1,14 +1,18 @@
 // Which GEMM kernel a product takes.
 //
-// A launch's time is predicted for every compiled tile as
+// A launch's time is predicted for every compiled tile and the smallest prediction is taken.  b = tiles of the busiest
+// compute unit = ceil(tiles / 256), K' = stages of K; us:
 //
-//   fixed + block b + max(latency c, rate K' b)        us, b = tiles of the busiest compute unit = ceil(tiles / 256),
-//                                                      K' = stages of K, c = the stages one wavefront walks
+//   small tiles, many to a compute unit   fixed + block b + max(latency c, rate K' b), c = the stages one wavefront walks
+//   tiles that share a unit two by two    fixed + block b + K' (pair floor(b / 2) + lone (b mod 2))
+//   tiles that have a unit to themselves  fixed + b (block + rate K' (idle + (1 - idle) fill)), fill = share of the b rounds'
+//                                         places that have a tile: the chip is limited by power, and a unit that has
+//                                         no tile leaves its share to the others
 //
-// (`block`: prologue and epilogue of a tile; `latency`: a stage when its tile has the compute unit to itself; `rate`: a stage's
-// share of a full compute unit) and the smallest prediction is taken.  The four constants of a tile are a robust fit
-// to 320 launches on shapes drawn over M 1 ... 8000, N 32 ... 12288, K 64 ... 15360; on other shapes the tile taken
-// costs 2 % more on average than the best of them would.
+// (`block`: prologue and epilogue of a tile; `latency`, `lone`: a stage of a tile that has the unit to itself; `rate`, `pair`: a
+// stage of a full unit.)  The constants are robust fits: of the first kind to 320 launches on shapes drawn over M 1 ... 8000,
+// N 32 ... 12288, K 64 ... 15360, of the other two to 230 over M 256 ... 16896, N 512 ... 12288, K 256 ... 15360 with at least
+// 1.2e10 products.  On the larger shapes the tile taken costs 0.5 % more on average than the best of them would, on the others 2 %.
 #pragma once
 #include <stdint.h>
 
@@ -25,18 +29,29 @@ enum class Plan {
     kSplit32x32,
     kSplit16x32,
     kSplit16x16,
+    kTile256x256,     // gemm_tiled.h: eight wavefronts, one block per compute unit
     kCount
 };
 
-struct Cost {
+struct Small {
     Plan plan;
     int tm, tn;
     int split;      // wavefronts that share the stages of K, or 1
     float fixed, block, latency, rate;
 };
 
-// The two large tiles.  Blocks are dealt to the 256 compute units as slots free up, so a launch lasts about as
-// long as the busiest unit's share, ceil(tiles / 256) blocks of TM x TN products each; the square tile
+struct Paired {
+    Plan plan;
+    int tm, tn;
+    float fixed, block, pair, lone;
+};
+
+struct Alone {
+    float fixed, block, rate, idle;
+};
+
+// The two large tiles of which two share a compute unit.  Blocks are dealt to the 256 units as slots free up, so a launch lasts
+// about as long as the busiest unit's share, ceil(tiles / 256) blocks of TM x TN products each; the square tile
 // moves fewer operand bytes per product and takes the ties.
 inline int large_tile_rows(int64_t M, int64_t N)
 {
@@ -51,46 +66,69 @@ template <int BITS>
 inline Plan choose(int64_t M, int64_t N, int64_t K)
 {
     static_assert(BITS == 4 || BITS == 8, "code widths");
-    static constexpr Cost k4[] = {
-        {Plan::kTile192x192, 192, 192, 1, 3.23f, 3.28f, 0.451f, 0.3642f},
-        {Plan::kTile256x128, 256, 128, 1, 3.06f, 3.15f, 0.426f, 0.3670f},
-        {Plan::kTile256x128w8, 256, 128, 1, 0.0f, 5.25f, 0.377f, 0.4045f},
-        {Plan::kTile128x128, 128, 128, 1, 2.69f, 2.13f, 0.266f, 0.2165f},
+    static constexpr Small small4[] = {
         {Plan::kTile64x64, 64, 64, 1, 2.47f, 0.58f, 0.153f, 0.1113f},
         {Plan::kSplit32x64, 32, 64, 8, 0.97f, 2.21f, 0.368f, 0.0958f},
         {Plan::kSplit32x32, 32, 32, 4, 2.41f, 0.43f, 0.250f, 0.0583f},
         {Plan::kSplit16x32, 16, 32, 8, 2.36f, 0.53f, 0.176f, 0.0440f},
         {Plan::kSplit16x16, 16, 16, 16, 1.90f, 0.98f, 0.445f, 0.0242f},
     };
-    static constexpr Cost k8[] = {
-        {Plan::kTile192x192, 192, 192, 1, 3.13f, 3.38f, 0.262f, 0.3407f},
-        {Plan::kTile256x128, 256, 128, 1, 3.56f, 2.61f, 0.327f, 0.3270f},
-        {Plan::kTile128x128, 128, 128, 1, 2.52f, 2.09f, 0.057f, 0.1869f},
+    static constexpr Small small8[] = {
         {Plan::kTile64x64, 64, 64, 1, 2.52f, 0.52f, 0.118f, 0.0849f},
         {Plan::kSplit32x64, 32, 64, 8, 2.06f, 1.07f, 0.246f, 0.0822f},
         {Plan::kSplit32x32, 32, 32, 4, 2.57f, 0.33f, 0.183f, 0.0539f},
         {Plan::kSplit16x32, 16, 32, 8, 2.29f, 0.42f, 0.321f, 0.0380f},
         {Plan::kSplit16x16, 16, 16, 16, 2.22f, 0.78f, 0.255f, 0.0243f},
     };
-    const Plan other_large = large_tile_rows(M, N) == 192 ? Plan::kTile256x128 : Plan::kTile192x192;
+    static constexpr Paired paired4[] = {
+        {Plan::kTile192x192, 192, 192, 3.62f, 2.92f, 0.719f, 0.592f},
+        {Plan::kTile256x128, 256, 128, 3.65f, 2.60f, 0.686f, 0.582f},
+        {Plan::kTile128x128, 128, 128, 2.96f, 1.36f, 0.479f, 0.280f},
+    };
+    static constexpr Paired paired8[] = {
+        {Plan::kTile192x192, 192, 192, 5.14f, 2.70f, 0.734f, 0.301f},
+        {Plan::kTile256x128, 256, 128, 3.96f, 2.63f, 0.674f, 0.284f},
+        {Plan::kTile128x128, 128, 128, 2.56f, 1.57f, 0.405f, 0.190f},
+    };
+    static constexpr Alone w8 = {2.00f, 3.84f, 0.419f, 0.80f};                                                  // 256 x 128, 4 bits
+    static constexpr Alone whole = BITS == 4 ? Alone{1.16f, 6.14f, 0.638f, 0.69f} : Alone{0.02f, 6.13f, 0.691f, 0.61f};     // 256 x 256
+
     const float stages = (float)(BITS == 4 ? (K + 127) / 128 : (K + 63) / 64);
     Plan best = Plan::kCount;
     float least = 0.0f;
-    auto consider = [&](const Cost &c) {
-        if (c.plan == other_large) return;
-        const int64_t tiles = ((M + c.tm - 1) / c.tm) * ((N + c.tn - 1) / c.tn);
-        const float b = (float)((tiles + 255) / 256), chain = (float)(((int64_t)stages + c.split - 1) / c.split);
-        const float alone = c.latency * chain, full = c.rate * stages * b;
-        const float t = c.fixed + c.block * b + (alone > full ? alone : full);
+    auto tiles = [&](int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
+    auto consider = [&](Plan plan, float t) {
         if (best == Plan::kCount || t < least) {
-            best = c.plan;
+            best = plan;
             least = t;
         }
     };
-    if constexpr (BITS == 4)
-        for (const Cost &c : k4) consider(c);
-    else
-        for (const Cost &c : k8) consider(c);
+    auto paired = [&](const Paired &c) {
+        const int64_t b = (tiles(c.tm, c.tn) + 255) / 256;
+        consider(c.plan, c.fixed + c.block * (float)b + stages * (c.pair * (float)(b / 2) + c.lone * (float)(b % 2)));
+    };
+    auto small = [&](const Small &c) {
+        const float b = (float)((tiles(c.tm, c.tn) + 255) / 256), chain = (float)(((int64_t)stages + c.split - 1) / c.split);
+        const float alone = c.latency * chain, full = c.rate * stages * b;
+        consider(c.plan, c.fixed + c.block * b + (alone > full ? alone : full));
+    };
+    auto alone = [&](Plan plan, int tm, int tn, const Alone &c) {
+        const int64_t n = tiles(tm, tn), b = (n + 255) / 256;
+        const float fill = (float)n / (256.0f * (float)b);
+        consider(plan, c.fixed + (float)b * (c.block + c.rate * stages * (c.idle + (1.0f - c.idle) * fill)));
+    };
+
+    if constexpr (BITS == 4) {
+        for (const Paired &c : paired4) paired(c);
+        for (const Small &c : small4) small(c);
+        alone(Plan::kTile256x128w8, 256, 128, w8);
+    } else {
+        for (const Paired &c : paired8) paired(c);
+        for (const Small &c : small8) small(c);
+    }
+    // With only a few stages a block that is alone on its unit cannot hide its first loads and its stores behind another one
+    // (M7557 x N3773 x K640: 24.6 us against 22.9 with 256 x 128 tiles), which the prediction knows nothing of.
+    if (stages >= 8.0f) alone(Plan::kTile256x256, 256, 256, whole);
     return best;
 }
 

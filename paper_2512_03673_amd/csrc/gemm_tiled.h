@@ -23,6 +23,13 @@
 // The MFMA's row operand is the W tile and its column operand the X tile, so that a lane ends up with four
 // consecutive n for one m; the epilogue scales, rounds to bf16, transposes through LDS and writes 16 bytes per lane,
 // whole contiguous rows of the wavefront's tile.
+//
+// What bounds the large tiles is power: the chip runs as many operand bytes and multiply-adds a second as its clock lets it, and
+// the clock falls with them.  So the tile that moves the fewest bytes a product wins where its rounds are not too uneven: 256 x 256
+// on eight wavefronts with a ring of three stages (150 KB, the compute unit to itself) against two 192 x 192 or 256 x 128 blocks
+// a unit, us: 4 bits M4608 x N3072 x K12288 73.1 / 71.1 -> 60.8, K3072 23.9 / 23.2 -> 20.2, N9216 70.2 / 69.7 -> 66.1; 8 bits
+// M4608 x N3072 x K12288 137.5 / 132.9 -> 126.  (A ring of two: 68.6 -> 80.6.  A 288 x 192 tile fills 256 units exactly at M4608 x N3072,
+// where 256 x 256 leaves 40 idle, and is slower, 72.5 against 68.6: idle units leave their power to the others.)
 #pragma once
 #include "gemm_common.h"
 
@@ -53,6 +60,7 @@ struct Stage {
     static constexpr int kRing = T::NS * kBytes;
     static constexpr int kScales = kRing > T::kEpiBytes ? kRing : T::kEpiBytes;     // scales and bias, past the ring
     static constexpr int kLds = kScales + (T::TM + 2 * T::TN) * 4;
+    static constexpr bool kAlone = kLds > 80 * 1024;          // a block has its compute unit to itself
     static_assert(kPieces * 1024 == kBytes && T::NW % 2 == 0, "stage must split into kilobytes");
     static_assert(T::NS >= 2 && T::NS <= 4 && T::kRows % 64 == 0, "ring");
     static_assert(kLds * (T::OCC * 4 / T::NW) <= 160 * 1024, "blocks per compute unit");
@@ -313,6 +321,8 @@ __global__ __launch_bounds__(T::kThreads, T::OCC) void gemm_tiled_kernel(
                     uint16_t *out = Y + (int64_t)mo * N + ncol;
                     if constexpr (decltype(EDGE)::value == 0) {
                         *reinterpret_cast<u32x4_row *>(out) = __builtin_bit_cast(u32x4_row, v);
+                    } else if constexpr (decltype(EDGE)::value == -1) {
+                        store_through(out, v);
                     } else if constexpr (decltype(EDGE)::value == 1) {
                         if (mo < M && ncol < N) *reinterpret_cast<u32x4_row *>(out) = __builtin_bit_cast(u32x4_row, v);
                     } else {
@@ -329,10 +339,15 @@ __global__ __launch_bounds__(T::kThreads, T::OCC) void gemm_tiled_kernel(
         };
         // Bounds checks only where the tile crosses the edge of Y, and element stores only where it ends inside a
         // 16-byte piece (uniform over the block; the edge bodies add a bias of zero where there is none).
+        // Rows that are multiples of 16 bytes are written through (store_through); a line that two rows share waits in the L2.
+        using Through = std::integral_constant<int, -1>;
         using Edge0 = std::integral_constant<int, 0>;
         using Edge1 = std::integral_constant<int, 1>;
         using Edge2 = std::integral_constant<int, 2>;
-        if (m0 + TM <= M && n0 + TN <= N) {
+        if (St::kAlone && (N & 7) == 0 && m0 + TM <= M && n0 + TN <= N) {
+            if (bias) body(Through{}, std::true_type{});
+            else body(Through{}, std::false_type{});
+        } else if (m0 + TM <= M && n0 + TN <= N) {
             if (bias) body(Edge0{}, std::true_type{});
             else body(Edge0{}, std::false_type{});
         } else if ((N & 7) == 0 || n0 + TN <= N) {

@@ -128,6 +128,7 @@ hipError_t launch_plan(gemm::Plan plan, const gemm::Operands &o)
         case Plan::kSplit32x32: return gemm::launch_small<Small4, 2, 2, 4, 3>(o);
         case Plan::kSplit16x32: return gemm::launch_small<Small4, 1, 2, 8, 4>(o);
         case Plan::kSplit16x16: return gemm::launch_small<Small4, 1, 1, 16, 4>(o);
+        case Plan::kTile256x256: return gemm::launch_tiled<Codes4, Tile<2, 4, 4, 2, 3, 2, 4>>(o);
         default: return hipErrorInvalidValue;
     }
 }

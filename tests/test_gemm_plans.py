@@ -15,7 +15,7 @@ from gpu_util import bf16_to_host_bits, bf16_ulp_diff, bits_to_f64, check_output
 from paper_2512_03673_amd import workloads as wl
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2512_03673_amd", "csrc")
-PLANS = ("192x192", "256x128", "256x128w8", "128x128", "64x64", "split32x64", "split32x32", "split16x32", "split16x16")
+PLANS = ("192x192", "256x128", "256x128w8", "128x128", "64x64", "split32x64", "split32x32", "split16x32", "split16x16", "256x256")
 
 # (M, N, K): the tile of the 4-bit layer, of the 8-bit one
 SHAPES = {
@@ -24,10 +24,11 @@ SHAPES = {
     (33, 4095, 96): ("split32x32", "split32x32"), (300, 520, 96): ("split32x32", "split32x32"), (40, 3000, 7264): ("split32x32", "split32x32"),
     (1, 9216, 3072): ("split32x64", "split16x32"), (65, 4095, 1056): ("split32x64", "split32x64"),
     (65, 4097, 160): ("64x64", "split32x64"), (191, 2050, 32): ("64x64", "64x64"), (1024, 1025, 1056): ("64x64", "64x64"),
-    (511, 4097, 96): ("64x64", "64x64"), (1023, 3070, 512): ("64x64", "128x128"), (513, 6100, 1056): ("128x128", "128x128"),
-    (513, 6100, 3072): ("128x128", "128x128"), (511, 12281, 544): ("256x128w8", "256x128"), (2300, 2300, 352): ("256x128w8", "256x128"),
-    (1537, 3070, 672): ("256x128w8", "256x128"), (4608, 3072, 128): ("256x128", "256x128"), (4601, 3068, 480): ("256x128", "256x128"),
-    (3001, 3070, 160): ("192x192", "192x192"), (2050, 4090, 1056): ("192x192", "192x192"),
+    (511, 4097, 96): ("64x64", "128x128"), (1023, 3070, 512): ("128x128", "128x128"), (513, 6100, 1056): ("128x128", "128x128"),
+    (513, 6100, 3072): ("128x128", "128x128"), (511, 12281, 544): ("256x128w8", "256x128"), (2300, 2300, 352): ("256x128w8", "128x128"),
+    (1537, 3070, 672): ("256x128w8", "256x128"), (4608, 3072, 128): ("128x128", "128x128"), (4601, 3068, 480): ("256x128", "256x256"),
+    (3001, 3070, 160): ("192x192", "192x192"), (2050, 4090, 1056): ("192x192", "192x192"), (3071, 4090, 1056): ("256x256", "256x256"),
+    (3100, 4088, 1056): ("256x256", "256x256"),
 }
 
 
@@ -40,8 +41,8 @@ def test_shapes_take_the_tiles_they_are_meant_for(tmp_path):
     exe = str(tmp_path / "plan")
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, "-o", exe, str(src)], check=True)
     # the benchmark's layers and the extremes of the argument range stay on the large tiles
-    large = {(4608, 3072 * 4, 3072): "192x192", (4608, 9216, 3072): "192x192", (16896, 3072, 12288): "192x192", (4608, 3072, 12288): "256x128",
-             (4608, 3072, 15360): "256x128", (2 ** 31 - 1, 2 ** 31 - 1, 65536): "256x128"}
+    large = {(4608, 3072 * 4, 3072): "192x192", (16896, 12288, 3072): "192x192", (16896, 3072, 12288): "192x192", (4608, 3072, 12288): "256x256",
+             (4608, 3072, 15360): "256x256", (2 ** 31 - 1, 2 ** 31 - 1, 65536): "192x192"}
     shapes = list(SHAPES) + list(large)
     out = subprocess.run([exe] + [str(d) for s in shapes for d in s], check=True, capture_output=True, text=True).stdout.split()
     got = {s: (PLANS[int(out[2 * i])], PLANS[int(out[2 * i + 1])]) for i, s in enumerate(shapes)}
