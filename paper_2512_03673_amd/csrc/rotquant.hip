@@ -15,8 +15,8 @@
 // every unit, which is what the otherwise idle matrix pipe does for 64 units at a time, the bf16 -> fp32
 // widening and the hand-over of each unit to its lane included (rotation_operand below): the vector ALU,
 // which bounds this kernel on small inputs, sees none of it.
-// Digits 2, 3 (g = 64, 256) run across lanes with DPP adds and digit 4 (g = 1024) with
-// wavefront shuffles; there the step is taken as y_j = s - 2 x_j (the matrix J - 2I, which is
+// Digits 2, 3 (g = 64, 256) run across lanes with DPP adds and digit 4 (g = 1024) over a lane's four units or, in
+// short rows, with wavefront shuffles; across lanes the step is taken as y_j = s - 2 x_j (the matrix J - 2I, which is
 // the printed matrix with its columns reversed) and the flip is applied once, for free, to the
 // lane's output address.  The 1/sqrt(g) = 2^-k normalisation is folded into the scale.
 //
@@ -125,7 +125,32 @@ __device__ __forceinline__ void rotate_units_mfma(const v8bf &rot0, const v8bf &
     for (int e = 0; e < kUnit; ++e) v[e] = d[e];
 }
 
-template <int G>
+// Which unit of its row lane t holds as its i-th.  With g = 1024 and four units a lane these are of one group, 16 apart: digit 4
+// runs over them and its radix-4 step is seven instructions on four values of one lane instead of three instructions and two wavefront
+// shuffles an element ([4608, 15360]: 48.4 -> 42.7 us).  16 lanes still load 512 bytes of a row at a time.  (The same for digit 3
+// of g = 256, where four lanes would load 128 bytes: no faster on large inputs, 15 % slower on 512 rows.)
+template <int G, int U>
+__device__ __forceinline__ int unit_of(int i, int t, int T)
+{
+    if constexpr (G == 1024 && U == 4) return ((t >> 4) << 6) + 16 * i + (t & 15);
+    else return i * T + t;
+}
+
+// Digit 4 over a lane's four units, in the printed matrix's order.
+__device__ __forceinline__ void rotate_registers(float (&v)[4][kUnit])
+{
+#pragma unroll
+    for (int e = 0; e < kUnit; ++e) {
+        const float x0 = v[0][e], x1 = v[1][e], x2 = v[2][e], x3 = v[3][e];
+        const float s = (x0 + x1) + (x2 + x3);
+        v[0][e] = fmaf(-2.0f, x3, s);
+        v[1][e] = fmaf(-2.0f, x2, s);
+        v[2][e] = fmaf(-2.0f, x1, s);
+        v[3][e] = fmaf(-2.0f, x0, s);
+    }
+}
+
+template <int G>      // of the digits across lanes
 constexpr int lane_flip_mask() { return G >= 1024 ? 63 : (G >= 256 ? 15 : (G >= 64 ? 3 : 0)); }
 
 template <int G>
@@ -135,8 +160,8 @@ constexpr float group_norm() { return G == 4 ? 0.5f : G == 16 ? 0.25f : G == 64 
 
 // T = lanes per row.  Two ways of laying rows over wavefronts:
 //   RPW = 1  a wavefront holds 64 lanes of one row (T = 64 * waves per row, BLOCK / T rows per block): any K, any g
-//   RPW = 4  a wavefront holds 16 lanes of each of 4 consecutive rows (T = BLOCK / 4, 4 rows per block): g <= 256
-//            (the cross-lane digits stay inside 16 lanes), used for K <= 4096.  The four rows' pieces of an output block
+//   RPW = 4  a wavefront holds 16 lanes of each of 4 consecutive rows (T = threads / 4, 4 rows per block): the cross-lane
+//            digits stay inside 16 lanes; used for K <= 4096.  The four rows' pieces of an output block
 //            are adjacent in memory, so a store instruction touches 256- and 128-byte runs instead of 64- and
 //            32-byte ones: as few cache lines per instruction as a row-major stream would.
 // grid.x = 8 * ceil(rows / (8 * group rows)) * group rows / rows per block (see the row mapping below).
@@ -149,7 +174,9 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 256 ? 2 : 1) void rotquant_kernel(c
                                                          int T, uint8_t *__restrict__ Xq,
                                                          float *__restrict__ scale)
 {
-    static_assert(RPW == 1 || (RPW == 4 && G <= 256), "four rows per wavefront need the rotation inside 16 lanes");
+    constexpr bool kDigit4 = G == 1024 && U == 4;   // over a lane's units (unit_of)
+    constexpr int kLaneG = kDigit4 ? 256 : G;       // the rest of the rotation: inside a unit and across lanes
+    static_assert(RPW == 1 || (RPW == 4 && kLaneG <= 256), "four rows per wavefront need the rotation inside 16 lanes");
     __shared__ float s_part[BLOCK / 64 * RPW];
 
     const int tid = threadIdx.x;
@@ -187,7 +214,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 256 ? 2 : 1) void rotquant_kernel(c
     for (int i = 0; i < U; ++i) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const int unit = min(i * T + t_src[h], units - 1);
+            const int unit = min(unit_of<G, U>(i, t_src[h], T), units - 1);
             raw[i][h] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src[h] + (int64_t)unit * kUnit));
         }
     }
@@ -195,14 +222,24 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 256 ? 2 : 1) void rotquant_kernel(c
 
     float v[U][kUnit];
     float amax = 0.0f;
+    if constexpr (kDigit4) {
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            rotate_units_mfma(rot0, rot1, raw[i][0], raw[i][1], v[i]);
+            rotate_lanes<kLaneG>(v[i]);
+        }
+        rotate_registers(v);
+    }
 #pragma unroll
     for (int i = 0; i < U; ++i) {
-        rotate_units_mfma(rot0, rot1, raw[i][0], raw[i][1], v[i]);
-        rotate_lanes<G>(v[i]);
+        if constexpr (!kDigit4) {
+            rotate_units_mfma(rot0, rot1, raw[i][0], raw[i][1], v[i]);
+            rotate_lanes<kLaneG>(v[i]);
+        }
         float m = 0.0f;
 #pragma unroll
         for (int e = 0; e < kUnit; ++e) m = fmaxf(m, fabsf(v[i][e]));
-        amax = (row_ok && i * T + t < units) ? fmaxf(amax, m) : amax;
+        amax = (row_ok && unit_of<G, U>(i, t, T) < units) ? fmaxf(amax, m) : amax;
     }
 
     // row absmax: butterfly over the row's lanes of this wavefront, then across the row's wavefronts through LDS
@@ -225,7 +262,8 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 256 ? 2 : 1) void rotquant_kernel(c
         __syncthreads();
         float a = s_part[rib];
 #pragma unroll
-        for (int w = 1; w < BLOCK / 64; ++w) a = fmaxf(a, s_part[w * RPW + rib]);
+        for (int w = 1; w < BLOCK / 64; ++w)
+            a = !kDigit4 || w * 16 < T ? fmaxf(a, s_part[w * RPW + rib]) : a;
         amax = a;
     }
 
@@ -249,7 +287,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 256 ? 2 : 1) void rotquant_kernel(c
     const float su = s / norm;                                      // scale in un-normalised units (exact)
     const float r_lo = r * (1.0f - 0x1p-21f), r_hi = r * (1.0f + 0x1p-21f);
     const float half_su = 0.5f * su;
-    const int tf = t ^ lane_flip_mask<G>();
+    const int tf = t ^ lane_flip_mask<kLaneG>();
     auto exact_code = [&](float z) {   // rne(z / su) as a float, from the exact residual
         float q = rintf(z * r);
         const float res = fmaf(-q, su, z);
@@ -276,7 +314,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 256 ? 2 : 1) void rotquant_kernel(c
             // unit next to it, which the neighbouring lane holds: its first 16 bytes go to the A plane of the
             // block, the other 8 to the B plane (e2m3_layout.h).  The even lane fetches the odd lane's first dword.
             const uint32_t nb0 = __builtin_amdgcn_update_dpp(0u, w0, 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
-            const int unit = i * T + tf;
+            const int unit = unit_of<G, U>(i, tf, T);
             if (!(row_ok && unit < padded_units)) return;
             uint32_t nb = nb0;
             if (unit >= units) w0 = w1 = w2 = nb = 0;               // K padding: zero codes (units come in pairs: K % 32 == 0)
@@ -366,7 +404,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 256 ? 2 : 1) void rotquant_kernel(c
             }
             // Panel layout: 1 KB panels of 16 rows x 64 bytes, a unit is 16 bytes of its row; units past the
             // row's end inside its last K-panel are stored as zero codes.
-            const int unit = i * T + tf;
+            const int unit = unit_of<G, U>(i, tf, T);
             constexpr int kUnitsPerPanelRow = panel::kRowBytes / kUnit;
             const int padded_units = (units + kUnitsPerPanelRow - 1) / kUnitsPerPanelRow * kUnitsPerPanelRow;
             if (row_ok && unit < padded_units) {
@@ -498,19 +536,39 @@ hipError_t launch_gu4(const void *X, int64_t rows, int K, void *Xq, float *scale
     return hipGetLastError();
 }
 
+// g = 1024: four units a lane (digit 4 over them), as many wavefronts as the row needs; up to K = 4096 16 lanes of each of four
+// rows a wavefront, for the stores' sake as above ([4608, 3072]: 13.4 us against 14.7 with one row a wavefront).  Rows of one
+// or two groups have too few wavefronts that way ([1000, 1024]: 4.9 us against 4.2) and take digit 4 across lanes.
+template <int BITS>
+hipError_t launch_1024(const void *X, int64_t rows, int K, void *Xq, float *scale, hipStream_t stream)
+{
+    constexpr int kGroupRows = BITS == 4 ? e2m3::kRows : panel::kRows;
+    auto go = [&](auto kernel, int rows_per_block, int threads, int T) {
+        const unsigned grid = (unsigned)(((rows + 8 * kGroupRows - 1) / (8 * kGroupRows)) * 8 * (kGroupRows / rows_per_block));
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, stream, (const uint16_t *)X, rows, K, T, (uint8_t *)Xq, scale);
+        return hipGetLastError();
+    };
+    const int groups = K / 1024;                             // 16 lanes each
+    if (groups == 1) return launch_gu<1024, 1, BITS>(X, rows, K, 1, Xq, scale, stream);
+    if (groups == 2) return launch_gu<1024, 2, BITS>(X, rows, K, 1, Xq, scale, stream);
+    if (groups <= 4) return go(rotquant_kernel<1024, 4, 256, BITS, 4>, 4, 64 * groups, 16 * groups);
+    const int T = (groups + 3) / 4 * 64;
+    if (T <= 256) return go(rotquant_kernel<1024, 4, 256, BITS, 1>, 256 / T, 256 / T * T, T);
+    if (T <= 512) return go(rotquant_kernel<1024, 4, 512, BITS, 1>, 1, T, T);
+    return go(rotquant_kernel<1024, 4, 1024, BITS, 1>, 1, T, T);
+}
+
 template <int G, int BITS>
 hipError_t launch_g(const void *X, int64_t rows, int K, void *Xq, float *scale, hipStream_t stream)
 {
-    if constexpr (G <= 256) {
-        // four rows per wavefront whenever 4 wavefronts x 16 lanes x 4 units hold a row (K <= 4096)
-        const int spans = (K / kUnit + 15) / 16;   // 256-element spans per row
-        if (spans <= 16) {
-            switch ((spans + 3) / 4) {
-                case 1: return launch_gu4<G, 1, BITS>(X, rows, K, Xq, scale, stream);
-                case 2: return launch_gu4<G, 2, BITS>(X, rows, K, Xq, scale, stream);
-                case 3: return launch_gu4<G, 3, BITS>(X, rows, K, Xq, scale, stream);
-                default: return launch_gu4<G, 4, BITS>(X, rows, K, Xq, scale, stream);
-            }
+    // four rows per wavefront whenever 4 wavefronts x 16 lanes x 4 units hold a row (K <= 4096)
+    const int spans = (K / kUnit + 15) / 16;   // 256-element spans per row
+    if (spans <= 16) {
+        switch ((spans + 3) / 4) {
+            case 1: return launch_gu4<G, 1, BITS>(X, rows, K, Xq, scale, stream);
+            case 2: return launch_gu4<G, 2, BITS>(X, rows, K, Xq, scale, stream);
+            case 3: return launch_gu4<G, 3, BITS>(X, rows, K, Xq, scale, stream);
+            default: return launch_gu4<G, 4, BITS>(X, rows, K, Xq, scale, stream);
         }
     }
     // Pick the wavefronts per row (1, 2, 4, 8 or 16) so that every lane holds at most 4 units,
@@ -535,7 +593,7 @@ hipError_t launch_bits(const void *X, int64_t rows, int64_t K, int group, void *
         case 16: return launch_g<16, BITS>(X, rows, (int)K, Xq, scale, stream);
         case 64: return launch_g<64, BITS>(X, rows, (int)K, Xq, scale, stream);
         case 256: return launch_g<256, BITS>(X, rows, (int)K, Xq, scale, stream);
-        case 1024: return launch_g<1024, BITS>(X, rows, (int)K, Xq, scale, stream);
+        case 1024: return launch_1024<BITS>(X, rows, (int)K, Xq, scale, stream);
         default: return hipErrorInvalidValue;
     }
 }
