@@ -113,7 +113,8 @@ const char *convrot_build_info(void);
 int convrot_init(void);
 
 /* Host.  X rows of the large block tile that suits an [M, N] output: 192 (tile 192 x 192) or 256 (tile
- * 256 x 128); 0 when M or N < 0.  Products too small to fill the device with such tiles take smaller ones.  The
+ * 256 x 128) of those of which two share a compute unit; 0 when M or N < 0.  Products too small to fill the device with such
+ * tiles take smaller ones, some large ones 256 x 256.  The
  * result of the GEMM does not depend on the tile; the query exists so that tests and tuning runs can tell which
  * kernel configuration a large shape exercises. */
 int convrot_gemm_tile_rows(int64_t M, int64_t N);

@@ -12,7 +12,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libconvrot.so")
 CALLS = os.path.join(HERE, "_torch_calls.so")
-SOURCES = ("convrot_api.hip", "rotquant.hip", "gemm_w4a4.hip", "gemm_w8a8.hip")
+SOURCES = ("convrot_api.hip", "rotquant.hip", "gemm_w4a4.hip", "gemm_w8a8.hip", "forward_small.hip")
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",

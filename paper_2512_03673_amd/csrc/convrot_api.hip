@@ -89,6 +89,17 @@ int check_forward(const void *X_bf16, const void *Wq, const float *w_scale, cons
     return CONVROT_OK;
 }
 
+// The forward of checked arguments; the codes and scales go to xq and xs.
+int launch_forward(const void *X_bf16, const void *Wq, const float *w_scale, const void *bias_bf16, int64_t M, int64_t N, int64_t K,
+                   int group, int bits, void *Y_bf16, uint8_t *xq, float *xs, hipStream_t s)
+{
+    if (M > 0 && N > 0 && convrot::launch_forward_small && convrot::gemm::forward_in_one(M, N, K))
+        return from_hip(convrot::launch_forward_small(X_bf16, Wq, w_scale, bias_bf16, M, N, K, group, bits, Y_bf16, xq, xs, s));
+    if (convrot::launch_rotquant(X_bf16, M, K, group, bits, xq, xs, s) != hipSuccess) return CONVROT_ERR_HIP;
+    return from_hip(bits == 4 ? convrot::launch_gemm_w4a4(xq, xs, Wq, w_scale, bias_bf16, M, N, K, Y_bf16, nullptr, s)
+                              : convrot::launch_gemm_w8a8(xq, xs, Wq, w_scale, bias_bf16, M, N, K, Y_bf16, nullptr, s));
+}
+
 }  // namespace
 
 extern "C" {
@@ -197,9 +208,7 @@ int convlinear4bit_forward(const void *X_bf16, const void *Wq, const float *w_sc
 
     uint8_t *xq = static_cast<uint8_t *>(workspace);
     float *xs = reinterpret_cast<float *>(xq + convrot_packed_bytes(M, K));
-    hipStream_t s = (hipStream_t)stream;
-    if (hipError_t e = convrot::launch_rotquant(X_bf16, M, K, group, 4, xq, xs, s); e != hipSuccess) return CONVROT_ERR_HIP;
-    return from_hip(convrot::launch_gemm_w4a4(xq, xs, Wq, w_scale, bias_bf16, M, N, K, Y_bf16, nullptr, s));
+    return launch_forward(X_bf16, Wq, w_scale, bias_bf16, M, N, K, group, 4, Y_bf16, xq, xs, (hipStream_t)stream);
 }
 
 int convlinear4bit_forward_noalloc(const void *X_bf16, const void *Wq, const float *w_scale, const void *bias_bf16,
@@ -214,9 +223,7 @@ int convlinear4bit_forward_noalloc(const void *X_bf16, const void *Wq, const flo
     // (K padding included) and all M scales before the GEMM reads them; what an earlier call left in the rows
     // past M of the last 32-row block only ever meets accumulators that are not stored.
     float *xs = reinterpret_cast<float *>(xq + convrot_packed_bytes(M, K));
-    hipStream_t s = (hipStream_t)stream;
-    if (hipError_t e = convrot::launch_rotquant(X_bf16, M, K, group, 4, xq, xs, s); e != hipSuccess) return CONVROT_ERR_HIP;
-    return from_hip(convrot::launch_gemm_w4a4(xq, xs, Wq, w_scale, bias_bf16, M, N, K, Y_bf16, nullptr, s));
+    return launch_forward(X_bf16, Wq, w_scale, bias_bf16, M, N, K, group, 4, Y_bf16, xq, xs, (hipStream_t)stream);
 }
 
 int convrot_rotated_absmax(const void *X_bf16, int64_t M, int64_t K, int group, int kind, float *row_absmax,
@@ -283,9 +290,7 @@ int convlinear8bit_forward(const void *X_bf16, const void *Wq, const float *w_sc
 
     uint8_t *xq = static_cast<uint8_t *>(workspace);
     float *xs = reinterpret_cast<float *>(xq + convrot_packed_bytes8(M, K));
-    hipStream_t s = (hipStream_t)stream;
-    if (hipError_t e = convrot::launch_rotquant(X_bf16, M, K, group, 8, xq, xs, s); e != hipSuccess) return CONVROT_ERR_HIP;
-    return from_hip(convrot::launch_gemm_w8a8(xq, xs, Wq, w_scale, bias_bf16, M, N, K, Y_bf16, nullptr, s));
+    return launch_forward(X_bf16, Wq, w_scale, bias_bf16, M, N, K, group, 8, Y_bf16, xq, xs, (hipStream_t)stream);
 }
 
 }  // extern "C"

@@ -14,12 +14,116 @@
 // `C` (Small4 / Small8) says what a lane holds of 16 rows x one K stage: lane l has row l % 16 and quarter l / 16 of the
 // stage, so that the lanes of a load cover whole contiguous lines; one MFMA per 16 x 16 tile and stage.
 #pragma once
+#include "e2m3_layout.h"
 #include "gemm_common.h"
+#include "panel_layout.h"
 
 namespace convrot {
 namespace gemm {
 
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+struct Small4 {   // stage of 128 codes: half of a 3 KB block (e2m3_layout.h); quarter = one chunk of 32 codes
+    struct Frag { v4i a; v2i b; };
+    typedef v4f Acc;
+    static __device__ __forceinline__ int stages(int K) { return (int)e2m3::stages(K); }
+    uint32_t a, b;
+    const uint8_t *base;
+    __device__ __forceinline__ void init(const uint8_t *m, int group, int rows, int KS, int lane)
+    {
+        const int g = min(group, (rows - 1) / 16), r = (g & 1) * 16 + (lane & 15), c = lane >> 4;
+        base = m + (int64_t)(g >> 1) * KS * e2m3::kBlockBytes;
+        a = e2m3::a_offset(r, c);
+        b = e2m3::b_offset(r, c);
+    }
+    __device__ __forceinline__ Frag load(int s) const
+    {
+        const uint8_t *p = base + (uint32_t)s * e2m3::kBlockBytes;
+        return {*reinterpret_cast<const v4i *>(p + a), *reinterpret_cast<const v2i *>(p + b)};
+    }
+    static __device__ __forceinline__ v8i op(const Frag &f)
+    {
+        const v4i b = {f.b.x, f.b.y, 0, 0};
+        return __builtin_shufflevector(f.a, b, 0, 1, 2, 3, 4, 5, -1, -1);
+    }
+    static __device__ __forceinline__ void mma(Acc &c, const Frag &w, const Frag &x)
+    {
+        c = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(op(w), op(x), c, 2, 2, 0, 0, 0, 0);
+    }
+};
+
+struct Small8 {   // stage of 64 codes: one 1 KB panel of 16 rows (panel_layout.h); quarter = 16 codes
+    struct Frag { v4i a; };
+    typedef v4i Acc;
+    static __device__ __forceinline__ int stages(int K) { return (int)panel::k_panels(K); }
+    uint32_t a;
+    const uint8_t *base;
+    __device__ __forceinline__ void init(const uint8_t *m, int group, int rows, int KS, int lane)
+    {
+        base = m + (int64_t)min(group, (rows - 1) / 16) * KS * panel::kBytes;
+        a = (lane & 15) * panel::kRowBytes + (lane >> 4) * 16;
+    }
+    __device__ __forceinline__ Frag load(int s) const { return {*reinterpret_cast<const v4i *>(base + (uint32_t)s * panel::kBytes + a)}; }
+    static __device__ __forceinline__ void mma(Acc &c, const Frag &w, const Frag &x)
+    {
+        c = __builtin_amdgcn_mfma_i32_16x16x64_i8(w.a, x.a, c, 0, 0, 0);
+    }
+};
+
 constexpr int kSlabBytes = 16 * 16 + 16;     // four consecutive n of 16 rows, padded so that a row's quads lie in different banks
+constexpr int kTileBytes = 4 * kSlabBytes;   // one 16 x 16 partial tile
+
+// The S partial tiles of the block's wavefronts, in LDS, to Y or to the raw accumulators; x_scale(m) is the scale of row m.
+template <class C, bool RAW, int XF, int WF, int S, class Scale>
+__device__ __forceinline__ void sum_and_store(const uint8_t *part, int tid, int m0, int n0, int M, int N, Scale x_scale,
+                                              const float *__restrict__ w_scale, const uint16_t *__restrict__ bias,
+                                              uint16_t *__restrict__ Y, int32_t *__restrict__ acc_out)
+{
+    constexpr int TM = 16 * XF, TN = 16 * WF, kThreads = 64 * S;
+    constexpr int kQuads = TM * TN / 4;
+#pragma unroll
+    for (int it = 0; it < (kQuads + kThreads - 1) / kThreads; ++it) {
+        const int u = it * kThreads + tid;
+        if (u >= kQuads) break;
+        const int ml = u / (TN / 4), q = u % (TN / 4);
+        const int m = m0 + ml, n = n0 + 4 * q;
+        if (m >= M || n >= N) continue;
+        const uint8_t *p = part + ((ml / 16) * WF + q / 4) * kTileBytes + (q % 4) * kSlabBytes + (ml % 16) * 16;
+        typename C::Acc v = *reinterpret_cast<const typename C::Acc *>(p);
+#pragma unroll
+        for (int s = 1; s < S; ++s) v += *reinterpret_cast<const typename C::Acc *>(p + s * (XF * WF * kTileBytes));
+        if constexpr (RAW) {
+            int32_t *dst = acc_out + (int64_t)m * N + n;
+            if ((N & 3) == 0) {
+                *reinterpret_cast<int4 *>(dst) = make_int4((int)v[0], (int)v[1], (int)v[2], (int)v[3]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (n + e < N) dst[e] = (int)v[e];
+            }
+        } else {
+            const float sx = x_scale(m);
+            float y[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int nn = min(n + e, N - 1);
+                const float t = (float)v[e] * sx;
+                y[e] = bias ? fmaf(t, w_scale[nn], bf16_to_f32(bias[nn])) : t * w_scale[nn];
+            }
+            const uint32_t lo = pack_bf16x2(y[0], y[1]), hi = pack_bf16x2(y[2], y[3]);
+            uint16_t *dst = Y + (int64_t)m * N + n;
+            if (n + 4 <= N) {
+                *reinterpret_cast<u32x2_row *>(dst) = u32x2_row{lo, hi};
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (n + e < N) dst[e] = (uint16_t)((e < 2 ? lo : hi) >> (16 * (e & 1)));
+            }
+        }
+    }
+}
 
 template <class C, bool RAW, int XF, int WF, int S, int PD>
 __global__ __launch_bounds__(64 * S) void gemm_small_kernel(const uint8_t *__restrict__ Xq, const float *__restrict__ x_scale,
@@ -28,8 +132,7 @@ __global__ __launch_bounds__(64 * S) void gemm_small_kernel(const uint8_t *__res
                                                             uint16_t *__restrict__ Y, int32_t *__restrict__ acc_out, int tiles_m,
                                                             int tiles_n)
 {
-    constexpr int TM = 16 * XF, TN = 16 * WF, kThreads = 64 * S;
-    constexpr int kTileBytes = 4 * kSlabBytes;                      // one 16 x 16 partial tile
+    constexpr int TM = 16 * XF, TN = 16 * WF;
     __shared__ __attribute__((aligned(16))) uint8_t part[S * XF * WF * kTileBytes];
 
     int tm, tn;
@@ -83,47 +186,7 @@ __global__ __launch_bounds__(64 * S) void gemm_small_kernel(const uint8_t *__res
         for (int j = 0; j < WF; ++j)
             *reinterpret_cast<typename C::Acc *>(part + ((wave * XF + i) * WF + j) * kTileBytes + (lane >> 4) * kSlabBytes + (lane & 15) * 16) = acc[i][j];
     __syncthreads();
-    constexpr int kQuads = TM * TN / 4;
-#pragma unroll
-    for (int it = 0; it < (kQuads + kThreads - 1) / kThreads; ++it) {
-        const int u = it * kThreads + tid;
-        if (u >= kQuads) break;
-        const int ml = u / (TN / 4), q = u % (TN / 4);
-        const int m = m0 + ml, n = n0 + 4 * q;
-        if (m >= M || n >= N) continue;
-        const uint8_t *p = part + ((ml / 16) * WF + q / 4) * kTileBytes + (q % 4) * kSlabBytes + (ml % 16) * 16;
-        typename C::Acc v = *reinterpret_cast<const typename C::Acc *>(p);
-#pragma unroll
-        for (int s = 1; s < S; ++s) v += *reinterpret_cast<const typename C::Acc *>(p + s * (XF * WF * kTileBytes));
-        if constexpr (RAW) {
-            int32_t *dst = acc_out + (int64_t)m * N + n;
-            if ((N & 3) == 0) {
-                *reinterpret_cast<int4 *>(dst) = make_int4((int)v[0], (int)v[1], (int)v[2], (int)v[3]);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (n + e < N) dst[e] = (int)v[e];
-            }
-        } else {
-            const float sx = x_scale[m];
-            float y[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int nn = min(n + e, N - 1);
-                const float t = (float)v[e] * sx;
-                y[e] = bias ? fmaf(t, w_scale[nn], bf16_to_f32(bias[nn])) : t * w_scale[nn];
-            }
-            const uint32_t lo = pack_bf16x2(y[0], y[1]), hi = pack_bf16x2(y[2], y[3]);
-            uint16_t *dst = Y + (int64_t)m * N + n;
-            if (n + 4 <= N) {
-                *reinterpret_cast<u32x2_row *>(dst) = u32x2_row{lo, hi};
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (n + e < N) dst[e] = (uint16_t)((e < 2 ? lo : hi) >> (16 * (e & 1)));
-            }
-        }
-    }
+    sum_and_store<C, RAW, XF, WF, S>(part, tid, m0, n0, M, N, [&](int m) { return x_scale[m]; }, w_scale, bias, Y, acc_out);
 }
 
 template <class C, int XF, int WF, int S, int PD>

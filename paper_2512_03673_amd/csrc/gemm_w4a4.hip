@@ -83,37 +83,6 @@ struct Codes4 {
     }
 };
 
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-struct Small4 {   // stage of 128 codes: half of a 3 KB block (e2m3_layout.h); quarter = one chunk of 32 codes
-    struct Frag { v4i a; v2i b; };
-    typedef v4f Acc;
-    static __device__ __forceinline__ int stages(int K) { return (int)e2m3::stages(K); }
-    uint32_t a, b;
-    const uint8_t *base;
-    __device__ __forceinline__ void init(const uint8_t *m, int group, int rows, int KS, int lane)
-    {
-        const int g = min(group, (rows - 1) / 16), r = (g & 1) * 16 + (lane & 15), c = lane >> 4;
-        base = m + (int64_t)(g >> 1) * KS * e2m3::kBlockBytes;
-        a = e2m3::a_offset(r, c);
-        b = e2m3::b_offset(r, c);
-    }
-    __device__ __forceinline__ Frag load(int s) const
-    {
-        const uint8_t *p = base + (uint32_t)s * e2m3::kBlockBytes;
-        return {*reinterpret_cast<const v4i *>(p + a), *reinterpret_cast<const v2i *>(p + b)};
-    }
-    static __device__ __forceinline__ v8i op(const Frag &f)
-    {
-        const v4i b = {f.b.x, f.b.y, 0, 0};
-        return __builtin_shufflevector(f.a, b, 0, 1, 2, 3, 4, 5, -1, -1);
-    }
-    static __device__ __forceinline__ void mma(Acc &c, const Frag &w, const Frag &x)
-    {
-        c = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(op(w), op(x), c, 2, 2, 0, 0, 0, 0);
-    }
-};
-
 hipError_t launch_plan(gemm::Plan plan, const gemm::Operands &o)
 {
     using gemm::Plan;
@@ -124,10 +93,10 @@ hipError_t launch_plan(gemm::Plan plan, const gemm::Operands &o)
         case Plan::kTile256x128w8: return gemm::launch_tiled<Codes4, Tile<4, 2, 2, 2, 3, 2, 8>>(o);
         case Plan::kTile128x128: return gemm::launch_tiled<Codes4, Tile<2, 2, 2, 2, 3, 2, 8>>(o);
         case Plan::kTile64x64: return gemm::launch_tiled<Codes4, Tile<2, 2, 1, 1, 3, 4, 8>>(o);
-        case Plan::kSplit32x64: return gemm::launch_small<Small4, 2, 4, 8, 2>(o);
-        case Plan::kSplit32x32: return gemm::launch_small<Small4, 2, 2, 4, 3>(o);
-        case Plan::kSplit16x32: return gemm::launch_small<Small4, 1, 2, 8, 4>(o);
-        case Plan::kSplit16x16: return gemm::launch_small<Small4, 1, 1, 16, 4>(o);
+        case Plan::kSplit32x64: return gemm::launch_small<gemm::Small4, 2, 4, 8, 2>(o);
+        case Plan::kSplit32x32: return gemm::launch_small<gemm::Small4, 2, 2, 4, 3>(o);
+        case Plan::kSplit16x32: return gemm::launch_small<gemm::Small4, 1, 2, 8, 4>(o);
+        case Plan::kSplit16x16: return gemm::launch_small<gemm::Small4, 1, 1, 16, 4>(o);
         case Plan::kTile256x256: return gemm::launch_tiled<Codes4, Tile<2, 4, 4, 2, 3, 2, 4>>(o);
         default: return hipErrorInvalidValue;
     }

@@ -60,24 +60,6 @@ struct Codes8 {
     static __device__ __forceinline__ void mma(Acc &c, const Op &w, const Op &x) { c = __builtin_amdgcn_mfma_i32_32x32x32_i8(w, x, c, 0, 0, 0); }
 };
 
-struct Small8 {   // stage of 64 codes: one 1 KB panel of 16 rows (panel_layout.h); quarter = 16 codes
-    struct Frag { v4i a; };
-    typedef v4i Acc;
-    static __device__ __forceinline__ int stages(int K) { return (int)panel::k_panels(K); }
-    uint32_t a;
-    const uint8_t *base;
-    __device__ __forceinline__ void init(const uint8_t *m, int group, int rows, int KS, int lane)
-    {
-        base = m + (int64_t)min(group, (rows - 1) / 16) * KS * panel::kBytes;
-        a = (lane & 15) * panel::kRowBytes + (lane >> 4) * 16;
-    }
-    __device__ __forceinline__ Frag load(int s) const { return {*reinterpret_cast<const v4i *>(base + (uint32_t)s * panel::kBytes + a)}; }
-    static __device__ __forceinline__ void mma(Acc &c, const Frag &w, const Frag &x)
-    {
-        c = __builtin_amdgcn_mfma_i32_16x16x64_i8(w.a, x.a, c, 0, 0, 0);
-    }
-};
-
 hipError_t launch_plan(gemm::Plan plan, const gemm::Operands &o)
 {
     using gemm::Plan;
@@ -87,10 +69,10 @@ hipError_t launch_plan(gemm::Plan plan, const gemm::Operands &o)
         case Plan::kTile256x128: return gemm::launch_tiled<Codes8, Tile<2, 2, 4, 2, 3, 2, 6>>(o);
         case Plan::kTile128x128: return gemm::launch_tiled<Codes8, Tile<2, 2, 2, 2, 4, 2, 8>>(o);
         case Plan::kTile64x64: return gemm::launch_tiled<Codes8, Tile<2, 2, 1, 1, 4, 4, 8>>(o);
-        case Plan::kSplit32x64: return gemm::launch_small<Small8, 2, 4, 8, 2>(o);
-        case Plan::kSplit32x32: return gemm::launch_small<Small8, 2, 2, 4, 3>(o);
-        case Plan::kSplit16x32: return gemm::launch_small<Small8, 1, 2, 8, 4>(o);
-        case Plan::kSplit16x16: return gemm::launch_small<Small8, 1, 1, 16, 4>(o);
+        case Plan::kSplit32x64: return gemm::launch_small<gemm::Small8, 2, 4, 8, 2>(o);
+        case Plan::kSplit32x32: return gemm::launch_small<gemm::Small8, 2, 2, 4, 3>(o);
+        case Plan::kSplit16x32: return gemm::launch_small<gemm::Small8, 1, 2, 8, 4>(o);
+        case Plan::kSplit16x16: return gemm::launch_small<gemm::Small8, 1, 1, 16, 4>(o);
         case Plan::kTile256x256: return gemm::launch_tiled<Codes8, Tile<2, 4, 4, 2, 3, 2, 4>>(o);
         default: return hipErrorInvalidValue;
     }
