@@ -12,7 +12,8 @@
 // (`block`: prologue and epilogue of a tile; `latency`, `lone`: a stage of a tile that has the unit to itself; `rate`, `pair`: a
 // stage of a full unit.)  The constants are robust fits: of the first kind to 320 launches on shapes drawn over M 1 ... 8000,
 // N 32 ... 12288, K 64 ... 15360, of the other two to 230 over M 256 ... 16896, N 512 ... 12288, K 256 ... 15360 with at least
-// 1.2e10 products.  On the larger shapes the tile taken costs 0.5 % more on average than the best of them would, on the others 2 %.
+// 1.2e10 products (128 x 192: to 220 with M 64 ... 8000 and 3e9 to 8e10 products).  On the larger shapes the tile taken costs
+// 0.5 % more on average than the best of them would, on the others 1 to 2 %.
 #pragma once
 #include <stdint.h>
 
@@ -30,6 +31,7 @@ enum class Plan {
     kSplit16x32,
     kSplit16x16,
     kTile256x256,     // gemm_tiled.h: eight wavefronts, one block per compute unit
+    kTile128x192,     // gemm_tiled.h
     kCount
 };
 
@@ -107,9 +109,14 @@ inline Plan choose(int64_t M, int64_t N, int64_t K)
         {Plan::kTile192x192, 192, 192, 5.14f, 2.70f, 0.734f, 0.301f},
         {Plan::kTile256x128, 256, 128, 3.96f, 2.63f, 0.674f, 0.284f},
         {Plan::kTile128x128, 128, 128, 2.56f, 1.57f, 0.405f, 0.190f},
+        {Plan::kTile128x192, 128, 192, 3.08f, 2.44f, 0.512f, 0.269f},
     };
     static constexpr Alone w8 = {2.00f, 3.84f, 0.419f, 0.80f};                                                  // 256 x 128, 4 bits
     static constexpr Alone whole = BITS == 4 ? Alone{1.16f, 6.14f, 0.638f, 0.69f} : Alone{0.02f, 6.13f, 0.691f, 0.61f};     // 256 x 256
+
+    // 128 x 192, 4 bits: one round of up to 256 tiles where 256 x 128 leaves units idle.  (Its fit times 1.05: a draw goes to
+    // the tiles that it is compared with, whose fits are of more shapes.)
+    static constexpr Alone middle = {1.70f, 4.55f, 0.347f, 0.98f};
 
     const float stages = (float)(BITS == 4 ? (K + 127) / 128 : (K + 63) / 64);
     Plan best = Plan::kCount;
@@ -140,6 +147,7 @@ inline Plan choose(int64_t M, int64_t N, int64_t K)
         for (const Paired &c : paired4) paired(c);
         for (const Small &c : small4) small(c);
         alone(Plan::kTile256x128w8, 256, 128, w8);
+        alone(Plan::kTile128x192, 128, 192, middle);
     } else {
         for (const Paired &c : paired8) paired(c);
         for (const Small &c : small8) small(c);

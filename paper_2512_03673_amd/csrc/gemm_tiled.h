@@ -30,6 +30,11 @@
 // a unit, us: 4 bits M4608 x N3072 x K12288 73.1 / 71.1 -> 60.8, K3072 23.9 / 23.2 -> 20.2, N9216 70.2 / 69.7 -> 66.1; 8 bits
 // M4608 x N3072 x K12288 137.5 / 132.9 -> 126.  (A ring of two: 68.6 -> 80.6.  A 288 x 192 tile fills 256 units exactly at M4608 x N3072,
 // where 256 x 256 leaves 40 idle, and is slower, 72.5 against 68.6: idle units leave their power to the others.)
+//
+// Products of one round or less are bound by a lone tile's walk along K, 0.3 to 0.4 us a stage whatever the ring's depth or how far
+// ahead fragments are read (a whole stage instead of a step: no difference), so the tile that spreads such a product over the most
+// units wins: 128 x 192, us: 4 bits M512 x N12288 x K3072 14.9 -> 13.8, M578 x N9408 x K9600 34.2 -> 31.0; 8 bits
+// M854 x N6464 x K1024 11.0 -> 10.1, M1803 x N5056 x K4992 49.2 -> 46.2.
 #pragma once
 #include "gemm_common.h"
 

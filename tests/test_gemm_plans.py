@@ -15,7 +15,8 @@ from gpu_util import bf16_to_host_bits, bf16_ulp_diff, bits_to_f64, check_output
 from paper_2512_03673_amd import workloads as wl
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2512_03673_amd", "csrc")
-PLANS = ("192x192", "256x128", "256x128w8", "128x128", "64x64", "split32x64", "split32x32", "split16x32", "split16x16", "256x256")
+PLANS = ("192x192", "256x128", "256x128w8", "128x128", "64x64", "split32x64", "split32x32", "split16x32", "split16x16", "256x256",
+         "128x192")
 
 # (M, N, K): the tile of the 4-bit layer, of the 8-bit one
 SHAPES = {
@@ -25,10 +26,11 @@ SHAPES = {
     (1, 9216, 3072): ("split32x64", "split16x32"), (65, 4095, 1056): ("split32x64", "split32x64"),
     (65, 4097, 160): ("64x64", "split32x64"), (191, 2050, 32): ("64x64", "64x64"), (1024, 1025, 1056): ("64x64", "64x64"),
     (511, 4097, 96): ("64x64", "128x128"), (1023, 3070, 512): ("128x128", "128x128"), (513, 6100, 1056): ("128x128", "128x128"),
-    (513, 6100, 3072): ("128x128", "128x128"), (511, 12281, 544): ("256x128w8", "256x128"), (2300, 2300, 352): ("256x128w8", "128x128"),
-    (1537, 3070, 672): ("256x128w8", "256x128"), (4608, 3072, 128): ("128x128", "128x128"), (4601, 3068, 480): ("256x128", "256x256"),
+    (513, 6100, 3072): ("128x128", "128x128"), (511, 12281, 544): ("256x128w8", "128x192"), (2300, 2300, 352): ("256x128w8", "128x192"),
+    (1537, 3070, 672): ("256x128w8", "128x192"), (4608, 3072, 128): ("128x128", "128x128"), (4601, 3068, 480): ("256x128", "256x256"),
     (3001, 3070, 160): ("192x192", "192x192"), (2050, 4090, 1056): ("192x192", "192x192"), (3071, 4090, 1056): ("256x256", "256x256"),
-    (3100, 4088, 1056): ("256x256", "256x256"),
+    (3100, 4088, 1056): ("256x256", "256x256"), (4696, 1201, 480): ("256x128w8", "256x128"), (3603, 3333, 224): ("256x128", "256x128"),
+    (509, 12281, 1056): ("128x192", "128x192"), (511, 12280, 1184): ("128x192", "128x192"), (1700, 2688, 768): ("256x128w8", "128x192"),
 }
 
 
