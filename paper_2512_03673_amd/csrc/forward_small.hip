@@ -73,8 +73,7 @@ __global__ __launch_bounds__(64 * kWaves) void forward_small_kernel(const uint16
 #pragma unroll
         for (int e = 0; e < kUnit; ++e) m = fmaxf(m, fabsf(v[i][e]));
         m = item % spans * 64 + lane < units ? m : 0.0f;
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
+        m = max_of_64(m);
         if (lane == 0) item_max[item] = m;
     }
     __syncthreads();

@@ -134,8 +134,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 256 ? 2 : 1) void rotquant_kernel(c
 
     // row absmax: butterfly over the row's lanes of this wavefront, then across the row's wavefronts through LDS
     if constexpr (RPW == 1) {
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) amax = fmaxf(amax, __shfl_xor(amax, m, 64));
+        amax = max_of_64(amax);
         if (T > 64) {
             if ((tid & 63) == 0) s_part[tid >> 6] = amax;
             __syncthreads();
@@ -146,8 +145,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK <= 256 ? 2 : 1) void rotquant_kernel(c
             amax = a;
         }
     } else {
-#pragma unroll
-        for (int m = 8; m >= 1; m >>= 1) amax = fmaxf(amax, __shfl_xor(amax, m, 64));
+        amax = max_of_16(amax);
         if ((tid & 15) == 0) s_part[(tid >> 6) * RPW + rib] = amax;
         __syncthreads();
         float a = s_part[rib];
@@ -284,8 +282,7 @@ __global__ __launch_bounds__(256, 2) void rotated_absmax_kernel(const uint16_t *
         for (int e = 0; e < kUnit; ++e) m = fmaxf(m, fabsf(v[e]));
         amax = ok ? fmaxf(amax, m) : amax;
     }
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) amax = fmaxf(amax, __shfl_xor(amax, m, 64));
+    amax = max_of_64(amax);
     if (lane == 0) out[row] = KIND == 0 ? amax : amax * group_norm<G>();
 }
 
