@@ -12,7 +12,7 @@
 // (`block`: prologue and epilogue of a tile; `latency`, `lone`: a stage of a tile that has the unit to itself; `rate`, `pair`: a
 // stage of a full unit.)  The constants are robust fits: of the first kind to 320 launches on shapes drawn over M 1 ... 8000,
 // N 32 ... 12288, K 64 ... 15360, of the other two to 230 over M 256 ... 16896, N 512 ... 12288, K 256 ... 15360 with at least
-// 1.2e10 products (128 x 192: to 220 with M 64 ... 8000 and 3e9 to 8e10 products).  On the larger shapes the tile taken costs
+// 1.2e10 products, the large 4-bit tiles also to 120 such with operands that change from launch to launch (128 x 192: to 220 with M 64 ... 8000 and 3e9 to 8e10 products).  On the larger shapes the tile taken costs
 // 0.5 % more on average than the best of them would, on the others 1 to 2 %.
 #pragma once
 #include <stdint.h>
@@ -70,6 +70,22 @@ struct Alone {
     float fixed, block, rate, idle;
 };
 
+struct Cut {        // a round of parts of 256 x 256 tiles
+    float block, rate;
+};
+
+// A 256 x 256 tile of 4-bit codes has a compute unit to itself, so a last round that few of an XCD's 32 units have a tile of
+// keeps the others waiting for a whole tile.  Such tiles are cut: into halves where they give every unit at most one, into
+// quarters where those do (us, whole / cut: M4608 x N12288 x K3072, 12 left over, 87.6 / 85.4; M16896 x N3072 x K12288, 3 left over,
+// 275.5 / 260.5; over 16 and 19 drawn shapes 6 and 14 % - more of them would take two rounds of parts and lose).  After
+// many rounds the units no longer finish together and parts only cost (M16896 x N12288 x K3072, 12 rounds, 296 / 305).  8-bit
+// products gain nothing there over 192 x 192 tiles.  Parts a tile is cut into, 1 if none is; `per_xcd` = tiles of an XCD.
+inline int parts_of_last_tiles(int64_t per_xcd)
+{
+    const int64_t rest = per_xcd % 32;
+    return per_xcd < 32 || per_xcd >= 5 * 32 || rest == 0 || rest > 16 ? 1 : rest > 8 ? 2 : 4;
+}
+
 // The two large tiles of which two share a compute unit.  Blocks are dealt to the 256 units as slots free up, so a launch lasts
 // about as long as the busiest unit's share, ceil(tiles / 256) blocks of TM x TN products each; the square tile
 // moves fewer operand bytes per product and takes the ties.
@@ -101,8 +117,8 @@ inline Plan choose(int64_t M, int64_t N, int64_t K)
         {Plan::kSplit16x16, 16, 16, 16, 2.22f, 0.78f, 0.255f, 0.0243f},
     };
     static constexpr Paired paired4[] = {
-        {Plan::kTile192x192, 192, 192, 3.62f, 2.92f, 0.719f, 0.592f},
-        {Plan::kTile256x128, 256, 128, 3.65f, 2.60f, 0.686f, 0.582f},
+        {Plan::kTile192x192, 192, 192, 3.62f, 2.92f, 0.745f, 0.592f},
+        {Plan::kTile256x128, 256, 128, 3.65f, 2.60f, 0.700f, 0.582f},
         {Plan::kTile128x128, 128, 128, 2.96f, 1.36f, 0.479f, 0.280f},
     };
     static constexpr Paired paired8[] = {
@@ -112,7 +128,7 @@ inline Plan choose(int64_t M, int64_t N, int64_t K)
         {Plan::kTile128x192, 128, 192, 3.08f, 2.44f, 0.512f, 0.269f},
     };
     static constexpr Alone w8 = {2.00f, 3.84f, 0.419f, 0.80f};                                                  // 256 x 128, 4 bits
-    static constexpr Alone whole = BITS == 4 ? Alone{1.16f, 6.14f, 0.638f, 0.69f} : Alone{0.02f, 6.13f, 0.691f, 0.61f};     // 256 x 256
+    static constexpr Alone whole = BITS == 4 ? Alone{1.10f, 5.83f, 0.606f, 0.69f} : Alone{0.02f, 6.13f, 0.691f, 0.61f};     // 256 x 256
 
     // 128 x 192, 4 bits: one round of up to 256 tiles where 256 x 128 leaves units idle.  (Its fit times 1.05: a draw goes to
     // the tiles that it is compared with, whose fits are of more shapes.)
@@ -154,7 +170,16 @@ inline Plan choose(int64_t M, int64_t N, int64_t K)
     }
     // With only a few stages a block that is alone on its unit cannot hide its first loads and its stores behind another one
     // (M7557 x N3773 x K640: 24.6 us against 22.9 with 256 x 128 tiles), which the prediction knows nothing of.
-    if (stages >= 8.0f) alone(Plan::kTile256x256, 256, 256, whole);
+    if (stages >= 8.0f) {
+        const int64_t per_xcd = (tiles(256, 256) + 7) / 8;
+        const int parts = BITS == 4 ? parts_of_last_tiles(per_xcd) : 1;
+        if (parts == 1) {
+            alone(Plan::kTile256x256, 256, 256, whole);
+        } else {      // full rounds and one of parts
+            const Cut c = parts == 2 ? Cut{3.90f, 0.340f} : Cut{3.30f, 0.240f};
+            consider(Plan::kTile256x256, whole.fixed + (float)(per_xcd / 32) * (whole.block + whole.rate * stages) + c.block + c.rate * stages);
+        }
+    }
     return best;
 }
 

@@ -71,23 +71,32 @@ struct Stage {
     static_assert(kLds * (T::OCC * 4 / T::NW) <= 160 * 1024, "blocks per compute unit");
 };
 
+struct Product {      // what every block of a launch is told
+    const uint8_t *Xq;
+    const float *x_scale;
+    const uint8_t *Wq;
+    const float *w_scale;
+    const uint16_t *bias;
+    int M, N, K;
+    uint16_t *Y;
+    int32_t *acc_out;
+};
+
+// The tile of the output from row m0 and column n0 on; `lds` holds Stage<C, T>::kLds bytes.
 template <class C, bool RAW, class T>
-__global__ __launch_bounds__(T::kThreads, T::OCC) void gemm_tiled_kernel(
-    const uint8_t *__restrict__ Xq, const float *__restrict__ x_scale, const uint8_t *__restrict__ Wq,
-    const float *__restrict__ w_scale, const uint16_t *__restrict__ bias, int M, int N, int K,
-    uint16_t *__restrict__ Y, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n)
+__device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, uint8_t *lds)
 {
     using St = Stage<C, T>;
     constexpr int TM = T::TM, TN = T::TN, WM = T::WM, WN = T::WN, XF = T::XF, WF = T::WF, NF = T::NF, NW = T::NW, NS = T::NS;
     constexpr int kMfmas = T::kMfmas, kEpiPitch = T::kEpiPitch, kLoads = St::kLoads, kMaxLoads = St::kMaxLoads;
     constexpr bool kUneven = St::kExtra != 0;
-    // Statically sized: above 64 KB a dynamic allocation would need a per-device function attribute set
-    // from the host before the first launch, i.e. hidden library state; a static one needs nothing.
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[St::kLds];
+    const uint8_t *const Xq = p.Xq, *const Wq = p.Wq;
+    const float *const x_scale = p.x_scale, *const w_scale = p.w_scale;
+    const uint16_t *const bias = p.bias;
+    const int M = p.M, N = p.N, K = p.K;
+    uint16_t *const Y = p.Y;
+    int32_t *const acc_out = p.acc_out;
 
-    int tm, tn;
-    if (!tile_of_block<T::kBandRows>(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
-    const int m0 = tm * TM, n0 = tn * TN;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm0 = (wave % T::WGM) * WM, wn0 = (wave / T::WGM) * WN;
     const int KS = C::stages(K);   // the last one is zero-padded
@@ -363,6 +372,46 @@ __global__ __launch_bounds__(T::kThreads, T::OCC) void gemm_tiled_kernel(
     }
 }
 
+// Statically sized LDS: above 64 KB a dynamic allocation would need a per-device function attribute set from the host
+// before the first launch, i.e. hidden library state; a static one needs nothing.
+template <class C, bool RAW, class T>
+__global__ __launch_bounds__(T::kThreads, T::OCC) void gemm_tiled_kernel(
+    const uint8_t *__restrict__ Xq, const float *__restrict__ x_scale, const uint8_t *__restrict__ Wq,
+    const float *__restrict__ w_scale, const uint16_t *__restrict__ bias, int M, int N, int K,
+    uint16_t *__restrict__ Y, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n)
+{
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[Stage<C, T>::kLds];
+    int tm, tn;
+    if (!tile_of_block<T::kBandRows>(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
+    tile_product<C, RAW, T>(Product{Xq, x_scale, Wq, w_scale, bias, M, N, K, Y, acc_out}, tm * T::TM, tn * T::TN, lds);
+}
+
+// Tiles of T, of which each XCD's last ones (from its `whole`-th on) are cut into `parts` of shape P: a block of T takes a
+// compute unit to itself, so a last round that few tiles share would keep most of the chip waiting for a whole tile.
+template <class C, bool RAW, class T, class P>
+__global__ __launch_bounds__(T::kThreads, T::OCC) void gemm_cut_kernel(
+    const uint8_t *__restrict__ Xq, const float *__restrict__ x_scale, const uint8_t *__restrict__ Wq,
+    const float *__restrict__ w_scale, const uint16_t *__restrict__ bias, int M, int N, int K,
+    uint16_t *__restrict__ Y, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, int whole)
+{
+    constexpr int kM = T::TM / P::TM, kN = T::TN / P::TN, kParts = kM * kN;
+    static_assert(T::kThreads == P::kThreads && kM * P::TM == T::TM && kN * P::TN == T::TN, "parts of a tile");
+    constexpr int kLds = Stage<C, T>::kLds > Stage<C, P>::kLds ? Stage<C, T>::kLds : Stage<C, P>::kLds;
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[kLds];
+    const Product p{Xq, x_scale, Wq, w_scale, bias, M, N, K, Y, acc_out};
+    const int xcd = blockIdx.x % kNumXcd, turn = blockIdx.x / kNumXcd;
+    int tm, tn;
+    if (turn < whole) {
+        if (!tile_of_block<T::kBandRows>(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
+        tile_product<C, RAW, T>(p, tm * T::TM, tn * T::TN, lds);
+    } else {
+        const int part = (turn - whole) % kParts;
+        if (!tile_of_block<T::kBandRows>((whole + (turn - whole) / kParts) * kNumXcd + xcd, tiles_m, tiles_n, tm, tn)) return;
+        const int m0 = tm * T::TM + part % kM * P::TM, n0 = tn * T::TN + part / kM * P::TN;
+        if (m0 < M && n0 < N) tile_product<C, RAW, P>(p, m0, n0, lds);
+    }
+}
+
 template <class C, class T>
 hipError_t launch_tiled(const Operands &o)
 {
@@ -376,6 +425,22 @@ hipError_t launch_tiled(const Operands &o)
         return hipGetLastError();
     };
     return o.acc ? go(gemm_tiled_kernel<C, true, T>) : go(gemm_tiled_kernel<C, false, T>);
+}
+
+// `cut` tiles of every XCD's share of T's go as parts of shape P.
+template <class C, class T, class P>
+hipError_t launch_cut(const Operands &o, int cut)
+{
+    const int tiles_m = (o.M + T::TM - 1) / T::TM, tiles_n = (o.N + T::TN - 1) / T::TN;
+    if ((int64_t)tiles_m * tiles_n > (1 << 28)) return hipErrorInvalidValue;   // the kernel counts parts in 32 bits
+    const int per_xcd = (tiles_m * tiles_n + kNumXcd - 1) / kNumXcd, whole = per_xcd - cut;
+    const int grid = (whole + cut * (T::TM / P::TM) * (T::TN / P::TN)) * kNumXcd;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(T::kThreads), 0, o.stream, (const uint8_t *)o.Xq, o.x_scale, (const uint8_t *)o.Wq,
+                           o.w_scale, (const uint16_t *)o.bias, o.M, o.N, o.K, (uint16_t *)o.Y, o.acc, tiles_m, tiles_n, whole);
+        return hipGetLastError();
+    };
+    return o.acc ? go(gemm_cut_kernel<C, true, T, P>) : go(gemm_cut_kernel<C, false, T, P>);
 }
 
 }  // namespace gemm

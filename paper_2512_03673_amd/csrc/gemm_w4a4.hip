@@ -83,6 +83,18 @@ struct Codes4 {
     }
 };
 
+hipError_t launch_256x256(const gemm::Operands &o)
+{
+    using gemm::Tile;
+    typedef Tile<2, 4, 4, 2, 3, 2, 4> Whole;
+    const int64_t per_xcd = ((int64_t)((o.M + 255) / 256) * ((o.N + 255) / 256) + 7) / 8;
+    switch (gemm::parts_of_last_tiles(per_xcd)) {
+        case 2: return gemm::launch_cut<Codes4, Whole, Tile<4, 2, 2, 2, 3, 2, 4>>(o, (int)(per_xcd % 32));
+        case 4: return gemm::launch_cut<Codes4, Whole, Tile<4, 2, 1, 2, 4, 2, 4>>(o, (int)(per_xcd % 32));
+        default: return gemm::launch_tiled<Codes4, Whole>(o);
+    }
+}
+
 hipError_t launch_plan(gemm::Plan plan, const gemm::Operands &o)
 {
     using gemm::Plan;
@@ -97,7 +109,7 @@ hipError_t launch_plan(gemm::Plan plan, const gemm::Operands &o)
         case Plan::kSplit32x32: return gemm::launch_small<gemm::Small4, 2, 2, 4, 3>(o);
         case Plan::kSplit16x32: return gemm::launch_small<gemm::Small4, 1, 2, 8, 4>(o);
         case Plan::kSplit16x16: return gemm::launch_small<gemm::Small4, 1, 1, 16, 4>(o);
-        case Plan::kTile256x256: return gemm::launch_tiled<Codes4, Tile<2, 4, 4, 2, 3, 2, 4>>(o);
+        case Plan::kTile256x256: return launch_256x256(o);
         case Plan::kTile128x192: return gemm::launch_tiled<Codes4, Tile<2, 2, 2, 3, 4, 1, 8>>(o);
         default: return hipErrorInvalidValue;
     }

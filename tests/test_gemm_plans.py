@@ -28,9 +28,12 @@ SHAPES = {
     (511, 4097, 96): ("64x64", "128x128"), (1023, 3070, 512): ("128x128", "128x128"), (513, 6100, 1056): ("128x128", "128x128"),
     (513, 6100, 3072): ("128x128", "128x128"), (511, 12281, 544): ("256x128w8", "128x192"), (2300, 2300, 352): ("256x128w8", "128x192"),
     (1537, 3070, 672): ("256x128w8", "128x192"), (4608, 3072, 128): ("128x128", "128x128"), (4601, 3068, 480): ("256x128", "256x256"),
-    (3001, 3070, 160): ("192x192", "192x192"), (2050, 4090, 1056): ("192x192", "192x192"), (3071, 4090, 1056): ("256x256", "256x256"),
+    (3001, 3070, 160): ("192x192", "192x192"), (2050, 4090, 1056): ("256x256", "192x192"), (3071, 4090, 1056): ("256x256", "256x256"),
     (3100, 4088, 1056): ("256x256", "256x256"), (4696, 1201, 480): ("256x128w8", "256x128"), (3603, 3333, 224): ("256x128", "256x128"),
     (509, 12281, 1056): ("128x192", "128x192"), (511, 12280, 1184): ("128x192", "128x192"), (1700, 2688, 768): ("256x128w8", "128x192"),
+    # more than a round of 256 x 256 tiles, the last ones in quarters and in halves
+    (4100, 4600, 928): ("256x256", "128x128"), (4351, 4601, 928): ("256x256", "128x128"), (4350, 5120, 928): ("256x256", "256x128"),
+    (4360, 4870, 928): ("256x256", "256x128"),
 }
 
 
@@ -44,14 +47,14 @@ def test_shapes_take_the_tiles_they_are_meant_for(tmp_path):
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, "-o", exe, str(src)], check=True)
     # the benchmark's layers and the extremes of the argument range stay on the large tiles
     large = {(4608, 3072 * 4, 3072): "192x192", (16896, 12288, 3072): "192x192", (16896, 3072, 12288): "192x192", (4608, 3072, 12288): "256x256",
-             (4608, 3072, 15360): "256x256", (2 ** 31 - 1, 2 ** 31 - 1, 65536): "192x192"}
+             (4608, 3072, 15360): "256x256", (2 ** 31 - 1, 2 ** 31 - 1, 65536): "192x192"}       # 8 bits; at 4 bits all of them 256 x 256
     shapes = list(SHAPES) + list(large)
     out = subprocess.run([exe] + [str(d) for s in shapes for d in s], check=True, capture_output=True, text=True).stdout.split()
     got = {s: (PLANS[int(out[2 * i])], PLANS[int(out[2 * i + 1])]) for i, s in enumerate(shapes)}
     for s, (p4, p8) in SHAPES.items():
         assert got[s] == (p4, p8), s
     for s, p in large.items():
-        assert got[s] == (p, p), s
+        assert got[s] == ("256x256", p), s
     assert {p for p, _ in SHAPES.values()} == set(PLANS) and {p for _, p in SHAPES.values()} == set(PLANS) - {"256x128w8"}
 
 
