@@ -79,7 +79,8 @@ struct Cut {        // a round of parts of 256 x 256 tiles
 // quarters where those do (us, whole / cut: M4608 x N12288 x K3072, 12 left over, 87.6 / 85.4; M16896 x N3072 x K12288, 3 left over,
 // 275.5 / 260.5; over 16 and 19 drawn shapes 6 and 14 % - more of them would take two rounds of parts and lose).  After
 // many rounds the units no longer finish together and parts only cost (M16896 x N12288 x K3072, 12 rounds, 296 / 305).  8-bit
-// products gain nothing there over 192 x 192 tiles.  Parts a tile is cut into, 1 if none is; `per_xcd` = tiles of an XCD.
+// products gain nothing there over 192 x 192 tiles.  (All with operands that change from launch to launch; on one set of buffers,
+// which the Infinity Cache holds, M4608 x N12288 x K3072 takes 84.5 us in halves and 80.4 with 192 x 192 tiles.)  Parts a tile is cut into, 1 if none is; `per_xcd` = tiles of an XCD.
 inline int parts_of_last_tiles(int64_t per_xcd)
 {
     const int64_t rest = per_xcd % 32;
