@@ -8,6 +8,7 @@
 
 #include <ATen/ops/empty.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "convrot.h"
@@ -126,9 +127,12 @@ int call(F f)
     return status;
 }
 
+// An error inside torch, a failed allocation above all, reaches the caller as it would from torch's own functions: torch's
+// exception types and messages, and a Python error that passed through its dispatcher as it was raised.
 template <class F>
 PyObject *guarded(Py_ssize_t n, Py_ssize_t expected, F f)
 {
+    HANDLE_TH_ERRORS
     if (n != expected) {
         PyErr_Format(PyExc_TypeError, "need %zd arguments, got %zd", expected, n);
         return nullptr;
@@ -136,10 +140,9 @@ PyObject *guarded(Py_ssize_t n, Py_ssize_t expected, F f)
     try {
         return f();
     } catch (const Failed &) {
-    } catch (const std::exception &e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
+        return nullptr;
     }
-    return nullptr;
+    END_HANDLE_TH_ERRORS
 }
 
 // (X, Wq, w_scale, group, Y, workspace, bias, stream) -> Y

@@ -3,6 +3,8 @@ import os
 
 import pytest
 import torch
+from torch._subclasses.fake_tensor import FakeTensorMode
+from torch.utils._python_dispatch import TorchDispatchMode
 
 
 @pytest.fixture(scope="module")
@@ -24,6 +26,43 @@ def test_rejects_what_is_no_gpu_tensor(cr):
             f(*args)
         with pytest.raises(TypeError, match="need a torch tensor"):
             f(*[7] * len(args))
+
+
+class _Refuses(TorchDispatchMode):
+    """Every new tensor fails with `error`."""
+
+    def __init__(self, error):
+        super().__init__()
+        self.error = error
+
+    def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+        if func is torch.ops.aten.empty.memory_format:
+            raise self.error
+        return func(*args, **(kwargs or {}))
+
+
+@pytest.mark.parametrize("error", (torch.OutOfMemoryError("no room"), KeyError("who")), ids=lambda e: type(e).__name__)
+def test_an_allocation_that_fails_keeps_its_exception(cr, error):
+    with FakeTensorMode():      # tensors that say that they are on a GPU
+        x = torch.empty(4, 32, dtype=torch.bfloat16, device="cuda")
+        q, s = torch.empty(3072, dtype=torch.uint8, device="cuda"), torch.empty(4, device="cuda")
+    for f, args in ((cr.convlinear4bit_forward, (x, q, s, 16)), (cr.convlinear8bit_forward, (x, q, s, 16)), (cr.convrot_prepare_weight, (x, 16)),
+                    (cr.convrot_rotquant_act8, (x, 16)), (cr.convrot_w4a4_gemm_dequant, (q, s, q, s, 32)),
+                    (cr.convrot_w8a8_gemm_dequant, (q, s, q, s, 32))):
+        with pytest.raises(type(error)) as caught, _Refuses(error):
+            f(*args)
+        assert caught.value is error
+
+
+@pytest.mark.gpu
+def test_out_of_device_memory_is_torchs_own_exception(cr):
+    n = 1 << 20                 # an output of 2 TB
+    x, s = torch.zeros(n, 32, dtype=torch.bfloat16, device="cuda"), torch.ones(n, device="cuda")
+    q = torch.zeros(cr.packed_bytes(n, 32), dtype=torch.uint8, device="cuda")
+    with pytest.raises(torch.OutOfMemoryError, match="out of memory"):
+        cr.convlinear4bit_forward(x, q, s, 16)
+    with pytest.raises(torch.OutOfMemoryError, match="out of memory"):
+        cr.convrot_w4a4_gemm_dequant(q, s, q, s, 32)
 
 
 @pytest.mark.gpu
