@@ -175,6 +175,14 @@ def _codes(t: torch.Tensor, nbytes: int, name: str) -> None:
         raise ValueError(f"{name}: need {nbytes} bytes (convrot_packed_bytes), got {t.numel()}")
 
 
+def _written(t: torch.Tensor, dtype: torch.dtype, rows: int, cols: int, name: str) -> None:
+    """Memory that a call writes: of `dtype` or, as raw memory, of integers; as long as the matrix (csrc/torch_calls.cpp)."""
+    if not (t.is_cuda and (t.dtype == dtype or not (t.is_floating_point() or t.is_complex() or t.dtype == torch.bool)) and t.is_contiguous()):
+        raise TypeError(f"{name}: need a contiguous {dtype} tensor on the GPU")
+    if t.nbytes < rows * cols * dtype.itemsize:
+        raise ValueError(f"{name}: need {rows * cols * dtype.itemsize} bytes, got {t.nbytes}")
+
+
 def convrot_prepare_weight(W: torch.Tensor, group: int, Wq: Optional[torch.Tensor] = None,
                            w_scale: Optional[torch.Tensor] = None, stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
     """W bf16 [N, K] -> (Wq uint8 [packed_bytes(N, K)], w_scale f32 [N])."""
@@ -192,6 +200,7 @@ def convrot_unpack_codes(Xq: torch.Tensor, rows: int, K: int, codes: Optional[to
     """4-bit code matrix -> int8 codes [rows, K] (gate / debug export)."""
     _codes(Xq, packed_bytes(rows, K), "Xq")
     codes = torch.empty((rows, K), dtype=torch.int8, device=Xq.device) if codes is None else codes
+    _written(codes, torch.int8, rows, K, "codes")
     _check(load().convrot_unpack_codes(_ptr(Xq), rows, K, _ptr(codes), _stream(stream)), "convrot_unpack_codes")
     return codes
 
@@ -208,6 +217,7 @@ def convrot_w4a4_gemm_i32(Xq: torch.Tensor, Wq: torch.Tensor, M: int, N: int, K:
     """Code matrices of [M, K] and [N, K] -> raw int32 accumulators [M, N] (gate / debug export)."""
     _codes(Xq, packed_bytes(M, K), "Xq"); _codes(Wq, packed_bytes(N, K), "Wq")
     acc = torch.empty((M, N), dtype=torch.int32, device=Xq.device) if acc is None else acc
+    _written(acc, torch.int32, M, N, "acc")
     _check(load().convrot_w4a4_gemm_i32(_ptr(Xq), _ptr(Wq), M, N, K, _ptr(acc), _stream(stream)),
            "convrot_w4a4_gemm_i32")
     return acc
@@ -235,6 +245,7 @@ def convrot_rotated_absmax(X: torch.Tensor, group: int, kind: int, out: Optional
     _dev(X, torch.bfloat16, "X")
     M, K = X.shape
     out = torch.empty((M,), dtype=torch.float32, device=X.device) if out is None else out
+    _written(out, torch.float32, M, 1, "out")
     _check(load().convrot_rotated_absmax(_ptr(X), M, K, group, kind, _ptr(out), _stream(stream)),
            "convrot_rotated_absmax")
     return out
@@ -265,6 +276,7 @@ def convrot_w8a8_gemm_i32(Xq: torch.Tensor, Wq: torch.Tensor, M: int, N: int, K:
     """8-bit code matrices of [M, K] and [N, K] -> raw int32 accumulators [M, N] (gate / debug export)."""
     _codes(Xq, packed_bytes8(M, K), "Xq"); _codes(Wq, packed_bytes8(N, K), "Wq")
     acc = torch.empty((M, N), dtype=torch.int32, device=Xq.device) if acc is None else acc
+    _written(acc, torch.int32, M, N, "acc")
     _check(load().convrot_w8a8_gemm_i32(_ptr(Xq), _ptr(Wq), M, N, K, _ptr(acc), _stream(stream)),
            "convrot_w8a8_gemm_i32")
     return acc

@@ -69,6 +69,7 @@ void matrix(const at::Tensor &t, const char *name, int64_t &rows, int64_t &cols)
 int64_t length(const at::Tensor &t, const char *name)
 {
     if (t.dim() < 1) fail(PyExc_ValueError, "%s: need a vector, got %lld dimensions", name, (long long)t.dim());
+    if (t.numel() < t.size(0)) fail(PyExc_ValueError, "%s: need a vector, got %lld elements in %lld rows", name, (long long)t.numel(), (long long)t.size(0));
     return t.size(0);
 }
 
@@ -95,26 +96,65 @@ at::Tensor new_on(const at::Tensor &like, at::IntArrayRef shape, at::ScalarType 
     return at::empty(shape, at::TensorOptions().dtype(type).device(like.device()));
 }
 
+// Memory of the caller's that a call writes `bytes` bytes of `type` to.  The kernels take its address and nothing else, so it is
+// looked at here: on the GPU, contiguous and long enough, of that type or, as raw memory, of integers.
+const at::Tensor &written(PyObject *o, at::ScalarType type, const char *type_name, int64_t bytes, const char *name)
+{
+    const at::Tensor &t = tensor(o, name);
+    const bool fits = t.scalar_type() == type || c10::isIntegralType(t.scalar_type(), false);
+    if (!(t.is_cuda() && fits && t.is_contiguous())) {
+        PyErr_Format(PyExc_TypeError, "%s: need a contiguous %s tensor on the GPU", name, type_name);
+        throw Failed{};
+    }
+    if ((int64_t)t.nbytes() < bytes) fail(PyExc_ValueError, "%s: need %lld bytes, got %lld", name, bytes, (long long)t.nbytes());
+    return t;
+}
+
+// Scratch memory of the caller's: of any type; the library looks at its length, numel() bytes.
+const at::Tensor &scratch(PyObject *o, const char *name)
+{
+    const at::Tensor &t = tensor(o, name);
+    if (!(t.is_cuda() && t.is_contiguous())) fail(PyExc_TypeError, "%s: need a contiguous tensor on the GPU", name);
+    return t;
+}
+
+// Bytes of a matrix; 0 for one so large that the library refuses it.
+int64_t bytes_of(int64_t rows, int64_t cols, int64_t each) { return rows <= INT32_MAX && cols <= INT32_MAX ? rows * cols * each : 0; }
+
 // An output: the caller's tensor, or a new one.
 struct Out {
     PyObject *given;
     at::Tensor made;
     void *ptr;
-    Out(PyObject *o, const char *name) : given(o), ptr(o == Py_None ? nullptr : tensor(o, name).data_ptr()) {}
-    void make(const at::Tensor &like, at::IntArrayRef shape, at::ScalarType type)
-    {
-        made = new_on(like, shape, type);
-        ptr = made.data_ptr();
-    }
+    Out(PyObject *o, const at::Tensor &checked) : given(o), ptr(checked.data_ptr()) {}
+    explicit Out(at::Tensor t) : given(nullptr), made(std::move(t)), ptr(made.data_ptr()) {}
     PyObject *release()
     {
-        if (given != Py_None) {
+        if (given) {
             Py_INCREF(given);
             return given;
         }
         return THPVariable_Wrap(std::move(made));
     }
 };
+
+Out out_bf16(PyObject *o, const at::Tensor &like, int64_t M, int64_t N, const char *name)
+{
+    if (o != Py_None) return Out(o, written(o, at::kBFloat16, "torch.bfloat16", bytes_of(M, N, 2), name));
+    return Out(new_on(like, {M, N}, at::kBFloat16));
+}
+
+Out out_f32(PyObject *o, const at::Tensor &like, int64_t rows, const char *name)
+{
+    if (o != Py_None) return Out(o, written(o, at::kFloat, "torch.float32", bytes_of(rows, 1, 4), name));
+    return Out(new_on(like, {rows}, at::kFloat));
+}
+
+Out out_codes(PyObject *o, const at::Tensor &like, size_t bytes, const char *name)
+{
+    if (o != Py_None) return Out(o, codes(o, bytes, name));
+    return Out(new_on(like, {(int64_t)bytes}, at::kByte));
+}
 
 // Runs the call without the interpreter lock; an error status goes back as an int for binding.py to raise.
 template <class F>
@@ -155,15 +195,13 @@ PyObject *forward(PyObject *, PyObject *const *a, Py_ssize_t n)
         matrix(X, "X", M, K);
         const int64_t N = length(ws, "w_scale");
         const at::Tensor &Wq = codes(a[1], BITS == 4 ? convrot_packed_bytes(N, K) : convrot_packed_bytes8(N, K), "Wq");
-        Out Y(a[4], "Y");
-        if (a[4] == Py_None) Y.make(X, {M, N}, at::kBFloat16);
+        const at::Tensor *workspace = a[5] == Py_None ? nullptr : &scratch(a[5], "workspace");
+        Out Y = out_bf16(a[4], X, M, N, "Y");
         at::Tensor own;
-        const at::Tensor *workspace = &own;
-        if (a[5] == Py_None) {
+        if (!workspace) {
             const int64_t bytes = BITS == 4 ? convrot_workspace_bytes(M, K) : convrot_workspace_bytes8(M, K);
             own = new_on(X, {std::max<int64_t>(bytes, 256)}, at::kByte);
-        } else {
-            workspace = &tensor(a[5], "workspace");
+            workspace = &own;
         }
         const void *bias = bias_of(a[6], N), *x = X.data_ptr(), *w = Wq.data_ptr();
         const float *s = (const float *)ws.data_ptr();
@@ -208,8 +246,7 @@ PyObject *gemm_dequant(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int64_t M = length(xs, "x_scale"), N = length(ws, "w_scale"), K = integer(a[4]);
         auto bytes = BITS == 4 ? convrot_packed_bytes : convrot_packed_bytes8;
         const at::Tensor &Xq = codes(a[0], bytes(M, K), "Xq"), &Wq = codes(a[2], bytes(N, K), "Wq");
-        Out Y(a[5], "Y");
-        if (a[5] == Py_None) Y.make(Xq, {M, N}, at::kBFloat16);
+        Out Y = out_bf16(a[5], Xq, M, N, "Y");
         const void *bias = bias_of(a[6], N), *x = Xq.data_ptr(), *w = Wq.data_ptr();
         const float *sx = (const float *)xs.data_ptr(), *sw = (const float *)ws.data_ptr();
         void *stream = stream_of(a[7]);
@@ -231,10 +268,7 @@ PyObject *rotquant(PyObject *, PyObject *const *a, Py_ssize_t n)
         int64_t rows, K;
         matrix(X, in_name, rows, K);
         const size_t bytes = BITS == 4 ? convrot_packed_bytes(rows, K) : convrot_packed_bytes8(rows, K);
-        Out Xq(a[2], out_name), scale(a[3], "scale");
-        if (a[2] == Py_None) Xq.make(X, {(int64_t)bytes}, at::kByte);
-        else codes(a[2], bytes, out_name);
-        if (a[3] == Py_None) scale.make(X, {rows}, at::kFloat);
+        Out Xq = out_codes(a[2], X, bytes, out_name), scale = out_f32(a[3], X, rows, "scale");
         const void *x = X.data_ptr();
         const int group = (int)integer(a[1]);
         void *stream = stream_of(a[4]);

@@ -54,6 +54,65 @@ def test_an_allocation_that_fails_keeps_its_exception(cr, error):
         assert caught.value is error
 
 
+BAD_OUTPUTS = {"on the host": (TypeError, lambda t: torch.empty(t.shape, dtype=t.dtype)), "transposed": (TypeError, lambda t: t.t()),
+               "stretched": (TypeError, lambda t: t[:1, :1].expand(t.shape)), "of another type": (TypeError, lambda t: t.to(torch.float64)),
+               "short": (ValueError, lambda t: t[:-1])}
+
+
+def _calls_with_outputs(cr, m, device):
+    """Every call that writes to memory of the caller's: a name, the output as it should be, the call."""
+    def new(*shape, dtype=torch.float32):
+        return torch.zeros(shape, dtype=dtype, device=device)
+    bf16, u8 = torch.bfloat16, torch.uint8
+    x, w, xs, ws = new(m, 32, dtype=bf16), new(8, 32, dtype=bf16), new(m), new(8)
+    q4, q8 = new(cr.packed_bytes(40, 32), dtype=u8), new(cr.packed_bytes8(40, 32), dtype=u8)
+    y, scale = new(m, 8, dtype=bf16), new(m, 1)
+    return [
+        ("Y", y, lambda o: cr.convlinear4bit_forward(x, q4, ws, 16, Y=o)), ("Y", y, lambda o: cr.convlinear8bit_forward(x, q8, ws, 16, Y=o)),
+        ("Y", y, lambda o: cr.convrot_w4a4_gemm_dequant(q4, xs, q4, ws, 32, Y=o)), ("Y", y, lambda o: cr.convrot_w8a8_gemm_dequant(q8, xs, q8, ws, 32, Y=o)),
+        ("scale", scale, lambda o: cr.convrot_rotquant_act(x, 16, x_scale=o)), ("scale", scale, lambda o: cr.convrot_rotquant_act8(x, 16, x_scale=o)),
+        ("scale", new(8, 1), lambda o: cr.convrot_prepare_weight(w, 16, w_scale=o)), ("scale", new(8, 1), lambda o: cr.convrot_prepare_weight8(w, 16, w_scale=o)),
+        ("acc", new(m, 8, dtype=torch.int32), lambda o: cr.convrot_w4a4_gemm_i32(q4, q4, m, 8, 32, acc=o)),
+        ("acc", new(m, 8, dtype=torch.int32), lambda o: cr.convrot_w8a8_gemm_i32(q8, q8, m, 8, 32, acc=o)),
+        ("codes", new(m, 32, dtype=torch.int8), lambda o: cr.convrot_unpack_codes(q4, m, 32, codes=o)),
+        ("out", scale, lambda o: cr.convrot_rotated_absmax(x, 16, 1, out=o)),
+    ]
+
+
+@pytest.mark.parametrize("bad", BAD_OUTPUTS)
+def test_rejects_memory_that_it_cannot_write_to(cr, bad):
+    error, spoil = BAD_OUTPUTS[bad]
+    with FakeTensorMode(allow_non_fake_inputs=True):
+        for name, good, call in _calls_with_outputs(cr, 4, "cuda"):
+            if good.shape[1] == 1 and bad in ("transposed", "stretched"):       # a vector stays one
+                continue
+            with pytest.raises(error, match=f"^{name}: need "):
+                call(spoil(good))
+
+
+def test_rejects_a_workspace_and_a_vector_that_are_none(cr):
+    with FakeTensorMode(allow_non_fake_inputs=True):
+        x, q = torch.empty(4, 32, dtype=torch.bfloat16, device="cuda"), torch.empty(3072, dtype=torch.uint8, device="cuda")
+        s, space = torch.empty(4, device="cuda"), torch.empty(64, 256, dtype=torch.uint8, device="cuda")
+        for forward in (cr.convlinear4bit_forward, cr.convlinear8bit_forward):
+            for bad in ("on the host", "transposed", "stretched"):
+                with pytest.raises(TypeError, match="^workspace: need "):
+                    forward(x, q, s, 16, workspace=BAD_OUTPUTS[bad][1](space))
+            with pytest.raises(ValueError, match="^w_scale: need a vector"):
+                forward(x, q, torch.empty(4, 0, device="cuda"), 16)
+
+
+@pytest.mark.gpu
+def test_writes_to_longer_and_raw_memory(cr):
+    for name, good, call in _calls_with_outputs(cr, 4, "cuda"):
+        size = good.nbytes
+        for o in (torch.full((size + 64,), 0x5A, dtype=torch.uint8, device="cuda"), torch.full((size // 4 + 16,), 0x5A5A5A5A, dtype=torch.int32, device="cuda")):
+            result = call(o)
+            torch.cuda.synchronize()
+            assert any(r is o for r in (result if isinstance(result, tuple) else (result,))), name
+            assert (o.view(torch.uint8)[:size] != 0x5A).any() and (o.view(torch.uint8)[size:] == 0x5A).all(), name
+
+
 @pytest.mark.gpu
 def test_out_of_device_memory_is_torchs_own_exception(cr):
     n = 1 << 20                 # an output of 2 TB
