@@ -158,6 +158,18 @@ def _stream(stream: Optional[torch.cuda.Stream]) -> Optional[int]:
     return s.cuda_stream or None
 
 
+def _new(shape: Tuple[int, ...], dtype: torch.dtype, device: torch.device, stream) -> torch.Tensor:
+    """An output of a call on `stream`: memory of that stream's, kept for torch's current one too (csrc/torch_calls.cpp)."""
+    current = None if stream is None else torch.cuda.current_stream(device)
+    if current is None or current.cuda_stream == stream.cuda_stream:
+        return torch.empty(shape, dtype=dtype, device=device)
+    handle = stream.cuda_stream
+    with torch.cuda.stream(torch.cuda.ExternalStream(handle, device=device) if handle else torch.cuda.default_stream(device)):
+        t = torch.empty(shape, dtype=dtype, device=device)
+    t.record_stream(current)
+    return t
+
+
 def _check(status: int, what: str) -> None:
     if status != 0:
         raise ConvRotError(status, what)
@@ -199,7 +211,7 @@ def convrot_unpack_codes(Xq: torch.Tensor, rows: int, K: int, codes: Optional[to
                          stream=None) -> torch.Tensor:
     """4-bit code matrix -> int8 codes [rows, K] (gate / debug export)."""
     _codes(Xq, packed_bytes(rows, K), "Xq")
-    codes = torch.empty((rows, K), dtype=torch.int8, device=Xq.device) if codes is None else codes
+    codes = _new((rows, K), torch.int8, Xq.device, stream) if codes is None else codes
     _written(codes, torch.int8, rows, K, "codes")
     _check(load().convrot_unpack_codes(_ptr(Xq), rows, K, _ptr(codes), _stream(stream)), "convrot_unpack_codes")
     return codes
@@ -216,7 +228,7 @@ def convrot_w4a4_gemm_i32(Xq: torch.Tensor, Wq: torch.Tensor, M: int, N: int, K:
                           acc: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """Code matrices of [M, K] and [N, K] -> raw int32 accumulators [M, N] (gate / debug export)."""
     _codes(Xq, packed_bytes(M, K), "Xq"); _codes(Wq, packed_bytes(N, K), "Wq")
-    acc = torch.empty((M, N), dtype=torch.int32, device=Xq.device) if acc is None else acc
+    acc = _new((M, N), torch.int32, Xq.device, stream) if acc is None else acc
     _written(acc, torch.int32, M, N, "acc")
     _check(load().convrot_w4a4_gemm_i32(_ptr(Xq), _ptr(Wq), M, N, K, _ptr(acc), _stream(stream)),
            "convrot_w4a4_gemm_i32")
@@ -244,7 +256,7 @@ def convrot_rotated_absmax(X: torch.Tensor, group: int, kind: int, out: Optional
     """Per-row max |R(X)| for kind ROT_NONE / ROT_REGULAR / ROT_SYLVESTER (diagnostic) -> f32 [M]."""
     _dev(X, torch.bfloat16, "X")
     M, K = X.shape
-    out = torch.empty((M,), dtype=torch.float32, device=X.device) if out is None else out
+    out = _new((M,), torch.float32, X.device, stream) if out is None else out
     _written(out, torch.float32, M, 1, "out")
     _check(load().convrot_rotated_absmax(_ptr(X), M, K, group, kind, _ptr(out), _stream(stream)),
            "convrot_rotated_absmax")
@@ -275,7 +287,7 @@ def convrot_w8a8_gemm_i32(Xq: torch.Tensor, Wq: torch.Tensor, M: int, N: int, K:
                           acc: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """8-bit code matrices of [M, K] and [N, K] -> raw int32 accumulators [M, N] (gate / debug export)."""
     _codes(Xq, packed_bytes8(M, K), "Xq"); _codes(Wq, packed_bytes8(N, K), "Wq")
-    acc = torch.empty((M, N), dtype=torch.int32, device=Xq.device) if acc is None else acc
+    acc = _new((M, N), torch.int32, Xq.device, stream) if acc is None else acc
     _written(acc, torch.int32, M, N, "acc")
     _check(load().convrot_w8a8_gemm_i32(_ptr(Xq), _ptr(Wq), M, N, K, _ptr(acc), _stream(stream)),
            "convrot_w8a8_gemm_i32")

@@ -91,9 +91,26 @@ void *stream_of(PyObject *o)
     return p;
 }
 
-at::Tensor new_on(const at::Tensor &like, at::IntArrayRef shape, at::ScalarType type)
+// A tensor that a call on `stream` writes.  Where that is not torch's current stream the memory has to be the call's stream's own:
+// torch hands memory that is freed on a stream to that stream's next tensors at once, so a block of the current stream's may
+// still be in use there when the call writes it, and one that is given back when the call returns may be written there before
+// the call's kernels have run.  An output, which the caller is free to use on the current stream once that has waited for the call, is
+// kept from new tensors until such work is done too.
+at::Tensor new_on(const at::Tensor &like, at::IntArrayRef shape, at::ScalarType type, PyObject *stream, bool output = true)
 {
-    return at::empty(shape, at::TensorOptions().dtype(type).device(like.device()));
+    const auto options = at::TensorOptions().dtype(type).device(like.device());
+    if (stream == Py_None) return at::empty(shape, options);
+    const auto handle = (hipStream_t)stream_of(stream);
+    const auto current = c10::hip::getCurrentHIPStream(like.device().index());
+    if (current.stream() == handle) return at::empty(shape, options);
+    struct Restore {
+        c10::hip::HIPStream s;
+        ~Restore() { c10::hip::setCurrentHIPStream(s); }
+    } restore{current};
+    c10::hip::setCurrentHIPStream(c10::hip::getStreamFromExternal(handle, like.device().index()));
+    at::Tensor t = at::empty(shape, options);
+    if (output) t.record_stream(c10::Stream(c10::Stream::UNSAFE, like.device(), current.id()));
+    return t;
 }
 
 // Memory of the caller's that a call writes `bytes` bytes of `type` to.  The kernels take its address and nothing else, so it is
@@ -138,22 +155,22 @@ struct Out {
     }
 };
 
-Out out_bf16(PyObject *o, const at::Tensor &like, int64_t M, int64_t N, const char *name)
+Out out_bf16(PyObject *o, const at::Tensor &like, int64_t M, int64_t N, PyObject *stream, const char *name)
 {
     if (o != Py_None) return Out(o, written(o, at::kBFloat16, "torch.bfloat16", bytes_of(M, N, 2), name));
-    return Out(new_on(like, {M, N}, at::kBFloat16));
+    return Out(new_on(like, {M, N}, at::kBFloat16, stream));
 }
 
-Out out_f32(PyObject *o, const at::Tensor &like, int64_t rows, const char *name)
+Out out_f32(PyObject *o, const at::Tensor &like, int64_t rows, PyObject *stream, const char *name)
 {
     if (o != Py_None) return Out(o, written(o, at::kFloat, "torch.float32", bytes_of(rows, 1, 4), name));
-    return Out(new_on(like, {rows}, at::kFloat));
+    return Out(new_on(like, {rows}, at::kFloat, stream));
 }
 
-Out out_codes(PyObject *o, const at::Tensor &like, size_t bytes, const char *name)
+Out out_codes(PyObject *o, const at::Tensor &like, size_t bytes, PyObject *stream, const char *name)
 {
     if (o != Py_None) return Out(o, codes(o, bytes, name));
-    return Out(new_on(like, {(int64_t)bytes}, at::kByte));
+    return Out(new_on(like, {(int64_t)bytes}, at::kByte, stream));
 }
 
 // Runs the call without the interpreter lock; an error status goes back as an int for binding.py to raise.
@@ -196,11 +213,11 @@ PyObject *forward(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int64_t N = length(ws, "w_scale");
         const at::Tensor &Wq = codes(a[1], BITS == 4 ? convrot_packed_bytes(N, K) : convrot_packed_bytes8(N, K), "Wq");
         const at::Tensor *workspace = a[5] == Py_None ? nullptr : &scratch(a[5], "workspace");
-        Out Y = out_bf16(a[4], X, M, N, "Y");
+        Out Y = out_bf16(a[4], X, M, N, a[7], "Y");
         at::Tensor own;
         if (!workspace) {
             const int64_t bytes = BITS == 4 ? convrot_workspace_bytes(M, K) : convrot_workspace_bytes8(M, K);
-            own = new_on(X, {std::max<int64_t>(bytes, 256)}, at::kByte);
+            own = new_on(X, {std::max<int64_t>(bytes, 256)}, at::kByte, a[7], false);
             workspace = &own;
         }
         const void *bias = bias_of(a[6], N), *x = X.data_ptr(), *w = Wq.data_ptr();
@@ -246,7 +263,7 @@ PyObject *gemm_dequant(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int64_t M = length(xs, "x_scale"), N = length(ws, "w_scale"), K = integer(a[4]);
         auto bytes = BITS == 4 ? convrot_packed_bytes : convrot_packed_bytes8;
         const at::Tensor &Xq = codes(a[0], bytes(M, K), "Xq"), &Wq = codes(a[2], bytes(N, K), "Wq");
-        Out Y = out_bf16(a[5], Xq, M, N, "Y");
+        Out Y = out_bf16(a[5], Xq, M, N, a[7], "Y");
         const void *bias = bias_of(a[6], N), *x = Xq.data_ptr(), *w = Wq.data_ptr();
         const float *sx = (const float *)xs.data_ptr(), *sw = (const float *)ws.data_ptr();
         void *stream = stream_of(a[7]);
@@ -268,7 +285,7 @@ PyObject *rotquant(PyObject *, PyObject *const *a, Py_ssize_t n)
         int64_t rows, K;
         matrix(X, in_name, rows, K);
         const size_t bytes = BITS == 4 ? convrot_packed_bytes(rows, K) : convrot_packed_bytes8(rows, K);
-        Out Xq = out_codes(a[2], X, bytes, out_name), scale = out_f32(a[3], X, rows, "scale");
+        Out Xq = out_codes(a[2], X, bytes, a[4], out_name), scale = out_f32(a[3], X, rows, a[4], "scale");
         const void *x = X.data_ptr();
         const int group = (int)integer(a[1]);
         void *stream = stream_of(a[4]);

@@ -156,3 +156,69 @@ def test_first_library_call_of_a_process_under_capture(bits):
     r = subprocess.run([sys.executable, "-c", _FIRST_CALL_CAPTURED, root, str(bits)], capture_output=True, text=True,
                        timeout=300)
     assert r.returncode == 0 and "first call captured: ok" in r.stdout, r.stdout + r.stderr
+
+
+def _stream_of_memory(t):
+    """The stream whose memory torch's allocator took the tensor from."""
+    found = [s["stream"] for s in torch.cuda.memory_snapshot() if s["address"] <= t.data_ptr() < s["address"] + s["total_size"]]
+    assert len(found) == 1
+    return found[0]
+
+
+def test_new_tensors_belong_to_the_stream_of_the_call(cr):
+    spec, x, w = layer(1200, 1024, 1000, 16, 41)
+    M, K, N, g = spec.M, spec.K, spec.N, 16
+    X, W, side = to_dev_bf16(x), to_dev_bf16(w), torch.cuda.Stream()
+    Xq, xs = cr.convrot_rotquant_act(X, g)
+    Wq, ws = cr.convrot_prepare_weight(W, g)
+    Xq8, xs8 = cr.convrot_rotquant_act8(X, g)
+    Wq8, ws8 = cr.convrot_prepare_weight8(W, g)
+    calls = [lambda s: cr.convrot_prepare_weight(W, g, stream=s), lambda s: cr.convrot_rotquant_act8(X, g, stream=s),
+             lambda s: cr.convrot_w4a4_gemm_dequant(Xq, xs, Wq, ws, K, stream=s), lambda s: cr.convrot_w8a8_gemm_dequant(Xq8, xs8, Wq8, ws8, K, stream=s),
+             lambda s: cr.convlinear4bit_forward(X, Wq, ws, g, stream=s), lambda s: cr.convlinear8bit_forward(X, Wq8, ws8, g, stream=s),
+             lambda s: cr.convrot_w4a4_gemm_i32(Xq, Wq, M, N, K, stream=s), lambda s: cr.convrot_w8a8_gemm_i32(Xq8, Wq8, M, N, K, stream=s),
+             lambda s: cr.convrot_unpack_codes(Xq, M, K, stream=s), lambda s: cr.convrot_rotated_absmax(X, g, 1, stream=s)]
+    torch.cuda.synchronize()
+    for i, call in enumerate(calls):
+        ref = call(None)
+        ref = ref if isinstance(ref, tuple) else (ref,)
+        torch.cuda.synchronize()
+        for stream in (side, torch.cuda.ExternalStream(side.cuda_stream), torch.cuda.current_stream()):
+            got = call(stream)
+            assert torch.cuda.current_stream() == torch.cuda.default_stream()
+            torch.cuda.synchronize()
+            for a, b in zip(got if isinstance(got, tuple) else (got,), ref):
+                assert _stream_of_memory(a) == stream.cuda_stream, (i, stream)
+                assert a.dtype == torch.uint8 or torch.equal(a, b)       # (a code matrix has bytes past its rows that nobody writes)
+        with torch.cuda.stream(side):
+            got = call(torch.cuda.default_stream())
+        torch.cuda.synchronize()
+        assert all(_stream_of_memory(t) == 0 for t in (got if isinstance(got, tuple) else (got,))), i
+
+
+@pytest.mark.parametrize("bits", (4, 8))
+def test_forward_without_buffers_on_another_stream(cr, bits):
+    # The side stream is held up, so that the call's kernels run after everything that the current stream is given next: new
+    # tensors of the sizes that the call made and gave back, written all over.  Then the current stream is held up while it reads an
+    # output that is given back, and the side stream runs on with new calls.
+    prep, fwd, wsbytes = ((cr.convrot_prepare_weight, cr.convlinear4bit_forward, cr.workspace_bytes) if bits == 4 else
+                          (cr.convrot_prepare_weight8, cr.convlinear8bit_forward, cr.workspace_bytes8))
+    spec, x, w = layer(1200, 1024, 1000, 16, 43)
+    X, side = to_dev_bf16(x), torch.cuda.Stream()
+    wq, ws = prep(to_dev_bf16(w), 16)
+    y_ref = fwd(X, wq, ws, 16).clone()
+    X2 = torch.full_like(X, 2.0)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        with torch.cuda.stream(side):
+            torch.cuda._sleep(20_000_000)
+        y = fwd(X, wq, ws, 16, stream=side)
+        junk = [torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda") for n in 4 * [wsbytes(spec.M, spec.K), 2 * spec.M * spec.N]]
+        torch.cuda.current_stream().wait_stream(side)
+        torch.cuda._sleep(20_000_000)
+        seen = y + 0
+        del y, junk
+        for _ in range(4):
+            fwd(X2, wq, ws, 16, stream=side)
+        torch.cuda.synchronize()
+        assert torch.equal(seen, y_ref)
