@@ -93,14 +93,15 @@ def load() -> ctypes.CDLL:
 
 
 def _load_calls():
-    """The extension module with the per-layer calls, built together with the library."""
+    """The extension module with the per-layer calls, bound to the library that load() opened."""
     global _calls
-    load()
+    lib = load()
     try:
         from . import _torch_calls
     except ImportError as e:
         raise ImportError("the extension module _torch_calls is not built (or built for another torch); "
                           "run `python -m paper_2512_03673_amd.build`") from e
+    _torch_calls.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _torch_calls.names.split()))
     _calls = _torch_calls
     return _calls
 

@@ -51,7 +51,7 @@ def build(verbose: bool = True, extra_flags=(), out: str = LIB) -> str:
 
 
 def build_calls(verbose: bool = True, out: str = CALLS) -> str:
-    """Compile the extension module (host code only; it calls the library next to it through the C ABI)."""
+    """Compile the extension module (host code only; it calls the C ABI of the library that binding.py loads)."""
     import torch    # headers and libraries; neither torch nor a GPU is used
     root = os.path.dirname(torch.__file__)
     lib = os.path.join(root, "lib")
@@ -60,7 +60,7 @@ def build_calls(verbose: bool = True, out: str = CALLS) -> str:
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", os.path.join(ROOT, "include"),
            "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
            "-isystem", sysconfig.get_path("include"), "-o", tmp, os.path.join(CSRC, "torch_calls.cpp"), "-L", lib, "-ltorch_python",
-           "-ltorch_cpu", "-lc10", "-lc10_hip", "-L", HERE, "-lconvrot", "-Wl,-rpath,$ORIGIN"]
+           "-ltorch_cpu", "-lc10", "-lc10_hip"]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)

@@ -15,6 +15,19 @@
 
 namespace {
 
+// The entry points, at the addresses that binding.py looked up in the library it loaded (bind): a process has one libconvrot, with
+// one static workspace, wherever binding.py takes it from.
+#define CONVROT_CALLS(F)                                                                                                     \
+    F(convrot_packed_bytes) F(convrot_packed_bytes8) F(convrot_workspace_bytes) F(convrot_workspace_bytes8)                  \
+    F(convrot_rotquant_act) F(convrot_rotquant_act8) F(convrot_w4a4_gemm_dequant) F(convrot_w8a8_gemm_dequant)               \
+    F(convlinear4bit_forward) F(convlinear4bit_forward_noalloc) F(convlinear8bit_forward)
+struct Library {
+#define CONVROT_MEMBER(name) decltype(&::name) name;
+    CONVROT_CALLS(CONVROT_MEMBER)
+#undef CONVROT_MEMBER
+} lib;
+bool bound = false;
+
 struct Failed {};   // a Python error is set
 
 [[noreturn]] void fail(PyObject *type, const char *format, const char *a, long long b = 0, long long c = 0)
@@ -194,6 +207,10 @@ PyObject *guarded(Py_ssize_t n, Py_ssize_t expected, F f)
         PyErr_Format(PyExc_TypeError, "need %zd arguments, got %zd", expected, n);
         return nullptr;
     }
+    if (!bound) {
+        PyErr_SetString(PyExc_RuntimeError, "not bound to a library");
+        return nullptr;
+    }
     try {
         return f();
     } catch (const Failed &) {
@@ -211,12 +228,12 @@ PyObject *forward(PyObject *, PyObject *const *a, Py_ssize_t n)
         int64_t M, K;
         matrix(X, "X", M, K);
         const int64_t N = length(ws, "w_scale");
-        const at::Tensor &Wq = codes(a[1], BITS == 4 ? convrot_packed_bytes(N, K) : convrot_packed_bytes8(N, K), "Wq");
+        const at::Tensor &Wq = codes(a[1], BITS == 4 ? lib.convrot_packed_bytes(N, K) : lib.convrot_packed_bytes8(N, K), "Wq");
         const at::Tensor *workspace = a[5] == Py_None ? nullptr : &scratch(a[5], "workspace");
         Out Y = out_bf16(a[4], X, M, N, a[7], "Y");
         at::Tensor own;
         if (!workspace) {
-            const int64_t bytes = BITS == 4 ? convrot_workspace_bytes(M, K) : convrot_workspace_bytes8(M, K);
+            const int64_t bytes = BITS == 4 ? lib.convrot_workspace_bytes(M, K) : lib.convrot_workspace_bytes8(M, K);
             own = new_on(X, {std::max<int64_t>(bytes, 256)}, at::kByte, a[7], false);
             workspace = &own;
         }
@@ -226,8 +243,8 @@ PyObject *forward(PyObject *, PyObject *const *a, Py_ssize_t n)
         void *stream = stream_of(a[7]), *wp = workspace->data_ptr();
         const size_t wn = workspace->numel();
         const int status = call([&] {
-            return BITS == 4 ? convlinear4bit_forward(x, w, s, bias, M, N, K, group, Y.ptr, wp, wn, stream)
-                             : convlinear8bit_forward(x, w, s, bias, M, N, K, group, Y.ptr, wp, wn, stream);
+            return BITS == 4 ? lib.convlinear4bit_forward(x, w, s, bias, M, N, K, group, Y.ptr, wp, wn, stream)
+                             : lib.convlinear8bit_forward(x, w, s, bias, M, N, K, group, Y.ptr, wp, wn, stream);
         });
         return status ? PyLong_FromLong(status) : Y.release();
     });
@@ -242,12 +259,12 @@ PyObject *forward_noalloc(PyObject *, PyObject *const *a, Py_ssize_t n)
         matrix(X, "X", M, K);
         const int64_t N = length(ws, "w_scale");
         if (Y.dim() != 2 || Y.size(0) != M || Y.size(1) != N) fail(PyExc_ValueError, "%s: need shape [M, N]", "Y");
-        const at::Tensor &Wq = codes(a[1], convrot_packed_bytes(N, K), "Wq");
+        const at::Tensor &Wq = codes(a[1], lib.convrot_packed_bytes(N, K), "Wq");
         const void *bias = bias_of(a[5], N), *x = X.data_ptr(), *w = Wq.data_ptr();
         const float *s = (const float *)ws.data_ptr();
         void *y = Y.data_ptr(), *stream = stream_of(a[6]);
         const int group = (int)integer(a[3]);
-        const int status = call([&] { return convlinear4bit_forward_noalloc(x, w, s, bias, M, N, K, group, y, stream); });
+        const int status = call([&] { return lib.convlinear4bit_forward_noalloc(x, w, s, bias, M, N, K, group, y, stream); });
         if (status) return PyLong_FromLong(status);
         Py_INCREF(a[4]);
         return a[4];
@@ -261,14 +278,14 @@ PyObject *gemm_dequant(PyObject *, PyObject *const *a, Py_ssize_t n)
     return guarded(n, 8, [&]() -> PyObject * {
         const at::Tensor &xs = f32(a[1], "x_scale"), &ws = f32(a[3], "w_scale");
         const int64_t M = length(xs, "x_scale"), N = length(ws, "w_scale"), K = integer(a[4]);
-        auto bytes = BITS == 4 ? convrot_packed_bytes : convrot_packed_bytes8;
+        auto bytes = BITS == 4 ? lib.convrot_packed_bytes : lib.convrot_packed_bytes8;
         const at::Tensor &Xq = codes(a[0], bytes(M, K), "Xq"), &Wq = codes(a[2], bytes(N, K), "Wq");
         Out Y = out_bf16(a[5], Xq, M, N, a[7], "Y");
         const void *bias = bias_of(a[6], N), *x = Xq.data_ptr(), *w = Wq.data_ptr();
         const float *sx = (const float *)xs.data_ptr(), *sw = (const float *)ws.data_ptr();
         void *stream = stream_of(a[7]);
         const int status = call([&] {
-            return (BITS == 4 ? convrot_w4a4_gemm_dequant : convrot_w8a8_gemm_dequant)(x, sx, w, sw, bias, M, N, K, Y.ptr, stream);
+            return (BITS == 4 ? lib.convrot_w4a4_gemm_dequant : lib.convrot_w8a8_gemm_dequant)(x, sx, w, sw, bias, M, N, K, Y.ptr, stream);
         });
         return status ? PyLong_FromLong(status) : Y.release();
     });
@@ -284,13 +301,13 @@ PyObject *rotquant(PyObject *, PyObject *const *a, Py_ssize_t n)
         const at::Tensor &X = bf16(a[0], in_name);
         int64_t rows, K;
         matrix(X, in_name, rows, K);
-        const size_t bytes = BITS == 4 ? convrot_packed_bytes(rows, K) : convrot_packed_bytes8(rows, K);
+        const size_t bytes = BITS == 4 ? lib.convrot_packed_bytes(rows, K) : lib.convrot_packed_bytes8(rows, K);
         Out Xq = out_codes(a[2], X, bytes, a[4], out_name), scale = out_f32(a[3], X, rows, a[4], "scale");
         const void *x = X.data_ptr();
         const int group = (int)integer(a[1]);
         void *stream = stream_of(a[4]);
         const int status = call([&] {
-            return (BITS == 4 ? convrot_rotquant_act : convrot_rotquant_act8)(x, rows, K, group, Xq.ptr, (float *)scale.ptr, stream);
+            return (BITS == 4 ? lib.convrot_rotquant_act : lib.convrot_rotquant_act8)(x, rows, K, group, Xq.ptr, (float *)scale.ptr, stream);
         });
         if (status) return PyLong_FromLong(status);
         PyObject *q = Xq.release(), *s = scale.release(), *pair = PyTuple_Pack(2, q, s);
@@ -300,7 +317,25 @@ PyObject *rotquant(PyObject *, PyObject *const *a, Py_ssize_t n)
     });
 }
 
+// (addresses of the entry points named in `names`, in their order)
+PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    Py_ssize_t i = 0;
+    Library l;
+#define CONVROT_TAKE(name)                                                       \
+    if (i >= n || !(l.name = (decltype(l.name))PyLong_AsVoidPtr(a[i++]))) {      \
+        if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "no " #name);   \
+        return nullptr;                                                          \
+    }
+    CONVROT_CALLS(CONVROT_TAKE)
+#undef CONVROT_TAKE
+    lib = l;
+    bound = true;
+    Py_RETURN_NONE;
+}
+
 PyMethodDef methods[] = {
+    {"bind", (PyCFunction)(void (*)(void))bind, METH_FASTCALL, nullptr},
     {"forward4", (PyCFunction)(void (*)(void))forward<4>, METH_FASTCALL, nullptr},
     {"forward8", (PyCFunction)(void (*)(void))forward<8>, METH_FASTCALL, nullptr},
     {"forward4_noalloc", (PyCFunction)(void (*)(void))forward_noalloc, METH_FASTCALL, nullptr},
@@ -315,4 +350,11 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_torch_calls", nullptr, -1, method
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__torch_calls() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__torch_calls()
+{
+    PyObject *m = PyModule_Create(&module);
+#define CONVROT_NAME(name) #name " "
+    if (m && PyModule_AddStringConstant(m, "names", CONVROT_CALLS(CONVROT_NAME)) < 0) Py_CLEAR(m);
+#undef CONVROT_NAME
+    return m;
+}

@@ -1,5 +1,8 @@
 """The extension module behind the per-layer calls of binding.py: what it rejects before anything is launched."""
 import os
+import shutil
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -26,6 +29,26 @@ def test_rejects_what_is_no_gpu_tensor(cr):
             f(*args)
         with pytest.raises(TypeError, match="need a torch tensor"):
             f(*[7] * len(args))
+
+
+_ANOTHER_LIBRARY = """
+import sys
+sys.path.insert(0, sys.argv[1])
+import torch
+from paper_2512_03673_amd import binding as cr
+cr.LIB_PATH = sys.argv[2]
+try:
+    cr.convrot_rotquant_act(torch.zeros(4, 32, dtype=torch.bfloat16), 16)
+except TypeError:
+    print(sorted({line.split()[-1] for line in open("/proc/self/maps") if "libconvrot" in line}))
+"""
+
+
+def test_the_per_layer_calls_run_in_the_library_that_was_loaded(cr, tmp_path):
+    path = shutil.copy(cr.LIB_PATH, tmp_path / "libconvrot_copy.so")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", _ANOTHER_LIBRARY, root, str(path)], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip() == str([str(path)]), r.stdout + r.stderr
 
 
 class _Refuses(TorchDispatchMode):
