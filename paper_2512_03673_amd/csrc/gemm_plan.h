@@ -35,6 +35,9 @@ enum class Plan {
     kCount
 };
 
+// Whether HIP can launch so many blocks: a grid has fewer than 2^32 threads.  (Blocks are dealt in eights: up to seven more.)
+inline bool launchable(int64_t blocks, int threads) { return blocks + 7 < ((int64_t)1 << 32) / threads; }
+
 // Stretches of up to 1024 elements in M rows, the unit of work of the one-launch forward (forward_small.hip).
 inline int64_t row_items(int64_t M, int64_t K) { return M * ((K + 1023) / 1024); }
 
@@ -67,6 +70,7 @@ struct Paired {
 };
 
 struct Alone {
+    int threads;
     float fixed, block, rate, idle;
 };
 
@@ -128,36 +132,41 @@ inline Plan choose(int64_t M, int64_t N, int64_t K)
         {Plan::kTile128x128, 128, 128, 2.56f, 1.57f, 0.405f, 0.190f},
         {Plan::kTile128x192, 128, 192, 3.08f, 2.44f, 0.512f, 0.269f},
     };
-    static constexpr Alone w8 = {2.00f, 3.84f, 0.419f, 0.80f};                                                  // 256 x 128, 4 bits
-    static constexpr Alone whole = BITS == 4 ? Alone{1.10f, 5.83f, 0.606f, 0.69f} : Alone{0.02f, 6.13f, 0.691f, 0.61f};     // 256 x 256
+    static constexpr Alone w8 = {512, 2.00f, 3.84f, 0.419f, 0.80f};                                                  // 256 x 128, 4 bits
+    static constexpr Alone whole = BITS == 4 ? Alone{512, 1.10f, 5.83f, 0.606f, 0.69f} : Alone{512, 0.02f, 6.13f, 0.691f, 0.61f};     // 256 x 256
 
     // 128 x 192, 4 bits: one round of up to 256 tiles where 256 x 128 leaves units idle.  (Its fit times 1.05: a draw goes to
     // the tiles that it is compared with, whose fits are of more shapes.)
-    static constexpr Alone middle = {1.70f, 4.55f, 0.347f, 0.98f};
+    static constexpr Alone middle = {256, 1.70f, 4.55f, 0.347f, 0.98f};
 
     const float stages = (float)(BITS == 4 ? (K + 127) / 128 : (K + 63) / 64);
     Plan best = Plan::kCount;
     float least = 0.0f;
+    bool best_fits = false;
     auto tiles = [&](int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
-    auto consider = [&](Plan plan, float t) {
-        if (best == Plan::kCount || t < least) {
+    // (A launch of more tiles than HIP takes at once is no candidate while there is another: M1 x N2^30 x K32 in 64 x 64 tiles.)
+    auto consider = [&](Plan plan, int64_t blocks, int threads, float t) {
+        const bool fits = launchable(blocks, threads);
+        if (best == Plan::kCount || (fits == best_fits ? t < least : fits)) {
             best = plan;
             least = t;
+            best_fits = fits;
         }
     };
     auto paired = [&](const Paired &c) {
-        const int64_t b = (tiles(c.tm, c.tn) + 255) / 256;
-        consider(c.plan, c.fixed + c.block * (float)b + stages * (c.pair * (float)(b / 2) + c.lone * (float)(b % 2)));
+        const int64_t n = tiles(c.tm, c.tn), b = (n + 255) / 256;
+        consider(c.plan, n, 256, c.fixed + c.block * (float)b + stages * (c.pair * (float)(b / 2) + c.lone * (float)(b % 2)));
     };
     auto small = [&](const Small &c) {
-        const float b = (float)((tiles(c.tm, c.tn) + 255) / 256), chain = (float)(((int64_t)stages + c.split - 1) / c.split);
+        const int64_t n = tiles(c.tm, c.tn);
+        const float b = (float)((n + 255) / 256), chain = (float)(((int64_t)stages + c.split - 1) / c.split);
         const float alone = c.latency * chain, full = c.rate * stages * b;
-        consider(c.plan, c.fixed + c.block * b + (alone > full ? alone : full));
+        consider(c.plan, n, c.split == 1 ? 256 : 64 * c.split, c.fixed + c.block * b + (alone > full ? alone : full));
     };
     auto alone = [&](Plan plan, int tm, int tn, const Alone &c) {
         const int64_t n = tiles(tm, tn), b = (n + 255) / 256;
         const float fill = (float)n / (256.0f * (float)b);
-        consider(plan, c.fixed + (float)b * (c.block + c.rate * stages * (c.idle + (1.0f - c.idle) * fill)));
+        consider(plan, n, c.threads, c.fixed + (float)b * (c.block + c.rate * stages * (c.idle + (1.0f - c.idle) * fill)));
     };
 
     if constexpr (BITS == 4) {
@@ -178,7 +187,7 @@ inline Plan choose(int64_t M, int64_t N, int64_t K)
             alone(Plan::kTile256x256, 256, 256, whole);
         } else {      // full rounds and one of parts
             const Cut c = parts == 2 ? Cut{3.90f, 0.340f} : Cut{3.30f, 0.240f};
-            consider(Plan::kTile256x256, whole.fixed + (float)(per_xcd / 32) * (whole.block + whole.rate * stages) + c.block + c.rate * stages);
+            consider(Plan::kTile256x256, 4 * 8 * per_xcd, whole.threads, whole.fixed + (float)(per_xcd / 32) * (whole.block + whole.rate * stages) + c.block + c.rate * stages);
         }
     }
     return best;

@@ -16,6 +16,7 @@
 #pragma once
 #include "e2m3_layout.h"
 #include "gemm_common.h"
+#include "gemm_plan.h"
 #include "panel_layout.h"
 
 namespace convrot {
@@ -193,7 +194,7 @@ template <class C, int XF, int WF, int S, int PD>
 hipError_t launch_small(const Operands &o)
 {
     const int tiles_m = (o.M + 16 * XF - 1) / (16 * XF), tiles_n = (o.N + 16 * WF - 1) / (16 * WF);
-    if ((int64_t)tiles_m * tiles_n > (1 << 30)) return hipErrorInvalidValue;   // the kernel counts tiles in 32 bits
+    if (!launchable((int64_t)tiles_m * tiles_n, 64 * S)) return hipErrorInvalidValue;
     const int ntiles = tiles_m * tiles_n, grid = (ntiles + kNumXcd - 1) / kNumXcd * kNumXcd;
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * S), 0, o.stream, (const uint8_t *)o.Xq, o.x_scale, (const uint8_t *)o.Wq,

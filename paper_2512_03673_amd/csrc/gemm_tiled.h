@@ -37,6 +37,7 @@
 // M854 x N6464 x K1024 11.0 -> 10.1, M1803 x N5056 x K4992 49.2 -> 46.2.
 #pragma once
 #include "gemm_common.h"
+#include "gemm_plan.h"
 
 namespace convrot {
 namespace gemm {
@@ -416,7 +417,7 @@ template <class C, class T>
 hipError_t launch_tiled(const Operands &o)
 {
     const int tiles_m = (o.M + T::TM - 1) / T::TM, tiles_n = (o.N + T::TN - 1) / T::TN;
-    if ((int64_t)tiles_m * tiles_n > (1 << 30)) return hipErrorInvalidValue;   // the kernel counts tiles in 32 bits
+    if (!launchable((int64_t)tiles_m * tiles_n, T::kThreads)) return hipErrorInvalidValue;
     const int ntiles = tiles_m * tiles_n;
     const int grid = ((ntiles + kNumXcd - 1) / kNumXcd) * kNumXcd;
     auto go = [&](auto kernel) {
@@ -432,7 +433,7 @@ template <class C, class T, class P>
 hipError_t launch_cut(const Operands &o, int cut)
 {
     const int tiles_m = (o.M + T::TM - 1) / T::TM, tiles_n = (o.N + T::TN - 1) / T::TN;
-    if ((int64_t)tiles_m * tiles_n > (1 << 28)) return hipErrorInvalidValue;   // the kernel counts parts in 32 bits
+    if (!launchable((int64_t)tiles_m * tiles_n * (T::TM / P::TM) * (T::TN / P::TN), T::kThreads)) return hipErrorInvalidValue;
     const int per_xcd = (tiles_m * tiles_n + kNumXcd - 1) / kNumXcd, whole = per_xcd - cut;
     const int grid = (whole + cut * (T::TM / P::TM) * (T::TN / P::TN)) * kNumXcd;
     auto go = [&](auto kernel) {

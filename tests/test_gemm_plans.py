@@ -37,20 +37,39 @@ SHAPES = {
 }
 
 
-@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not installed")
-def test_shapes_take_the_tiles_they_are_meant_for(tmp_path):
+def plans_of(shapes, tmp_path):
+    """What gemm_plan.h chooses for each shape: the tile of the 4-bit layer, of the 8-bit one."""
     src = tmp_path / "plan.cpp"
     src.write_text('#include "gemm_plan.h"\n#include <cstdio>\n#include <cstdlib>\nint main(int n, char **v) {\n'
                    '  for (int i = 1; i + 2 < n; i += 3)\n    std::printf("%d %d\\n", (int)convrot::gemm::choose<4>(atol(v[i]), atol(v[i + 1]), '
                    'atol(v[i + 2])), (int)convrot::gemm::choose<8>(atol(v[i]), atol(v[i + 1]), atol(v[i + 2])));\n}\n')
     exe = str(tmp_path / "plan")
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, "-o", exe, str(src)], check=True)
+    out = subprocess.run([exe] + [str(d) for s in shapes for d in s], check=True, capture_output=True, text=True).stdout.split()
+    return {s: (PLANS[int(out[2 * i])], PLANS[int(out[2 * i + 1])]) for i, s in enumerate(shapes)}
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not installed")
+def test_no_shape_takes_a_tile_that_cannot_be_launched(tmp_path):
+    # a HIP launch has fewer than 2^32 threads; 192 x 192 tiles of 256 threads stay below it in all of these
+    threads = {"256x128w8": 512, "256x256": 512, "split32x64": 512, "split16x32": 512, "split16x16": 1024}
+    sizes = [2 ** e + d for e in (0, 4, 6, 7, 9, 12, 16, 20, 24, 27, 28, 29, 30) for d in (0, 1)] + [2 ** 31 - 256]
+    shapes = [(M, N, K) for M in sizes for N in sizes for K in (32, 128, 1024, 65536) if -(-M // 192) * -(-N // 192) * 256 < 2 ** 32 - 2048]
+    assert (1, 2 ** 30, 32) in shapes and (2 ** 30, 64, 128) in shapes
+    for start in range(0, len(shapes), 500):
+        for (M, N, K), plans in plans_of(shapes[start:start + 500], tmp_path).items():
+            for p in plans:
+                tm, tn = (int(d) for d in p.removeprefix("split").removesuffix("w8").split("x"))
+                assert (-(-M // tm) * -(-N // tn) + 7) * threads.get(p, 256) < 2 ** 32, (M, N, K, p)
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not installed")
+def test_shapes_take_the_tiles_they_are_meant_for(tmp_path):
     # the benchmark's layers and the extremes of the argument range stay on the large tiles
     large = {(4608, 3072 * 4, 3072): "192x192", (16896, 12288, 3072): "192x192", (16896, 3072, 12288): "192x192", (4608, 3072, 12288): "256x256",
              (4608, 3072, 15360): "256x256", (2 ** 31 - 1, 2 ** 31 - 1, 65536): "192x192"}       # 8 bits; at 4 bits all of them 256 x 256
     shapes = list(SHAPES) + list(large)
-    out = subprocess.run([exe] + [str(d) for s in shapes for d in s], check=True, capture_output=True, text=True).stdout.split()
-    got = {s: (PLANS[int(out[2 * i])], PLANS[int(out[2 * i + 1])]) for i, s in enumerate(shapes)}
+    got = plans_of(shapes, tmp_path)
     for s, (p4, p8) in SHAPES.items():
         assert got[s] == (p4, p8), s
     for s, p in large.items():
