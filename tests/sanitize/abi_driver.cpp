@@ -1,13 +1,16 @@
 // Host sanitizer run of the C ABI's host side: every entry point with arguments that validation must reject
-// (or that are no-ops) before anything touches a device, the size queries over a sweep of shapes, and the
-// status strings.  Built with -fsanitize=address,undefined on the host pass and run by
+// (or that are no-ops) before anything touches a device, the size queries over a sweep of shapes, which kernels a valid
+// forward launches, and the status strings.  Built with -fsanitize=address,undefined on the host pass and run by
 // tests/test_host_sanitizers.py; needs no GPU.
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <string>
 
 #include "convrot.h"
+
+extern std::string *launches_seen;      // launch_stubs.cpp
 
 #define CHECK(cond)                                                                       \
     do {                                                                                  \
@@ -96,6 +99,21 @@ int main()
     CHECK(convrot_unpack_codes(nullptr, 0, 1024, nullptr, nullptr) == CONVROT_OK);
     CHECK(convrot_rotated_absmax(nullptr, 0, 1024, 16, 2, nullptr, nullptr) == CONVROT_OK);
     CHECK(convlinear4bit_forward_noalloc(nullptr, A, F, nullptr, 0, 4, 1024, 16, nullptr, nullptr) == CONVROT_OK);
+    // a few rows take one launch, more of them two; neither with a byte of workspace missing
+    std::string seen;
+    launches_seen = &seen;
+    CHECK(convlinear4bit_forward(A, A, F, nullptr, 4, 64, 1024, 16, A, A, convrot_workspace_bytes(4, 1024), nullptr) == CONVROT_OK);
+    CHECK(convlinear8bit_forward(A, A, F, nullptr, 4, 64, 1024, 16, A, A, convrot_workspace_bytes8(4, 1024), nullptr) == CONVROT_OK);
+    CHECK(seen == "forward_small forward_small ");
+    seen.clear();
+    CHECK(convlinear4bit_forward(A, A, F, nullptr, 400, 64, 1024, 16, A, A, convrot_workspace_bytes(400, 1024), nullptr) == CONVROT_OK);
+    CHECK(convlinear8bit_forward(A, A, F, nullptr, 400, 64, 1024, 16, A, A, convrot_workspace_bytes8(400, 1024), nullptr) == CONVROT_OK);
+    CHECK(seen == "rotquant gemm_w4a4 rotquant gemm_w8a8 ");
+    seen.clear();
+    CHECK(convlinear4bit_forward(A, A, F, nullptr, 4, 64, 1024, 16, A, A, convrot_workspace_bytes(4, 1024) - 1, nullptr) == CONVROT_ERR_WORKSPACE);
+    CHECK(convlinear4bit_forward(A, A, F, nullptr, 4, 0, 1024, 16, A, A, convrot_workspace_bytes(4, 1024), nullptr) == CONVROT_OK);
+    CHECK(seen == "rotquant ");
+    launches_seen = nullptr;
     std::puts("C ABI host side under sanitizers: ok");
     return 0;
 }

@@ -3,6 +3,8 @@ validation returns the documented status before anything is launched (no GPU nee
 import ctypes
 import os
 import re
+import shutil
+import subprocess
 
 import pytest
 
@@ -32,6 +34,15 @@ def test_header_symbols_are_exported(lib):
     assert sorted(binding.EXPORTS) == names
     for n in names:
         assert getattr(lib, n) is not None
+
+
+@pytest.mark.skipif(shutil.which("nm") is None, reason="nm not installed")
+def test_launchers_cannot_be_missing(lib):
+    # a weak definition could be left out of a build, or taken over by another library of the process
+    from paper_2512_03673_amd import binding
+    out = subprocess.run(["nm", "-D", "-C", "--defined-only", binding.LIB_PATH], check=True, capture_output=True, text=True).stdout
+    launchers = [line.split(None, 2)[1:] for line in out.splitlines() if "convrot::launch_" in line and "(" in line]
+    assert len(launchers) == 6 and all(kind == "T" for kind, _ in launchers), launchers
 
 
 def test_size_queries_and_strings(lib):

@@ -4,7 +4,8 @@
     buffers for every group size and both code widths;
   * the host side of the C ABI (csrc/convrot_api.hip: validation, size queries, the static-workspace
     bookkeeping), driven by tests/sanitize/abi_driver.cpp with the kernel launchers replaced by stubs
-    (tests/sanitize/launch_stubs.cpp) - every call is one that validation must reject or an empty no-op.
+    (tests/sanitize/launch_stubs.cpp) - calls that validation must reject, empty no-ops, and which launchers a
+    forward reaches.
 
 The drivers are stand-alone executables (the sanitizer runtimes are linked in), so nothing is preloaded into
 the Python process.
