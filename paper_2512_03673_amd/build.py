@@ -6,6 +6,7 @@ import subprocess
 import sys
 import sysconfig
 from concurrent.futures import ThreadPoolExecutor
+from typing import Optional
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -50,10 +51,17 @@ def build(verbose: bool = True, extra_flags=(), out: str = LIB) -> str:
     return out
 
 
-def build_calls(verbose: bool = True, out: str = CALLS) -> str:
-    """Compile the extension module (host code only; it calls the C ABI of the library that binding.py loads)."""
-    import torch    # headers and libraries; neither torch nor a GPU is used
-    root = os.path.dirname(torch.__file__)
+def build_calls(verbose: bool = True, out: str = CALLS) -> Optional[str]:
+    """Compile the extension module (host code only; it calls the C ABI of the library that binding.py loads).  Returns None
+    where there is no torch to build it for: the library stands without it, for programs that call the C ABI."""
+    try:
+        import torch    # headers and libraries; neither torch nor a GPU is used
+        root = os.path.dirname(torch.__file__)
+    except ImportError:
+        root = None
+    if root is None or not os.path.isdir(os.path.join(root, "include", "torch", "csrc")):
+        print(f"no torch with headers: {os.path.basename(out)}, which binding.py needs, is not built", file=sys.stderr, flush=True)
+        return None
     lib = os.path.join(root, "lib")
     tmp = out + f".tmp{os.getpid()}"
     cmd = ["hipcc", "--offload-arch=gfx950", "--offload-host-only", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-DUSE_ROCM",

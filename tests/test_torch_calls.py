@@ -31,6 +31,31 @@ def test_rejects_what_is_no_gpu_tensor(cr):
             f(*[7] * len(args))
 
 
+_WITHOUT_TORCH = """
+import subprocess, sys
+sys.path.insert(0, sys.argv[1])
+sys.modules["torch"] = None                 # importing it fails
+from paper_2512_03673_amd import build
+ran = []
+def run(cmd, **kw):                         # the compiler's part is left out; what it would write is there
+    ran.append(cmd)
+    open(cmd[cmd.index("-o") + 1], "w").close()
+subprocess.run = run
+build.LIB = sys.argv[2]
+build.HERE = build.os.path.dirname(build.LIB)
+print(build.build(verbose=False, out=build.LIB), len(ran), "torch" in " ".join(map(str, sum(ran, []))))
+"""
+
+
+def test_the_library_builds_without_torch(tmp_path):
+    out = tmp_path / "libconvrot.so"
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", _WITHOUT_TORCH, root, str(out)], capture_output=True, text=True, timeout=300)
+    from paper_2512_03673_amd import build
+    assert r.returncode == 0 and r.stdout.split() == [str(out), str(len(build.SOURCES) + 1), "False"], r.stdout + r.stderr
+    assert "_torch_calls.so, which binding.py needs, is not built" in r.stderr and out.exists()
+
+
 _ANOTHER_LIBRARY = """
 import sys
 sys.path.insert(0, sys.argv[1])
