@@ -112,11 +112,10 @@ const char *convrot_build_info(void);
  */
 int convrot_init(void);
 
-/* Host.  X rows of the large block tile that suits an [M, N] output: 192 (tile 192 x 192) or 256 (tile
- * 256 x 128) of those of which two share a compute unit; 0 when M or N < 0.  Products too small to fill the device with such
- * tiles take smaller ones, some large ones 256 x 256.  The
- * result of the GEMM does not depend on the tile; the query exists so that tests and tuning runs can tell which
- * kernel configuration a large shape exercises. */
+/* Host.  Which of two block tiles leaves the busiest of 256 compute units the smaller share of an [M, N] output: 192
+ * (tile 192 x 192) or 256 (tile 256 x 128); 0 when M or N < 0.  Kept for programs written when the GEMM had these two
+ * tiles and chose between them so.  It does not say which kernel a product takes: there are more tiles now, and the
+ * choice depends on K and the width of the codes as well.  The result of the GEMM does not depend on the tile. */
 int convrot_gemm_tile_rows(int64_t M, int64_t N);
 
 /* Host.  Bytes of a 4-bit code matrix with `rows` rows of K codes in the layout above

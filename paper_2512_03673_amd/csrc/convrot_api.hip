@@ -136,7 +136,9 @@ int convrot_init(void)
 int convrot_gemm_tile_rows(int64_t M, int64_t N)
 {
     if (M < 0 || N < 0) return 0;
-    return convrot::gemm_tile_rows(M, N);
+    // Tiles of the busiest of 256 compute units times a tile's products; the square one moves fewer bytes a product and takes the ties.
+    auto share = [&](int64_t tm, int64_t tn) { return (((M + tm - 1) / tm * ((N + tn - 1) / tn)) + 255) / 256 * tm * tn; };
+    return share(192, 192) <= share(256, 128) ? 192 : 256;
 }
 
 size_t convrot_packed_bytes(int64_t rows, int64_t K)

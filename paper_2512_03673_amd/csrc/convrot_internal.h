@@ -8,9 +8,6 @@
 
 namespace convrot {
 
-// X rows of the large block tile that suits an [M, N] output: 192 (with 192 W rows) or 256 (with 128); see gemm_plan.h.
-inline int gemm_tile_rows(int64_t M, int64_t N) { return gemm::large_tile_rows(M, N); }
-
 // Rotate + quantise + pack `rows` rows of K bf16 values (group in {4,16,64,256,1024}; bits 4: FP6 E2M3
 // codes in the layout of e2m3_layout.h, bits 8: one int8 per code in the layout of panel_layout.h).
 hipError_t launch_rotquant(const void *X, int64_t rows, int64_t K, int group, int bits, void *Xq, float *scale,

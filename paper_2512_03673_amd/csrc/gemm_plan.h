@@ -91,18 +91,6 @@ inline int parts_of_last_tiles(int64_t per_xcd)
     return per_xcd < 32 || per_xcd >= 5 * 32 || rest == 0 || rest > 16 ? 1 : rest > 8 ? 2 : 4;
 }
 
-// The two large tiles of which two share a compute unit.  Blocks are dealt to the 256 units as slots free up, so a launch lasts
-// about as long as the busiest unit's share, ceil(tiles / 256) blocks of TM x TN products each; the square tile
-// moves fewer operand bytes per product and takes the ties.
-inline int large_tile_rows(int64_t M, int64_t N)
-{
-    auto work = [&](int64_t tm, int64_t tn) {
-        const int64_t tiles = ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
-        return ((tiles + 255) / 256) * tm * tn;
-    };
-    return work(192, 192) <= work(256, 128) ? 192 : 256;
-}
-
 template <int BITS>
 inline Plan choose(int64_t M, int64_t N, int64_t K)
 {

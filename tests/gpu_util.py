@@ -1,4 +1,8 @@
-"""Helpers shared by the GPU parity tests: host <-> device marshalling and the parity gates."""
+"""Helpers shared by the GPU parity tests: host <-> device marshalling, the parity gates, the GEMM's choice of tiles."""
+import os
+import subprocess
+import tempfile
+
 import numpy as np
 import torch
 
@@ -189,3 +193,23 @@ def bf16_ulp_diff(a_bits: np.ndarray, b_bits: np.ndarray) -> np.ndarray:
         x = x.astype(np.int32)
         return np.where(x & 0x8000, -(x & 0x7FFF), x & 0x7FFF)
     return np.abs(key(a_bits) - key(b_bits))
+
+
+# ---- which tile the GEMMs take for a product: csrc/gemm_plan.h, compiled for the host and asked
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2512_03673_amd", "csrc")
+PLANS = ("192x192", "256x128", "256x128w8", "128x128", "64x64", "split32x64", "split32x32", "split16x32", "split16x16", "256x256",
+         "128x192")
+
+
+def gemm_plans(shapes):
+    """{(M, N, K): (tile of the 4-bit layer, tile of the 8-bit one)}"""
+    shapes = list(shapes)
+    with tempfile.TemporaryDirectory() as d:
+        src, exe = os.path.join(d, "plan.cpp"), os.path.join(d, "plan")
+        with open(src, "w") as f:
+            f.write('#include "gemm_plan.h"\n#include <cstdio>\nint main() {\n  long M, N, K;\n  while (std::scanf("%ld %ld %ld", &M, &N, &K) == 3)\n'
+                    '    std::printf("%d %d\\n", (int)convrot::gemm::choose<4>(M, N, K), (int)convrot::gemm::choose<8>(M, N, K));\n}\n')
+        subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, "-o", exe, src], check=True)
+        out = subprocess.run([exe], check=True, capture_output=True, text=True, input="\n".join(" ".join(map(str, s)) for s in shapes)).stdout.split()
+    assert len(out) == 2 * len(shapes)
+    return {s: (PLANS[int(out[2 * i])], PLANS[int(out[2 * i + 1])]) for i, s in enumerate(shapes)}

@@ -68,13 +68,14 @@ def test_size_queries_and_strings(lib):
     assert b.status_string(-99) == "unknown status"
 
 
-def test_gemm_tile_choice(lib):
+def test_gemm_tile_rows_query(lib):
+    # the smaller share of two tiles, by its definition; which tile a product takes is tests/test_gemm_plans.py
     from paper_2512_03673_amd import binding as b
     # up to 256 tiles of either shape the smaller tile (256 x 128) has less work per block
     assert b.gemm_tile_rows(256, 1024) == 256 and b.gemm_tile_rows(4608, 3072) == 256
     # 256 square tiles against 288 of the other shape: one block per compute unit against two
     assert b.gemm_tile_rows(3072, 3072) == 192 and b.gemm_tile_rows(3001, 3070) == 192
-    # headline shape: 1536 square tiles (6 per unit) against 1728 (7 per unit)
+    # 1536 square tiles (6 per unit) against 1728 (7 per unit)
     assert b.gemm_tile_rows(4608, 12288) == 192
     assert b.gemm_tile_rows(-1, 5) == 0 and b.gemm_tile_rows(5, -1) == 0
 

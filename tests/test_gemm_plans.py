@@ -3,20 +3,16 @@ edges in both directions, a K whose stages do not divide among the wavefronts th
 of each ring.  Which tile a shape takes is a host function (csrc/gemm_plan.h), compiled and asked here on the CPU, so
 that the list keeps naming the tiles it means to."""
 import os
+import re
 import shutil
-import subprocess
 
 import numpy as np
 import pytest
 import torch
 
 import oracle
-from gpu_util import bf16_to_host_bits, bf16_ulp_diff, bits_to_f64, check_output, codes4_to_dev, codes8_to_dev, to_dev_bf16
+from gpu_util import CSRC, PLANS, bf16_to_host_bits, bf16_ulp_diff, bits_to_f64, check_output, codes4_to_dev, codes8_to_dev, gemm_plans, to_dev_bf16
 from paper_2512_03673_amd import workloads as wl
-
-CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2512_03673_amd", "csrc")
-PLANS = ("192x192", "256x128", "256x128w8", "128x128", "64x64", "split32x64", "split32x32", "split16x32", "split16x16", "256x256",
-         "128x192")
 
 # (M, N, K): the tile of the 4-bit layer, of the 8-bit one
 SHAPES = {
@@ -25,6 +21,7 @@ SHAPES = {
     (33, 4095, 96): ("split32x32", "split32x32"), (300, 520, 96): ("split32x32", "split32x32"), (40, 3000, 7264): ("split32x32", "split32x32"),
     (1, 9216, 3072): ("split32x64", "split16x32"), (65, 4095, 1056): ("split32x64", "split32x64"),
     (65, 4097, 160): ("64x64", "split32x64"), (191, 2050, 32): ("64x64", "64x64"), (1024, 1025, 1056): ("64x64", "64x64"),
+    (5, 4100, 4224): ("split16x32", "split16x32"), (4609, 3457, 1056): ("192x192", "192x192"),
     (511, 4097, 96): ("64x64", "128x128"), (1023, 3070, 512): ("128x128", "128x128"), (513, 6100, 1056): ("128x128", "128x128"),
     (513, 6100, 3072): ("128x128", "128x128"), (511, 12281, 544): ("256x128w8", "128x192"), (2300, 2300, 352): ("256x128w8", "128x192"),
     (1537, 3070, 672): ("256x128w8", "128x192"), (4608, 3072, 128): ("128x128", "128x128"), (4601, 3068, 480): ("256x128", "256x256"),
@@ -37,44 +34,46 @@ SHAPES = {
 }
 
 
-def plans_of(shapes, tmp_path):
-    """What gemm_plan.h chooses for each shape: the tile of the 4-bit layer, of the 8-bit one."""
-    src = tmp_path / "plan.cpp"
-    src.write_text('#include "gemm_plan.h"\n#include <cstdio>\n#include <cstdlib>\nint main(int n, char **v) {\n'
-                   '  for (int i = 1; i + 2 < n; i += 3)\n    std::printf("%d %d\\n", (int)convrot::gemm::choose<4>(atol(v[i]), atol(v[i + 1]), '
-                   'atol(v[i + 2])), (int)convrot::gemm::choose<8>(atol(v[i]), atol(v[i + 1]), atol(v[i + 2])));\n}\n')
-    exe = str(tmp_path / "plan")
-    subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, "-o", exe, str(src)], check=True)
-    out = subprocess.run([exe] + [str(d) for s in shapes for d in s], check=True, capture_output=True, text=True).stdout.split()
-    return {s: (PLANS[int(out[2 * i])], PLANS[int(out[2 * i + 1])]) for i, s in enumerate(shapes)}
-
-
 @pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not installed")
-def test_no_shape_takes_a_tile_that_cannot_be_launched(tmp_path):
+def test_no_shape_takes_a_tile_that_cannot_be_launched():
     # a HIP launch has fewer than 2^32 threads; 192 x 192 tiles of 256 threads stay below it in all of these
     threads = {"256x128w8": 512, "256x256": 512, "split32x64": 512, "split16x32": 512, "split16x16": 1024}
     sizes = [2 ** e + d for e in (0, 4, 6, 7, 9, 12, 16, 20, 24, 27, 28, 29, 30) for d in (0, 1)] + [2 ** 31 - 256]
     shapes = [(M, N, K) for M in sizes for N in sizes for K in (32, 128, 1024, 65536) if -(-M // 192) * -(-N // 192) * 256 < 2 ** 32 - 2048]
     assert (1, 2 ** 30, 32) in shapes and (2 ** 30, 64, 128) in shapes
-    for start in range(0, len(shapes), 500):
-        for (M, N, K), plans in plans_of(shapes[start:start + 500], tmp_path).items():
-            for p in plans:
-                tm, tn = (int(d) for d in p.removeprefix("split").removesuffix("w8").split("x"))
-                assert (-(-M // tm) * -(-N // tn) + 7) * threads.get(p, 256) < 2 ** 32, (M, N, K, p)
+    for (M, N, K), plans in gemm_plans(shapes).items():
+        for p in plans:
+            tm, tn = (int(d) for d in p.removeprefix("split").removesuffix("w8").split("x"))
+            assert (-(-M // tm) * -(-N // tn) + 7) * threads.get(p, 256) < 2 ** 32, (M, N, K, p)
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not installed")
-def test_shapes_take_the_tiles_they_are_meant_for(tmp_path):
+def test_shapes_take_the_tiles_they_are_meant_for():
     # the benchmark's layers and the extremes of the argument range stay on the large tiles
     large = {(4608, 3072 * 4, 3072): "192x192", (16896, 12288, 3072): "192x192", (16896, 3072, 12288): "192x192", (4608, 3072, 12288): "256x256",
              (4608, 3072, 15360): "256x256", (2 ** 31 - 1, 2 ** 31 - 1, 65536): "192x192"}       # 8 bits; at 4 bits all of them 256 x 256
     shapes = list(SHAPES) + list(large)
-    got = plans_of(shapes, tmp_path)
+    got = gemm_plans(shapes)
     for s, (p4, p8) in SHAPES.items():
         assert got[s] == (p4, p8), s
     for s, p in large.items():
         assert got[s] == ("256x256", p), s
     assert {p for p, _ in SHAPES.values()} == set(PLANS) and {p for _, p in SHAPES.values()} == set(PLANS) - {"256x128w8"}
+
+
+@pytest.mark.parametrize("bits", (4, 8))
+def test_shapes_reach_the_steady_loop_of_every_tile(bits):
+    """SHAPES has, for each tile, a K of more stages than the tile's prologue and drain take: a stage more than the ring of a
+    gemm_tiled.h tile, a round of requests of all wavefronts that split K."""
+    with open(os.path.join(CSRC, f"gemm_w{bits}a{bits}.hip")) as f:
+        source = f.read()
+    depth = {"256x256": 4}                 # (4-bit codes: whole tiles a ring of three, their halves three, their quarters four)
+    for name, tile, split in re.findall(r"case Plan::k(\w+): return gemm::launch_(?:tiled<Codes\d, Tile<([\d, ]+)>>|small<gemm::Small\d, ([\d, ]+)>)", source):
+        n = [int(d) for d in (tile or split).split(",")]
+        depth[name.removeprefix("Tile").replace("Split", "split")] = n[4] + 1 if tile else n[2] * n[3]
+    assert set(depth) == {p[bits == 8] for p in SHAPES.values()}
+    for plan, stages in depth.items():
+        assert max(-(-K // (128 if bits == 4 else 64)) for (_, _, K), p in SHAPES.items() if p[bits == 8] == plan) > stages, plan
 
 
 @pytest.mark.gpu

@@ -10,7 +10,7 @@ import torch
 
 import oracle
 from gpu_util import (bf16_to_host_bits, bf16_ulp_diff, bits_to_f64, check_codes, check_output, codes4_to_dev,
-                      encode_e2m3, to_dev_bf16, unpack_host)
+                      encode_e2m3, gemm_plans, to_dev_bf16, unpack_host)
 from paper_2512_03673_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -133,7 +133,8 @@ def test_prepare_weight_is_the_same_operation(cr):
 # ------------------------------------------------------------------ kernel B: integer GEMM
 @pytest.mark.parametrize("M,N,K", [(256, 256, 128), (300, 520, 1024), (1, 1, 32), (33, 7, 96), (257, 513, 3072),
                                    (64, 1030, 12288), (513, 258, 160), (40, 136, 65536), (3, 2, 65504),
-                                   (192, 192, 128), (193, 385, 160), (191, 383, 96), (577, 190, 416)])
+                                   (192, 192, 128), (193, 385, 160), (191, 383, 96), (577, 190, 416),
+                                   (3072, 3072, 3072), (3001, 3070, 1056)])
 def test_gemm_i32_bit_exact(cr, M, N, K):
     rng = np.random.default_rng(M * 7 + N * 3 + K)
     qx = rng.integers(-7, 8, size=(M, K)).astype(np.int8)
@@ -146,14 +147,13 @@ def test_gemm_i32_bit_exact(cr, M, N, K):
     assert np.array_equal(acc.cpu().numpy(), oracle.int_gemm(qx, qw))
 
 
-@pytest.mark.parametrize("M,N,K", [(3072, 3072, 128), (3001, 3070, 160), (3072, 3072, 3072), (3001, 3070, 1056),
+@pytest.mark.parametrize("M,N,K", [(3072, 3072, 128), (3001, 3070, 160), (4609, 3457, 1056), (5400, 3070, 1312),
                                    (3072, 3072, 384), (3001, 3070, 512)])
 def test_gemm_i32_bit_exact_on_square_tiles(cr, M, N, K):
-    # The shapes above all take the 256 x 128 block tile (at most 256 tiles of either shape); these take the
-    # 192 x 192 one: 256 square tiles against 288, whole and with ragged edges in both directions.  K = 128 and
-    # 160 are one and two K128 stages (the pipeline's prologue and drain only); K = 384, 512, 1056 and 3072 are 3, 4,
-    # 9 (the last one padded) and 24 stages, which run the steady-state loop that refills the ring.
-    assert cr.gemm_tile_rows(M, N) == 192 and cr.gemm_tile_rows(300, 520) == 256
+    # The 192 x 192 block tile, whole and with ragged edges in both directions.  K = 128 and 160 are one and two K128
+    # stages (the pipeline's prologue and drain only); K = 384, 512, 1056 and 1312 are 3, 4, 9 and 11 (the last one padded)
+    # stages, which run the steady-state loop that refills the ring.
+    assert gemm_plans([(M, N, K)])[M, N, K][0] == "192x192"
     rng = np.random.default_rng(M + N + K)
     qx = rng.integers(-7, 8, size=(M, K)).astype(np.int8)
     qw = rng.integers(-7, 8, size=(N, K)).astype(np.int8)
@@ -229,7 +229,7 @@ def test_gemm_dequant_with_bias(cr, M, N, K):
 @pytest.mark.parametrize("M,N,K", [(3001, 3070, 96), (3072, 3067, 224)])
 def test_gemm_dequant_with_bias_on_square_tiles(cr, M, N, K):
     # the 192 x 192 block tile's epilogue: interior tiles, ragged rows, and rows of Y that are not 16-byte multiples
-    assert cr.gemm_tile_rows(M, N) == 192
+    assert gemm_plans([(M, N, K)])[M, N, K][0] == "192x192"
     rng = np.random.default_rng(M * N + K)
     qx = rng.integers(-7, 8, size=(M, K)).astype(np.int8)
     qw = rng.integers(-7, 8, size=(N, K)).astype(np.int8)

@@ -13,7 +13,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_util import bf16_to_host_bits, check_output, to_dev_bf16
+from gpu_util import bf16_to_host_bits, check_output, gemm_plans, to_dev_bf16
 from paper_2512_03673_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -60,8 +60,7 @@ def test_forward_runs_on_the_given_stream(cr):
 
 
 def test_calls_on_two_streams_do_not_disturb_each_other(cr):
-    # two layers of different shape (one per block tile shape of the GEMM), each with its own buffers, queued
-    # alternately on two streams
+    # two layers whose GEMMs take different tiles, each with its own buffers, queued alternately on two streams
     cases = []
     for M, K, N, g, seed in ((3072, 256, 3072, 16, 21), (700, 2048, 900, 64, 22)):
         spec, x, w = layer(M, K, N, g, seed)
@@ -71,7 +70,7 @@ def test_calls_on_two_streams_do_not_disturb_each_other(cr):
         Y = torch.empty_like(y_ref)
         wsb = torch.empty((cr.workspace_bytes(M, K),), dtype=torch.uint8, device="cuda")
         cases.append((X, wq, ws, g, Y, wsb, y_ref, torch.cuda.Stream()))
-    assert cr.gemm_tile_rows(3072, 3072) == 192 and cr.gemm_tile_rows(700, 900) == 256
+    assert {p4 for p4, _ in gemm_plans([(3072, 3072, 256), (700, 900, 2048)]).values()} == {"192x192", "64x64"}
     torch.cuda.synchronize()
     for rep in range(10):
         for X, wq, ws, g, Y, wsb, y_ref, s in cases:

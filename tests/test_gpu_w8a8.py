@@ -8,7 +8,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_util import (bf16_to_host_bits, bf16_ulp_diff, bits_to_f64, check_output, codes8_to_dev, to_dev_bf16,
+from gpu_util import (bf16_to_host_bits, bf16_ulp_diff, bits_to_f64, check_output, codes8_to_dev, gemm_plans, to_dev_bf16,
                       ulp_diff_f32, unpack_host8)
 from paper_2512_03673_amd import workloads as wl
 
@@ -63,7 +63,7 @@ def test_rotquant8_closed_forms(cr):
 
 
 @pytest.mark.parametrize("M,N,K", [(256, 128, 64), (300, 520, 1024), (1, 1, 64), (33, 7, 192), (257, 513, 3072), (35, 19, 96),
-                                   (64, 1030, 12288), (513, 258, 128), (40, 136, 65536)])
+                                   (64, 1030, 12288), (513, 258, 128), (40, 136, 65536), (3072, 3072, 64)])
 def test_gemm8_i32_bit_exact(cr, M, N, K):
     rng = np.random.default_rng(M * 5 + N * 3 + K)
     qx = rng.integers(-127, 128, size=(M, K)).astype(np.int8)
@@ -75,14 +75,13 @@ def test_gemm8_i32_bit_exact(cr, M, N, K):
     assert np.array_equal(acc.cpu().numpy(), oracle.int_gemm(qx, qw))
 
 
-@pytest.mark.parametrize("M,N,K", [(3072, 3072, 64), (3001, 3067, 160), (3072, 3072, 3072), (3001, 3070, 1056),
+@pytest.mark.parametrize("M,N,K", [(3072, 3072, 96), (3001, 3067, 160), (3072, 3072, 3072), (3001, 3070, 1056),
                                    (3001, 3067, 256)])
 def test_gemm8_on_square_tiles(cr, M, N, K):
-    # The shapes above all take the 256 x 128 block tile (at most 256 tiles of either shape); these take the
-    # 192 x 192 one, whole and with ragged edges: raw accumulators bit-exact, then the dequantising epilogue.
-    # K = 64 and 160 stay inside the ring's prologue; K = 256, 1056 and 3072 are 4, 17 (the last one padded) and 48
+    # The 192 x 192 block tile, whole and with ragged edges: raw accumulators bit-exact, then the dequantising epilogue.
+    # K = 96 and 160 stay inside the ring's prologue; K = 256, 1056 and 3072 are 4, 17 (the last one padded) and 48
     # stages of 64 codes, which run the steady-state loop that refills the ring.
-    assert cr.gemm_tile_rows(M, N) == 192 and cr.gemm_tile_rows(300, 520) == 256
+    assert gemm_plans([(M, N, K)])[M, N, K][1] == "192x192"
     rng = np.random.default_rng(M + N + K)
     qx = rng.integers(-127, 128, size=(M, K)).astype(np.int8)
     qw = rng.integers(-127, 128, size=(N, K)).astype(np.int8)
