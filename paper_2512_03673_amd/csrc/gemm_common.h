@@ -1,5 +1,5 @@
 // Shared pieces of the GEMM kernels of libconvrot, 4-bit and 8-bit (LDS swizzle, LDS-direct loads,
-// tile order).  See gemm_w4a4.hip for the description of the method.
+// tile order).  gemm_tiled.h and gemm_small.h describe the method.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -12,8 +12,11 @@
 // (`block`: prologue and epilogue of a tile; `latency`, `lone`: a stage of a tile that has the unit to itself; `rate`, `pair`: a
 // stage of a full unit.)  The constants are robust fits: of the first kind to 320 launches on shapes drawn over M 1 ... 8000,
 // N 32 ... 12288, K 64 ... 15360, of the other two to 230 over M 256 ... 16896, N 512 ... 12288, K 256 ... 15360 with at least
-// 1.2e10 products, the large 4-bit tiles also to 120 such with operands that change from launch to launch (128 x 192: to 220 with M 64 ... 8000 and 3e9 to 8e10 products).  On the larger shapes the tile taken costs
-// 0.5 % more on average than the best of them would, on the others 1 to 2 %.
+// 1.2e10 products, the large 4-bit tiles also to 120 such with operands that change from launch to launch (128 x 192: to 220
+// with M 64 ... 8000 and 3e9 to 8e10 products).  On the larger shapes the tile taken costs 0.5 % more on average than the best of
+// them would, on the others 1 to 2 %.  All fits but those of the large 4-bit tiles are thus of operands that the Infinity Cache holds,
+// which favours these tiles in a comparison (one set of buffers against three in turn, M4608 x N12288 x K3072: 80.4 / 91.6 us with 192 x 192
+// tiles, 84.5 / 88.3 with 256 x 256).
 #pragma once
 #include <stdint.h>
 
@@ -84,7 +87,8 @@ struct Cut {        // a round of parts of 256 x 256 tiles
 // 275.5 / 260.5; over 16 and 19 drawn shapes 6 and 14 % - more of them would take two rounds of parts and lose).  After
 // many rounds the units no longer finish together and parts only cost (M16896 x N12288 x K3072, 12 rounds, 296 / 305).  8-bit
 // products gain nothing there over 192 x 192 tiles.  (All with operands that change from launch to launch; on one set of buffers,
-// which the Infinity Cache holds, M4608 x N12288 x K3072 takes 84.5 us in halves and 80.4 with 192 x 192 tiles.)  Parts a tile is cut into, 1 if none is; `per_xcd` = tiles of an XCD.
+// which the Infinity Cache holds, M4608 x N12288 x K3072 takes 81.4 to 85.2 us in halves, by the box, and 80.4 to 82.1 with
+// 192 x 192 tiles.)  Parts a tile is cut into, 1 if none is; `per_xcd` = tiles of an XCD.
 inline int parts_of_last_tiles(int64_t per_xcd)
 {
     const int64_t rest = per_xcd % 32;
