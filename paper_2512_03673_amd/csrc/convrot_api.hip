@@ -93,7 +93,10 @@ int check_forward(const void *X_bf16, const void *Wq, const float *w_scale, cons
 int launch_forward(const void *X_bf16, const void *Wq, const float *w_scale, const void *bias_bf16, int64_t M, int64_t N, int64_t K,
                    int group, int bits, void *Y_bf16, uint8_t *xq, float *xs, hipStream_t s)
 {
-    if (M > 0 && N > 0 && convrot::gemm::forward_in_one(M, N, K))
+    // In the one launch blocks write Y while others still read X: an output laid over its input takes the two.
+    const uintptr_t x = reinterpret_cast<uintptr_t>(X_bf16), y = reinterpret_cast<uintptr_t>(Y_bf16);
+    const bool apart = x + (uintptr_t)(M * K) * 2 <= y || y + (uintptr_t)(M * N) * 2 <= x;
+    if (M > 0 && N > 0 && apart && convrot::gemm::forward_in_one(M, N, K))
         return from_hip(convrot::launch_forward_small(X_bf16, Wq, w_scale, bias_bf16, M, N, K, group, bits, Y_bf16, xq, xs, s));
     if (convrot::launch_rotquant(X_bf16, M, K, group, bits, xq, xs, s) != hipSuccess) return CONVROT_ERR_HIP;
     return from_hip(bits == 4 ? convrot::launch_gemm_w4a4(xq, xs, Wq, w_scale, bias_bf16, M, N, K, Y_bf16, nullptr, s)

@@ -102,8 +102,9 @@ int main()
     // a few rows take one launch, more of them two; neither with a byte of workspace missing
     std::string seen;
     launches_seen = &seen;
-    CHECK(convlinear4bit_forward(A, A, F, nullptr, 4, 64, 1024, 16, A, A, convrot_workspace_bytes(4, 1024), nullptr) == CONVROT_OK);
-    CHECK(convlinear8bit_forward(A, A, F, nullptr, 4, 64, 1024, 16, A, A, convrot_workspace_bytes8(4, 1024), nullptr) == CONVROT_OK);
+    void *const Y = reinterpret_cast<void *>(0x800000);
+    CHECK(convlinear4bit_forward(A, A, F, nullptr, 4, 64, 1024, 16, Y, A, convrot_workspace_bytes(4, 1024), nullptr) == CONVROT_OK);
+    CHECK(convlinear8bit_forward(A, A, F, nullptr, 4, 64, 1024, 16, Y, A, convrot_workspace_bytes8(4, 1024), nullptr) == CONVROT_OK);
     CHECK(seen == "forward_small forward_small ");
     seen.clear();
     CHECK(convlinear4bit_forward(A, A, F, nullptr, 400, 64, 1024, 16, A, A, convrot_workspace_bytes(400, 1024), nullptr) == CONVROT_OK);
@@ -113,6 +114,16 @@ int main()
     CHECK(convlinear4bit_forward(A, A, F, nullptr, 4, 64, 1024, 16, A, A, convrot_workspace_bytes(4, 1024) - 1, nullptr) == CONVROT_ERR_WORKSPACE);
     CHECK(convlinear4bit_forward(A, A, F, nullptr, 4, 0, 1024, 16, A, A, convrot_workspace_bytes(4, 1024), nullptr) == CONVROT_OK);
     CHECK(seen == "rotquant ");
+    // an output laid over the input: every block of the one launch reads all of X, so X has to be read before Y is written
+    seen.clear();
+    char *const X = static_cast<char *>(A);
+    for (int64_t d : {0, 8 * 1024 * 2 - 16, -(8 * 64 * 2 - 16)})
+        CHECK(convlinear4bit_forward(X, A, F, nullptr, 8, 64, 1024, 16, X + d, A, convrot_workspace_bytes(8, 1024), nullptr) == CONVROT_OK);
+    CHECK(seen == "rotquant gemm_w4a4 rotquant gemm_w4a4 rotquant gemm_w4a4 ");
+    seen.clear();
+    for (int64_t d : {8 * 1024 * 2, -(8 * 64 * 2)})
+        CHECK(convlinear8bit_forward(X, A, F, nullptr, 8, 64, 1024, 16, X + d, A, convrot_workspace_bytes8(8, 1024), nullptr) == CONVROT_OK);
+    CHECK(seen == "forward_small forward_small ");
     launches_seen = nullptr;
     std::puts("C ABI host side under sanitizers: ok");
     return 0;

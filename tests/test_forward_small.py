@@ -14,7 +14,7 @@ from gpu_util import bf16_to_host_bits, check_output, to_dev_bf16
 from paper_2512_03673_amd import workloads as wl
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2512_03673_amd", "csrc")
-SHAPES = [(1, 1, 32), (1, 33, 96), (3, 77, 160), (8, 300, 1024), (8, 4097, 672), (7, 257, 256), (2, 4096, 4096), (4, 4096, 4096),
+SHAPES = [(1, 1, 32), (8, 1024, 1024), (1, 33, 96), (3, 77, 160), (8, 300, 1024), (8, 4097, 672), (7, 257, 256), (2, 4096, 4096), (4, 4096, 4096),
           (1, 4095, 16384), (1, 9216, 3072), (4, 16384, 64), (3, 1000, 5120), (5, 8192, 1024), (1, 8192, 15360)]
 TWO_LAUNCHES = [(9, 64, 256), (8, 16384, 64), (1, 16385, 64), (5, 64, 4096), (1, 64, 17408), (1, 8193, 15360), (64, 3072, 3072), (0, 64, 64)]
 
@@ -60,6 +60,11 @@ def test_one_launch_equals_two(M, N, K, bits):
             assert torch.equal(y[:M], ref) and (y[M] == 3.0).all(), g
             assert torch.equal(workspace[:size], Xq) and torch.equal(workspace[size:size + 4 * M].view(torch.float32), xs), g
             assert (workspace[size + 4 * M:] == 0x5A).all(), g
+        if N == K:          # in place: the two launches read all of X before Y is written, and so does a forward laid over its input
+            inout = X.clone()
+            forward(inout, Wq, ws, g, Y=inout)
+            torch.cuda.synchronize()
+            assert torch.equal(inout, gemm(Xq, xs, Wq, ws, K)), g
     g = 16 if K % 16 == 0 else 4
     if N * K <= 2 ** 22 and bits == 4:
         Wq, ws = prepare(W, g)
