@@ -87,7 +87,7 @@ struct Cut {        // a round of parts of 256 x 256 tiles
 // 275.5 / 260.5; over 16 and 19 drawn shapes 6 and 14 % - more of them would take two rounds of parts and lose).  After
 // many rounds the units no longer finish together and parts only cost (M16896 x N12288 x K3072, 12 rounds, 296 / 305).  8-bit
 // products gain nothing there over 192 x 192 tiles.  (All with operands that change from launch to launch; on one set of buffers,
-// which the Infinity Cache holds, M4608 x N12288 x K3072 takes 81.4 to 85.2 us in halves, by the box, and 80.4 to 82.1 with
+// which the Infinity Cache holds, M4608 x N12288 x K3072 takes 81.4 to 85.2 us in halves, from card to card, and 80.4 to 82.1 with
 // 192 x 192 tiles.)  Parts a tile is cut into, 1 if none is; `per_xcd` = tiles of an XCD.
 inline int parts_of_last_tiles(int64_t per_xcd)
 {
