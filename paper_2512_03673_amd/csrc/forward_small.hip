@@ -38,14 +38,15 @@ __global__ __launch_bounds__(64 * kWaves) void forward_small_kernel(const uint16
     const int KS = C::stages(K), units = K / kUnit, spans = (units + 63) / 64, items = M * spans;
 
     // ---- X first, then W: the rotation must not wait for W
-    u32x4 raw[I][2];
+    using It = Item<G>;
+    u32x4 raw[I][It::kLoads];
 #pragma unroll
     for (int i = 0; i < I; ++i) {
         const int item = min(wave + S * i, items - 1), row = item / spans, span = item - row * spans;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int unit = min(span * 64 + 32 * h + (lane & 31), units - 1);
-            raw[i][h] = *reinterpret_cast<const u32x4 *>(X + row * (int64_t)K + unit * kUnit + 8 * (lane >> 5));
+        for (int c = 0; c < It::kLoads; ++c) {
+            const int unit = min(span * 64 + It::source_unit(lane, c), units - 1);
+            raw[i][c] = *reinterpret_cast<const u32x4 *>(X + row * (int64_t)K + unit * kUnit + 8 * (lane >> 5));
         }
     }
     C w[WF];
@@ -61,19 +62,18 @@ __global__ __launch_bounds__(64 * kWaves) void forward_small_kernel(const uint16
         if (wave + p * S < KS) fetch(p, wave + p * S);
 
     // ---- rotate; row maxima through LDS
-    const v8bf rot0 = rotation_operand<G>(lane, 0), rot1 = rotation_operand<G>(lane, 1);
+    const Rotation<G> rot(lane);
     float v[I][kUnit];
 #pragma unroll
     for (int i = 0; i < I; ++i) {
         const int item = wave + S * i;
         if (item >= items) break;
-        rotate_units_mfma(rot0, rot1, raw[i][0], raw[i][1], v[i]);
-        rotate_lanes<G>(v[i]);
+        It::rotate(rot, raw[i], v[i]);
         float m = 0.0f;
 #pragma unroll
         for (int e = 0; e < kUnit; ++e) m = fmaxf(m, fabsf(v[i][e]));
-        m = item % spans * 64 + lane < units ? m : 0.0f;
-        m = max_of_64(m);
+        m = item % spans * 64 + It::unit(lane) < units ? m : 0.0f;
+        m = max_of_lanes<32>(m);
         if (lane == 0) item_max[item] = m;
     }
     __syncthreads();
@@ -93,7 +93,7 @@ __global__ __launch_bounds__(64 * kWaves) void forward_small_kernel(const uint16
             row_scale[row] = q.s;
             if (tn == 0) x_scale[row] = q.s;
         }
-        const int unit = span * 64 + (lane ^ lane_flip_mask<G>()), s = unit / kStageUnits;
+        const int unit = span * 64 + It::out_unit(lane), s = unit / kStageUnits;
         if constexpr (BITS == 4) {
             const v6u packed = codes4(q, false, as_vector(v[i]), as_vector(v[i]));
             if (s >= KS) continue;

@@ -1,5 +1,5 @@
-// Shared pieces of the GEMM kernels of libconvrot, 4-bit and 8-bit (LDS swizzle, LDS-direct loads,
-// tile order).  gemm_tiled.h and gemm_small.h describe the method.
+// Shared pieces of the GEMM kernels of libconvrot, 4-bit and 8-bit (LDS swizzle, LDS-direct loads, which the
+// rotate+quantise kernel uses too, tile order).  gemm_tiled.h and gemm_small.h describe the method.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -46,10 +46,14 @@ __device__ __forceinline__ void wait_vmcnt_lgkm0()
 // so it would only look like a guarantee.  None of the instructions above occurs in the GEMM kernels besides this
 // one (the build prints the hipcc version it ran with, and the bit-exact GEMM tests are the check that a new
 // toolchain still behaves so: a stale M0 sends a kilobyte of operands to the wrong place in the ring).
+// (STREAM: data that is read once and should not push other lines out of the caches.)
+template <bool STREAM = false>
 __device__ __forceinline__ void lds_dma16(const uint8_t *base, uint32_t lane_off, uint32_t lds_addr)
 {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :: "v"(lane_off), "s"(base), "s"(lds_addr) : "memory");
+    if constexpr (STREAM)
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" :: "v"(lane_off), "s"(base), "s"(lds_addr) : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" :: "v"(lane_off), "s"(base), "s"(lds_addr) : "memory");
 }
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 

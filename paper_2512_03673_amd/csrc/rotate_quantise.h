@@ -1,20 +1,18 @@
-// The rotation and the quantiser of the rotate+quantise kernels, on units of 16 consecutive elements of a row that
-// belong to one lane each.
+// The rotation and the quantiser of the rotate+quantise kernels, on units of 16 consecutive elements of a row; four units
+// are a column of 64.
 //
 // Rotation.  H_g = H_4 (x) ... (x) H_4 (Thm 3.3) is separable: one radix-4 step per base-4 digit
 // of the in-group index.  With the printed H_4 (all ones, -1 on the anti-diagonal) a step is
 //     y_j = (x_0 + x_1 + x_2 + x_3) - 2 x_{3-j}.
-// Digits 0 and 1 live inside a lane's 16 elements: a 16 x 16 matrix of +-1 (H_4 (x) H_4) applied to
-// every unit, which is what the otherwise idle matrix pipe does for 64 units at a time, the bf16 -> fp32
-// widening and the hand-over of each unit to its lane included (rotation_operand below): the vector ALU,
-// which bounds this kernel on small inputs, sees none of it.
-// Digits 2, 3 (g = 64, 256) run across lanes with DPP adds and digit 4 (g = 1024) over a lane's four units or, in
-// short rows, with lane swaps; across lanes the step is taken as y_j = s - 2 x_j (the matrix J - 2I, which is
-// the printed matrix with its columns reversed) and the flip is applied once, for free, to the
+// Digits 0 and 1 live inside a unit and digit 2 inside a column: a matrix of +-1 (H_4 (x) H_4 (x) H_4) applied to every column,
+// which is what the otherwise idle matrix pipe does, the bf16 -> fp32 widening and the hand-over of each unit to its lane
+// included (Rotation below): the vector ALU, which bounds these kernels as much as memory does, sees none of it.
+// Digits 3 and 4 (g = 256, 1024) run across lanes with DPP adds; there the step is taken as y_j = s - 2 x_j (the matrix
+// J - 2I, which is the printed matrix with its columns reversed) and the flip is applied once, for free, to the
 // lane's output address.  The 1/sqrt(g) = 2^-k normalisation is folded into the scale.
 //
 // Quantiser.  a = 2^-k max|z| (exact), s = a / 7 (IEEE division), r = 2^-k / s (IEEE division),
-// q = rne(z / (2^k s)) decided exactly from two bracketing multiply-adds, with an exact-residual
+// q = rne(z / (2^k s)) decided exactly from a multiplication and its residual, with an exact
 // fallback for the few wavefronts that hold a (near-)tie (see the comment at the code).
 // |z| / (2^k s) <= 7 (1 + 2^-22), so no clamp is needed.
 //
@@ -41,27 +39,17 @@ __device__ __forceinline__ float dpp_f32(float x)
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
 }
 
-// s - 2 x with s the sum over the four lanes that differ in one base-4 digit of the lane id.
+// s - 2 x with s the sum over the four lanes that differ in one base-4 digit of the lane id: the neighbour's value minus the lane's
+// own, plus the sum of the other two.  (Three roundings of sums of at most two, two and four values; s first and then s - 2 x as a
+// fused multiply-add takes three instructions too and rounds one more time.)
 template <int CTRL_A, int CTRL_B>
 __device__ __forceinline__ float radix4_lanes_dpp(float x)
 {
-    float t = x + dpp_f32<CTRL_A>(x);
-    float s = t + dpp_f32<CTRL_B>(t);
-    return fmaf(-2.0f, x, s);
+    const float y = dpp_f32<CTRL_A>(x);
+    return (y - x) + dpp_f32<CTRL_B>(x + y);
 }
 
-// The values of lanes l and l ^ 16 (l ^ 32), in the same order on both: v_permlane16_swap / v_permlane32_swap of a register with
-// its copy.  A vector instruction where a wavefront shuffle is a trip through LDS.
-__device__ __forceinline__ float radix4_lanes_16_32(float x)
-{
-    const uint32_t u = __float_as_uint(x);
-    const auto p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    const float t = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(t), __float_as_uint(t), false, false);
-    return fmaf(-2.0f, x, __uint_as_float(q[0]) + __uint_as_float(q[1]));
-}
-
-// Maximum over the lane's row of 16 lanes, and over the whole wavefront, of values that are neither negative nor NaN: their bits
+// Maximum over the lane's C consecutive lanes and those P, 2 P, ... further on (C = 4 ... 32, P = 16 or 32), of values that are neither negative nor NaN: their bits
 // order as they do, and integers need no canonicalising moves.  (A butterfly of wavefront shuffles waits for LDS four to six times,
 // and a rotate+quantise block can do nothing else meanwhile: [12288, 3072] at g = 256 21.7 -> 21.0 us, [8000, 1024] 6.6 -> 6.3.)
 template <int CTRL>
@@ -69,90 +57,143 @@ __device__ __forceinline__ uint32_t max_dpp(uint32_t x)
 {
     return max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, false));
 }
-__device__ __forceinline__ float max_of_16(float x)
+template <int C, int P = 32>
+__device__ __forceinline__ float max_of_lanes(float x)
 {
+    static_assert((C == 4 || C == 8 || C == 16 || C == 32) && (P == 16 || P == 32) && C <= P, "lanes");
     uint32_t u = max_dpp<0xB1>(__float_as_uint(x));      // quad_perm [1,0,3,2]
     u = max_dpp<0x4E>(u);                                // quad_perm [2,3,0,1]
-    return __uint_as_float(max_dpp<0x128>(max_dpp<0x124>(u)));   // row_ror:4, row_ror:8
-}
-__device__ __forceinline__ float max_of_64(float x)
-{
-    const uint32_t u = __float_as_uint(max_of_16(x));
-    const auto p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    const uint32_t m = max((uint32_t)p[0], (uint32_t)p[1]);
-    const auto q = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+    if constexpr (C >= 8) u = max_dpp<0x141>(u);         // row_half_mirror: the other quad of eight lanes
+    if constexpr (C >= 16) u = max_dpp<0x128>(u);        // row_ror:8
+    if constexpr (C == 32 || P == 16) {
+        const auto p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+        u = max((uint32_t)p[0], (uint32_t)p[1]);
+    }
+    const auto q = __builtin_amdgcn_permlane32_swap(u, u, false, false);
     return __uint_as_float(max((uint32_t)q[0], (uint32_t)q[1]));
 }
 
-// The digits that live across lanes (in-group index digits 2 and up), on a unit whose digits 0 and 1 are done.
+// The digits that live across lanes (in-group index digits 3 and up), on a unit whose digits 0 to 2 are done; neighbouring
+// lanes hold neighbouring columns.
 template <int G>
 __device__ __forceinline__ void rotate_lanes(float (&v)[kUnit])
 {
-    if constexpr (G >= 64) {  // lanes l ^ 1, l ^ 2: quad_perm [1,0,3,2] then [2,3,0,1]
+    if constexpr (G >= 256) {  // lanes l ^ 1, l ^ 2: quad_perm [1,0,3,2] then [2,3,0,1]
 #pragma unroll
         for (int e = 0; e < kUnit; ++e) v[e] = radix4_lanes_dpp<0xB1, 0x4E>(v[e]);
     }
-    if constexpr (G >= 256) {  // lanes l ^ 8, l ^ 4 inside a row of 16: row_ror:8 then row_ror:4
+    if constexpr (G >= 1024) {  // lanes l ^ 8, l ^ 4 inside a row of 16: row_ror:8 then row_ror:4
 #pragma unroll
         for (int e = 0; e < kUnit; ++e) v[e] = radix4_lanes_dpp<0x128, 0x124>(v[e]);
     }
-    if constexpr (G >= 1024) {
-#pragma unroll
-        for (int e = 0; e < kUnit; ++e) v[e] = radix4_lanes_16_32(v[e]);
-    }
 }
 
-// The digits inside a unit on the matrix pipe.  v_mfma_f32_32x32x16_bf16 computes D = A B with B a 16 x 32
+// Where the result of lane l's column belongs: column number ^ flip.
+template <int G>
+constexpr int column_flip() { return G >= 1024 ? 15 : (G >= 256 ? 3 : 0); }
+
+// The digits inside a column on the matrix pipe.  v_mfma_f32_32x32x16_bf16 computes D = A B + C with B a 16 x 32
 // matrix of bf16 whose column n is spread over lanes n (rows 0-7) and n + 32 (rows 8-15), eight consecutive
 // rows = 16 contiguous bytes each, and leaves column n of D in lanes n (rows 8 b + r) and n + 32 (rows
-// 8 b + 4 + r), register 4 b + r.  With the 32 units of lanes 0-31 as the columns of B and the 16 rows of
-// R = H_4 (x) H_4 (I_4 (x) H_4 for g = 4; both symmetric) put at the rows 8 b + r of A, zeros elsewhere, lane n
-// receives its whole rotated unit in element order, as fp32; a second MFMA with the rows of R at 8 b + 4 + r and
-// the units of lanes 32-63 as B accumulates the other half of the wavefront on top.  Products with +-1 are
-// exact and the sums are taken in fp32, as the register butterflies take them; the bf16 -> fp32 widening
-// comes with it.  The price is that a lane fetches halves of two other lanes' units instead of its own.
-// Returns this lane's eight entries of A for the MFMA that serves lanes 32 * half ... 32 * half + 31.
+// 8 b + 4 + r), register 4 b + r.  B is unit c of 32 columns; a lane's sixteen rows of D are one unit in element order,
+// as fp32.  With R = H_4 (x) H_4 (both halves of A's rows may hold it, with a sign each; I_4 (x) H_4 for g = 4):
+//   g <= 16   lane n gets R x_c of one unit, lane n + 32 of another: two MFMAs, each with zeros in the other's rows of A
+//   g >= 64   out_u = R (x_0 + x_1 + x_2 + x_3 - 2 x_{3-u}): four MFMAs with the signs of rows u of H_4 (lanes n) and
+//             u + 2 (lanes n + 32) accumulate the whole 64-term sum, 0.125 cycles an element on a pipe that has nothing else
+//             to do, where a radix-4 step across lanes took three vector instructions an element
+// The odd units (1 and 3) are the even ones' sums with x_c and x_{c^1} exchanged, so that A is the same and a lane may as well
+// be given either kind.  Products with +-1 are exact, sums are fp32; the bf16 -> fp32 widening
+// comes with it.  The price is that a lane fetches parts of the columns' units instead of its own.  What one column holds never
+// meets another (0 x infinity), and a column lies in one row.
 template <int G>
-__device__ __forceinline__ v8bf rotation_operand(int lane, int half)
-{
-    const int i = lane & 31, kb = lane >> 5;
-    const int o = 4 * (i >> 3) + (i & 3);             // element of the unit that accumulator row i holds
-    const bool mine = ((i >> 2) & 1) == half;
-    union { v8bf v; uint16_t u[8]; } a;
+struct Rotation {
+    static constexpr int kTerms = G >= 64 ? 4 : 2;
+    v8bf a[G >= 64 ? 3 : 2];
+
+    __device__ __forceinline__ explicit Rotation(int lane)
+    {
+        // Row i of A: element o = 4 (i / 8) + i % 4 of the unit of lanes n (i / 4 even) or n + 32; this lane's entries are rows
+        // k = 8 (lane / 32) + x of R's column o, -1 where the digits (o, k) sum to 3 in one of their two places.
+        const int kb = lane >> 5, o1 = (lane >> 3) & 3;
+        const bool upper = (lane & 4) != 0;
+        const uint64_t minus = (uint64_t)0x8000 << (16 * (3 - (lane & 3)));     // digit 0: four entries of two bytes
+        const uint32_t m[2] = {(uint32_t)minus, (uint32_t)(minus >> 32)};
+        uint32_t base[4];
 #pragma unroll
-    for (int x = 0; x < 8; ++x) {
-        const int k = 8 * kb + x;
-        const bool neg = ((o & 3) + (k & 3) == 3) != (G >= 16 && (o >> 2) + (k >> 2) == 3);
-        const bool zero = !mine || (G < 16 && (o >> 2) != (k >> 2));
-        a.u[x] = zero ? (uint16_t)0 : (neg ? (uint16_t)0xBF80 : (uint16_t)0x3F80);    // bf16 0, -1, +1
+        for (int x1 = 0; x1 < 2; ++x1) {
+            const int k1 = 2 * kb + x1;
+#pragma unroll
+            for (int w = 0; w < 2; ++w)
+                base[2 * x1 + w] = G < 16 ? (o1 == k1 ? 0x3F803F80u ^ m[w] : 0u) : (o1 + k1 == 3 ? 0xBF80BF80u : 0x3F803F80u) ^ m[w];
+        }
+        u32x4 r[3];
+        const uint32_t u = upper ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            if constexpr (G >= 64) {
+                r[0][w] = base[w];
+                r[1][w] = base[w] ^ (u & 0x80008000u);       // minus in the rows of lanes n + 32
+                r[2][w] = base[w] ^ (~u & 0x80008000u);      // minus in the rows of lanes n
+            } else {
+                r[0][w] = base[w] & ~u;
+                r[1][w] = base[w] & u;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < (G >= 64 ? 3 : 2); ++i) a[i] = __builtin_bit_cast(v8bf, r[i]);
     }
-    return a.v;
-}
 
-// Digits 0 and 1 of 64 units, one per lane: b0 / b1 = bytes 16 (lane / 32) ... + 15 of the units owned by lanes
-// lane % 32 and lane % 32 + 32; v = this lane's unit.
-__device__ __forceinline__ void rotate_units_mfma(const v8bf &rot0, const v8bf &rot1, const u32x4 &b0, const u32x4 &b1,
-                                                  float (&v)[kUnit])
-{
-    v16f d = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rot0, __builtin_bit_cast(v8bf, b0), d, 0, 0, 0);
-    d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rot1, __builtin_bit_cast(v8bf, b1), d, 0, 0, 0);
+    // This lane's unit: of an even pair (unit 0, in lanes n + 32 unit 2) from the bytes b(c) of unit c, of an odd pair (1, 3)
+    // from those of unit c ^ 1.  b(c) = 16 (lane / 32) ... + 15 of the unit's 32 bytes; g <= 16 asks for c = 0 and 2 only.
+    template <class B>
+    __device__ __forceinline__ void apply(B b, float (&v)[kUnit]) const
+    {
+        v16f d = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+        if constexpr (G >= 64) {      // rows 0 and 2 of H_4: + + + -, + - + +
+            d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], __builtin_bit_cast(v8bf, b(0)), d, 0, 0, 0);
+            d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], __builtin_bit_cast(v8bf, b(1)), d, 0, 0, 0);
+            d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], __builtin_bit_cast(v8bf, b(2)), d, 0, 0, 0);
+            d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], __builtin_bit_cast(v8bf, b(3)), d, 0, 0, 0);
+        } else {
+            d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], __builtin_bit_cast(v8bf, b(0)), d, 0, 0, 0);
+            d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], __builtin_bit_cast(v8bf, b(2)), d, 0, 0, 0);
+        }
 #pragma unroll
-    for (int e = 0; e < kUnit; ++e) v[e] = d[e];
-}
+        for (int e = 0; e < kUnit; ++e) v[e] = d[e];
+    }
+};
 
-template <int G>      // of the digits across lanes
-constexpr int lane_flip_mask() { return G >= 1024 ? 63 : (G >= 256 ? 15 : (G >= 64 ? 3 : 0)); }
+// One lane's unit of 1024 elements of a row that a wavefront shares (an item): lane l's unit of the item, before and after the
+// flip of the digits across lanes.
+template <int G>
+struct Item {
+    static constexpr int kLoads = Rotation<G>::kTerms;
+    // the unit that this lane fetches its part of for term c
+    static __device__ __forceinline__ int source_unit(int lane, int c)
+    {
+        const int odd = (lane >> 4) & 1;
+        return 4 * (lane & 15) + (G >= 64 ? c ^ odd : 2 * c + odd);
+    }
+    static __device__ __forceinline__ int unit(int lane) { return 4 * (lane & 15) + ((lane >> 4) & 1) + 2 * (lane >> 5); }
+    static __device__ __forceinline__ int out_unit(int lane) { return unit(lane ^ column_flip<G>()); }
+    static __device__ __forceinline__ void rotate(const Rotation<G> &rot, const u32x4 (&raw)[kLoads], float (&v)[kUnit])
+    {
+        rot.apply([&](int c) { return raw[G >= 64 ? c : c / 2]; }, v);
+        rotate_lanes<G>(v);
+    }
+};
 
 template <int G>
 constexpr float group_norm() { return G == 4 ? 0.5f : G == 16 ? 0.25f : G == 64 ? 0.125f : G == 256 ? 0.0625f : 0.03125f; }
 
 // Codes.  a = 2^-k max|z| (exact), s = a / qmax, q = rne(z / su) with su = s / norm, decided exactly although the lane only
-// multiplies.  r approximates 1 / su to 2^-24, so z / su lies strictly between z * r_lo and z * r_hi
-// (r_lo, r_hi = r (1 -+ 2^-21)); rounding to an integer is monotonic, hence when both products
-// round to the same integer so does the exact quotient.  One fused multiply-add against
-// 1.5 * 2^23 (+ an offset) rounds a product to nearest, ties to even, and leaves the integer in
-// the low mantissa bits.  A wavefront in which any pair disagrees (a few in a thousand on random
+// multiplies.  One fused multiply-add against 1.5 * 2^23 (+ an offset) rounds a product to nearest, ties to even, and leaves the
+// integer in the low mantissa bits.  Whether the exact quotient rounds to the same integer is known from
+//   4 bits   the residual z r - q: r approximates 1 / su to 2^-24, so it is within 7 * 2^-24 + 2^-26 < 2^-20 of z / su - q, and a
+//            residual of at most 1/2 - 2^-20 says that q is the nearest integer
+//   8 bits   a second product: z / su lies strictly between z * r_lo and z * r_hi (r_lo, r_hi = r (1 -+ 2^-21)), rounding is
+//            monotonic, hence when both round to the same integer so does the exact quotient
+// A wavefront in which any code is not known so (a few in a thousand on random
 // data; every exact tie, which bf16-grid inputs do produce when the scale is a short dyadic
 // number) redoes its codes through the exact residual e = z - q su (one rounding of a quantity
 // that is representable whenever q is the nearest or a neighbouring integer), which decides the
@@ -199,24 +240,22 @@ __device__ __forceinline__ v16f as_vector(const float (&v)[kUnit])
 __device__ __forceinline__ v6u codes4(const Quantiser &q, bool pair, v16f v0, v16f v1)
 {
     constexpr float kMagic = 12582912.0f;                       // 1.5 * 2^23
-    // the two brackets agree on every code exactly when the sum of |difference of their bit patterns|
-    // is zero (the patterns share their upper halves, so the 16-bit SAD sees the whole difference)
-    uint32_t disagree = 0;
+    float worst = 0.0f;                                         // largest residual
     v16f qa, qb;    // conversion sources; the halves of a missing second unit stay unset (their output is not used)
 #pragma unroll
     for (int e = 0; e < kUnit; ++e) {
-        const float lo0 = fmaf(v0[e], q.r_lo, kMagic), hi0 = fmaf(v0[e], q.r_hi, kMagic);
-        disagree = __builtin_amdgcn_sad_u16(__float_as_uint(lo0), __float_as_uint(hi0), disagree);
-        if (e < 8) qa[e] = lo0 - kMagic;
-        else qb[e - 8] = lo0 - kMagic;
+        const float q0 = fmaf(v0[e], q.r, kMagic) - kMagic;
+        worst = fmaxf(worst, fabsf(fmaf(v0[e], q.r, -q0)));
+        if (e < 8) qa[e] = q0;
+        else qb[e - 8] = q0;
         if (pair) {
-            const float lo1 = fmaf(v1[e], q.r_lo, kMagic), hi1 = fmaf(v1[e], q.r_hi, kMagic);
-            disagree = __builtin_amdgcn_sad_u16(__float_as_uint(lo1), __float_as_uint(hi1), disagree);
-            if (e < 8) qa[8 + e] = lo1 - kMagic;
-            else qb[e] = lo1 - kMagic;
+            const float q1 = fmaf(v1[e], q.r, kMagic) - kMagic;
+            worst = fmaxf(worst, fabsf(fmaf(v1[e], q.r, -q1)));
+            if (e < 8) qa[8 + e] = q1;
+            else qb[e] = q1;
         }
     }
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(disagree != 0) != 0, 0)) {   // wavefront-uniform, rare
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(worst > 0.5f - 0x1p-20f) != 0, 0)) {   // wavefront-uniform, rare
 #pragma unroll
         for (int e = 0; e < kUnit; ++e) {
             const float q0 = q.exact(v0[e]);

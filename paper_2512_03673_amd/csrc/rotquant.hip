@@ -2,11 +2,15 @@
 // quantisation + packing of the codes, one pass over the bf16 input (ConvRot paper Sec. 4.2 Eq. 11-13,
 // Eq. 1, Sec. 5.2).  Serves activations (rows = tokens) and weights (rows = output channels).
 //
-// Work split.  A "unit" is 16 consecutive elements of a row (32 B of bf16 in, 12 B of codes out)
-// and belongs to one lane.  A row is spread over T = 64*Wv lanes (Wv wavefronts); lane t of the
-// row owns units t, t+T, t+2T, ... (U of them), so the two load instructions of a wavefront for one
-// such set of units cover a contiguous 2 KB span of the row.  The whole row stays in registers between the absmax
+// Work split.  A column is 64 consecutive elements of a row: 128 bytes of bf16 in, two chunks of 32 codes (four units) out.  A
+// chunk is what one lane feeds one MFMA of the GEMM; a wavefront rotates 16 or 32 columns at a time (a set) and a lane ends up
+// with a unit or with a whole chunk.  The whole row stays in registers between the absmax
 // reduction and the rounding, so X is read from HBM exactly once.
+//
+// What bounds it: memory, 2.75 bytes an element (a large copy runs at 6.1 TB/s), on rows of 3072 elements and more; the launch and one
+// pass of every wavefront through load, arithmetic and store on smaller inputs.  Vector instructions, 7.5 to 9 an element
+// (g <= 64) to 13.4 (g = 1024), would take two thirds of that time and overlap with it.  With digit 2 on the vector ALU, a bracketing
+// second product for every code and a unit's 12 bytes stored in two places by pairs of lanes they were 10.9 to 18.
 //
 // The rotation and the quantiser themselves are rotate_quantise.h.
 #include <hip/hip_runtime.h>
@@ -14,6 +18,7 @@
 
 #include "convrot_internal.h"
 #include "e2m3_layout.h"
+#include "gemm_common.h"
 #include "panel_layout.h"
 #include "rotate_quantise.h"
 
@@ -21,188 +26,170 @@ namespace convrot {
 
 namespace {
 
-// Which unit of its row lane t holds as its i-th.  With g = 1024 and four units a lane these are of one group, 16 apart: digit 4
-// runs over them and its radix-4 step is seven instructions on four values of one lane instead of three instructions and two wavefront
-// shuffles an element ([4608, 15360]: 48.4 -> 42.7 us).  16 lanes still load 512 bytes of a row at a time.  (The same for digit 3
-// of g = 256, where four lanes would load 128 bytes: no faster on large inputs, 15 % slower on 512 rows.)
-template <int G, int U>
-__device__ __forceinline__ int unit_of(int i, int t, int T)
+// All but the last N * n of this wavefront's loads have landed (n is known where the call is inlined).
+template <int N>
+__device__ __forceinline__ void wait_loads(int n)
 {
-    if constexpr (G == 1024 && U == 4) return ((t >> 4) << 6) + 16 * i + (t & 15);
-    else return i * T + t;
-}
-
-// Digit 4 over a lane's four units, in the printed matrix's order.
-__device__ __forceinline__ void rotate_registers(float (&v)[4][kUnit])
-{
-#pragma unroll
-    for (int e = 0; e < kUnit; ++e) {
-        const float x0 = v[0][e], x1 = v[1][e], x2 = v[2][e], x3 = v[3][e];
-        const float s = (x0 + x1) + (x2 + x3);
-        v[0][e] = fmaf(-2.0f, x3, s);
-        v[1][e] = fmaf(-2.0f, x2, s);
-        v[2][e] = fmaf(-2.0f, x1, s);
-        v[3][e] = fmaf(-2.0f, x0, s);
-    }
+    if (n == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    else if (n == 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
+    else if (n == 2) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * N) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(3 * N) : "memory");
 }
 
 }  // namespace
 
-// T = lanes per row.  Two ways of laying rows over wavefronts:
-//   RPW = 1  a wavefront holds 64 lanes of one row (T = 64 * waves per row, BLOCK / T rows per block): any K, any g
-//   RPW = 4  a wavefront holds 16 lanes of each of 4 consecutive rows (T = threads / 4, 4 rows per block): the cross-lane
-//            digits stay inside 16 lanes; used for K <= 4096.  The four rows' pieces of an output block
-//            are adjacent in memory, so a store instruction touches 256- and 128-byte runs instead of 64- and
-//            32-byte ones: as few cache lines per instruction as a row-major stream would.
-// grid.x = 8 * ceil(rows / (8 * group rows)) * group rows / rows per block (see the row mapping below).
+// A set is what a wavefront rotates at a time: 16 U columns, U units a lane, 16 U / RPW columns of each of RPW consecutive rows.
+// A wavefront holds S sets of its rows and WPR wavefronts side by side, one block, hold the whole rows.
+//   U = 2  lanes n and n + 32 hold the even and the odd chunk of column n and store them whole
+//   U = 1  lanes n, n + 16, n + 32, n + 48 hold the units of column n: twice the wavefronts, for short rows
 // BITS = 4: codes in [-7, 7], stored as FP6 E2M3 (e2m3_layout.h); BITS = 8 (the W8A8 variant of the layer): one
 // int8 per code, [-127, 127] (panel_layout.h).
-// (At least two wavefronts per SIMD, i.e. at most 256 registers per lane: then the compiler keeps the MFMA results in
-// ordinary registers instead of copying them out of the accumulation registers, one move per element.)
-template <int G, int U, int BLOCK, int BITS, int RPW>
-__global__ __launch_bounds__(BLOCK, BLOCK <= 256 ? 2 : 1) void rotquant_kernel(const uint16_t *__restrict__ X, int64_t rows, int K,
-                                                         int T, uint8_t *__restrict__ Xq,
-                                                         float *__restrict__ scale)
-{
-    constexpr bool kDigit4 = G == 1024 && U == 4;   // over a lane's units (unit_of)
-    constexpr int kLaneG = kDigit4 ? 256 : G;       // the rest of the rotation: inside a unit and across lanes
-    static_assert(RPW == 1 || (RPW == 4 && kLaneG <= 256), "four rows per wavefront need the rotation inside 16 lanes");
-    __shared__ float s_part[BLOCK / 64 * RPW];
+template <int U, int RPW, int WPR, int S>
+struct Split {
+    static constexpr int kThreads = 64 * WPR;
+    // (At least two wavefronts per SIMD, i.e. at most 256 registers per lane: then the compiler keeps the MFMA results in
+    // ordinary registers instead of copying them out of the accumulation registers, one move per element.)
+    static constexpr int kOccupancy = WPR <= 4 ? 2 : 1;
+    static constexpr int kColumns = 16 * U / RPW;             // of a row, in one set
+    static constexpr int kSetBytes = 2048 * U;
+    static_assert((U == 1 || U == 2) && WPR <= 16 && S <= 4, "split");
+};
 
-    const int tid = threadIdx.x;
-    const int rib = RPW == 1 ? tid / T : (tid & 63) >> 4;                        // row inside the block
-    const int t = RPW == 1 ? tid - rib * T : (tid >> 6) * 16 + (tid & 15);       // lane index inside the row
-    const int rows_per_block = RPW == 1 ? BLOCK / T : RPW;
-    // Blocks are dealt round-robin to the 8 XCDs, each with an L2 of its own.  The 16 rows of an output
-    // panel go to consecutive blocks of one XCD, so that the 64-byte row pieces of a panel meet in one
+template <int G, int BITS, int U, int RPW, int WPR, int S>
+__global__ __launch_bounds__((Split<U, RPW, WPR, S>::kThreads), (Split<U, RPW, WPR, S>::kOccupancy)) void rotquant_kernel(
+    const uint16_t *__restrict__ X, int64_t rows, int K, uint8_t *__restrict__ Xq, float *__restrict__ scale)
+{
+    using Sp = Split<U, RPW, WPR, S>;
+    constexpr int C = Sp::kColumns;
+    static_assert(G <= 64 || G / 64 <= C, "the lanes of a rotation group lie in one row");
+    __shared__ float part[WPR * RPW];
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // Blocks are dealt round-robin to the 8 XCDs, each with an L2 of its own.  The rows of an output
+    // block go to consecutive thread blocks of one XCD, so that their pieces of a line meet in one
     // L2 and leave it as whole lines.
     constexpr int kGroupRows = BITS == 4 ? e2m3::kRows : panel::kRows;   // rows that share an output block
-    const int bpp = kGroupRows / rows_per_block;              // thread blocks per group of rows
+    constexpr int kBlocks = kGroupRows / RPW;                            // thread blocks per group of rows
     const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
-    const int64_t row = ((int64_t)(idx / bpp) * 8 + xcd) * kGroupRows + (idx % bpp) * rows_per_block + rib;
-    const bool row_ok = row < rows;
-    const int units = K / kUnit;
+    const int64_t row0 = ((int64_t)(idx / kBlocks) * 8 + xcd) * kGroupRows + idx % kBlocks * RPW;
+    if (row0 >= rows) return;
+    const int left = (int)min((int64_t)RPW, rows - row0) - 1;            // the last of its rows that exists
+    const int rib = (lane & (16 * U - 1)) / C;                           // row of the block
+    const bool row_ok = rib <= left;
+    const int h = lane >> 5, odd16 = (lane >> 4) & 1, chunks = K / 32;
+    const int column0 = wave * C + (lane & (C - 1));                     // this lane's column of the first set
 
-    // All loads are issued up front and unconditionally: a unit (or row) that does not exist is replaced
-    // by the last unit of the last row, and its owner is masked out of the absmax and the stores.
+    // The columns come through LDS: lanes n and n + 32 need the 16-byte halves of the four units of column n, 32 lines of 32 bytes
+    // for a load straight into registers; copied there (LDS-direct, a kilobyte of consecutive columns at a time) the
+    // lines are read whole.  Slot p of column n holds piece p ^ (n & 7), so that eight lanes read different banks.
+    // All loads are issued up front and unconditionally: a column (or row) that does not exist is replaced
+    // by the last one of the row (of the last row), and its owner is masked out of the absmax and the stores.
     // K % g == 0 makes a rotation group all-valid or all-invalid, so such lanes never feed valid ones.
-    // The units are fetched as operands of the rotation MFMAs (rotation_operand): for h = 0, 1 this lane
-    // loads bytes 16 kb ... 16 kb + 15 (kb = lane / 32) of the units owned by lane (lane % 32) + 32 h.
-    const int lane = tid & 63;
-    const uint16_t *src[2];
-    int t_src[2];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[WPR * S * Sp::kSetBytes];
+    uint8_t *const mine = lds + wave * (S * Sp::kSetBytes);
+    {
+        const uint8_t *const x = reinterpret_cast<const uint8_t *>(X + row0 * K);
+        const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)mine;
+        const int n0 = lane >> 3, p = (lane & 7) ^ n0;       // column of the first kilobyte, its piece
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int otid = (tid & ~63) | (lane & 31) | (h << 5);                     // the owner
-        const int orib = RPW == 1 ? rib : (otid & 63) >> 4;                        // (a wavefront lies inside one row if RPW == 1)
-        t_src[h] = RPW == 1 ? otid - rib * T : (otid >> 6) * 16 + (otid & 15);
-        const int64_t orow = row - rib + orib;
-        src[h] = X + (orow < rows ? orow : rows - 1) * (int64_t)K + 8 * (lane >> 5);
+        for (int i = 0; i < S; ++i)
+#pragma unroll
+            for (int j = 0; j < 2 * U; ++j) {
+                const int n = 8 * j + n0;
+                const int piece = min(8 * ((wave + i * WPR) * C + (n & (C - 1))) + p, 4 * chunks - 1);
+                gemm::lds_dma16<true>(x, (uint32_t)min(n / C, left) * (uint32_t)K * 2 + 16 * piece, base + (i * 2 * U + j) * 1024);
+            }
     }
-    u32x4 raw[U][2];
-#pragma unroll
-    for (int i = 0; i < U; ++i) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int unit = min(unit_of<G, U>(i, t_src[h], T), units - 1);
-            raw[i][h] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src[h] + (int64_t)unit * kUnit));
-        }
-    }
-    const v8bf rot0 = rotation_operand<G>(lane, 0), rot1 = rotation_operand<G>(lane, 1);
+    const Rotation<G> rot(lane);
 
-    float v[U][kUnit];
+    float v[S][U][kUnit];
     float amax = 0.0f;
-    if constexpr (kDigit4) {
 #pragma unroll
-        for (int i = 0; i < U; ++i) {
-            rotate_units_mfma(rot0, rot1, raw[i][0], raw[i][1], v[i]);
-            rotate_lanes<kLaneG>(v[i]);
-        }
-        rotate_registers(v);
-    }
-#pragma unroll
-    for (int i = 0; i < U; ++i) {
-        if constexpr (!kDigit4) {
-            rotate_units_mfma(rot0, rot1, raw[i][0], raw[i][1], v[i]);
-            rotate_lanes<kLaneG>(v[i]);
-        }
+    for (int i = 0; i < S; ++i) {
         float m = 0.0f;
+        wait_loads<2 * U>(S - 1 - i);
+        auto piece = [&](int c) { return *reinterpret_cast<const u32x4 *>(mine + i * Sp::kSetBytes + (lane & (16 * U - 1)) * 128 + (((2 * c + h) ^ (lane & 7)) << 4)); };
+        if constexpr (U == 2) {
+            u32x4 raw[4];
 #pragma unroll
-        for (int e = 0; e < kUnit; ++e) m = fmaxf(m, fabsf(v[i][e]));
-        amax = (row_ok && unit_of<G, U>(i, t, T) < units) ? fmaxf(amax, m) : amax;
+            for (int c = 0; c < 4; ++c) raw[c] = piece(c);
+#pragma unroll
+            for (int odd = 0; odd < 2; ++odd) rot.apply([&](int c) { return raw[c ^ odd]; }, v[i][odd]);
+        } else {
+            rot.apply([&](int c) { return piece(c ^ odd16); }, v[i][0]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) rotate_lanes<G>(v[i][u]);
+#pragma unroll
+        for (int e = 0; e < U * kUnit; ++e) m = fmaxf(m, fabsf(v[i][e / kUnit][e % kUnit]));
+        amax = 2 * (column0 + i * WPR * C) + h < chunks ? fmaxf(amax, m) : amax;
     }
 
-    // row absmax: butterfly over the row's lanes of this wavefront, then across the row's wavefronts through LDS
-    if constexpr (RPW == 1) {
-        amax = max_of_64(amax);
-        if (T > 64) {
-            if ((tid & 63) == 0) s_part[tid >> 6] = amax;
-            __syncthreads();
-            const int w0 = (rib * T) >> 6;
-            const int wv = T >> 6;
-            float a = s_part[w0];
-            for (int w = 1; w < wv; ++w) a = fmaxf(a, s_part[w0 + w]);
-            amax = a;
-        }
-    } else {
-        amax = max_of_16(amax);
-        if ((tid & 15) == 0) s_part[(tid >> 6) * RPW + rib] = amax;
+    // row absmax: the row's lanes of this wavefront, then the row's wavefronts through LDS
+    amax = max_of_lanes<C, 16 * U>(amax);
+    if constexpr (WPR > 1) {
+        if ((lane & (C - 1)) == 0 && h == 0 && (U == 2 || odd16 == 0)) part[wave * RPW + rib] = amax;
         __syncthreads();
-        float a = s_part[rib];
+        amax = part[rib];
 #pragma unroll
-        for (int w = 1; w < BLOCK / 64; ++w)
-            a = !kDigit4 || w * 16 < T ? fmaxf(a, s_part[w * RPW + rib]) : a;
-        amax = a;
+        for (int w = 1; w < WPR; ++w) amax = fmaxf(amax, part[w * RPW + rib]);
     }
 
     const Quantiser q(amax, group_norm<G>(), BITS == 4 ? 7.0f : 127.0f);
-    if (row_ok && t == 0) scale[row] = q.s;
-    const int tf = t ^ lane_flip_mask<kLaneG>();
+    if (row_ok && column0 + h + (U == 2 ? 0 : odd16) == 0) scale[row0 + rib] = q.s;
 
+    const int out0 = column0 ^ column_flip<G>();             // (sets are apart by multiples of the flipped columns)
+    const int r = (int)(row0 % kGroupRows) + rib;
     if constexpr (BITS == 4) {
-        const int padded_units = (units + e2m3::kUnitsPerStage - 1) / e2m3::kUnitsPerStage * e2m3::kUnitsPerStage;
-        const int64_t stages = padded_units / e2m3::kUnitsPerStage;
-        uint8_t *const row_block = Xq + (row / e2m3::kRows) * stages * e2m3::kBlockBytes;
-        const int r32 = (int)(row % e2m3::kRows);
-        auto store_unit = [&](int i, uint32_t w0, uint32_t w1, uint32_t w2) {
-            // A 24-byte chunk (the 32 codes one MFMA lane consumes) is an even unit followed by the odd
-            // unit next to it, which the neighbouring lane holds: its first 16 bytes go to the A plane of the
-            // block, the other 8 to the B plane (e2m3_layout.h).  The even lane fetches the odd lane's first dword.
-            const uint32_t nb0 = __builtin_amdgcn_update_dpp(0u, w0, 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
-            const int unit = unit_of<G, U>(i, tf, T);
-            if (!(row_ok && unit < padded_units)) return;
-            uint32_t nb = nb0;
-            if (unit >= units) w0 = w1 = w2 = nb = 0;               // K padding: zero codes (units come in pairs: K % 32 == 0)
-            uint8_t *blk = row_block + (int64_t)(unit / e2m3::kUnitsPerStage) * e2m3::kBlockBytes;
-            const int c = (unit % e2m3::kUnitsPerStage) >> 1;       // chunk of the K128 stage
-            if ((unit & 1) == 0) {
-                *reinterpret_cast<u32x4 *>(blk + e2m3::a_offset(r32, c)) = u32x4{w0, w1, w2, nb};
-            } else {
-                *reinterpret_cast<u32x2 *>(blk + e2m3::b_offset(r32, c)) = u32x2{w1, w2};
-            }
-        };
+        const int stages = (K + e2m3::kStageCodes - 1) / e2m3::kStageCodes;
+        uint8_t *const out = Xq + row0 / e2m3::kRows * stages * e2m3::kBlockBytes;
 #pragma unroll
-        for (int i = 0; i < U; i += 2) {
-            const bool pair = i + 1 < U;
-            const v6u packed = codes4(q, pair, as_vector(v[i]), as_vector(v[pair ? i + 1 : i]));
-            store_unit(i, packed[0], packed[1], packed[2]);
-            if (pair) store_unit(i + 1, packed[3], packed[4], packed[5]);
+        for (int i = 0; i < S; ++i) {
+            const v6u packed = codes4(q, U == 2, as_vector(v[i][0]), as_vector(v[i][U - 1]));
+            const int chunk = 2 * (out0 + i * WPR * C) + h;
+            const bool pad = chunk >= chunks;                // K padding: zero codes
+            uint8_t *const block = out + (uint32_t)(chunk >> 2) * (uint32_t)e2m3::kBlockBytes;
+            if constexpr (U == 2) {
+                if (!(row_ok && chunk < 4 * stages)) continue;
+                *reinterpret_cast<u32x4 *>(block + e2m3::a_offset(r, chunk & 3)) =
+                    pad ? u32x4{0, 0, 0, 0} : u32x4{packed[0], packed[1], packed[2], packed[3]};
+                *reinterpret_cast<u32x2 *>(block + e2m3::b_offset(r, chunk & 3)) = pad ? u32x2{0, 0} : u32x2{packed[4], packed[5]};
+            } else {        // lanes 16 further on hold the chunk's odd units
+                const uint32_t next = __builtin_amdgcn_permlane16_swap(packed[0], packed[0], false, false)[1];
+                if (!(row_ok && chunk < 4 * stages)) continue;
+                if (odd16 == 0)
+                    *reinterpret_cast<u32x4 *>(block + e2m3::a_offset(r, chunk & 3)) = pad ? u32x4{0, 0, 0, 0} : u32x4{packed[0], packed[1], packed[2], next};
+                else
+                    *reinterpret_cast<u32x2 *>(block + e2m3::b_offset(r, chunk & 3)) = pad ? u32x2{0, 0} : u32x2{packed[1], packed[2]};
+            }
         }
     } else {
+        // a column is a panel's 64 bytes of its row, four units
+        const int panels = (K + panel::kRowBytes - 1) / panel::kRowBytes;
+        const bool odd = (out0 & 1) != 0;
+        uint8_t *const out = Xq + row0 / panel::kRows * panels * panel::kBytes + (uint32_t)(r * panel::kRowBytes + 32 * h);
 #pragma unroll
-        for (int i = 0; i < U; ++i) {
-            u32x4 code = codes8(q, as_vector(v[i]));
-            // Panel layout: 1 KB panels of 16 rows x 64 bytes, a unit is 16 bytes of its row; units past the
-            // row's end inside its last K-panel are stored as zero codes.
-            const int unit = unit_of<G, U>(i, tf, T);
-            constexpr int kUnitsPerPanelRow = panel::kRowBytes / kUnit;
-            const int padded_units = (units + kUnitsPerPanelRow - 1) / kUnitsPerPanelRow * kUnitsPerPanelRow;
-            if (row_ok && unit < padded_units) {
-                if (unit >= units) code = u32x4{0, 0, 0, 0};
-                uint8_t *o = Xq + ((row >> 4) * (int64_t)(padded_units / kUnitsPerPanelRow) + unit / kUnitsPerPanelRow) * panel::kBytes +
-                             (int)(row & 15) * panel::kRowBytes + (unit % kUnitsPerPanelRow) * kUnit;
-                // plain (cacheable) stores: the pieces of a line are merged in L2
-                *reinterpret_cast<u32x4 *>(o) = code;
+        for (int i = 0; i < S; ++i) {
+            const int column = out0 + i * WPR * C;
+            u32x4 a = codes8(q, as_vector(v[i][0]));
+            u32x4 *const o = reinterpret_cast<u32x4 *>(out + (uint32_t)column * (uint32_t)panel::kBytes);
+            const bool ok = row_ok && column < panels, pad = 2 * column + h >= chunks;      // K padding: zero codes
+            if constexpr (U == 1) {
+                if (ok) o[odd16] = pad ? u32x4{0, 0, 0, 0} : a;
+            } else {
+                // Neighbouring lanes exchange one unit each, so that a store instruction writes whole columns, the even ones first.
+                u32x4 b = codes8(q, as_vector(v[i][1]));
+                if (pad) a = b = u32x4{0, 0, 0, 0};
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const uint32_t other = __builtin_amdgcn_update_dpp(0u, odd ? a[w] : b[w], 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
+                    a[w] = odd ? other : a[w];
+                    b[w] = odd ? b[w] : other;
+                }
+                const int even = column & ~1;
+                u32x4 *const oe = reinterpret_cast<u32x4 *>(out + (odd ? 16 : 0) + (uint32_t)even * (uint32_t)panel::kBytes);
+                if (row_ok && even < panels) oe[0] = a;
+                if (row_ok && even + 1 < panels) oe[panel::kBytes / 16] = b;
             }
         }
     }
@@ -252,20 +239,18 @@ __global__ __launch_bounds__(256, 2) void rotated_absmax_kernel(const uint16_t *
     const int units = K / kUnit;
     const uint16_t *xrow = X + row * (int64_t)K;
     float amax = 0.0f;
-    v8bf rot0, rot1;
-    if constexpr (KIND == 1) { rot0 = rotation_operand<G>(lane, 0); rot1 = rotation_operand<G>(lane, 1); }
+    const Rotation<G> rot(lane);
     for (int base = 0; base < units; base += 64) {
-        const int unit = base + lane;
+        const int unit = base + (KIND == 1 ? Item<G>::unit(lane) : lane);
         const bool ok = unit < units;            // K % g == 0: a rotation group is all-valid or all-invalid
         float v[kUnit];
         if constexpr (KIND == 1) {
             // the layer's rotation, with the arithmetic of the rotate+quantise kernel (bit-identical maxima)
-            const int u0 = min(base + (lane & 31), units - 1), u1 = min(base + (lane & 31) + 32, units - 1);
-            const uint16_t *half = xrow + 8 * (lane >> 5);
-            const u32x4 b0 = *reinterpret_cast<const u32x4 *>(half + (int64_t)u0 * kUnit);
-            const u32x4 b1 = *reinterpret_cast<const u32x4 *>(half + (int64_t)u1 * kUnit);
-            rotate_units_mfma(rot0, rot1, b0, b1, v);
-            rotate_lanes<G>(v);
+            u32x4 raw[Item<G>::kLoads];
+#pragma unroll
+            for (int c = 0; c < Item<G>::kLoads; ++c)
+                raw[c] = *reinterpret_cast<const u32x4 *>(xrow + (int64_t)min(base + Item<G>::source_unit(lane, c), units - 1) * kUnit + 8 * (lane >> 5));
+            Item<G>::rotate(rot, raw, v);
         } else {
             const u32x4 *p = reinterpret_cast<const u32x4 *>(xrow + (int64_t)(ok ? unit : units - 1) * kUnit);
             const u32x4 lo = p[0], hi = p[1];
@@ -282,93 +267,66 @@ __global__ __launch_bounds__(256, 2) void rotated_absmax_kernel(const uint16_t *
         for (int e = 0; e < kUnit; ++e) m = fmaxf(m, fabsf(v[e]));
         amax = ok ? fmaxf(amax, m) : amax;
     }
-    amax = max_of_64(amax);
+    amax = max_of_lanes<32>(amax);
     if (lane == 0) out[row] = KIND == 0 ? amax : amax * group_norm<G>();
 }
 
 namespace {
 
-template <int G, int U, int BITS>
-hipError_t launch_gu(const void *X, int64_t rows, int K, int waves_per_row, void *Xq, float *scale,
-                     hipStream_t stream)
+template <int G, int BITS, int U, int RPW, int WPR, int S>
+hipError_t launch_rows(const void *X, int64_t rows, int K, void *Xq, float *scale, hipStream_t stream)
 {
-    const int T = 64 * waves_per_row;
-    // grid: 8 XCDs x whole row groups per XCD x blocks per group (see the row mapping in the kernel)
-    constexpr int kGroupRows = BITS == 4 ? e2m3::kRows : panel::kRows;
-    auto grid_for = [&](int rpb) { return (unsigned)(((rows + 8 * kGroupRows - 1) / (8 * kGroupRows)) * 8 * (kGroupRows / rpb)); };
-    if (T <= 256) {
-        const int rpb = 256 / T;
-        hipLaunchKernelGGL((rotquant_kernel<G, U, 256, BITS, 1>), dim3(grid_for(rpb)), dim3(256), 0, stream,
-                           (const uint16_t *)X, rows, K, T, (uint8_t *)Xq, scale);
-    } else if (T <= 512) {
-        hipLaunchKernelGGL((rotquant_kernel<G, U, 512, BITS, 1>), dim3(grid_for(1)), dim3(512), 0, stream,
-                           (const uint16_t *)X, rows, K, 512, (uint8_t *)Xq, scale);
-    } else {
-        hipLaunchKernelGGL((rotquant_kernel<G, U, 1024, BITS, 1>), dim3(grid_for(1)), dim3(1024), 0, stream,
-                           (const uint16_t *)X, rows, K, 1024, (uint8_t *)Xq, scale);
+    constexpr int kThreads = Split<U, RPW, WPR, S>::kThreads, kGroupRows = BITS == 4 ? e2m3::kRows : panel::kRows;
+    constexpr int64_t kStep = 8 * kGroupRows;                // a row group for each XCD (see the row mapping in the kernel)
+    constexpr int64_t kMost = ((int64_t)1 << 32) / kThreads * RPW / kStep * kStep - kStep;      // HIP launches fewer than 2^32 threads
+    for (int64_t r = 0; r < rows; r += kMost) {
+        const int64_t n = rows - r < kMost ? rows - r : kMost;
+        const unsigned grid = (unsigned)((n + kStep - 1) / kStep * kStep / RPW);
+        const int64_t bytes = BITS == 4 ? e2m3::matrix_bytes(r, K) : panel::matrix_bytes(r, K);
+        hipLaunchKernelGGL((rotquant_kernel<G, BITS, U, RPW, WPR, S>), dim3(grid), dim3(kThreads), 0, stream,
+                           (const uint16_t *)X + r * K, n, K, (uint8_t *)Xq + bytes, scale + r);
+        if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
-// four rows per wavefront: 4 wavefronts of 16 lanes per row (blocks of 256 threads; with larger blocks, i.e.
-// longer rows, the mapping loses more to the block-wide barrier than the stores gain: measured)
-template <int G, int U, int BITS>
-hipError_t launch_gu4(const void *X, int64_t rows, int K, void *Xq, float *scale, hipStream_t stream)
-{
-    constexpr int kGroupRows = BITS == 4 ? e2m3::kRows : panel::kRows;
-    const unsigned grid = (unsigned)(((rows + 8 * kGroupRows - 1) / (8 * kGroupRows)) * 8 * (kGroupRows / 4));
-    hipLaunchKernelGGL((rotquant_kernel<G, U, 256, BITS, 4>), dim3(grid), dim3(256), 0, stream, (const uint16_t *)X, rows, K,
-                       64, (uint8_t *)Xq, scale);
-    return hipGetLastError();
-}
-
-// g = 1024: four units a lane (digit 4 over them), as many wavefronts as the row needs; up to K = 4096 16 lanes of each of four
-// rows a wavefront, for the stores' sake as above ([4608, 3072]: 13.4 us against 14.7 with one row a wavefront).  Rows of one
-// or two groups have too few wavefronts that way ([1000, 1024]: 4.9 us against 4.2) and take digit 4 across lanes.
-template <int BITS>
-hipError_t launch_1024(const void *X, int64_t rows, int K, void *Xq, float *scale, hipStream_t stream)
-{
-    constexpr int kGroupRows = BITS == 4 ? e2m3::kRows : panel::kRows;
-    auto go = [&](auto kernel, int rows_per_block, int threads, int T) {
-        const unsigned grid = (unsigned)(((rows + 8 * kGroupRows - 1) / (8 * kGroupRows)) * 8 * (kGroupRows / rows_per_block));
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, stream, (const uint16_t *)X, rows, K, T, (uint8_t *)Xq, scale);
-        return hipGetLastError();
-    };
-    const int groups = K / 1024;                             // 16 lanes each
-    if (groups == 1) return launch_gu<1024, 1, BITS>(X, rows, K, 1, Xq, scale, stream);
-    if (groups == 2) return launch_gu<1024, 2, BITS>(X, rows, K, 1, Xq, scale, stream);
-    if (groups <= 4) return go(rotquant_kernel<1024, 4, 256, BITS, 4>, 4, 64 * groups, 16 * groups);
-    const int T = (groups + 3) / 4 * 64;
-    if (T <= 256) return go(rotquant_kernel<1024, 4, 256, BITS, 1>, 256 / T, 256 / T * T, T);
-    if (T <= 512) return go(rotquant_kernel<1024, 4, 512, BITS, 1>, 1, T, T);
-    return go(rotquant_kernel<1024, 4, 1024, BITS, 1>, 1, T, T);
-}
-
+// The split of a row, by its length.  Enough wavefronts first: with U = 1 twice as many that do half the work each, and one or two sets
+// of each; rows side by side in a wavefront as long as their digits across lanes fit (g / 64 columns), so that a store
+// instruction finds more of an output block's 64- and 32-byte row pieces adjacent.  Past 4096 elements a block is one row of whole
+// chunks, as few wavefronts as hold it once.  us, cold, against a kernel of 16 consecutive elements a lane with digit 2 by DPP:
+//   [8000, 256] g64 5.2 -> 3.9, [8000, 512] g64 5.6 -> 4.2, [12288, 1024] g256 9.6 -> 9.0, [4608, 3072] g16 8.9 -> 8.5, g256 11.2 -> 9.8,
+//   [12288, 3072] g256 20.6 -> 18.5, [4608, 4096] g64 13.5 -> 10.5, [4608, 12288] g16 28.4 -> 27.9, [4608, 15360] g1024 43.8 -> 40.5,
+//   8 bits [16896, 12288] g16 121 -> 103
+// and the other splits at those sizes: U = 2 [8000, 512] 5.0, [4608, 1024] g256 5.7 against 5.0; one row a wavefront [4608, 3072] g16 8.9;
+// two rows a block [4608, 12288] 28.2 to 30.5, four rows 36.3; half the wavefronts with two sets each 28.1.
 template <int G, int BITS>
 hipError_t launch_g(const void *X, int64_t rows, int K, void *Xq, float *scale, hipStream_t stream)
 {
-    // four rows per wavefront whenever 4 wavefronts x 16 lanes x 4 units hold a row (K <= 4096)
-    const int spans = (K / kUnit + 15) / 16;   // 256-element spans per row
-    if (spans <= 16) {
-        switch ((spans + 3) / 4) {
-            case 1: return launch_gu4<G, 1, BITS>(X, rows, K, Xq, scale, stream);
-            case 2: return launch_gu4<G, 2, BITS>(X, rows, K, Xq, scale, stream);
-            case 3: return launch_gu4<G, 3, BITS>(X, rows, K, Xq, scale, stream);
-            default: return launch_gu4<G, 4, BITS>(X, rows, K, Xq, scale, stream);
-        }
+#define CONVROT_ROWS(U, RPW, WPR, S) launch_rows<G, BITS, U, RPW, WPR, S>(X, rows, K, Xq, scale, stream)
+    if constexpr (G <= 256) {
+        if (K <= 256) return CONVROT_ROWS(1, 4, 1, 1);
+        if (K <= 512) return CONVROT_ROWS(1, 2, 1, 1);
     }
-    // Pick the wavefronts per row (1, 2, 4, 8 or 16) so that every lane holds at most 4 units,
-    // preferring 3-4 units per lane (enough bytes in flight per wavefront, registers under 128).
-    const int chunks = (K / kUnit + 63) / 64;  // 1024-element spans per row
-    int wv = 1;
-    while (wv < 16 && (chunks + wv - 1) / wv > 4) wv *= 2;
-    const int u = (chunks + wv - 1) / wv;
-    switch (u) {
-        case 1: return launch_gu<G, 1, BITS>(X, rows, K, wv, Xq, scale, stream);
-        case 2: return launch_gu<G, 2, BITS>(X, rows, K, wv, Xq, scale, stream);
-        case 3: return launch_gu<G, 3, BITS>(X, rows, K, wv, Xq, scale, stream);
-        default: return launch_gu<G, 4, BITS>(X, rows, K, wv, Xq, scale, stream);
+    if (K <= 1024) return CONVROT_ROWS(1, 1, 1, 1);
+    if constexpr (G <= 256) {
+        if (K <= 2048) return CONVROT_ROWS(1, 2, 2, 2);
+        if (K <= 3072) return CONVROT_ROWS(1, 2, 3, 2);
+        if (K <= 4096) return CONVROT_ROWS(1, 2, 4, 2);
+    } else {
+        if (K <= 2048) return CONVROT_ROWS(2, 2, 2, 1);
+        if (K <= 3072) return CONVROT_ROWS(2, 2, 3, 1);
+        if (K <= 4096) return CONVROT_ROWS(2, 2, 4, 1);
     }
+    switch ((K + 2047) / 2048) {
+        case 3: return CONVROT_ROWS(2, 1, 3, 1);
+        case 4: return CONVROT_ROWS(2, 1, 4, 1);
+        case 5: return CONVROT_ROWS(2, 1, 5, 1);
+        case 6: return CONVROT_ROWS(2, 1, 6, 1);
+        case 7: return CONVROT_ROWS(2, 1, 7, 1);
+        case 8: return CONVROT_ROWS(2, 1, 8, 1);
+        default: return K <= 32768 ? CONVROT_ROWS(2, 1, 8, 2) : CONVROT_ROWS(2, 1, 8, 4);
+    }
+#undef CONVROT_ROWS
 }
 
 template <int BITS>
@@ -379,7 +337,7 @@ hipError_t launch_bits(const void *X, int64_t rows, int64_t K, int group, void *
         case 16: return launch_g<16, BITS>(X, rows, (int)K, Xq, scale, stream);
         case 64: return launch_g<64, BITS>(X, rows, (int)K, Xq, scale, stream);
         case 256: return launch_g<256, BITS>(X, rows, (int)K, Xq, scale, stream);
-        case 1024: return launch_1024<BITS>(X, rows, (int)K, Xq, scale, stream);
+        case 1024: return launch_g<1024, BITS>(X, rows, (int)K, Xq, scale, stream);
         default: return hipErrorInvalidValue;
     }
 }
