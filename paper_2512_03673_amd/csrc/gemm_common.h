@@ -55,6 +55,11 @@ __device__ __forceinline__ void lds_dma16(const uint8_t *base, uint32_t lane_off
     else
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" :: "v"(lane_off), "s"(base), "s"(lds_addr) : "memory");
 }
+// A sum that is to stay one: constants added to it later become offsets of the memory instructions, where the compiler would
+// rather hold base + constant of each of them in a register through a loop and add to it every time (fragment reads: 4 additions
+// a step instead of 12, M512 x N12288 x K3072 13.7 -> 13.1 us, M2000 x N3072 x K3072 13.8 -> 13.1).
+__device__ __forceinline__ void keep(uint32_t &v) { asm("" : "+v"(v)); }
+
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b)
@@ -68,15 +73,13 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b)
 typedef uint32_t u32x4_row __attribute__((ext_vector_type(4), aligned(2)));
 typedef uint32_t u32x2_row __attribute__((ext_vector_type(2), aligned(2)));
 
-// The same, written through the L2.  Blocks that have a compute unit to themselves end their tiles together: 128 KB of Y from
-// each of an XCD's 32 units, as much as its L2 holds.  Written through, the lines are on their way to memory at once instead of
-// when the next tiles' lines push them out (256 x 256 tiles: M4608 x N12288 x K3072 90.1 -> 86.2 us, N3072 24.0 -> 23.4; two blocks
-// a unit: no difference).  The wait state is the one that a store of more than 64 bits needs before its data registers
-// are written again, which the compiler cannot see here.
-__device__ __forceinline__ void store_through(uint16_t *out, const v4i &v)
-{
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" :: "v"(out), "v"(v) : "memory");
-}
+// The same where all rows of Y are multiples of 16 bytes, past the caches' lines in use: what a tile writes, megabytes from an XCD's
+// units at once, pushes the operands that they share out of its L2 and those of the next call out of the Infinity Cache, and nobody
+// reads it before the product is done.  us, GEMM alone with operands that change from launch to launch, cached (256 x 256
+// tiles: written through) / this: 4 bits M4608 x N12288 x K3072 85 / 79 (192 x 192 tiles 90 / 78), N9216 64 / 62, M16896 x N12288 x K3072 301 / 275,
+// M16896 x N4096 x K3072 119 / 98, M8192 x N8192 x K2048 86 / 70, M4608 x N3072 x K12288 76 / 62, all of it from memory 79 / 77;
+// 8 bits M4608 x N12288 x K3072 144 / 132, M16896 x N3072 x K12288 477 / 467.  On one set of buffers 83 / 81 at the first.
+__device__ __forceinline__ void store_past_caches(uint16_t *out, const v4i &v) { __builtin_nontemporal_store(v, reinterpret_cast<v4i *>(out)); }
 
 // Tile order: blocks are dealt round-robin to the 8 XCDs by the hardware, each XCD has its own
 // L2.  Give every XCD one contiguous range of logical tile ids, and walk that range in bands of

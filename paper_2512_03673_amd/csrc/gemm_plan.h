@@ -14,9 +14,10 @@
 // N 32 ... 12288, K 64 ... 15360, of the other two to 230 over M 256 ... 16896, N 512 ... 12288, K 256 ... 15360 with at least
 // 1.2e10 products, the large 4-bit tiles also to 120 such with operands that change from launch to launch (128 x 192: to 220
 // with M 64 ... 8000 and 3e9 to 8e10 products).  On the larger shapes the tile taken costs 0.5 % more on average than the best of
-// them would, on the others 1 to 2 %.  All fits but those of the large 4-bit tiles are thus of operands that the Infinity Cache holds,
-// which favours these tiles in a comparison (one set of buffers against three in turn, M4608 x N12288 x K3072: 80.4 / 91.6 us with 192 x 192
-// tiles, 84.5 / 88.3 with 256 x 256).
+// them would, on the others 1 to 2 %.  All fits but those of the large 4-bit tiles are thus of operands that the Infinity Cache holds.
+// The fits are of kernels whose output went through the caches.  With it past them (store_past_caches) the tiles' times fell
+// together: over 150 shapes (4 bits) and 130 (8 bits) of 1e9 to 6.4e11 products with operands that change from launch to launch the
+// tile taken costs 1.3 and 1.9 % more than the best, with constants fitted again to these 1.5 and 1.7 %.
 #pragma once
 #include <stdint.h>
 
@@ -86,9 +87,8 @@ struct Cut {        // a round of parts of 256 x 256 tiles
 // quarters where those do (us, whole / cut: M4608 x N12288 x K3072, 12 left over, 87.6 / 85.4; M16896 x N3072 x K12288, 3 left over,
 // 275.5 / 260.5; over 16 and 19 drawn shapes 6 and 14 % - more of them would take two rounds of parts and lose).  After
 // many rounds the units no longer finish together and parts only cost (M16896 x N12288 x K3072, 12 rounds, 296 / 305).  8-bit
-// products gain nothing there over 192 x 192 tiles.  (All with operands that change from launch to launch; on one set of buffers,
-// which the Infinity Cache holds, M4608 x N12288 x K3072 takes 81.4 to 85.2 us in halves, from card to card, and 80.4 to 82.1 with
-// 192 x 192 tiles.)  Parts a tile is cut into, 1 if none is; `per_xcd` = tiles of an XCD.
+// products gain nothing there over 192 x 192 tiles.  (All with operands that change from launch to launch and outputs in the caches;
+// with outputs past them M4608 x N12288 x K3072 takes 78.8 to 80 us in halves and 77.6 with 192 x 192 tiles.)  Parts a tile is cut into, 1 if none is; `per_xcd` = tiles of an XCD.
 inline int parts_of_last_tiles(int64_t per_xcd)
 {
     const int64_t rest = per_xcd % 32;

@@ -22,7 +22,7 @@
 //
 // The MFMA's row operand is the W tile and its column operand the X tile, so that a lane ends up with four
 // consecutive n for one m; the epilogue scales, rounds to bf16, transposes through LDS and writes 16 bytes per lane,
-// whole contiguous rows of the wavefront's tile.
+// whole contiguous rows of the wavefront's tile, past the caches (store_past_caches).
 //
 // What bounds the large tiles is power: the chip runs as many operand bytes and multiply-adds a second as its clock lets it, and
 // the clock falls with them.  So the tile that moves the fewest bytes a product wins where its rounds are not too uneven: 256 x 256
@@ -66,7 +66,6 @@ struct Stage {
     static constexpr int kRing = T::NS * kBytes;
     static constexpr int kScales = kRing > T::kEpiBytes ? kRing : T::kEpiBytes;     // scales and bias, past the ring
     static constexpr int kLds = kScales + (T::TM + 2 * T::TN) * 4;
-    static constexpr bool kAlone = kLds > 80 * 1024;          // a block has its compute unit to itself
     static_assert(kPieces * 1024 == kBytes && T::NW % 2 == 0, "stage must split into kilobytes");
     static_assert(T::NS >= 2 && T::NS <= 4 && T::kRows % 64 == 0, "ring");
     static_assert(kLds * (T::OCC * 4 / T::NW) <= 160 * 1024, "blocks per compute unit");
@@ -160,11 +159,12 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
     };
 
     // ---- LDS -> registers
-    typename C::Reader reader(lane, T::kRows);
+    typename C::Reader reader(lane, T::kRows, wm0, TM + wn0);
     typename C::Op op[2][NF];   // [step parity][fragment]: 0..XF-1 X rows 32 f .., then W rows 32 (f - XF) ..
-    auto read_frag = [&](uint32_t buf, auto KSI, auto F) {
+    auto read_frag = [&](auto KSI, auto F) {      // of the step that the reader is aimed at
         constexpr int ks = decltype(KSI)::value, f = decltype(F)::value;
-        if constexpr (f < NF) op[ks][f] = reader.template read<ks>(lds + buf, f < XF ? wm0 + f * 32 : TM + wn0 + (f - XF) * 32);
+        if constexpr (f < XF) op[ks][f] = reader.template read<0, f>(lds);
+        else if constexpr (f < NF) op[ks][f] = reader.template read<1, f - XF>(lds);
     };
 
     typename C::Acc acc[XF][WF];
@@ -175,12 +175,13 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
 
-    // One step, slot by slot, in issue order.  Slot m: MFMA (i = m / WF, j = m % WF: the X fragment stays for WF MFMAs,
+    // One step, slot by slot, in issue order.  Slot m: MFMA (i = m / WF; the X fragment stays for WF MFMAs,
     // measured 1 % faster than the W fragment staying); with REFILL this slot's share of the LDS-direct loads of
     // stage rs into buffer rbuf; a fragment of the next step (the other step parity; stage buffer nbuf) in each of the first
     // slots, or two if there are more fragments than slots.
-    auto slot = [&](auto MI, auto KSI, auto REFILL, uint32_t nbuf, int rs, uint32_t rbuf) {
-        constexpr int m = decltype(MI)::value, ks = decltype(KSI)::value, i = m / WF, j = m % WF;
+    auto slot = [&](auto MI, auto KSI, auto REFILL, int rs, uint32_t rbuf) {
+        constexpr int m = decltype(MI)::value, ks = decltype(KSI)::value, i = m / WF;
+        constexpr int j = i % 2 ? WF - 1 - m % WF : m % WF;      // there and back: one operand stays from every MFMA to the next (up to 1 %)
         if constexpr (m < kMfmas) {
             C::mma(acc[i][j], op[ks][XF + j], op[ks][i]);
             if constexpr (decltype(REFILL)::value) {
@@ -195,14 +196,15 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
             }
             constexpr int f0 = kMfmas >= NF ? m : m * NF / kMfmas, f1 = kMfmas >= NF ? m + 1 : (m + 1) * NF / kMfmas;
             static_assert(f1 - f0 <= 2, "fragments per slot");
-            read_frag(nbuf, std::integral_constant<int, 1 - ks>{}, std::integral_constant<int, f0>{});
-            if constexpr (f0 + 1 < f1) read_frag(nbuf, std::integral_constant<int, 1 - ks>{}, std::integral_constant<int, f0 + 1>{});
+            read_frag(std::integral_constant<int, 1 - ks>{}, std::integral_constant<int, f0>{});
+            if constexpr (f0 + 1 < f1) read_frag(std::integral_constant<int, 1 - ks>{}, std::integral_constant<int, f0 + 1>{});
             __builtin_amdgcn_sched_barrier(0);
         }
     };
     auto step = [&](auto KSI, auto REFILL, uint32_t nbuf, int rs, uint32_t rbuf) {
         __builtin_amdgcn_sched_barrier(0);
-#define CONVROT_SLOT(m) slot(std::integral_constant<int, m>{}, KSI, REFILL, nbuf, rs, rbuf);
+        reader.template aim<1 - decltype(KSI)::value>(nbuf);
+#define CONVROT_SLOT(m) slot(std::integral_constant<int, m>{}, KSI, REFILL, rs, rbuf);
         CONVROT_SLOT(0) CONVROT_SLOT(1) CONVROT_SLOT(2) CONVROT_SLOT(3) CONVROT_SLOT(4) CONVROT_SLOT(5) CONVROT_SLOT(6) CONVROT_SLOT(7)
         CONVROT_SLOT(8)
 #undef CONVROT_SLOT
@@ -222,7 +224,8 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
     wait_loads_upto(min(KS, NS) - 1);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-#define CONVROT_F(f) read_frag(0, K0{}, std::integral_constant<int, f>{});
+    reader.template aim<0>(0);
+#define CONVROT_F(f) read_frag(K0{}, std::integral_constant<int, f>{});
     CONVROT_F(0) CONVROT_F(1) CONVROT_F(2) CONVROT_F(3) CONVROT_F(4) CONVROT_F(5)
 #undef CONVROT_F
     static_assert(NF <= 6, "fragments of a step");
@@ -334,12 +337,12 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
                     const v4i v = *reinterpret_cast<const v4i *>(stage_lds + r * kEpiPitch + piece * 16);
                     const int mo = mrow + r, ncol = n0 + wn0 + piece * 8;
                     uint16_t *out = Y + (int64_t)mo * N + ncol;
-                    if constexpr (decltype(EDGE)::value == 0) {
+                    if constexpr (decltype(EDGE)::value == -1) {
+                        store_past_caches(out, v);
+                    } else if constexpr (decltype(EDGE)::value == 0) {
                         *reinterpret_cast<u32x4_row *>(out) = __builtin_bit_cast(u32x4_row, v);
-                    } else if constexpr (decltype(EDGE)::value == -1) {
-                        store_through(out, v);
                     } else if constexpr (decltype(EDGE)::value == 1) {
-                        if (mo < M && ncol < N) *reinterpret_cast<u32x4_row *>(out) = __builtin_bit_cast(u32x4_row, v);
+                        if (mo < M && ncol < N) store_past_caches(out, v);
                     } else {
                         if (mo < M && ncol + 8 <= N) {
                             *reinterpret_cast<u32x4_row *>(out) = __builtin_bit_cast(u32x4_row, v);
@@ -354,18 +357,19 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
         };
         // Bounds checks only where the tile crosses the edge of Y, and element stores only where it ends inside a
         // 16-byte piece (uniform over the block; the edge bodies add a bias of zero where there is none).
-        // Rows that are multiples of 16 bytes are written through (store_through); a line that two rows share waits in the L2.
-        using Through = std::integral_constant<int, -1>;
+        // A line that two rows share waits in the caches, others pass them.
+        using Inside = std::integral_constant<int, -1>;
         using Edge0 = std::integral_constant<int, 0>;
         using Edge1 = std::integral_constant<int, 1>;
         using Edge2 = std::integral_constant<int, 2>;
-        if (St::kAlone && (N & 7) == 0 && m0 + TM <= M && n0 + TN <= N) {
-            if (bias) body(Through{}, std::true_type{});
-            else body(Through{}, std::false_type{});
-        } else if (m0 + TM <= M && n0 + TN <= N) {
+        const bool inside = m0 + TM <= M && n0 + TN <= N;
+        if ((N & 7) == 0 && inside) {
+            if (bias) body(Inside{}, std::true_type{});
+            else body(Inside{}, std::false_type{});
+        } else if (inside) {
             if (bias) body(Edge0{}, std::true_type{});
             else body(Edge0{}, std::false_type{});
-        } else if ((N & 7) == 0 || n0 + TN <= N) {
+        } else if ((N & 7) == 0) {
             body(Edge1{}, std::true_type{});
         } else {
             body(Edge2{}, std::true_type{});

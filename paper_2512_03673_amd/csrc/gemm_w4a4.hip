@@ -55,26 +55,41 @@ struct Codes4 {
     static __device__ __forceinline__ uint32_t lane_offset(int lane, int) { return lane * 16; }
 
     struct Reader {      // lane l holds chunk 2 ks + l / 32 of row l % 32
-        int offa[2], offb[2];     // per step: byte offsets of the lane's A part and B part inside a 32-row group
-        __device__ __forceinline__ Reader(int lane, int rows)
+        uint32_t a[2][2], b[2][2];     // [step][operand]: byte offsets of the lane's A part and B part of the wavefront's first 32 rows of X (0), W (1)
+        uint32_t at_a[2], at_b[2];     // of the step and stage that reads come from: fragments are constants further on
+        __device__ __forceinline__ Reader(int lane, int rows, int x_row, int w_row)
         {
             const int r = lane & 31;
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
                 const int c = 2 * ks + (lane >> 5);
-                offa[ks] = r * e2m3::kARowBytes + ((c ^ e2m3::swz_a(r)) << 4);
-                offb[ks] = rows * e2m3::kARowBytes + r * e2m3::kBRowBytes + ((c ^ e2m3::swz_b(r)) << 3);
+#pragma unroll
+                for (int o = 0; o < 2; ++o) {
+                    a[ks][o] = (r + (o ? w_row : x_row)) * e2m3::kARowBytes + ((c ^ e2m3::swz_a(r)) << 4);
+                    b[ks][o] = rows * e2m3::kARowBytes + (r + (o ? w_row : x_row)) * e2m3::kBRowBytes + ((c ^ e2m3::swz_b(r)) << 3);
+                }
             }
         }
         template <int ks>
-        __device__ __forceinline__ Op read(const uint8_t *stage, int row0) const
+        __device__ __forceinline__ void aim(uint32_t stage)
         {
-            const v4i a = *reinterpret_cast<const v4i *>(stage + offa[ks] + row0 * e2m3::kARowBytes);
-            const v2i b = *reinterpret_cast<const v2i *>(stage + offb[ks] + row0 * e2m3::kBRowBytes);
-            Op o = __builtin_shufflevector(a, a, 0, 1, 2, 3, -1, -1, -1, -1);
-            o[4] = b.x;
-            o[5] = b.y;
-            return o;
+#pragma unroll
+            for (int o = 0; o < 2; ++o) {
+                at_a[o] = stage + a[ks][o];
+                at_b[o] = stage + b[ks][o];
+                gemm::keep(at_a[o]);
+                gemm::keep(at_b[o]);
+            }
+        }
+        template <int o, int f>
+        __device__ __forceinline__ Op read(const uint8_t *lds) const
+        {
+            const v4i a = *reinterpret_cast<const v4i *>(lds + at_a[o] + f * e2m3::kAPlaneBytes);
+            const v2i b = *reinterpret_cast<const v2i *>(lds + at_b[o] + f * e2m3::kBPlaneBytes);
+            Op v = __builtin_shufflevector(a, a, 0, 1, 2, 3, -1, -1, -1, -1);
+            v[4] = b.x;
+            v[5] = b.y;
+            return v;
         }
     };
     static __device__ __forceinline__ void mma(Acc &c, const Op &w, const Op &x)

@@ -44,17 +44,29 @@ struct Codes8 {
     }
 
     struct Reader {      // lane l holds piece 2 ks + l / 32 of row l % 32
-        int off[2];
-        __device__ __forceinline__ Reader(int lane, int)
+        uint32_t a[2][2], at[2];     // as in gemm_w4a4.hip
+        __device__ __forceinline__ Reader(int lane, int, int x_row, int w_row)
         {
             const int r = lane & 31;
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks) off[ks] = r * panel::kRowBytes + (((2 * ks + (lane >> 5)) ^ gemm::swz(r)) << 4);
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int o = 0; o < 2; ++o)
+                    a[ks][o] = (r + (o ? w_row : x_row)) * panel::kRowBytes + (((2 * ks + (lane >> 5)) ^ gemm::swz(r)) << 4);
         }
         template <int ks>
-        __device__ __forceinline__ Op read(const uint8_t *stage, int row0) const
+        __device__ __forceinline__ void aim(uint32_t stage)
         {
-            return *reinterpret_cast<const v4i *>(stage + off[ks] + row0 * panel::kRowBytes);
+#pragma unroll
+            for (int o = 0; o < 2; ++o) {
+                at[o] = stage + a[ks][o];
+                gemm::keep(at[o]);
+            }
+        }
+        template <int o, int f>
+        __device__ __forceinline__ Op read(const uint8_t *lds) const
+        {
+            return *reinterpret_cast<const v4i *>(lds + at[o] + f * 32 * panel::kRowBytes);
         }
     };
     static __device__ __forceinline__ void mma(Acc &c, const Op &w, const Op &x) { c = __builtin_amdgcn_mfma_i32_32x32x32_i8(w, x, c, 0, 0, 0); }
