@@ -169,7 +169,12 @@ hipError_t launch(const gemm::Operands &o, void *Xq, float *x_scale)
         return items <= kWaves ? go(forward_small_kernel<BITS, G, wf, 1>, wf) : go(forward_small_kernel<BITS, G, wf, 2>, wf);
     };
     if (items > 2 * kWaves || o.M > 16) return hipErrorInvalidValue;      // forward_in_one names no such shape
-    return gemm::forward_in_one_columns(o.N) == 16 ? width(std::integral_constant<int, 1>{}) : width(std::integral_constant<int, 2>{});
+    switch (gemm::forward_in_one_columns(o.N)) {
+        case 16: return width(std::integral_constant<int, 1>{});
+        case 32: return width(std::integral_constant<int, 2>{});
+        case 48: return width(std::integral_constant<int, 3>{});
+        default: return width(std::integral_constant<int, 4>{});
+    }
 }
 
 template <int BITS>

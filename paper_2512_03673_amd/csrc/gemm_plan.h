@@ -45,17 +45,19 @@ inline bool launchable(int64_t blocks, int threads) { return blocks + 7 < ((int6
 // Stretches of up to 1024 elements in M rows, the unit of work of the one-launch forward (forward_small.hip).
 inline int64_t row_items(int64_t M, int64_t K) { return M * ((K + 1023) / 1024); }
 
-// Columns of a block of that forward: 32, or 16 in layers so narrow that 32 would leave half of the compute units idle.
-inline int forward_in_one_columns(int64_t N) { return N <= 4096 ? 16 : 32; }
+// Columns of a block of that forward: as few as leave every compute unit at most one block, which rotates all rows first (of up to 16384:
+// forward_in_one).  us, 32 columns / this: M1 x N9216 x K3072 7.1 / 6.15 (64 columns 6.45), M2 x N9216 x K3072 at 8 bits 9.2 / 8.2,
+// M1 x N12288 x K3072 7.5 / 7.1, M2 x N12010 x K1024 at 8 bits 6.55 / 5.6; over 110 drawn shapes 0.1 % slower than the best width.
+inline int forward_in_one_columns(int64_t N) { return N <= 16 * 256 ? 16 : N <= 32 * 256 ? 32 : N <= 48 * 256 ? 48 : 64; }
 
 // Whether a forward takes that one launch, in which every block repeats the rows' rotation, or two.  Two launches cost 1 us (short
-// rows) to 4 us (long ones) more and the rotation 0.15 us an item for each block of a compute unit.  Over 110 drawn shapes
+// rows) to 4 us (long ones) more and the rotation 0.15 us an item for each block (of 16 or 32 columns) of a compute unit.  Over 110 drawn shapes
 // (M 1-16, N 64-40000, K 64-15360) the line drawn here gives 0.5 to 5 us, us two / one: M1 x N9216 x K3072 10.8 / 7.3,
 // M1 x N3072 x K12288 12.7 / 9.0, M4 x N3072 x K3072 8.7 / 6.1, M8 x N608 x K1024 6.3 / 5.2, M1 x N394 x K128 5.3 / 3.8; past it
 // M12 x N9068 x K256 5.6 / 8.7, M14 x N1933 x K1088 6.0 / 7.0, M2 x N18018 x K192 5.8 / 6.9.
 inline bool forward_in_one(int64_t M, int64_t N, int64_t K)
 {
-    const int64_t items = row_items(M, K), blocks = (N + forward_in_one_columns(N) - 1) / forward_in_one_columns(N);
+    const int64_t items = row_items(M, K), columns = N <= 4096 ? 16 : 32, blocks = (N + columns - 1) / columns;
     if (blocks > 512) return false;
     return items * (blocks > 256 ? blocks : 256) <= 8 * 256 || (M <= 4 && items <= 16 && blocks <= 256);
 }
