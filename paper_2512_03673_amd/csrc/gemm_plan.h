@@ -62,6 +62,14 @@ inline bool forward_in_one(int64_t M, int64_t N, int64_t K)
     return items * (blocks > 256 ? blocks : 256) <= 8 * 256 || (M <= 4 && items <= 16 && blocks <= 256);
 }
 
+inline int64_t tiles_of(int64_t M, int64_t N, int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); }
+
+// Whether tiles that otherwise share a compute unit two by two take a ring of four stages: in a launch of one round each has its unit to
+// itself, with LDS to spare, and what it waits for is operands (with a few stages there is nothing to run ahead with).  us, two / four
+// stages: 4 bits, 192 x 192, M3000 x N3072 x K3072 25 / 16.3, geometric mean over 91 drawn shapes 1.35; three / four: 8 bits, 128 x 192, M300 x N12288 x
+// K12288 80 / 65, over 69 shapes 1.11.  (No gain: 192 x 192 at 8 bits, 128 x 128 at 4 bits, 256 x 128 on eight wavefronts.)
+inline bool deep_ring(int64_t tiles, int64_t stages) { return tiles <= 256 && stages >= 16; }
+
 struct Small {
     Plan plan;
     int tm, tn;
@@ -90,7 +98,8 @@ struct Cut {        // a round of parts of 256 x 256 tiles
 // 275.5 / 260.5; over 16 and 19 drawn shapes 6 and 14 % - more of them would take two rounds of parts and lose).  After
 // many rounds the units no longer finish together and parts only cost (M16896 x N12288 x K3072, 12 rounds, 296 / 305).  8-bit
 // products gain nothing there over 192 x 192 tiles.  (All with operands that change from launch to launch and outputs in the caches;
-// with outputs past them M4608 x N12288 x K3072 takes 78.8 to 80 us in halves and 77.6 with 192 x 192 tiles.)  Parts a tile is cut into, 1 if none is; `per_xcd` = tiles of an XCD.
+// with outputs past them M4608 x N12288 x K3072 takes 78.8 to 80 us in halves and 77.6 with 192 x 192 tiles.)  Parts a tile is cut
+// into, 1 if none is; `per_xcd` = tiles of an XCD.
 inline int parts_of_last_tiles(int64_t per_xcd)
 {
     const int64_t rest = per_xcd % 32;
@@ -133,11 +142,14 @@ inline Plan choose(int64_t M, int64_t N, int64_t K)
     // the tiles that it is compared with, whose fits are of more shapes.)
     static constexpr Alone middle = {256, 1.70f, 4.55f, 0.347f, 0.98f};
 
+    // 192 x 192, 4 bits, with a deep ring: between 128 x 192, of which such a product has more than a round, and 256 x 256, which leave units idle.
+    static constexpr Alone square = {256, 1.99f, 4.53f, 0.493f, 0.532f};
+
     const float stages = (float)(BITS == 4 ? (K + 127) / 128 : (K + 63) / 64);
     Plan best = Plan::kCount;
     float least = 0.0f;
     bool best_fits = false;
-    auto tiles = [&](int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
+    auto tiles = [&](int tm, int tn) { return tiles_of(M, N, tm, tn); };
     // (A launch of more tiles than HIP takes at once is no candidate while there is another: M1 x N2^30 x K32 in 64 x 64 tiles.)
     auto consider = [&](Plan plan, int64_t blocks, int threads, float t) {
         const bool fits = launchable(blocks, threads);
@@ -164,7 +176,10 @@ inline Plan choose(int64_t M, int64_t N, int64_t K)
     };
 
     if constexpr (BITS == 4) {
-        for (const Paired &c : paired4) paired(c);
+        const bool deep = deep_ring(tiles(192, 192), (int64_t)stages);
+        for (const Paired &c : paired4)
+            if (!(deep && c.plan == Plan::kTile192x192)) paired(c);
+        if (deep) alone(Plan::kTile192x192, 192, 192, square);
         for (const Small &c : small4) small(c);
         alone(Plan::kTile256x128w8, 256, 128, w8);
         alone(Plan::kTile128x192, 128, 192, middle);

@@ -76,6 +76,8 @@ hipError_t launch_plan(gemm::Plan plan, const gemm::Operands &o)
 {
     using gemm::Plan;
     using gemm::Tile;
+    if (plan == Plan::kTile128x192 && gemm::deep_ring(gemm::tiles_of(o.M, o.N, 128, 192), panel::k_panels(o.K)))
+        return gemm::launch_tiled<Codes8, Tile<2, 2, 2, 3, 4, 1, 8>>(o);
     switch (plan) {
         case Plan::kTile192x192: return gemm::launch_tiled<Codes8, Tile<2, 2, 3, 3, 3, 2, 8>>(o);
         case Plan::kTile256x128: return gemm::launch_tiled<Codes8, Tile<2, 2, 4, 2, 3, 2, 6>>(o);
