@@ -101,11 +101,11 @@ struct Codes4 {
 hipError_t launch_256x256(const gemm::Operands &o)
 {
     using gemm::Tile;
-    typedef Tile<2, 4, 4, 2, 3, 2, 4> Whole;
+    typedef Tile<2, 4, 4, 2, 3, 2, 0> Whole;
     const int64_t per_xcd = ((int64_t)((o.M + 255) / 256) * ((o.N + 255) / 256) + 7) / 8;
     switch (gemm::parts_of_last_tiles(per_xcd)) {
-        case 2: return gemm::launch_cut<Codes4, Whole, Tile<4, 2, 2, 2, 3, 2, 4>>(o, (int)(per_xcd % 32));
-        case 4: return gemm::launch_cut<Codes4, Whole, Tile<4, 2, 1, 2, 4, 2, 4>>(o, (int)(per_xcd % 32));
+        case 2: return gemm::launch_cut<Codes4, Whole, Tile<4, 2, 2, 2, 3, 2, 0>>(o, (int)(per_xcd % 32));
+        case 4: return gemm::launch_cut<Codes4, Whole, Tile<4, 2, 1, 2, 4, 2, 0>>(o, (int)(per_xcd % 32));
         default: return gemm::launch_tiled<Codes4, Whole>(o);
     }
 }

@@ -87,7 +87,7 @@ hipError_t launch_plan(gemm::Plan plan, const gemm::Operands &o)
         case Plan::kSplit32x32: return gemm::launch_small<gemm::Small8, 2, 2, 4, 3>(o);
         case Plan::kSplit16x32: return gemm::launch_small<gemm::Small8, 1, 2, 8, 4>(o);
         case Plan::kSplit16x16: return gemm::launch_small<gemm::Small8, 1, 1, 16, 4>(o);
-        case Plan::kTile256x256: return gemm::launch_tiled<Codes8, Tile<2, 4, 4, 2, 3, 2, 4>>(o);
+        case Plan::kTile256x256: return gemm::launch_tiled<Codes8, Tile<2, 4, 4, 2, 3, 2, 0>>(o);
         case Plan::kTile128x192: return gemm::launch_tiled<Codes8, Tile<2, 2, 2, 3, 3, 2, 8>>(o);
         default: return hipErrorInvalidValue;
     }
