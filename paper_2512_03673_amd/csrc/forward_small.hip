@@ -39,15 +39,12 @@ __global__ __launch_bounds__(64 * kWaves) void forward_small_kernel(const uint16
 
     // ---- X first, then W: the rotation must not wait for W
     using It = Item<G>;
-    u32x4 raw[I][It::kLoads];
+    __shared__ __attribute__((aligned(16))) uint8_t columns[I * S * It::kBytes];
+    u32x4 raw[I][2];
 #pragma unroll
     for (int i = 0; i < I; ++i) {
         const int item = min(wave + S * i, items - 1), row = item / spans, span = item - row * spans;
-#pragma unroll
-        for (int c = 0; c < It::kLoads; ++c) {
-            const int unit = min(span * 64 + It::source_unit(lane, c), units - 1);
-            raw[i][c] = *reinterpret_cast<const u32x4 *>(X + row * (int64_t)K + unit * kUnit + 8 * (lane >> 5));
-        }
+        It::load(X + row * (int64_t)K, span * 64, units, lane, raw[i]);
     }
     C w[WF];
 #pragma unroll
@@ -64,17 +61,30 @@ __global__ __launch_bounds__(64 * kWaves) void forward_small_kernel(const uint16
     // ---- rotate; row maxima through LDS
     const Rotation<G> rot(lane);
     float v[I][kUnit];
-#pragma unroll
-    for (int i = 0; i < I; ++i) {
+    auto rotate = [&](int i) { It::rotate(rot, raw[i], columns + (wave + S * i) * It::kBytes, lane, v[i]); };
+    auto maximum = [&](int i) {
         const int item = wave + S * i;
-        if (item >= items) break;
-        It::rotate(rot, raw[i], v[i]);
         float m = 0.0f;
 #pragma unroll
         for (int e = 0; e < kUnit; ++e) m = fmaxf(m, fabsf(v[i][e]));
         m = item % spans * 64 + It::unit(lane) < units ? m : 0.0f;
         m = max_of_lanes<32>(m);
         if (lane == 0) item_max[item] = m;
+    };
+    // A wavefront with all its items: no branch between their chains of MFMAs (M4 x N3072 x K3072 at g = 256 and 8 bits, graph: 5.93 -> 5.65 us).
+    // The others rotate what they have; chains of repeated items would cost M1 x N9216 x K3072 1 us of 6.4.
+    if (I > 1 && wave + S * (I - 1) < items) {
+#pragma unroll
+        for (int i = 0; i < I; ++i) rotate(i);
+#pragma unroll
+        for (int i = 0; i < I; ++i) maximum(i);
+    } else {
+#pragma unroll
+        for (int i = 0; i < I; ++i) {
+            if (wave + S * i >= items) break;
+            rotate(i);
+            maximum(i);
+        }
     }
     __syncthreads();
 

@@ -107,7 +107,6 @@ constexpr int column_flip() { return G >= 1024 ? 15 : (G >= 256 ? 3 : 0); }
 // meets another (0 x infinity), and a column lies in one row.
 template <int G>
 struct Rotation {
-    static constexpr int kTerms = G >= 64 ? 4 : 2;
     v8bf a[G >= 64 ? 3 : 2];
 
     __device__ __forceinline__ explicit Rotation(int lane)
@@ -163,22 +162,31 @@ struct Rotation {
     }
 };
 
-// One lane's unit of 1024 elements of a row that a wavefront shares (an item): lane l's unit of the item, before and after the
-// flip of the digits across lanes.
+// 1024 elements of a row (64 units from unit `base` on, 16 columns) that a wavefront rotates at a time, a unit a lane.  They are loaded as
+// they lie, a kilobyte an instruction, and change lanes in kBytes of LDS that are the wavefront's own: lanes n and n + 32 need the
+// halves of column n's units, which as loads would be pieces of 32 bytes (one-launch forwards, device time, us, so / through LDS / with
+// consecutive units and digit 2 across lanes: M3 x N512 x K2816 at g = 256 6.0 / 5.0 / 5.2, M4 x N3072 x K3072 at g = 64 and 8 bits 6.7 / 5.4 / 5.3,
+// M1 x N3072 x K3072 at g = 1024 4.55 / 4.15 / 4.5).  Piece p of column n lies in slot p ^ (n & 7), so that eight lanes read and write different banks.
 template <int G>
 struct Item {
-    static constexpr int kLoads = Rotation<G>::kTerms;
-    // the unit that this lane fetches its part of for term c
-    static __device__ __forceinline__ int source_unit(int lane, int c)
-    {
-        const int odd = (lane >> 4) & 1;
-        return 4 * (lane & 15) + (G >= 64 ? c ^ odd : 2 * c + odd);
-    }
+    static constexpr int kBytes = 2048;
     static __device__ __forceinline__ int unit(int lane) { return 4 * (lane & 15) + ((lane >> 4) & 1) + 2 * (lane >> 5); }
     static __device__ __forceinline__ int out_unit(int lane) { return unit(lane ^ column_flip<G>()); }
-    static __device__ __forceinline__ void rotate(const Rotation<G> &rot, const u32x4 (&raw)[kLoads], float (&v)[kUnit])
+    static __device__ __forceinline__ void load(const uint16_t *row, int base, int units, int lane, u32x4 (&raw)[2])
     {
-        rot.apply([&](int c) { return raw[G >= 64 ? c : c / 2]; }, v);
+#pragma unroll
+        for (int j = 0; j < 2; ++j)      // past the row's end its last 16 bytes again
+            raw[j] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const uint8_t *>(row) + min(base * 32 + j * 1024 + lane * 16, units * 32 - 16));
+    }
+    static __device__ __forceinline__ void rotate(const Rotation<G> &rot, const u32x4 (&raw)[2], uint8_t *lds, int lane, float (&v)[kUnit])
+    {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            *reinterpret_cast<u32x4 *>(lds + j * 1024 + (lane >> 3) * 128 + (((lane & 7) ^ (lane >> 3)) << 4)) = raw[j];
+        asm volatile("" ::: "memory");       // (other lanes' pieces; a wavefront's LDS operations stay in order)
+        const int odd = (lane >> 4) & 1, h = lane >> 5;
+        rot.apply([&](int c) { return *reinterpret_cast<const u32x4 *>(lds + (lane & 15) * 128 + (((2 * (c ^ odd) + h) ^ (lane & 7)) << 4)); }, v);
+        asm volatile("" ::: "memory");
         rotate_lanes<G>(v);
     }
 };

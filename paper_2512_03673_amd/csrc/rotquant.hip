@@ -233,6 +233,7 @@ template <int G, int KIND>
 __global__ __launch_bounds__(256, 2) void rotated_absmax_kernel(const uint16_t *__restrict__ X, int64_t rows, int K,
                                                              float *__restrict__ out)
 {
+    __shared__ __attribute__((aligned(16))) uint8_t columns[KIND == 1 ? 4 * Item<G>::kBytes : 16];
     const int lane = threadIdx.x & 63;
     const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= rows) return;                     // wavefront-uniform
@@ -246,11 +247,9 @@ __global__ __launch_bounds__(256, 2) void rotated_absmax_kernel(const uint16_t *
         float v[kUnit];
         if constexpr (KIND == 1) {
             // the layer's rotation, with the arithmetic of the rotate+quantise kernel (bit-identical maxima)
-            u32x4 raw[Item<G>::kLoads];
-#pragma unroll
-            for (int c = 0; c < Item<G>::kLoads; ++c)
-                raw[c] = *reinterpret_cast<const u32x4 *>(xrow + (int64_t)min(base + Item<G>::source_unit(lane, c), units - 1) * kUnit + 8 * (lane >> 5));
-            Item<G>::rotate(rot, raw, v);
+            u32x4 raw[2];
+            Item<G>::load(xrow, base, units, lane, raw);
+            Item<G>::rotate(rot, raw, columns + (threadIdx.x >> 6) * Item<G>::kBytes, lane, v);
         } else {
             const u32x4 *p = reinterpret_cast<const u32x4 *>(xrow + (int64_t)(ok ? unit : units - 1) * kUnit);
             const u32x4 lo = p[0], hi = p[1];
