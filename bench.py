@@ -40,7 +40,7 @@ TRAFFIC_SOURCE = ("rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of `python bench.py -
 # statistics (8 wavefronts per compute unit, no memory traffic; 9.9 POP/s on all-zero operands): the chip lowers its
 # clock with operand activity, so this, not the nominal figure, is what a perfect kernel could reach on this data.
 MEASURED_FP6_MFMA_LOOP_TOPS = 6600.0
-MFMA_LOOP_SOURCE = "register-only v_mfma_f32_32x32x64_f8f6f4 loop on workload-like FP6 operands, MI355X of this pool"
+MFMA_LOOP_SOURCE = "register-only v_mfma_f32_32x32x64_f8f6f4 loop on workload-like FP6 operands, on an MI355X"
 PREWARM_MS = 200.0           # load put on the device before anything is timed, whatever --warmup says
 COPY_BYTES = 512 << 20       # size of the calibration copy (--calibrate-copy)
 COLD_FOOTPRINT = 768 << 20   # kernel A, cold: bytes touched between two uses of one buffer set
