@@ -9,7 +9,7 @@
 //
 // What bounds it: memory, 2.75 bytes an element (a large copy runs at 6.1 TB/s), on rows of 3072 elements and more; the launch and one
 // pass of every wavefront through load, arithmetic and store on smaller inputs.  Vector instructions, 7.5 to 9 an element
-// (g <= 64) to 13.4 (g = 1024), would take two thirds of that time and overlap with it.  With digit 2 on the vector ALU, a bracketing
+// (g <= 64; 9.7 counted on [4608, 3072] at g = 16, where lanes hold single units) to 13.4 (g = 1024), would take two thirds of that time and overlap with it.  With digit 2 on the vector ALU, a bracketing
 // second product for every code and a unit's 12 bytes stored in two places by pairs of lanes they were 10.9 to 18.
 //
 // The rotation and the quantiser themselves are rotate_quantise.h.
