@@ -6,6 +6,8 @@
 
 #include <type_traits>
 
+#include "gemm_plan.h"
+
 namespace convrot {
 namespace gemm {
 
@@ -73,13 +75,15 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b)
 typedef uint32_t u32x4_row __attribute__((ext_vector_type(4), aligned(2)));
 typedef uint32_t u32x2_row __attribute__((ext_vector_type(2), aligned(2)));
 
-// The same where all rows of Y are multiples of 16 bytes, past the caches' lines in use: what a tile writes, megabytes from an XCD's
-// units at once, pushes the operands that they share out of its L2 and those of the next call out of the Infinity Cache, and nobody
-// reads it before the product is done.  us, GEMM alone with operands that change from launch to launch, cached (256 x 256
-// tiles: written through) / this: 4 bits M4608 x N12288 x K3072 85 / 79 (192 x 192 tiles 90 / 78), N9216 64 / 62, M16896 x N12288 x K3072 301 / 275,
-// M16896 x N4096 x K3072 119 / 98, M8192 x N8192 x K2048 86 / 70, M4608 x N3072 x K12288 76 / 62, all of it from memory 79 / 77;
-// 8 bits M4608 x N12288 x K3072 144 / 132, M16896 x N3072 x K12288 477 / 467.  On one set of buffers 83 / 81 at the first.
-__device__ __forceinline__ void store_past_caches(uint16_t *out, const v4i &v) { __builtin_nontemporal_store(v, reinterpret_cast<v4i *>(out)); }
+// Eight bf16 of a row of Y; but for kCached `out` is a multiple of 16 bytes.  (The wait state is the one that a store of more than 64 bits
+// needs before its data registers are written again, which the compiler cannot see in the asm.)
+template <Store KIND>
+__device__ __forceinline__ void store_row(uint16_t *out, const v4i &v)
+{
+    if constexpr (KIND == Store::kPast) __builtin_nontemporal_store(v, reinterpret_cast<v4i *>(out));
+    else if constexpr (KIND == Store::kThrough) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" :: "v"(out), "v"(v) : "memory");
+    else *reinterpret_cast<u32x4_row *>(out) = __builtin_bit_cast(u32x4_row, v);
+}
 
 // Tile order: blocks are dealt round-robin to the 8 XCDs by the hardware, each XCD has its own
 // L2.  Give every XCD one contiguous range of logical tile ids, and walk that range in bands of
@@ -118,6 +122,7 @@ struct Operands {
     void *Y;          // bf16 output, or
     int32_t *acc;     // raw accumulators
     hipStream_t stream;
+    Store store = Store::kCached;     // of Y, where a tiled kernel writes it
 };
 
 }  // namespace gemm

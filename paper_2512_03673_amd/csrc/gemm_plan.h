@@ -15,8 +15,8 @@
 // 1.2e10 products, the large 4-bit tiles also to 120 such with operands that change from launch to launch (128 x 192: to 220
 // with M 64 ... 8000 and 3e9 to 8e10 products).  On the larger shapes the tile taken costs 0.5 % more on average than the best of
 // them would, on the others 1 to 2 %.  All fits but those of the large 4-bit tiles are thus of operands that the Infinity Cache holds.
-// The fits are of kernels whose output went through the caches.  With it past them (store_past_caches) the tiles' times fell
-// together: over 150 shapes (4 bits) and 130 (8 bits) of 1e9 to 6.4e11 products with operands that change from launch to launch the
+// The fits are of kernels whose output went through the caches.  With every output past them the tiles' times fell together: over
+// 150 shapes (4 bits) and 130 (8 bits) of 1e9 to 6.4e11 products with operands that change from launch to launch the
 // tile taken costs 1.3 and 1.9 % more than the best, with constants fitted again to these 1.5 and 1.7 %.
 #pragma once
 #include <stdint.h>
@@ -69,6 +69,39 @@ inline int64_t tiles_of(int64_t M, int64_t N, int tm, int tn) { return ((M + tm 
 // stages: 4 bits, 192 x 192, M3000 x N3072 x K3072 25 / 16.3, geometric mean over 91 drawn shapes 1.35; three / four: 8 bits, 128 x 192, M300 x N12288 x
 // K12288 80 / 65, over 69 shapes 1.11.  (No gain: 192 x 192 at 8 bits, 128 x 128 at 4 bits, 256 x 128 on eight wavefronts.)
 inline bool deep_ring(int64_t tiles, int64_t stages) { return tiles <= 256 && stages >= 16; }
+
+// How the tiled kernels store Y (gemm_tiled.h).
+enum class Store {
+    kCached,      // left to the caches
+    kThrough,     // written through the L2: a line is on its way to memory at once, not when the next tiles' lines push it out or the kernel ends
+    kPast,        // nontemporally, past the lines in use: operands that tiles and launches share stay in the L2 and the Infinity Cache
+};
+
+// Which of them a product takes; `y` = address of Y.
+//   Rows of whole lines of 128 bytes: past the caches where a launch takes some 25 us or more, through otherwise.  A long product loses
+//   more to the operands that its output pushes out than its stores cost, in a short one the stores are the time and past the caches they
+//   run at the rate of the memory.
+//   Lines that two rows share: never past the caches (two half lines, each written to memory by itself).  Through while the L2s hold
+//   all of Y, which would otherwise be written back when the kernel ends; cached beyond, where a line mostly gets its second half before
+//   it leaves (8-bit 256 x 256 tiles, alone on their unit, end together with 128 KB each: no gain there).
+// us, GEMM on three sets of buffers in turn, cached / through / past, 4 bits if not said:
+//   M6398 x N11328 x K64 at 8 bits 32.3 / 32.5 / 35.6, M7023 x N4864 x K64 16.3 / 15.5 / 18.8, M4189 x N8768 x K1024 26.4 / 26.1 / 29.3, M423 x N8896 x K512
+//   6.1 / 5.4 / 5.6, M4608 x N3072 x K3072 21.7 / 21.2 / 21.7; M4608 x N12288 x K3072 85.1 / 86.9 / 78.9 and at 8 bits 143 / 144 / 136, M4608 x N3072 x K12288
+//   72.7 / 73.5 / 60.1, M16896 x N4096 x K3072 113 / 113 / 97; half lines: M13207 x N5816 x K64 46.5 / 90.4 / 86.8, M5644 x N3832 x K512 16.9 / 17.8 / 25.1,
+//   M10772 x N672 x K512 8.3 / 6.6 / 6.9, M7622 x N10104 x K1024 74 / 110 / 97, M5082 x N6320 x K768 at 8 bits 37.6 / 33.5 / 47.1
+// The next layer, which reads Y from memory where it went past the caches, takes part of that back; GEMM and its rotate+quantise: M4608 x N12288 x K3072
+// 106.5 / 108.7 / 106.9, at 8 bits 165 / 166 / 168, M4608 x N3072 x K12288 80.0 / 79.8 / 80.5, M16896 x N4096 x K3072 137 / 136 / 131.
+// Over 336 shapes with whole lines and 264 without (4 and 8 bits, Y of 4 to 415 MB, K 64 ... 15360; mean of GEMM alone, into one output, with the
+// next layer's rotate+quantise, whole forward) the rule is 5.2 and 4.3 % faster than cached stores (through where a block has its unit to itself)
+// on average and 4 and 7 % slower at most; everything past the caches 2.6 % faster and 8 % slower, at most 18 and 120 % slower.
+template <int BITS>
+inline Store store_kind(Plan plan, int64_t M, int64_t N, int64_t K, uintptr_t y)
+{
+    const double outputs = (double)M * (double)N;
+    if (N % 64 == 0 && y % 128 == 0) return K >= 512 && outputs * (double)K * (BITS / 4) >= 6e10 ? Store::kPast : Store::kThrough;
+    if (N % 8 != 0 || y % 16 != 0) return Store::kCached;
+    return 2.0 * outputs <= 8 * 4.0 * 1048576 || (BITS == 8 && plan == Plan::kTile256x256) ? Store::kThrough : Store::kCached;
+}
 
 struct Small {
     Plan plan;

@@ -22,7 +22,7 @@
 //
 // The MFMA's row operand is the W tile and its column operand the X tile, so that a lane ends up with four
 // consecutive n for one m; the epilogue scales, rounds to bf16, transposes through LDS and writes 16 bytes per lane,
-// whole contiguous rows of the wavefront's tile, past the caches (store_past_caches).
+// whole contiguous rows of the wavefront's tile, in or past the caches (store_kind).
 //
 // What bounds the large tiles is power: the chip runs as many operand bytes and multiply-adds a second as its clock lets it, and
 // the clock falls with them.  So the tile that moves the fewest bytes a product wins where its rounds are not too uneven: 256 x 256
@@ -80,6 +80,7 @@ struct Product {      // what every block of a launch is told
     int M, N, K;
     uint16_t *Y;
     int32_t *acc_out;
+    Store store;
 };
 
 // The tile of the output from row m0 and column n0 on; `lds` holds Stage<C, T>::kLds bytes.
@@ -307,7 +308,7 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
 #pragma unroll
             for (int rb = 0; rb < 4; ++rb)
                 swv[j][rb] = *reinterpret_cast<const float4 *>(sw_lds + wn0 + j * 32 + rb * 8 + (lane >> 5) * 4);
-        auto body = [&](auto EDGE, auto BIAS) {
+        auto body = [&](auto EDGE, auto BIAS, auto KIND) {
 #pragma unroll
             for (int i = 0; i < XF; ++i) {
                 const int mrow = m0 + wm0 + i * 32;
@@ -337,15 +338,13 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
                     const v4i v = *reinterpret_cast<const v4i *>(stage_lds + r * kEpiPitch + piece * 16);
                     const int mo = mrow + r, ncol = n0 + wn0 + piece * 8;
                     uint16_t *out = Y + (int64_t)mo * N + ncol;
-                    if constexpr (decltype(EDGE)::value == -1) {
-                        store_past_caches(out, v);
-                    } else if constexpr (decltype(EDGE)::value == 0) {
-                        *reinterpret_cast<u32x4_row *>(out) = __builtin_bit_cast(u32x4_row, v);
+                    if constexpr (decltype(EDGE)::value == 0) {
+                        store_row<decltype(KIND)::value>(out, v);
                     } else if constexpr (decltype(EDGE)::value == 1) {
-                        if (mo < M && ncol < N) store_past_caches(out, v);
+                        if (mo < M && ncol < N) store_row<decltype(KIND)::value>(out, v);
                     } else {
                         if (mo < M && ncol + 8 <= N) {
-                            *reinterpret_cast<u32x4_row *>(out) = __builtin_bit_cast(u32x4_row, v);
+                            store_row<decltype(KIND)::value>(out, v);
                         } else if (mo < M) {
 #pragma unroll
                             for (int e = 0; e < 8; ++e)
@@ -357,23 +356,20 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
         };
         // Bounds checks only where the tile crosses the edge of Y, and element stores only where it ends inside a
         // 16-byte piece (uniform over the block; the edge bodies add a bias of zero where there is none).
-        // A line that two rows share waits in the caches, others pass them.
-        using Inside = std::integral_constant<int, -1>;
         using Edge0 = std::integral_constant<int, 0>;
         using Edge1 = std::integral_constant<int, 1>;
         using Edge2 = std::integral_constant<int, 2>;
+        using Cached = std::integral_constant<Store, Store::kCached>;
         const bool inside = m0 + TM <= M && n0 + TN <= N;
-        if ((N & 7) == 0 && inside) {
-            if (bias) body(Inside{}, std::true_type{});
-            else body(Inside{}, std::false_type{});
-        } else if (inside) {
-            if (bias) body(Edge0{}, std::true_type{});
-            else body(Edge0{}, std::false_type{});
-        } else if ((N & 7) == 0) {
-            body(Edge1{}, std::true_type{});
-        } else {
-            body(Edge2{}, std::true_type{});
-        }
+        auto rows = [&](auto KIND) {
+            if (!inside) body(Edge1{}, std::true_type{}, KIND);
+            else if (bias) body(Edge0{}, std::true_type{}, KIND);
+            else body(Edge0{}, std::false_type{}, KIND);
+        };
+        if (!inside && (N & 7) != 0) body(Edge2{}, std::true_type{}, Cached{});
+        else if (p.store == Store::kPast) rows(std::integral_constant<Store, Store::kPast>{});
+        else if (p.store == Store::kThrough) rows(std::integral_constant<Store, Store::kThrough>{});
+        else rows(Cached{});
     }
 }
 
@@ -383,12 +379,12 @@ template <class C, bool RAW, class T>
 __global__ __launch_bounds__(T::kThreads, T::OCC) void gemm_tiled_kernel(
     const uint8_t *__restrict__ Xq, const float *__restrict__ x_scale, const uint8_t *__restrict__ Wq,
     const float *__restrict__ w_scale, const uint16_t *__restrict__ bias, int M, int N, int K,
-    uint16_t *__restrict__ Y, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n)
+    uint16_t *__restrict__ Y, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, Store store)
 {
     __shared__ __attribute__((aligned(1024))) uint8_t lds[Stage<C, T>::kLds];
     int tm, tn;
     if (!tile_of_block<T::kBandRows>(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
-    tile_product<C, RAW, T>(Product{Xq, x_scale, Wq, w_scale, bias, M, N, K, Y, acc_out}, tm * T::TM, tn * T::TN, lds);
+    tile_product<C, RAW, T>(Product{Xq, x_scale, Wq, w_scale, bias, M, N, K, Y, acc_out, store}, tm * T::TM, tn * T::TN, lds);
 }
 
 // Tiles of T, of which each XCD's last ones (from its `whole`-th on) are cut into `parts` of shape P: a block of T takes a
@@ -397,13 +393,13 @@ template <class C, bool RAW, class T, class P>
 __global__ __launch_bounds__(T::kThreads, T::OCC) void gemm_cut_kernel(
     const uint8_t *__restrict__ Xq, const float *__restrict__ x_scale, const uint8_t *__restrict__ Wq,
     const float *__restrict__ w_scale, const uint16_t *__restrict__ bias, int M, int N, int K,
-    uint16_t *__restrict__ Y, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, int whole)
+    uint16_t *__restrict__ Y, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, int whole, Store store)
 {
     constexpr int kM = T::TM / P::TM, kN = T::TN / P::TN, kParts = kM * kN;
     static_assert(T::kThreads == P::kThreads && kM * P::TM == T::TM && kN * P::TN == T::TN, "parts of a tile");
     constexpr int kLds = Stage<C, T>::kLds > Stage<C, P>::kLds ? Stage<C, T>::kLds : Stage<C, P>::kLds;
     __shared__ __attribute__((aligned(1024))) uint8_t lds[kLds];
-    const Product p{Xq, x_scale, Wq, w_scale, bias, M, N, K, Y, acc_out};
+    const Product p{Xq, x_scale, Wq, w_scale, bias, M, N, K, Y, acc_out, store};
     const int xcd = blockIdx.x % kNumXcd, turn = blockIdx.x / kNumXcd;
     int tm, tn;
     if (turn < whole) {
@@ -426,7 +422,7 @@ hipError_t launch_tiled(const Operands &o)
     const int grid = ((ntiles + kNumXcd - 1) / kNumXcd) * kNumXcd;
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(T::kThreads), 0, o.stream, (const uint8_t *)o.Xq, o.x_scale, (const uint8_t *)o.Wq,
-                           o.w_scale, (const uint16_t *)o.bias, o.M, o.N, o.K, (uint16_t *)o.Y, o.acc, tiles_m, tiles_n);
+                           o.w_scale, (const uint16_t *)o.bias, o.M, o.N, o.K, (uint16_t *)o.Y, o.acc, tiles_m, tiles_n, o.store);
         return hipGetLastError();
     };
     return o.acc ? go(gemm_tiled_kernel<C, true, T>) : go(gemm_tiled_kernel<C, false, T>);
@@ -442,7 +438,7 @@ hipError_t launch_cut(const Operands &o, int cut)
     const int grid = (whole + cut * (T::TM / P::TM) * (T::TN / P::TN)) * kNumXcd;
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(T::kThreads), 0, o.stream, (const uint8_t *)o.Xq, o.x_scale, (const uint8_t *)o.Wq,
-                           o.w_scale, (const uint16_t *)o.bias, o.M, o.N, o.K, (uint16_t *)o.Y, o.acc, tiles_m, tiles_n, whole);
+                           o.w_scale, (const uint16_t *)o.bias, o.M, o.N, o.K, (uint16_t *)o.Y, o.acc, tiles_m, tiles_n, whole, o.store);
         return hipGetLastError();
     };
     return o.acc ? go(gemm_cut_kernel<C, true, T, P>) : go(gemm_cut_kernel<C, false, T, P>);

@@ -139,8 +139,9 @@ hipError_t launch_gemm_w4a4(const void *Xq, const float *x_scale, const void *Wq
                             int32_t *acc_i32, hipStream_t stream)
 {
     if (M == 0 || N == 0) return hipSuccess;
-    const gemm::Operands o{Xq, x_scale, Wq, w_scale, bias_bf16, (int)M, (int)N, (int)K, Y_bf16, acc_i32, stream};
-    return launch_plan(gemm::choose<4>(M, N, K), o);
+    const gemm::Plan plan = gemm::choose<4>(M, N, K);
+    const gemm::Store store = gemm::store_kind<4>(plan, M, N, K, reinterpret_cast<uintptr_t>(Y_bf16));
+    return launch_plan(plan, gemm::Operands{Xq, x_scale, Wq, w_scale, bias_bf16, (int)M, (int)N, (int)K, Y_bf16, acc_i32, stream, store});
 }
 
 }  // namespace convrot
