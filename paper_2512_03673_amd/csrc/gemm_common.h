@@ -89,10 +89,7 @@ __device__ __forceinline__ void store_row(uint16_t *out, const v4i &v)
 // L2.  Give every XCD one contiguous range of logical tile ids, and walk that range in bands of
 // `GM` tile rows (a template parameter: 6 suits 256 x 128 tiles, 8 square ones) so that tiles that run together share X and W panels.  `bid` may run past the
 // grid (a persistent block asks for bid + gridDim.x, ...): false when XCD bid % 8 has no such tile.
-// GM = 0: bands of 4 where they come out even, else of 6, for 256 x 256 tiles, of which an XCD runs 32 at a time: 4 x 8 and 6 x 5.3 share
-// operands about alike, and a last band of one to three rows shares little (66 tile rows, M16896 x N3072 x K12288, bands of 4 / 6 / 8: 268 / 256 /
-// 277 us; 18, M4608 x N12288 x K3072, 78.8 / 76.7 / 77.6; 32, M8192 x N8192 x K4096, 107.8 / 110.2 / 112.2; over 23 shapes within 0.5 % of
-// the better but for M17408 x N3072 x K6144, 139 / 135).
+// GM = 0: band_of_256 says.
 template <int GM = 6>
 __device__ __forceinline__ bool tile_of_block(int bid, int tiles_m, int tiles_n, int &tm, int &tn)
 {
@@ -101,7 +98,7 @@ __device__ __forceinline__ bool tile_of_block(int bid, int tiles_m, int tiles_n,
     if (bid / kNumXcd >= per_xcd) return false;
     const int id = (bid % kNumXcd) * per_xcd + bid / kNumXcd;
     if (id >= ntiles) return false;
-    const int gm = GM != 0 ? GM : tiles_m % 4 == 0 ? 4 : 6;
+    const int gm = GM != 0 ? GM : band_of_256(tiles_m);
     const int band = id / (gm * tiles_n);
     const int first_m = band * gm;
     const int rows_in_band = min(gm, tiles_m - first_m);

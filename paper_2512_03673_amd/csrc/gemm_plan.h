@@ -70,6 +70,14 @@ inline int64_t tiles_of(int64_t M, int64_t N, int tm, int tn) { return ((M + tm 
 // K12288 80 / 65, over 69 shapes 1.11.  (No gain: 192 x 192 at 8 bits, 128 x 128 at 4 bits, 256 x 128 on eight wavefronts.)
 inline bool deep_ring(int64_t tiles, int64_t stages) { return tiles <= 256 && stages >= 16; }
 
+// Tile rows of a band of 256 x 256 tiles (tile_of_block, gemm_common.h), of which an XCD runs 32 at a time: 4 x 8 and 6 x 5.3 share
+// operands about alike, and a last band of one to three rows shares little.  So four where they come out even or leave more rows over than
+// six do, else six.  us, bands of 4 / 6: 66 tile rows, M16896 x N3072 x K12288, 268 / 256 (8: 277); 18, M4608 x N12288 x K3072, 78.8 / 76.7 (8: 77.6);
+// 32, M8192 x N8192 x K4096, 107.8 / 110.2 (8: 112.2); 19, M4864 x N9152 x K12288, 199 / 217.  Over 23 shapes of 7, 19, 31, 43 and 55
+// rows, where six would leave one over and four three, bands of four are 1 % faster on average and 2 % slower at most, over 142 others that are
+// not even 0.4 % slower on average (22 rows, M5632 x N7680 x K12288, 198 / 209, the widest apart the other way).
+constexpr int band_of_256(int tiles_m) { return tiles_m % 4 == 0 || tiles_m % 12 == 7 ? 4 : 6; }
+
 // How the tiled kernels store Y (gemm_tiled.h).
 enum class Store {
     kCached,      // left to the caches

@@ -5,6 +5,7 @@ that the list keeps naming the tiles it means to."""
 import os
 import re
 import shutil
+import subprocess
 
 import numpy as np
 import pytest
@@ -112,3 +113,14 @@ def test_every_tile_against_the_oracle(M, N, K, bits):
             mag = np.maximum(np.abs(bits_to_f64(yo)), np.abs(bits_to_f64(b))[None, :])
             assert (np.abs(bits_to_f64(yb) - bits_to_f64(yo)) <= mag * 2.0 ** -7).all()
         check_output(yb, yo, f"{bits} bits")
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not installed")
+def test_bands_of_256_leave_the_larger_last_band(tmp_path):
+    src, exe = tmp_path / "band.cpp", str(tmp_path / "band")
+    src.write_text('#include "gemm_plan.h"\n#include <cstdio>\nint main() { for (int t = 1; t <= 300; ++t) std::printf("%d\\n", convrot::gemm::band_of_256(t)); }\n')
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, "-o", exe, str(src)], check=True)
+    bands = [int(b) for b in subprocess.run([exe], check=True, capture_output=True, text=True).stdout.split()]
+    for t, b in enumerate(bands, 1):
+        last = {n: (t - 1) % n + 1 for n in (4, 6)}
+        assert b == (4 if last[4] == 4 or last[4] > last[6] else 6), t
