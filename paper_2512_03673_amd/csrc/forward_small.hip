@@ -27,7 +27,11 @@ __global__ __launch_bounds__(64 * kWaves) void forward_small_kernel(const uint16
     constexpr int kStageUnits = BITS == 4 ? e2m3::kUnitsPerStage : panel::kRowBytes / kUnit;
     constexpr int kMaxRowStages = I * S * (64 / kStageUnits);            // rows x stages
     constexpr int kRowStageBytes = BITS == 4 ? e2m3::kARowBytes + e2m3::kBRowBytes : panel::kRowBytes;
-    __shared__ __attribute__((aligned(16))) uint8_t codes[kMaxRowStages * kRowStageBytes];
+    // Bytes between the stages of 8-bit codes.  Lanes of neighbouring columns write neighbouring stages, M * 64 bytes apart, which are the same
+    // banks; an odd multiple of 16 bytes apart they are not (M2 x N750 x K6144 at g = 64 5.95 -> 5.81 us, M4 x N3072 x K2816 5.81 -> 5.63, M1 x N1000 x K12288 at
+    // g = 256 8.71 -> 8.55).  With g <= 16 four lanes write a stage (1 % slower so), with 4 bits two (no difference).
+    constexpr int kPad = BITS == 8 && G >= 64 ? 16 : 0;
+    __shared__ __attribute__((aligned(16))) uint8_t codes[kMaxRowStages * (kRowStageBytes + kPad)];
     __shared__ __attribute__((aligned(16))) uint8_t part[S * WF * gemm::kTileBytes];
     __shared__ float item_max[I * S], row_scale[16];
 
@@ -126,7 +130,7 @@ __global__ __launch_bounds__(64 * kWaves) void forward_small_kernel(const uint16
             if (s >= KS) continue;
             if (unit >= units) o = u32x4{0, 0, 0, 0};        // K padding
             const int c = unit % kStageUnits;
-            *reinterpret_cast<u32x4 *>(codes + (s * M + row) * panel::kRowBytes + c * 16) = o;
+            *reinterpret_cast<u32x4 *>(codes + (s * M + row) * panel::kRowBytes + s * kPad + c * 16) = o;
             if (tn == 0) *reinterpret_cast<u32x4 *>(Xq + s * panel::kBytes + row * panel::kRowBytes + c * 16) = o;
         }
     }
@@ -143,7 +147,7 @@ __global__ __launch_bounds__(64 * kWaves) void forward_small_kernel(const uint16
             x.a = *reinterpret_cast<const gemm::v4i *>(codes + (s * M + xrow) * e2m3::kARowBytes + quarter * 16);
             x.b = *reinterpret_cast<const gemm::v2i *>(bpart + (s * M + xrow) * e2m3::kBRowBytes + quarter * 8);
         } else {
-            x.a = *reinterpret_cast<const gemm::v4i *>(codes + (s * M + xrow) * panel::kRowBytes + quarter * 16);
+            x.a = *reinterpret_cast<const gemm::v4i *>(codes + (s * M + xrow) * panel::kRowBytes + s * kPad + quarter * 16);
         }
 #pragma unroll
         for (int j = 0; j < WF; ++j) C::mma(acc[j], fw[b][j], x);

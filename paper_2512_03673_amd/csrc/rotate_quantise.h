@@ -162,32 +162,43 @@ struct Rotation {
     }
 };
 
-// 1024 elements of a row (64 units from unit `base` on, 16 columns) that a wavefront rotates at a time, a unit a lane.  They are loaded as
-// they lie, a kilobyte an instruction, and change lanes in kBytes of LDS that are the wavefront's own: lanes n and n + 32 need the
-// halves of column n's units, which as loads would be pieces of 32 bytes (one-launch forwards, device time, us, so / through LDS / with
-// consecutive units and digit 2 across lanes: M3 x N512 x K2816 at g = 256 6.0 / 5.0 / 5.2, M4 x N3072 x K3072 at g = 64 and 8 bits 6.7 / 5.4 / 5.3,
-// M1 x N3072 x K3072 at g = 1024 4.55 / 4.15 / 4.5).  Piece p of column n lies in slot p ^ (n & 7), so that eight lanes read and write different banks.
+// 1024 elements of a row (64 units from unit `base` on, 16 columns) that a wavefront rotates at a time, a unit a lane, loaded a
+// kilobyte an instruction: every block of a launch asks for the same few lines, and an instruction that takes halves of them asks twice.
+// With g >= 64 they are loaded as they lie and change lanes in kBytes of LDS that are the wavefront's own: lanes n and n + 32 need the
+// halves of column n's units (one-launch forwards, us, through LDS / units n in 64-byte pieces straight to their lanes, with the
+// pairs that two lanes need loaded twice / loaded once and exchanged between rows of 16 lanes: M2 x N1536 x K3072 at g = 64 and 8 bits 4.39 / 5.07 / 4.72,
+// M4 x N3072 x K3072 at 4 bits 5.04 / 6.34 / 5.58).  Piece p of column n lies in slot p ^ (n & 7), so that eight lanes read and write different banks.
+// With g <= 16 no digit needs a column: lanes n and n + 32 load the halves of unit n, then of unit n + 32, which is where the MFMAs want them
+// (through LDS / so: M4 x N3072 x K3072 at g = 4 and 8 bits 6.54 / 6.35, M2 x N750 x K6144 6.23 / 6.07, M8 x N1024 x K1024 at 4 bits 4.05 / 3.92).
 template <int G>
 struct Item {
-    static constexpr int kBytes = 2048;
-    static __device__ __forceinline__ int unit(int lane) { return 4 * (lane & 15) + ((lane >> 4) & 1) + 2 * (lane >> 5); }
+    static constexpr bool kColumns = G >= 64;
+    static constexpr int kBytes = kColumns ? 2048 : 16;
+    static __device__ __forceinline__ int unit(int lane) { return kColumns ? 4 * (lane & 15) + ((lane >> 4) & 1) + 2 * (lane >> 5) : lane; }
     static __device__ __forceinline__ int out_unit(int lane) { return unit(lane ^ column_flip<G>()); }
     static __device__ __forceinline__ void load(const uint16_t *row, int base, int units, int lane, u32x4 (&raw)[2])
     {
 #pragma unroll
-        for (int j = 0; j < 2; ++j)      // past the row's end its last 16 bytes again
-            raw[j] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const uint8_t *>(row) + min(base * 32 + j * 1024 + lane * 16, units * 32 - 16));
+        for (int j = 0; j < 2; ++j) {
+            const int at = kColumns ? min(base * 32 + j * 1024 + lane * 16, units * 32 - 16)      // past the row's end its last 16 bytes again
+                                    : min(base + j * 32 + (lane & 31), units - 1) * 32 + (lane >> 5) * 16;      // ... its last unit
+            raw[j] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const uint8_t *>(row) + at);
+        }
     }
     static __device__ __forceinline__ void rotate(const Rotation<G> &rot, const u32x4 (&raw)[2], uint8_t *lds, int lane, float (&v)[kUnit])
     {
+        if constexpr (kColumns) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-            *reinterpret_cast<u32x4 *>(lds + j * 1024 + (lane >> 3) * 128 + (((lane & 7) ^ (lane >> 3)) << 4)) = raw[j];
-        asm volatile("" ::: "memory");       // (other lanes' pieces; a wavefront's LDS operations stay in order)
-        const int odd = (lane >> 4) & 1, h = lane >> 5;
-        rot.apply([&](int c) { return *reinterpret_cast<const u32x4 *>(lds + (lane & 15) * 128 + (((2 * (c ^ odd) + h) ^ (lane & 7)) << 4)); }, v);
-        asm volatile("" ::: "memory");
-        rotate_lanes<G>(v);
+            for (int j = 0; j < 2; ++j)
+                *reinterpret_cast<u32x4 *>(lds + j * 1024 + (lane >> 3) * 128 + (((lane & 7) ^ (lane >> 3)) << 4)) = raw[j];
+            asm volatile("" ::: "memory");       // (other lanes' pieces; a wavefront's LDS operations stay in order)
+            const int odd = (lane >> 4) & 1, h = lane >> 5;
+            rot.apply([&](int c) { return *reinterpret_cast<const u32x4 *>(lds + (lane & 15) * 128 + (((2 * (c ^ odd) + h) ^ (lane & 7)) << 4)); }, v);
+            asm volatile("" ::: "memory");
+            rotate_lanes<G>(v);
+        } else {
+            rot.apply([&](int c) { return raw[c / 2]; }, v);
+        }
     }
 };
 
