@@ -17,7 +17,8 @@
 // them would, on the others 1 to 2 %.  All fits but those of the large 4-bit tiles are thus of operands that the Infinity Cache holds.
 // The fits are of kernels whose output went through the caches.  With every output past them the tiles' times fell together: over
 // 150 shapes (4 bits) and 130 (8 bits) of 1e9 to 6.4e11 products with operands that change from launch to launch the
-// tile taken costs 1.3 and 1.9 % more than the best, with constants fitted again to these 1.5 and 1.7 %.
+// tile taken costs 1.3 and 1.9 % more than the best, with constants fitted again to these 1.5 and 1.7 %.  (Tiles against each other;
+// the stores themselves: store_kind.  The 8-bit 128 x 192 tile is predicted with its three stages also where deep_ring gives it four.)
 #pragma once
 #include <stdint.h>
 
@@ -54,7 +55,8 @@ inline int forward_in_one_columns(int64_t N) { return N <= 16 * 256 ? 16 : N <= 
 // rows) to 4 us (long ones) more and the rotation 0.15 us an item for each block (of 16 or 32 columns) of a compute unit.  Over 110 drawn shapes
 // (M 1-16, N 64-40000, K 64-15360) the line drawn here gives 0.5 to 5 us, us two / one: M1 x N9216 x K3072 10.8 / 7.3,
 // M1 x N3072 x K12288 12.7 / 9.0, M4 x N3072 x K3072 8.7 / 6.1, M8 x N608 x K1024 6.3 / 5.2, M1 x N394 x K128 5.3 / 3.8; past it
-// M12 x N9068 x K256 5.6 / 8.7, M14 x N1933 x K1088 6.0 / 7.0, M2 x N18018 x K192 5.8 / 6.9.
+// M12 x N9068 x K256 5.6 / 8.7, M14 x N1933 x K1088 6.0 / 7.0, M2 x N18018 x K192 5.8 / 6.9.  (All of blocks of 16 or 32 columns, and the line still counts
+// these: it has not been drawn again for N of 8193 and more, whose blocks are fewer and wider now.  M8 x N9216 x K1024 takes two launches by it.)
 inline bool forward_in_one(int64_t M, int64_t N, int64_t K)
 {
     const int64_t items = row_items(M, K), columns = N <= 4096 ? 16 : 32, blocks = (N + columns - 1) / columns;

@@ -31,9 +31,10 @@
 // M4608 x N3072 x K12288 137.5 / 132.9 -> 126.  (A ring of two: 68.6 -> 80.6.  A 288 x 192 tile fills 256 units exactly at M4608 x N3072,
 // where 256 x 256 leaves 40 idle, and is slower, 72.5 against 68.6: idle units leave their power to the others.)
 //
-// Products of one round or less are bound by a lone tile's walk along K, 0.3 to 0.4 us a stage whatever the ring's depth or how far
-// ahead fragments are read (a whole stage instead of a step: no difference), so the tile that spreads such a product over the most
-// units wins: 128 x 192, us: 4 bits M512 x N12288 x K3072 14.9 -> 13.8, M578 x N9408 x K9600 34.2 -> 31.0; 8 bits
+// Products of one round or less are bound by a lone tile's walk along K, 0.3 to 0.4 us a stage.  Tiles that otherwise share a unit two by
+// two wait for operands there and take a ring of four stages, which their lone unit has the LDS for (deep_ring); for 128 x 128 at 4 bits, 256 x 128 on
+// eight wavefronts and 192 x 192 at 8 bits a fourth stage made no difference, nor did fragments read a whole stage ahead instead of a step on any tile.
+// What is left is to spread such a product over the most units: 128 x 192, us: 4 bits M512 x N12288 x K3072 14.9 -> 13.8, M578 x N9408 x K9600 34.2 -> 31.0; 8 bits
 // M854 x N6464 x K1024 11.0 -> 10.1, M1803 x N5056 x K4992 49.2 -> 46.2.
 #pragma once
 #include "gemm_common.h"

@@ -294,7 +294,7 @@ hipError_t launch_rows(const void *X, int64_t rows, int K, void *Xq, float *scal
 // instruction finds more of an output block's 64- and 32-byte row pieces adjacent.  Past 4096 elements a block is one row of whole
 // chunks, as few wavefronts as hold it once.  us, cold, against a kernel of 16 consecutive elements a lane with digit 2 by DPP:
 //   [8000, 256] g64 5.2 -> 3.9, [8000, 512] g64 5.6 -> 4.2, [12288, 1024] g256 9.6 -> 9.0, [4608, 3072] g16 8.9 -> 8.5, g256 11.2 -> 9.8,
-//   [12288, 3072] g256 20.6 -> 18.5, [4608, 4096] g64 13.5 -> 10.5, [4608, 12288] g16 28.4 -> 27.9, [4608, 15360] g1024 43.8 -> 40.5,
+//   [12288, 3072] g256 23.0 -> 22.1 (weights prepared in turn: 21.3 -> 19.9 on one box, 21.8 -> 21.8 on another), [4608, 4096] g64 13.5 -> 10.5, [4608, 12288] g16 28.4 -> 27.9, [4608, 15360] g1024 43.8 -> 40.5,
 //   8 bits [16896, 12288] g16 121 -> 103
 // and the other splits at those sizes: U = 2 [8000, 512] 5.0, [4608, 1024] g256 5.7 against 5.0; one row a wavefront [4608, 3072] g16 8.9;
 // two rows a block [4608, 12288] 28.2 to 30.5, four rows 36.3; half the wavefronts with two sets each 28.1.
