@@ -88,20 +88,25 @@ enum class Store {
 };
 
 // Which of them a product takes; `y` = address of Y.
-//   Rows of whole lines of 128 bytes: past the caches where a launch takes some 12 us or more, through otherwise.  A long product loses
+//   Rows of whole lines of 128 bytes: past the caches where a launch takes some 12 us or more, through otherwise, cached if Y is large.  A long product loses
 //   more to the operands that its output pushes out than its stores cost, its own and those of the layers that follow; in a short one the
-//   stores are the time and past the caches they run at the rate of the memory.
-//   Lines that two rows share: never past the caches (two half lines, each written to memory by itself).  Through while the L2s hold
-//   all of Y, which would otherwise be written back when the kernel ends; cached beyond, where a line mostly gets its second half before
-//   it leaves (8-bit 256 x 256 tiles, alone on their unit, end together with 128 KB each: no gain there).
+//   stores are the time and past the caches they run at the rate of the memory, and so they do written through when outputs, three of one activation
+//   among them, no longer fit the Infinity Cache.
+//   Lines that two rows share: never past the caches (two half lines, each written to memory by itself).  Through in short products while the L2s
+//   hold all of Y, which would otherwise be written back when the kernel ends; cached beyond, where a line mostly gets its second half before
+//   it leaves (8-bit 256 x 256 tiles, alone on their unit, end together with 128 KB each: no gain there in a short product).
 // One activation that feeds three layers, three sets of operands in turn, through / past: M4608 x N3072 x K3072 91.1 / 88.8, M1891 x N6400 x K4224
 // 106.3 / 100.0, M2824 x N7616 x K960 at 8 bits 109 / 91; over 36 shapes of 1.2e10 to 7e10 products past is 3 % faster there, the same in a GEMM alone
 // or a forward (0.3 % slower) and 0.4 % faster with the next layer's rotate+quantise; of 1e9 to 1.5e10 products through is 0.2 % faster there and 4 % in the others.
+// K below 512, GEMM alone / three layers of one activation, cached : through: Y of 31 MB, M6978 x N2240 x K64 10.8 : 9.6 / 35.7 : 31.7, of 60 MB, M9929 x N3008 x K448
+// 19.2 : 18.9 / 66.6 : 67.2, of 117 MB, M7861 x N7424 x K64 at 8 bits 25.1 : 24.8 / 87.7 : 92.4, of 149 MB, M9753 x N7616 x K384 40.6 : 42.3 / 123 : 130, of 237 MB,
+// M10684 x N11072 x K64 51.3 : 55.9 / 158 : 165 (past the caches 57.1 / 176).
 // us, GEMM on three sets of buffers in turn, cached / through / past, 4 bits if not said:
 //   M6398 x N11328 x K64 at 8 bits 32.3 / 32.5 / 35.6, M7023 x N4864 x K64 16.3 / 15.5 / 18.8, M4189 x N8768 x K1024 26.4 / 26.1 / 29.3, M423 x N8896 x K512
 //   6.1 / 5.4 / 5.6; M4608 x N3072 x K3072 21.7 / 21.2 / 21.7, M4608 x N12288 x K3072 85.1 / 86.9 / 78.9 and at 8 bits 143 / 144 / 136, M4608 x N3072 x K12288
 //   72.7 / 73.5 / 60.1, M16896 x N4096 x K3072 113 / 113 / 97; half lines: M13207 x N5816 x K64 46.5 / 90.4 / 86.8, M5644 x N3832 x K512 16.9 / 17.8 / 25.1,
-//   M10772 x N672 x K512 8.3 / 6.6 / 6.9, M7622 x N10104 x K1024 74 / 110 / 97, M5082 x N6320 x K768 at 8 bits 37.6 / 33.5 / 47.1
+//   M10772 x N672 x K512 8.3 / 6.6 / 6.9, M7622 x N10104 x K1024 74 / 110 / 97, M5082 x N6320 x K768 at 8 bits 37.6 / 33.5 / 47.1; long ones with Y of 17 to 25 MB,
+//   M13752 x N856 x K5056 at 8 bits 71.9 / 74.0 / 69.0, M13111 x N888 x K14912 103.1 / 105.8 / 103.6, three layers of M3378 x N3640 x K8192 196 / 207 / 199
 // The next layer, which reads Y from memory where it went past the caches, takes part of that back; GEMM and its rotate+quantise: M4608 x N12288 x K3072
 // 106.5 / 108.7 / 106.9, at 8 bits 165 / 166 / 168, M4608 x N3072 x K12288 80.0 / 79.8 / 80.5, M16896 x N4096 x K3072 137 / 136 / 131.
 // Over 336 shapes with whole lines and 264 without (4 and 8 bits, Y of 4 to 415 MB, K 64 ... 15360; mean of GEMM alone, into one output, with the
@@ -110,9 +115,12 @@ enum class Store {
 template <int BITS>
 inline Store store_kind(Plan plan, int64_t M, int64_t N, int64_t K, uintptr_t y)
 {
-    const double outputs = (double)M * (double)N;
-    if (N % 64 == 0 && y % 128 == 0) return K >= 512 && outputs * (double)K * (BITS / 4) >= 1.5e10 ? Store::kPast : Store::kThrough;
-    if (N % 8 != 0 || y % 16 != 0) return Store::kCached;
+    const double outputs = (double)M * (double)N, products = outputs * (double)K * (BITS / 4);
+    if (N % 64 == 0 && y % 128 == 0) {
+        if (K >= 512 && products >= 1.5e10) return Store::kPast;
+        return 2.0 * outputs <= 96e6 ? Store::kThrough : Store::kCached;
+    }
+    if (N % 8 != 0 || y % 16 != 0 || products >= 6e10) return Store::kCached;
     return 2.0 * outputs <= 8 * 4.0 * 1048576 || (BITS == 8 && plan == Plan::kTile256x256) ? Store::kThrough : Store::kCached;
 }
 
