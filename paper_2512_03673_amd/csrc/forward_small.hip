@@ -20,7 +20,7 @@ template <int BITS, int G, int WF, int I>
 __global__ __launch_bounds__(64 * kWaves) void forward_small_kernel(const uint16_t *__restrict__ X, const uint8_t *__restrict__ Wq,
                                                                     const float *__restrict__ w_scale, const uint16_t *__restrict__ bias,
                                                                     int M, int N, int K, uint16_t *__restrict__ Y,
-                                                                    uint8_t *__restrict__ Xq, float *__restrict__ x_scale, int tiles_n)
+                                                                    uint8_t *__restrict__ Xq, float *__restrict__ x_scale, int per_xcd)
 {
     using C = std::conditional_t<BITS == 4, gemm::Small4, gemm::Small8>;
     constexpr int S = kWaves, PD = BITS == 4 ? 4 : 6;
@@ -35,9 +35,9 @@ __global__ __launch_bounds__(64 * kWaves) void forward_small_kernel(const uint16
     __shared__ __attribute__((aligned(16))) uint8_t part[S * WF * gemm::kTileBytes];
     __shared__ float item_max[I * S], row_scale[16];
 
-    int tm, tn;
-    if (!gemm::tile_of_block<8>(blockIdx.x, 1, tiles_n, tm, tn)) return;
-    const int n0 = tn * 16 * WF;
+    // as tile_of_block (gemm_plan.h): each XCD has one contiguous range of the tiles
+    const int turn = (int)(blockIdx.x / gemm::kNumXcd), tn = (int)(blockIdx.x % gemm::kNumXcd) * per_xcd + turn, n0 = tn * 16 * WF;
+    if (turn >= per_xcd || n0 >= N) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int KS = C::stages(K), units = K / kUnit, spans = (units + 63) / 64, items = M * spans;
 
@@ -173,9 +173,9 @@ hipError_t launch(const gemm::Operands &o, void *Xq, float *x_scale)
 {
     const int items = (int)gemm::row_items(o.M, o.K);
     auto go = [&](auto kernel, int wf) {
-        const int tiles_n = (o.N + 16 * wf - 1) / (16 * wf), grid = (tiles_n + gemm::kNumXcd - 1) / gemm::kNumXcd * gemm::kNumXcd;
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * kWaves), 0, o.stream, (const uint16_t *)o.Xq, (const uint8_t *)o.Wq, o.w_scale,
-                           (const uint16_t *)o.bias, o.M, o.N, o.K, (uint16_t *)o.Y, (uint8_t *)Xq, x_scale, tiles_n);
+        const int tiles_n = (o.N + 16 * wf - 1) / (16 * wf), per_xcd = (tiles_n + gemm::kNumXcd - 1) / gemm::kNumXcd;
+        hipLaunchKernelGGL(kernel, dim3(per_xcd * gemm::kNumXcd), dim3(64 * kWaves), 0, o.stream, (const uint16_t *)o.Xq, (const uint8_t *)o.Wq, o.w_scale,
+                           (const uint16_t *)o.bias, o.M, o.N, o.K, (uint16_t *)o.Y, (uint8_t *)Xq, x_scale, per_xcd);
         return hipGetLastError();
     };
     auto width = [&](auto WF) {

@@ -18,7 +18,6 @@ typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 
 constexpr int kRowBytes = 64;                 // bytes of K per row per stage: 128 4-bit codes or 64 8-bit codes
 constexpr int kSubSteps = kRowBytes / 32;     // MFMA K-steps of 32 bytes per row (one ds_read_b128 per fragment) per stage
-constexpr int kNumXcd = 8;
 
 // Which of the four 16-byte slots of its LDS row a piece lands in: slot = piece ^ swz(row).
 // For any 8 consecutive rows the (row & 1, slot) pairs are distinct (32 banks), and for any 16
@@ -83,29 +82,6 @@ __device__ __forceinline__ void store_row(uint16_t *out, const v4i &v)
     if constexpr (KIND == Store::kPast) __builtin_nontemporal_store(v, reinterpret_cast<v4i *>(out));
     else if constexpr (KIND == Store::kThrough) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" :: "v"(out), "v"(v) : "memory");
     else *reinterpret_cast<u32x4_row *>(out) = __builtin_bit_cast(u32x4_row, v);
-}
-
-// Tile order: blocks are dealt round-robin to the 8 XCDs by the hardware, each XCD has its own
-// L2.  Give every XCD one contiguous range of logical tile ids, and walk that range in bands of
-// `GM` tile rows (a template parameter: 6 suits 256 x 128 tiles, 8 square ones) so that tiles that run together share X and W panels.  `bid` may run past the
-// grid (a persistent block asks for bid + gridDim.x, ...): false when XCD bid % 8 has no such tile.
-// GM = 0: band_of_256 says.
-template <int GM = 6>
-__device__ __forceinline__ bool tile_of_block(int bid, int tiles_m, int tiles_n, int &tm, int &tn)
-{
-    const int ntiles = tiles_m * tiles_n;
-    const int per_xcd = (ntiles + kNumXcd - 1) / kNumXcd;
-    if (bid / kNumXcd >= per_xcd) return false;
-    const int id = (bid % kNumXcd) * per_xcd + bid / kNumXcd;
-    if (id >= ntiles) return false;
-    const int gm = GM != 0 ? GM : band_of_256(tiles_m);
-    const int band = id / (gm * tiles_n);
-    const int first_m = band * gm;
-    const int rows_in_band = min(gm, tiles_m - first_m);
-    const int local = id - band * gm * tiles_n;
-    tm = first_m + local % rows_in_band;
-    tn = local / rows_in_band;
-    return true;
 }
 
 // One product, as the launchers pass it on: the arguments of launch_gemm_w4a4 / launch_gemm_w8a8.

@@ -25,6 +25,8 @@
 namespace convrot {
 namespace gemm {
 
+constexpr int kNumXcd = 8;
+
 enum class Plan {
     kTile192x192,     // gemm_tiled.h
     kTile256x128,
@@ -79,6 +81,52 @@ inline bool deep_ring(int64_t tiles, int64_t stages) { return tiles <= 256 && st
 // rows, where six would leave one over and four three, bands of four are 1 % faster on average and 2 % slower at most, over 142 others that are
 // not even 0.4 % slower on average (22 rows, M5632 x N7680 x K12288, 198 / 209, the widest apart the other way).
 constexpr int band_of_256(int tiles_m) { return tiles_m % 4 == 0 || tiles_m % 12 == 7 ? 4 : 6; }
+
+// Tile order: blocks are dealt round-robin to the 8 XCDs by the hardware, each XCD has its own
+// L2.  Give every XCD one contiguous range of logical tile ids, and walk that range in bands of
+// `rows` tile rows (6 suits 256 x 128 tiles, 8 square ones, band_of_256 says for 256 x 256) so that tiles that run together share X and W
+// panels.  Every block of a launch starts here, with nothing to hide it behind, so the host prepares the two divisions (two by run-time
+// numbers take 60 scalar and vector instructions in a chain): quotient = high half of n times ceil(2^32 / d), one too many at most.
+struct TileOrder {
+    int per_xcd;        // tiles of an XCD's range
+    int tiles_m, rows, span;      // span = tiles of a whole band
+    uint32_t by_span, by_rows, by_tail;      // reciprocals of span, rows and the rows of the last band
+};
+
+constexpr uint32_t reciprocal(int d) { return d == 1 ? 0xFFFFFFFFu : (uint32_t)((((uint64_t)1 << 32) + (uint64_t)d - 1) / (uint64_t)d); }
+
+// n / d for n < 2^31, d < 2^31, with m = reciprocal(d).  (m d is 2^32 plus less than d, so n m / 2^32 is n / d plus less than 1; d = 1 has one
+// too little instead, for any n > 0.)
+constexpr int divide(int n, int d, uint32_t m)
+{
+    int q = (int)(((uint64_t)(uint32_t)n * m) >> 32);
+    const int rest = n - q * d;
+    q -= rest < 0;
+    return q + (rest >= d);
+}
+
+// (Of a launch that HIP takes: below 2^26 tiles.)
+constexpr TileOrder tile_order(int tiles_m, int tiles_n, int rows)
+{
+    const int tail = tiles_m % rows ? tiles_m % rows : rows, span = rows * tiles_n;
+    return {(tiles_m * tiles_n + kNumXcd - 1) / kNumXcd, tiles_m, rows, span, reciprocal(span), reciprocal(rows), reciprocal(tail)};
+}
+
+// The tile of block `bid`.  False where there is none; a block past an XCD's range or the last tile may also get a tile that lies
+// outside Y (tn past the last column of tiles), which its caller looks at.
+constexpr bool tile_of_block(const TileOrder &o, uint32_t bid, int &tm, int &tn)
+{
+    const int turn = (int)(bid / kNumXcd), id = (int)(bid % kNumXcd) * o.per_xcd + turn;
+    if (turn >= o.per_xcd) return false;
+    const int band = divide(id, o.span, o.by_span), first = band * o.rows, left = o.tiles_m - first;
+    if (left <= 0) return false;
+    const int local = id - band * o.span;
+    const bool tail = left < o.rows;
+    const int rows = tail ? left : o.rows;
+    tn = divide(local, rows, tail ? o.by_tail : o.by_rows);
+    tm = first + local - tn * rows;
+    return true;
+}
 
 // How the tiled kernels store Y (gemm_tiled.h).
 enum class Store {

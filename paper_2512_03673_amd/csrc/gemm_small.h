@@ -29,7 +29,7 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 struct Small4 {   // stage of 128 codes: half of a 3 KB block (e2m3_layout.h); quarter = one chunk of 32 codes
     struct Frag { v4i a; v2i b; };
     typedef v4f Acc;
-    static __device__ __forceinline__ int stages(int K) { return (int)e2m3::stages(K); }
+    static __device__ __forceinline__ int stages(int K) { return (K + e2m3::kStageCodes - 1) / e2m3::kStageCodes; }
     uint32_t a, b;
     const uint8_t *base;
     __device__ __forceinline__ void init(const uint8_t *m, int group, int rows, int KS, int lane)
@@ -58,7 +58,7 @@ struct Small4 {   // stage of 128 codes: half of a 3 KB block (e2m3_layout.h); q
 struct Small8 {   // stage of 64 codes: one 1 KB panel of 16 rows (panel_layout.h); quarter = 16 codes
     struct Frag { v4i a; };
     typedef v4i Acc;
-    static __device__ __forceinline__ int stages(int K) { return (int)panel::k_panels(K); }
+    static __device__ __forceinline__ int stages(int K) { return (K + panel::kRowBytes - 1) / panel::kRowBytes; }
     uint32_t a;
     const uint8_t *base;
     __device__ __forceinline__ void init(const uint8_t *m, int group, int rows, int KS, int lane)
@@ -127,18 +127,19 @@ __device__ __forceinline__ void sum_and_store(const uint8_t *part, int tid, int 
 }
 
 template <class C, bool RAW, int XF, int WF, int S, int PD>
-__global__ __launch_bounds__(64 * S) void gemm_small_kernel(const uint8_t *__restrict__ Xq, const float *__restrict__ x_scale,
-                                                            const uint8_t *__restrict__ Wq, const float *__restrict__ w_scale,
-                                                            const uint16_t *__restrict__ bias, int M, int N, int K,
-                                                            uint16_t *__restrict__ Y, int32_t *__restrict__ acc_out, int tiles_m,
-                                                            int tiles_n)
+__global__ __launch_bounds__(64 * S) void gemm_small_kernel(const uint8_t *__restrict__ Xq, const uint8_t *__restrict__ Wq, int M, int N, int K,
+                                                            int per_xcd, int tiles_m, int rows, int span, uint32_t by_span, uint32_t by_rows,
+                                                            uint32_t by_tail, const float *__restrict__ x_scale,
+                                                            const float *__restrict__ w_scale, const uint16_t *__restrict__ bias,
+                                                            uint16_t *__restrict__ Y, int32_t *__restrict__ acc_out)
 {
     constexpr int TM = 16 * XF, TN = 16 * WF;
     __shared__ __attribute__((aligned(16))) uint8_t part[S * XF * WF * kTileBytes];
 
     int tm, tn;
-    if (!tile_of_block<8>(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
+    if (!tile_of_block({per_xcd, tiles_m, rows, span, by_span, by_rows, by_tail}, blockIdx.x, tm, tn)) return;
     const int m0 = tm * TM, n0 = tn * TN;
+    if (n0 >= N) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int KS = C::stages(K);
 
@@ -195,10 +196,11 @@ hipError_t launch_small(const Operands &o)
 {
     const int tiles_m = (o.M + 16 * XF - 1) / (16 * XF), tiles_n = (o.N + 16 * WF - 1) / (16 * WF);
     if (!launchable((int64_t)tiles_m * tiles_n, 64 * S)) return hipErrorInvalidValue;
-    const int ntiles = tiles_m * tiles_n, grid = (ntiles + kNumXcd - 1) / kNumXcd * kNumXcd;
+    const TileOrder t = tile_order(tiles_m, tiles_n, 8);
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * S), 0, o.stream, (const uint8_t *)o.Xq, o.x_scale, (const uint8_t *)o.Wq,
-                           o.w_scale, (const uint16_t *)o.bias, o.M, o.N, o.K, (uint16_t *)o.Y, o.acc, tiles_m, tiles_n);
+        hipLaunchKernelGGL(kernel, dim3(t.per_xcd * kNumXcd), dim3(64 * S), 0, o.stream, (const uint8_t *)o.Xq, (const uint8_t *)o.Wq, o.M, o.N,
+                           o.K, t.per_xcd, t.tiles_m, t.rows, t.span, t.by_span, t.by_rows, t.by_tail, o.x_scale, o.w_scale,
+                           (const uint16_t *)o.bias, (uint16_t *)o.Y, o.acc);
         return hipGetLastError();
     };
     return o.acc ? go(gemm_small_kernel<C, true, XF, WF, S, PD>) : go(gemm_small_kernel<C, false, XF, WF, S, PD>);

@@ -7,7 +7,7 @@
 // multiplied; `T` (Tile) is the block's share of the output.
 //
 // Data movement.  A block of WGM x WGN wavefronts owns a TM x TN tile of the output.  A K stage of the tile's operand
-// rows is kPieces contiguous kilobytes in memory, copied by LDS-direct loads (dealt round-robin to the wavefronts)
+// rows is kPieces contiguous kilobytes in memory, copied by LDS-direct loads (dealt evenly to the wavefronts)
 // into a ring of NS stage buffers.  A stage is two K steps; a wavefront reads the fragments of a step (32 rows each)
 // one step ahead, into the other half of a double-buffered register set, so that no MFMA waits for LDS.
 //
@@ -16,6 +16,14 @@
 // refill has to be issued at once, in the second step of stage s; with more stages half of it waits for the first
 // step of stage s + 1, so that the load path has work in both halves of the stage (it would otherwise idle in one and
 // hold up the MFMAs in the other: 256 x 128 tiles, eight wavefronts, M512 x N12288 x K3072, 17.2 -> 16.4 us).
+//
+// A block's first MFMA waits for the arguments, the tile's place, addresses and the first stage's way from memory, with nothing to hide them
+// behind but, in products of a few rounds, another block.  So arguments come in registers, in the order they are needed, the place without divisions,
+// a wavefront loads whole groups of rows (one address for three pieces), the first stage is issued before anything else is asked for, and
+// the last buffer's stage not before the first MFMAs.  By the device's clock from a block's start, 256 x 256 tiles at 4 bits with a bias: first
+// operands there after 1.4 us, where five dependent loads of arguments, two divisions and a bias that was widened (hence waited for) first
+// took 3.1; M2000 x N3072 x K3072 13.7 -> 13.25 us, M500 x N4096 x K2048 at 8 bits 9.1 -> 8.5, M300 x N2000 x K512 (gemm_small.h) 3.6 -> 3.35, a product of three
+// rounds, where the power that is saved in a pause is spent after it, 0.5 to 3 %.
 //
 // A wavefront issues in order, so every memory instruction gets an MFMA slot of its own (scheduling barriers pin the
 // order) instead of queueing up in a burst.
@@ -72,6 +80,8 @@ struct Stage {
     static_assert(kLds * (T::OCC * 4 / T::NW) <= 160 * 1024, "blocks per compute unit");
 };
 
+enum class Refill { kNone, kShare, kAll };      // the loads of a stage that a step issues: its share of them, or all
+
 struct Product {      // what every block of a launch is told
     const uint8_t *Xq;
     const float *x_scale;
@@ -103,29 +113,28 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
     const int wm0 = (wave % T::WGM) * WM, wn0 = (wave / T::WGM) * WN;
     const int KS = C::stages(K);   // the last one is zero-padded
 
-    // ---- dequantisation scales of the tile's rows and columns: thread t fetches x_scale[m0 + t] and
-    // w_scale[n0 + t] now, so that the latency hides under the main loop, and parks them in LDS (past
-    // the ring) once the loop is over.
-    static_assert(TM <= T::kThreads && TN <= T::kThreads, "one scale per thread");
-    float my_sx = 0.0f, my_sw = 0.0f, my_b = 0.0f;
-    if constexpr (!RAW) {
-        if (tid < TM && m0 + tid < M) my_sx = x_scale[m0 + tid];
-        if (tid < TN && n0 + tid < N) {
-            my_sw = w_scale[n0 + tid];
-            if (bias) my_b = bf16_to_f32(bias[n0 + tid]);
-        }
-    }
-
-    // ---- global -> LDS (direct).  Load j of a stage copies the j-th kilobyte of the tile's operand rows (C::piece:
-    // where it lies in memory and in a stage buffer); wavefront w issues loads w, w + NW, ...  Rows past the
+    // ---- global -> LDS (direct).  A stage of kGroupRows rows is kGroupPieces consecutive kilobytes.  Wavefront w loads groups w, w + NW, ... of the
+    // tile's (X rows first) whole and a share of the pieces of those that are left.  Rows past the
     // operand's last block (edge tiles) re-read that block, whose results are never stored.
+    constexpr int kGroups = T::kRows / C::kGroupRows, kXGroups = TM / C::kGroupRows, kOwn = kGroups / NW, kP = C::kGroupPieces;
+    constexpr int kOwnLoads = kOwn * kP, kRest = (kGroups - kOwn * NW) * kP;
+    static_assert(kGroups * kP == St::kPieces && kXGroups * C::kGroupRows == TM, "groups of a stage");
     const uint8_t *src[kMaxLoads];   // stage 0 source of each of this wavefront's loads (wavefront-uniform)
     uint32_t dst[kMaxLoads];         // its place in a stage buffer
     const int swave = __builtin_amdgcn_readfirstlane(wave);
+    const uint32_t group_bytes = (uint32_t)KS * C::kStageStride;
+    auto group_source = [&](int g) {
+        const bool is_x = g < kXGroups;
+        const int at = is_x ? min(m0 / C::kGroupRows + g, (M - 1) / C::kGroupRows) : min(n0 / C::kGroupRows + g - kXGroups, (N - 1) / C::kGroupRows);
+        return (is_x ? Xq : Wq) + (uint64_t)(uint32_t)at * group_bytes;
+    };
 #pragma unroll
     for (int i = 0; i < kMaxLoads; ++i) {
-        const int j = kUneven ? min(swave + NW * i, St::kPieces - 1) : swave + NW * i;
-        C::template piece<TM, T::kRows>(j, Xq, Wq, m0, n0, M, N, KS, src[i], dst[i]);
+        const int j = swave + NW * (i - kOwnLoads);            // past the wavefront's own groups
+        const int rest = kUneven ? min(j, kRest - 1) : j;
+        const int g = i < kOwnLoads ? swave + NW * (i / kP) : kOwn * NW + rest / kP, part = i < kOwnLoads ? i % kP : rest % kP;
+        src[i] = group_source(g) + part * 1024;
+        dst[i] = C::template piece_place<T::kRows>(g, part);
     }
     const bool extra = kUneven && swave < St::kExtra;    // this wavefront has kMaxLoads loads
     // LDS-direct loads are issued from inline assembly so that the compiler does not serialise every
@@ -186,9 +195,10 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
         constexpr int j = i % 2 ? WF - 1 - m % WF : m % WF;      // there and back: one operand stays from every MFMA to the next (up to 1 %)
         if constexpr (m < kMfmas) {
             C::mma(acc[i][j], op[ks][XF + j], op[ks][i]);
-            if constexpr (decltype(REFILL)::value) {
+            if constexpr (decltype(REFILL)::value != Refill::kNone) {
                 // NS = 2: everything in the second step; otherwise its second half in the first step of the next stage
-                constexpr int half = NS > 2 ? kMaxLoads / 2 : kMaxLoads;
+                constexpr bool all = decltype(REFILL)::value == Refill::kAll;
+                constexpr int half = all ? 0 : NS > 2 ? kMaxLoads / 2 : kMaxLoads;
                 constexpr int first = ks == 1 ? 0 : half, count = ks == 1 ? half : kMaxLoads - half;
                 constexpr int l0 = first + m * count / kMfmas, l1 = first + (m + 1) * count / kMfmas;
                 static_assert(l1 - l0 <= 3, "loads per slot");
@@ -216,14 +226,31 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
     // ---- pipeline
     using K0 = std::integral_constant<int, 0>;
     using K1 = std::integral_constant<int, 1>;
-    using No = std::false_type;
-    using Yes = std::true_type;
-    using Rest = std::integral_constant<bool, (NS > 2)>;      // the part of a refill that waits for the next stage's first step
+    using No = std::integral_constant<Refill, Refill::kNone>;
+    using Yes = std::integral_constant<Refill, Refill::kShare>;
+    using All = std::integral_constant<Refill, Refill::kAll>;
     load_stage(0, 0);
+    // Dequantisation scales of the tile's rows and columns: thread t fetches x_scale[m0 + t] and
+    // w_scale[n0 + t] now, so that the latency hides under the main loop, and parks them in LDS (past
+    // the ring) once the loop is over.  Behind the first stage and with nothing done to them, so that no operand waits for them (vmcnt counts in order;
+    // with the bias widened here the whole block waited for it first); past an operand's end the last one again.
+    static_assert(TM <= T::kThreads && TN <= T::kThreads, "one scale per thread");
+    float my_sx = 0.0f, my_sw = 0.0f;
+    uint16_t my_b = 0;
+    if constexpr (!RAW) {
+        __builtin_amdgcn_sched_barrier(0);
+        my_sx = x_scale[min((uint32_t)m0 + tid, (uint32_t)M - 1)];
+        const uint32_t n = min((uint32_t)n0 + tid, (uint32_t)N - 1);
+        my_sw = w_scale[n];
+        if (bias) my_b = bias[n];
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // (The last buffer's stage can wait for the first MFMAs, unless the product is shorter than the ring.)
+    const bool late = NS > 2 && KS > NS;
 #pragma unroll
     for (int p = 1; p < NS; ++p)
-        if (p < KS) load_stage(p, p * St::kBytes);
-    wait_loads_upto(min(KS, NS) - 1);
+        if (p < KS && !(p == NS - 1 && late)) load_stage(p, p * St::kBytes);
+    wait_loads_upto((late ? NS - 1 : min(KS, NS)) - 1);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     reader.template aim<0>(0);
@@ -251,9 +278,9 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
     if constexpr (NS == 2) {
         while (s < KS - NS) stage(No{}, Yes{}, steady);
     } else if (KS > NS) {
-        stage(No{}, Yes{}, steady);
-        while (s < KS - NS) stage(Rest{}, Yes{}, steady);
-        stage(Rest{}, No{}, steady);
+        stage(All{}, Yes{}, steady);
+        while (s < KS - NS) stage(Yes{}, Yes{}, steady);
+        stage(Yes{}, No{}, steady);
     }
     while (s < KS) stage(No{}, No{}, drain);          // (what the very last step fetches is unused)
 
@@ -289,7 +316,7 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
         if (tid < TM) sx_lds[tid] = my_sx;
         if (tid < TN) {
             sw_lds[tid] = my_sw;
-            sw_lds[TN + tid] = my_b;
+            sw_lds[TN + tid] = bf16_to_f32(my_b);
         }
         __syncthreads();     // every wavefront has finished reading the ring; the scales are visible
         float sxm[XF];
@@ -376,42 +403,55 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
 
 // Statically sized LDS: above 64 KB a dynamic allocation would need a per-device function attribute set from the host
 // before the first launch, i.e. hidden library state; a static one needs nothing.
+// (Arguments in the order they are needed: the first fourteen words of them come in registers.)
+#define CONVROT_TILED_FIRST const uint8_t *__restrict__ Xq, const uint8_t *__restrict__ Wq, int M, int N, int K, int per_xcd, int tiles_m
+#define CONVROT_TILED_LAST                                                                                                          \
+    int span, uint32_t by_span, uint32_t by_rows, uint32_t by_tail, const float *__restrict__ x_scale, const float *__restrict__ w_scale, \
+        const uint16_t *__restrict__ bias, uint16_t *__restrict__ Y, int32_t *__restrict__ acc_out, Store store
 template <class C, bool RAW, class T>
-__global__ __launch_bounds__(T::kThreads, T::OCC) void gemm_tiled_kernel(
-    const uint8_t *__restrict__ Xq, const float *__restrict__ x_scale, const uint8_t *__restrict__ Wq,
-    const float *__restrict__ w_scale, const uint16_t *__restrict__ bias, int M, int N, int K,
-    uint16_t *__restrict__ Y, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, Store store)
+__global__ __launch_bounds__(T::kThreads, T::OCC) void gemm_tiled_kernel(CONVROT_TILED_FIRST, int rows, CONVROT_TILED_LAST)
 {
     __shared__ __attribute__((aligned(1024))) uint8_t lds[Stage<C, T>::kLds];
     int tm, tn;
-    if (!tile_of_block<T::kBandRows>(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
-    tile_product<C, RAW, T>(Product{Xq, x_scale, Wq, w_scale, bias, M, N, K, Y, acc_out, store}, tm * T::TM, tn * T::TN, lds);
+    if (!tile_of_block({per_xcd, tiles_m, rows, span, by_span, by_rows, by_tail}, blockIdx.x, tm, tn)) return;
+    const int m0 = tm * T::TM, n0 = tn * T::TN;
+    if (n0 < N) tile_product<C, RAW, T>(Product{Xq, x_scale, Wq, w_scale, bias, M, N, K, Y, acc_out, store}, m0, n0, lds);
 }
 
 // Tiles of T, of which each XCD's last ones (from its `whole`-th on) are cut into `parts` of shape P: a block of T takes a
 // compute unit to itself, so a last round that few tiles share would keep most of the chip waiting for a whole tile.
 template <class C, bool RAW, class T, class P>
-__global__ __launch_bounds__(T::kThreads, T::OCC) void gemm_cut_kernel(
-    const uint8_t *__restrict__ Xq, const float *__restrict__ x_scale, const uint8_t *__restrict__ Wq,
-    const float *__restrict__ w_scale, const uint16_t *__restrict__ bias, int M, int N, int K,
-    uint16_t *__restrict__ Y, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, int whole, Store store)
+__global__ __launch_bounds__(T::kThreads, T::OCC) void gemm_cut_kernel(CONVROT_TILED_FIRST, int rows_whole, CONVROT_TILED_LAST)
 {
-    constexpr int kM = T::TM / P::TM, kN = T::TN / P::TN, kParts = kM * kN;
+    constexpr uint32_t kM = T::TM / P::TM, kN = T::TN / P::TN, kParts = kM * kN;
     static_assert(T::kThreads == P::kThreads && kM * P::TM == T::TM && kN * P::TN == T::TN, "parts of a tile");
     constexpr int kLds = Stage<C, T>::kLds > Stage<C, P>::kLds ? Stage<C, T>::kLds : Stage<C, P>::kLds;
     __shared__ __attribute__((aligned(1024))) uint8_t lds[kLds];
     const Product p{Xq, x_scale, Wq, w_scale, bias, M, N, K, Y, acc_out, store};
-    const int xcd = blockIdx.x % kNumXcd, turn = blockIdx.x / kNumXcd;
+    const TileOrder order{per_xcd, tiles_m, rows_whole & 0xFF, span, by_span, by_rows, by_tail};
+    const uint32_t xcd = blockIdx.x % kNumXcd, turn = blockIdx.x / kNumXcd, whole = (uint32_t)rows_whole >> 8;
+    const uint32_t part = turn < whole ? 0 : (turn - whole) % kParts, tile_turn = turn < whole ? turn : whole + (turn - whole) / kParts;
     int tm, tn;
-    if (turn < whole) {
-        if (!tile_of_block<T::kBandRows>(blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
-        tile_product<C, RAW, T>(p, tm * T::TM, tn * T::TN, lds);
-    } else {
-        const int part = (turn - whole) % kParts;
-        if (!tile_of_block<T::kBandRows>((whole + (turn - whole) / kParts) * kNumXcd + xcd, tiles_m, tiles_n, tm, tn)) return;
-        const int m0 = tm * T::TM + part % kM * P::TM, n0 = tn * T::TN + part / kM * P::TN;
-        if (m0 < M && n0 < N) tile_product<C, RAW, P>(p, m0, n0, lds);
-    }
+    if (!tile_of_block(order, tile_turn * kNumXcd + xcd, tm, tn)) return;
+    const int m0 = tm * T::TM + (int)(part % kM) * P::TM, n0 = tn * T::TN + (int)(part / kM) * P::TN;
+    if (m0 >= M || n0 >= N) return;
+    if (turn < whole) tile_product<C, RAW, T>(p, m0, n0, lds);
+    else tile_product<C, RAW, P>(p, m0, n0, lds);
+}
+#undef CONVROT_TILED_FIRST
+#undef CONVROT_TILED_LAST
+
+template <class T>
+int band_rows(int tiles_m) { return T::kBandRows != 0 ? T::kBandRows : band_of_256(tiles_m); }
+
+// `rows`: of a band of tiles, and for the cut kernel more.
+template <class Kernel>
+hipError_t launch_order(Kernel kernel, const Operands &o, const TileOrder &t, int rows, int grid, int threads)
+{
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, o.stream, (const uint8_t *)o.Xq, (const uint8_t *)o.Wq, o.M, o.N, o.K, t.per_xcd,
+                       t.tiles_m, rows, t.span, t.by_span, t.by_rows, t.by_tail, o.x_scale, o.w_scale, (const uint16_t *)o.bias, (uint16_t *)o.Y,
+                       o.acc, o.store);
+    return hipGetLastError();
 }
 
 template <class C, class T>
@@ -419,13 +459,8 @@ hipError_t launch_tiled(const Operands &o)
 {
     const int tiles_m = (o.M + T::TM - 1) / T::TM, tiles_n = (o.N + T::TN - 1) / T::TN;
     if (!launchable((int64_t)tiles_m * tiles_n, T::kThreads)) return hipErrorInvalidValue;
-    const int ntiles = tiles_m * tiles_n;
-    const int grid = ((ntiles + kNumXcd - 1) / kNumXcd) * kNumXcd;
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(T::kThreads), 0, o.stream, (const uint8_t *)o.Xq, o.x_scale, (const uint8_t *)o.Wq,
-                           o.w_scale, (const uint16_t *)o.bias, o.M, o.N, o.K, (uint16_t *)o.Y, o.acc, tiles_m, tiles_n, o.store);
-        return hipGetLastError();
-    };
+    const TileOrder t = tile_order(tiles_m, tiles_n, band_rows<T>(tiles_m));
+    auto go = [&](auto kernel) { return launch_order(kernel, o, t, t.rows, t.per_xcd * kNumXcd, T::kThreads); };
     return o.acc ? go(gemm_tiled_kernel<C, true, T>) : go(gemm_tiled_kernel<C, false, T>);
 }
 
@@ -435,13 +470,9 @@ hipError_t launch_cut(const Operands &o, int cut)
 {
     const int tiles_m = (o.M + T::TM - 1) / T::TM, tiles_n = (o.N + T::TN - 1) / T::TN;
     if (!launchable((int64_t)tiles_m * tiles_n * (T::TM / P::TM) * (T::TN / P::TN), T::kThreads)) return hipErrorInvalidValue;
-    const int per_xcd = (tiles_m * tiles_n + kNumXcd - 1) / kNumXcd, whole = per_xcd - cut;
-    const int grid = (whole + cut * (T::TM / P::TM) * (T::TN / P::TN)) * kNumXcd;
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(T::kThreads), 0, o.stream, (const uint8_t *)o.Xq, o.x_scale, (const uint8_t *)o.Wq,
-                           o.w_scale, (const uint16_t *)o.bias, o.M, o.N, o.K, (uint16_t *)o.Y, o.acc, tiles_m, tiles_n, whole, o.store);
-        return hipGetLastError();
-    };
+    const TileOrder t = tile_order(tiles_m, tiles_n, band_rows<T>(tiles_m));
+    const int whole = t.per_xcd - cut, grid = (whole + cut * (T::TM / P::TM) * (T::TN / P::TN)) * kNumXcd;
+    auto go = [&](auto kernel) { return launch_order(kernel, o, t, t.rows | whole << 8, grid, T::kThreads); };
     return o.acc ? go(gemm_cut_kernel<C, true, T, P>) : go(gemm_cut_kernel<C, false, T, P>);
 }
 

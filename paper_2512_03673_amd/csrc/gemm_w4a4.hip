@@ -37,20 +37,16 @@ struct Codes4 {
     static constexpr int kRowBytes = e2m3::kARowBytes + e2m3::kBRowBytes;     // of one row per stage
     static constexpr uint32_t kStageStride = e2m3::kBlockBytes;               // from a row's stage to its next one
 
-    static __device__ __forceinline__ int stages(int K) { return (int)e2m3::stages(K); }
+    static constexpr int kGroupRows = e2m3::kRows, kGroupPieces = e2m3::kBlockBytes / 1024;
 
-    // Kilobyte j % 3 of the block of the tile's 32-row group j / 3: kilobytes 0, 1 are the A plane (rows 0-15, 16-31),
+    static __device__ __forceinline__ int stages(int K) { return (K + e2m3::kStageCodes - 1) / e2m3::kStageCodes; }
+
+    // Where kilobyte `part` of the block of the tile's 32-row group g goes: kilobytes 0, 1 are the A plane (rows 0-15, 16-31),
     // kilobyte 2 the B plane.  A stage buffer holds the A parts of all the tile's rows, then the B parts.
-    template <int TM, int ROWS>
-    static __device__ __forceinline__ void piece(int j, const uint8_t *Xq, const uint8_t *Wq, int m0, int n0, int M, int N, int KS,
-                                                 const uint8_t *&src, uint32_t &dst)
+    template <int ROWS>
+    static __device__ __forceinline__ uint32_t piece_place(int g, int part)
     {
-        const int grp = j / 3, part = j % 3;
-        const bool is_x = grp < TM / e2m3::kRows;
-        const int x_groups = (M + e2m3::kRows - 1) / e2m3::kRows, w_groups = (N + e2m3::kRows - 1) / e2m3::kRows;
-        const int g = is_x ? min(m0 / e2m3::kRows + grp, x_groups - 1) : min(n0 / e2m3::kRows + grp - TM / e2m3::kRows, w_groups - 1);
-        src = (is_x ? Xq : Wq) + (int64_t)g * KS * e2m3::kBlockBytes + part * 1024;
-        dst = part < 2 ? grp * e2m3::kAPlaneBytes + part * 1024 : ROWS * e2m3::kARowBytes + grp * e2m3::kBPlaneBytes;
+        return part < 2 ? g * e2m3::kAPlaneBytes + part * 1024 : ROWS * e2m3::kARowBytes + g * e2m3::kBPlaneBytes;
     }
     static __device__ __forceinline__ uint32_t lane_offset(int lane, int) { return lane * 16; }
 

@@ -24,18 +24,12 @@ struct Codes8 {
     static constexpr int kRowBytes = panel::kRowBytes;
     static constexpr uint32_t kStageStride = panel::kBytes;
 
-    static __device__ __forceinline__ int stages(int K) { return (int)panel::k_panels(K); }
+    static constexpr int kGroupRows = panel::kRows, kGroupPieces = 1;
 
-    // Kilobyte j is the panel of the tile's rows 16 j ... 16 j + 15.
-    template <int TM, int ROWS>
-    static __device__ __forceinline__ void piece(int j, const uint8_t *Xq, const uint8_t *Wq, int m0, int n0, int M, int N, int KS,
-                                                 const uint8_t *&src, uint32_t &dst)
-    {
-        const bool is_x = j < TM / panel::kRows;
-        const int p = is_x ? min(m0 / panel::kRows + j, (M - 1) / panel::kRows) : min(n0 / panel::kRows + j - TM / panel::kRows, (N - 1) / panel::kRows);
-        src = (is_x ? Xq : Wq) + (int64_t)p * KS * panel::kBytes;
-        dst = j * 1024;
-    }
+    static __device__ __forceinline__ int stages(int K) { return (K + panel::kRowBytes - 1) / panel::kRowBytes; }
+
+    template <int>
+    static __device__ __forceinline__ uint32_t piece_place(int g, int) { return g * panel::kBytes; }
     // Lane l fills 16-byte slot l % 4 of row l / 4 of the panel in LDS, where the swizzle keeps piece slot ^ swz(row).
     // (A wavefront's panels are all even or all odd: swz of the tile row depends on no more than that.)
     static __device__ __forceinline__ uint32_t lane_offset(int lane, int wave)
