@@ -36,6 +36,20 @@ __device__ __forceinline__ void wait_loads(int n)
     else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(3 * N) : "memory");
 }
 
+// Codes to memory, left to the L2 or written through it.  (The wait state: see gemm::store_row.)
+template <bool THROUGH>
+__device__ __forceinline__ void store16(void *out, u32x4 v)
+{
+    if constexpr (THROUGH) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" :: "v"(out), "v"(v) : "memory");
+    else *reinterpret_cast<u32x4 *>(out) = v;
+}
+template <bool THROUGH>
+__device__ __forceinline__ void store8(void *out, u32x2 v)
+{
+    if constexpr (THROUGH) asm volatile("global_store_dwordx2 %0, %1, off sc1" :: "v"(out), "v"(v) : "memory");
+    else *reinterpret_cast<u32x2 *>(out) = v;
+}
+
 }  // namespace
 
 // A set is what a wavefront rotates at a time: 16 U columns, U units a lane, 16 U / RPW columns of each of RPW consecutive rows.
@@ -55,12 +69,21 @@ struct Split {
     static_assert((U == 1 || U == 2) && WPR <= 16 && S <= 4, "split");
 };
 
+// Whether codes are written through the L2: where a store instruction holds two rows' pieces side by side (128 bytes of an output block's A plane or
+// of two panel rows).  Left to the L2 they go to memory when the kernel ends, all at once and with nothing to do meanwhile.  us, left / written
+// through: [4608, 3072] g256 9.8 / 8.7, [12288, 3072] g256 21.4 / 19.4, 8 bits [9000, 2048] g256 14.1 / 12.4, over 63 shapes of 3000 to 30000 rows of 1280 to
+// 4096 elements 4.4 % less; with the GEMM that reads them M4608 x N12288 x K3072 at 8 bits 159.9 / 158.7.  Not the pieces of single rows, which then go to memory by themselves ([8000, 1024]
+// 5.9 / 6.5, [16896, 12288] 92 / 136), nor, at g <= 16 and 4 bits, rows of four wavefronts of U = 1 ([3000, 4096] 7.4 / 7.6).
+template <int G, int BITS, int U, int RPW, int WPR>
+constexpr bool kThrough = RPW >= 2 && WPR >= 2 && (BITS == 8 || G >= 64 || U == 2 || WPR <= 3);
+
 template <int G, int BITS, int U, int RPW, int WPR, int S>
 __global__ __launch_bounds__((Split<U, RPW, WPR, S>::kThreads), (Split<U, RPW, WPR, S>::kOccupancy)) void rotquant_kernel(
     const uint16_t *__restrict__ X, int64_t rows, int K, uint8_t *__restrict__ Xq, float *__restrict__ scale)
 {
     using Sp = Split<U, RPW, WPR, S>;
     constexpr int C = Sp::kColumns;
+    constexpr bool kThru = kThrough<G, BITS, U, RPW, WPR>;
     static_assert(G <= 64 || G / 64 <= C, "the lanes of a rotation group lie in one row");
     __shared__ float part[WPR * RPW];
 
@@ -151,16 +174,15 @@ __global__ __launch_bounds__((Split<U, RPW, WPR, S>::kThreads), (Split<U, RPW, W
             uint8_t *const block = out + (uint32_t)(chunk >> 2) * (uint32_t)e2m3::kBlockBytes;
             if constexpr (U == 2) {
                 if (!(row_ok && chunk < 4 * stages)) continue;
-                *reinterpret_cast<u32x4 *>(block + e2m3::a_offset(r, chunk & 3)) =
-                    pad ? u32x4{0, 0, 0, 0} : u32x4{packed[0], packed[1], packed[2], packed[3]};
-                *reinterpret_cast<u32x2 *>(block + e2m3::b_offset(r, chunk & 3)) = pad ? u32x2{0, 0} : u32x2{packed[4], packed[5]};
+                store16<kThru>(block + e2m3::a_offset(r, chunk & 3), pad ? u32x4{0, 0, 0, 0} : u32x4{packed[0], packed[1], packed[2], packed[3]});
+                store8<kThru>(block + e2m3::b_offset(r, chunk & 3), pad ? u32x2{0, 0} : u32x2{packed[4], packed[5]});
             } else {        // lanes 16 further on hold the chunk's odd units
                 const uint32_t next = __builtin_amdgcn_permlane16_swap(packed[0], packed[0], false, false)[1];
                 if (!(row_ok && chunk < 4 * stages)) continue;
                 if (odd16 == 0)
-                    *reinterpret_cast<u32x4 *>(block + e2m3::a_offset(r, chunk & 3)) = pad ? u32x4{0, 0, 0, 0} : u32x4{packed[0], packed[1], packed[2], next};
+                    store16<kThru>(block + e2m3::a_offset(r, chunk & 3), pad ? u32x4{0, 0, 0, 0} : u32x4{packed[0], packed[1], packed[2], next});
                 else
-                    *reinterpret_cast<u32x2 *>(block + e2m3::b_offset(r, chunk & 3)) = pad ? u32x2{0, 0} : u32x2{packed[1], packed[2]};
+                    store8<kThru>(block + e2m3::b_offset(r, chunk & 3), pad ? u32x2{0, 0} : u32x2{packed[1], packed[2]});
             }
         }
     } else {
@@ -175,7 +197,7 @@ __global__ __launch_bounds__((Split<U, RPW, WPR, S>::kThreads), (Split<U, RPW, W
             u32x4 *const o = reinterpret_cast<u32x4 *>(out + (uint32_t)column * (uint32_t)panel::kBytes);
             const bool ok = row_ok && column < panels, pad = 2 * column + h >= chunks;      // K padding: zero codes
             if constexpr (U == 1) {
-                if (ok) o[odd16] = pad ? u32x4{0, 0, 0, 0} : a;
+                if (ok) store16<kThru>(o + odd16, pad ? u32x4{0, 0, 0, 0} : a);
             } else {
                 // Neighbouring lanes exchange one unit each, so that a store instruction writes whole columns, the even ones first.
                 u32x4 b = codes8(q, as_vector(v[i][1]));
@@ -188,8 +210,8 @@ __global__ __launch_bounds__((Split<U, RPW, WPR, S>::kThreads), (Split<U, RPW, W
                 }
                 const int even = column & ~1;
                 u32x4 *const oe = reinterpret_cast<u32x4 *>(out + (odd ? 16 : 0) + (uint32_t)even * (uint32_t)panel::kBytes);
-                if (row_ok && even < panels) oe[0] = a;
-                if (row_ok && even + 1 < panels) oe[panel::kBytes / 16] = b;
+                if (row_ok && even < panels) store16<kThru>(oe, a);
+                if (row_ok && even + 1 < panels) store16<kThru>(oe + panel::kBytes / 16, b);
             }
         }
     }
@@ -289,9 +311,15 @@ hipError_t launch_rows(const void *X, int64_t rows, int K, void *Xq, float *scal
     return hipSuccess;
 }
 
-// The split of a row, by its length.  Enough wavefronts first: with U = 1 twice as many that do half the work each, and one or two sets
+// Wavefronts of `rows` rows, 1024 elements each.
+inline int64_t row_waves(int64_t rows, int64_t K) { return rows * ((K + 1023) / 1024); }
+
+// The split of a row, by its length.  A few rows (up to 12 wavefronts a compute unit, rows of up to 12288 elements) are one pass of each wavefront through load,
+// arithmetic and store: a row a block, 1024 elements a wavefront (us, as more rows are split / so: [77, 3072] g16 3.1 / 2.8, [512, 2048] g256 3.75 / 3.5,
+// [256, 12288] g256 4.7 / 3.9, [1000, 3072] 3.7 / 3.45; past the line [1000, 12288] 7.6 / 8.9, [2000, 4096] at 8 bits 9.0 / 9.5).  For more rows: enough wavefronts first: with U = 1 twice as many that do half the work each, and one or two sets
 // of each; rows side by side in a wavefront as long as their digits across lanes fit (g / 64 columns), so that a store
-// instruction finds more of an output block's 64- and 32-byte row pieces adjacent.  Past 4096 elements a block is one row of whole
+// instruction finds more of an output block's 64- and 32-byte row pieces adjacent, and from 2e7 elements on (4 bits) lanes that store whole chunks
+// ([12288, 3072] g16 18.0 / 17.6, g256 19.4 / 18.8, [30000, 3072] g256 42.8 / 38.7; [4608, 3072] g256 8.7 / 8.9).  Past 4096 elements a block is one row of whole
 // chunks, as few wavefronts as hold it once.  us, cold, against a kernel of 16 consecutive elements a lane with digit 2 by DPP:
 //   [8000, 256] g64 5.2 -> 3.9, [8000, 512] g64 5.6 -> 4.2, [12288, 1024] g256 9.6 -> 9.0, [4608, 3072] g16 8.9 -> 8.5, g256 11.2 -> 9.8,
 //   [12288, 3072] g256 23.0 -> 22.1 (weights prepared in turn: 21.3 -> 19.9 on one box, 21.8 -> 21.8 on another), [4608, 4096] g64 13.5 -> 10.5, [4608, 12288] g16 28.4 -> 27.9, [4608, 15360] g1024 43.8 -> 40.5,
@@ -307,6 +335,23 @@ hipError_t launch_g(const void *X, int64_t rows, int K, void *Xq, float *scale, 
         if (K <= 512) return CONVROT_ROWS(1, 2, 1, 1);
     }
     if (K <= 1024) return CONVROT_ROWS(1, 1, 1, 1);
+    if (K <= 12288 && row_waves(rows, K) <= 12 * 256) {
+        switch ((K + 1023) / 1024) {
+            case 2: return CONVROT_ROWS(1, 1, 2, 1);
+            case 3: return CONVROT_ROWS(1, 1, 3, 1);
+            case 4: return CONVROT_ROWS(1, 1, 4, 1);
+            case 5: case 6: return CONVROT_ROWS(1, 1, 6, 1);
+            case 7: case 8: return CONVROT_ROWS(1, 1, 8, 1);
+            default: return CONVROT_ROWS(1, 1, 12, 1);
+        }
+    }
+    if constexpr (BITS == 4) {
+        if (K <= 4096 && rows * K >= 20000000) {
+            if (K <= 2048) return CONVROT_ROWS(2, 2, 2, 1);
+            if (K <= 3072) return CONVROT_ROWS(2, 2, 3, 1);
+            return CONVROT_ROWS(2, 2, 4, 1);
+        }
+    }
     if constexpr (G <= 256) {
         if (K <= 2048) return CONVROT_ROWS(1, 2, 2, 2);
         if (K <= 3072) return CONVROT_ROWS(1, 2, 3, 2);
