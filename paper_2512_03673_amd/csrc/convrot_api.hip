@@ -96,7 +96,7 @@ int launch_forward(const void *X_bf16, const void *Wq, const float *w_scale, con
     // In the one launch blocks write Y while others still read X: an output laid over its input takes the two.
     const uintptr_t x = reinterpret_cast<uintptr_t>(X_bf16), y = reinterpret_cast<uintptr_t>(Y_bf16);
     const bool apart = x + (uintptr_t)(M * K) * 2 <= y || y + (uintptr_t)(M * N) * 2 <= x;
-    if (M > 0 && N > 0 && apart && convrot::gemm::forward_in_one(M, N, K))
+    if (M > 0 && N > 0 && apart && (convrot::gemm::forward_in_one(M, N, K) || convrot::gemm::forward_in_row_tiles(M, N, K, bits)))
         return from_hip(convrot::launch_forward_small(X_bf16, Wq, w_scale, bias_bf16, M, N, K, group, bits, Y_bf16, xq, xs, s));
     if (convrot::launch_rotquant(X_bf16, M, K, group, bits, xq, xs, s) != hipSuccess) return CONVROT_ERR_HIP;
     return from_hip(bits == 4 ? convrot::launch_gemm_w4a4(xq, xs, Wq, w_scale, bias_bf16, M, N, K, Y_bf16, nullptr, s)

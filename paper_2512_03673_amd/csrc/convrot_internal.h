@@ -32,7 +32,7 @@ hipError_t launch_gemm_w8a8(const void *Xq, const float *x_scale, const void *Wq
                             const void *bias_bf16, int64_t M, int64_t N, int64_t K, void *Y_bf16,
                             int32_t *acc_i32, hipStream_t stream);
 
-// The whole forward of a few rows in one launch (gemm::forward_in_one says which); bits 4 or 8.  Writes the codes and the scales
+// The whole forward of a few rows in one launch (gemm::forward_in_one and forward_in_row_tiles say which); bits 4 or 8.  Writes the codes and the scales
 // to Xq and x_scale as launch_rotquant does.
 hipError_t launch_forward_small(const void *X, const void *Wq, const float *w_scale, const void *bias_bf16, int64_t M, int64_t N,
                                 int64_t K, int group, int bits, void *Y_bf16, void *Xq, float *x_scale, hipStream_t stream);

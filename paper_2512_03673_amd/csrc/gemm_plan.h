@@ -66,6 +66,31 @@ inline bool forward_in_one(int64_t M, int64_t N, int64_t K)
     return items * (blocks > 256 ? blocks : 256) <= 8 * 256 || (M <= 4 && items <= 16 && blocks <= 256);
 }
 
+// The one-launch forward of more rows: tiles of as many rows as sixteen wavefronts rotate at once (a stretch of 1024 elements each), whose
+// rotation every block of the same rows repeats, and as few columns as leave every compute unit at most one block.
+struct RowTiles {
+    int rows, columns;      // of a block
+};
+inline RowTiles forward_row_tiles(int64_t M, int64_t N, int64_t K)
+{
+    const int64_t most = 16 / row_items(1, K), tiles = (M + most - 1) / most, rows = (M + tiles - 1) / tiles;
+    return {(int)rows, tiles * ((N + 31) / 32) <= 256 ? 32 : tiles * ((N + 63) / 64) <= 256 ? 64 : 128};
+}
+
+// Whether a forward takes that.  One launch takes 5.1 us of the calling thread where two take 8 to 9, which is what such calls cost unless a graph
+// replays them; on the device a launch less and the rotation in every block come out about even while a block's share of W is small.  us, two
+// launches / one, called one after another: M256 x N1024 x K1024 g16 8.9 / 5.1, M389 x N437 x K1056 g4 7.8 / 6.4; replayed from a graph, 4 bits: 5.5 / 5.5 and
+// 6.1 / 6.4, M77 x N3072 x K1024 g16 5.8 / 5.2, M20 x N512 x K2048 g64 5.5 / 4.9, M60 x N1000 x K1536 g256 5.35 / 5.3, M256 x N1024 x K1024 g256 5.5 / 5.8, M1500 x N256 x
+// K1024 g64 7.2 / 6.65, M512 x N1024 x K512 g256 6.15 / 6.45; 8 bits M64 x N1024 x K1024 g64 5.7 / 5.35, M17 x N8192 x K1024 g64 6.0 / 5.2, M32 x N3072 x K2048 g64 6.5 / 7.05.
+// Past the line (a block's columns times K): M250 x N1000 x K1280 g16 5.65 / 6.4, M120 x N2048 x K2048 g256 6.4 / 7.2, M60 x N1024 x K3072 g256 5.75 / 6.25, 8 bits M256 x N2048 x K1024 g256
+// 7.3 / 8.0, M48 x N1000 x K3072 g256 6.9 / 8.0, two stretches a wavefront (it spills) M77 x N3072 x K3072 g64 8.5 / 22.
+inline bool forward_in_row_tiles(int64_t M, int64_t N, int64_t K, int bits)
+{
+    if (M < 1 || M > 4096 || N > 32768 || K > 4096) return false;
+    const RowTiles t = forward_row_tiles(M, N, K);
+    return (M + t.rows - 1) / t.rows * ((N + t.columns - 1) / t.columns) <= 256 && K * t.columns * (bits / 4) <= 144 * 1024;
+}
+
 inline int64_t tiles_of(int64_t M, int64_t N, int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); }
 
 // Whether tiles that otherwise share a compute unit two by two take a ring of four stages: in a launch of one round each has its unit to
