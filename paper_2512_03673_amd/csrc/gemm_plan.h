@@ -96,7 +96,9 @@ inline int64_t tiles_of(int64_t M, int64_t N, int tm, int tn) { return ((M + tm 
 // Whether tiles that otherwise share a compute unit two by two take a ring of four stages: in a launch of one round each has its unit to
 // itself, with LDS to spare, and what it waits for is operands (with a few stages there is nothing to run ahead with).  us, two / four
 // stages: 4 bits, 192 x 192, M3000 x N3072 x K3072 25 / 16.3, geometric mean over 91 drawn shapes 1.35; three / four: 8 bits, 128 x 192, M300 x N12288 x
-// K12288 80 / 65, over 69 shapes 1.11.  (No gain: 192 x 192 at 8 bits, 128 x 128 at 4 bits, 256 x 128 on eight wavefronts.)
+// K12288 80 / 65, over 69 shapes 1.11; 4 bits, 64 x 64, whose stages take 0.157 us so instead of 0.214, operands from the Infinity Cache: M700 x N1000 x K2048
+// 5.7 / 5.1, M256 x N3072 x K3072 7.55 / 6.4, M1024 x N1024 x K4096 9.15 / 7.55 (six stages 5.55, 6.9, 8.0; of more than a round, where four blocks a unit
+// become three, M512 x N3072 x K3072 8.2 / 8.45).  (No gain: 192 x 192 at 8 bits, 128 x 128 at 4 bits, 256 x 128 on eight wavefronts.)
 inline bool deep_ring(int64_t tiles, int64_t stages) { return tiles <= 256 && stages >= 16; }
 
 // Tile rows of a band of 256 x 256 tiles (tile_of_block, gemm_common.h), of which an XCD runs 32 at a time: 4 x 8 and 6 x 5.3 share

@@ -112,6 +112,8 @@ hipError_t launch_plan(gemm::Plan plan, const gemm::Operands &o)
     using gemm::Tile;
     if (plan == Plan::kTile192x192 && gemm::deep_ring(gemm::tiles_of(o.M, o.N, 192, 192), e2m3::stages(o.K)))
         return gemm::launch_tiled<Codes4, Tile<2, 2, 3, 3, 4, 1, 8>>(o);
+    if (plan == Plan::kTile64x64 && gemm::deep_ring(gemm::tiles_of(o.M, o.N, 64, 64), e2m3::stages(o.K)))
+        return gemm::launch_tiled<Codes4, Tile<2, 2, 1, 1, 4, 3, 8>>(o);
     switch (plan) {
         case Plan::kTile192x192: return gemm::launch_tiled<Codes4, Tile<2, 2, 3, 3, 2, 2, 8>>(o);
         case Plan::kTile256x128: return gemm::launch_tiled<Codes4, Tile<2, 2, 4, 2, 2, 2, 6>>(o);
