@@ -140,7 +140,7 @@ constexpr TileOrder tile_order(int tiles_m, int tiles_n, int rows)
 }
 
 // The tile of block `bid`.  False where there is none; a block past an XCD's range or the last tile may also get a tile that lies
-// outside Y (tn past the last column of tiles), which its caller looks at.
+// outside Y (tn past the last column of tiles), for which its caller asks starts_inside.
 constexpr bool tile_of_block(const TileOrder &o, uint32_t bid, int &tm, int &tn)
 {
     const int turn = (int)(bid / kNumXcd), id = (int)(bid % kNumXcd) * o.per_xcd + turn;
@@ -154,6 +154,10 @@ constexpr bool tile_of_block(const TileOrder &o, uint32_t bid, int &tm, int &tn)
     tm = first + local - tn * rows;
     return true;
 }
+
+// Whether a column of tiles of `width` columns starts inside N columns.  (Without signs: a tile outside starts up to seven widths past the
+// last one, which is past 2^31 for the largest N.)
+constexpr bool starts_inside(int tn, int width, int N) { return (uint32_t)tn * (uint32_t)width < (uint32_t)N; }
 
 // How the tiled kernels store Y (gemm_tiled.h).
 enum class Store {

@@ -137,9 +137,8 @@ __global__ __launch_bounds__(64 * S) void gemm_small_kernel(const uint8_t *__res
     __shared__ __attribute__((aligned(16))) uint8_t part[S * XF * WF * kTileBytes];
 
     int tm, tn;
-    if (!tile_of_block({per_xcd, tiles_m, rows, span, by_span, by_rows, by_tail}, blockIdx.x, tm, tn)) return;
+    if (!tile_of_block({per_xcd, tiles_m, rows, span, by_span, by_rows, by_tail}, blockIdx.x, tm, tn) || !starts_inside(tn, TN, N)) return;
     const int m0 = tm * TM, n0 = tn * TN;
-    if (n0 >= N) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int KS = C::stages(K);
 

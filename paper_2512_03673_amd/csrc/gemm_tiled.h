@@ -413,9 +413,8 @@ __global__ __launch_bounds__(T::kThreads, T::OCC) void gemm_tiled_kernel(CONVROT
 {
     __shared__ __attribute__((aligned(1024))) uint8_t lds[Stage<C, T>::kLds];
     int tm, tn;
-    if (!tile_of_block({per_xcd, tiles_m, rows, span, by_span, by_rows, by_tail}, blockIdx.x, tm, tn)) return;
-    const int m0 = tm * T::TM, n0 = tn * T::TN;
-    if (n0 < N) tile_product<C, RAW, T>(Product{Xq, x_scale, Wq, w_scale, bias, M, N, K, Y, acc_out, store}, m0, n0, lds);
+    if (!tile_of_block({per_xcd, tiles_m, rows, span, by_span, by_rows, by_tail}, blockIdx.x, tm, tn) || !starts_inside(tn, T::TN, N)) return;
+    tile_product<C, RAW, T>(Product{Xq, x_scale, Wq, w_scale, bias, M, N, K, Y, acc_out, store}, tm * T::TM, tn * T::TN, lds);
 }
 
 // Tiles of T, of which each XCD's last ones (from its `whole`-th on) are cut into `parts` of shape P: a block of T takes a
@@ -432,7 +431,7 @@ __global__ __launch_bounds__(T::kThreads, T::OCC) void gemm_cut_kernel(CONVROT_T
     const uint32_t xcd = blockIdx.x % kNumXcd, turn = blockIdx.x / kNumXcd, whole = (uint32_t)rows_whole >> 8;
     const uint32_t part = turn < whole ? 0 : (turn - whole) % kParts, tile_turn = turn < whole ? turn : whole + (turn - whole) / kParts;
     int tm, tn;
-    if (!tile_of_block(order, tile_turn * kNumXcd + xcd, tm, tn)) return;
+    if (!tile_of_block(order, tile_turn * kNumXcd + xcd, tm, tn) || !starts_inside(tn, T::TN, N)) return;
     const int m0 = tm * T::TM + (int)(part % kM) * P::TM, n0 = tn * T::TN + (int)(part / kM) * P::TN;
     if (m0 >= M || n0 >= N) return;
     if (turn < whole) tile_product<C, RAW, T>(p, m0, n0, lds);

@@ -5,7 +5,7 @@ import subprocess
 
 import pytest
 
-from gpu_util import CSRC
+from gpu_util import CSRC, gemm_plans
 
 SOURCE = r"""
 #include "gemm_plan.h"
@@ -61,3 +61,38 @@ def test_blocks_and_tiles_are_one_to_one(tmp_path):
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, "-o", exe, str(tmp_path / "order.cpp")], check=True)
     run = subprocess.run([exe], capture_output=True, text=True)
     assert run.stdout.strip() == "ok", run.stdout
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not installed")
+def test_no_block_takes_a_tile_outside_the_widest_outputs(tmp_path):
+    # One row of 192-column tiles (M up to 192) up to the widest output whose tiles are counted in 32 bits: a tile past the last one starts
+    # past 2^31 columns there.
+    (tmp_path / "wide.cpp").write_text("""
+#include "gemm_plan.h"
+#include <cstdio>
+#include <initializer_list>
+using namespace convrot::gemm;
+int main()
+{
+    for (int N : {2147483136, 2147483137, 2147483300, 2147483456, 1073741825, 191, 193}) {
+        const int tiles = (N + 191) / 192;
+        const TileOrder o = tile_order(1, tiles, 8);
+        int inside = 0, outside = 0;
+        for (int bid = (o.per_xcd > 9 ? o.per_xcd - 9 : 0) * kNumXcd; bid < (o.per_xcd + 9) * kNumXcd; ++bid) {
+            int tm = -1, tn = -1;
+            if (!tile_of_block(o, bid, tm, tn)) continue;
+            (starts_inside(tn, 192, N) ? inside : outside)++;
+            if (tm != 0 || starts_inside(tn, 192, N) != (tn < tiles)) { std::printf("N %d: tile %d\\n", N, tn); return 1; }
+        }
+        if (outside != o.per_xcd * kNumXcd - tiles || inside < 1) { std::printf("N %d: %d outside\\n", N, outside); return 1; }
+    }
+    std::puts("ok");
+}
+""")
+    exe = str(tmp_path / "wide")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, "-o", exe, str(tmp_path / "wide.cpp")], check=True)
+    run = subprocess.run([exe], capture_output=True, text=True)
+    assert run.stdout.strip() == "ok", run.stdout
+    # ... and such products are 192 columns wide
+    widest = [(1, 2147483300, 32), (192, 2147483137, 64), (1, 2147483456, 128)]
+    assert {p.split("x")[1] for plans in gemm_plans(widest).values() for p in plans} == {"192"}
