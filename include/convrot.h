@@ -160,8 +160,8 @@ int convrot_w4a4_gemm_dequant(const void *Xq, const float *x_scale, const void *
 
 /*
  * The whole ConvLinear4bit forward (Sec. 4.3): what convrot_rotquant_act into the workspace and then
- * convrot_w4a4_gemm_dequant give, on one stream; for a few rows (or some hundred short ones) one kernel does both, with the same bytes in Y and in
- * the workspace.
+ * convrot_w4a4_gemm_dequant give, on one stream; for a few rows (or some hundred short ones, fewer of them
+ * while the stream is captured into a graph) one kernel does both, with the same bytes in Y and in the workspace.
  *   X_bf16     DEVICE in   [M, K] bf16
  *   Wq         DEVICE in   codes [N, K] from convrot_prepare_weight (same `group`)
  *   w_scale    DEVICE in   [N]

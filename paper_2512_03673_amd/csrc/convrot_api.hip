@@ -89,6 +89,16 @@ int check_forward(const void *X_bf16, const void *Wq, const float *w_scale, cons
     return CONVROT_OK;
 }
 
+// Whether the stream is being recorded into a graph.  (The null stream cannot be.)
+bool captured(hipStream_t s)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (s == nullptr) return false;
+    if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();      // of a bad stream, which the launch will say again
+    return false;
+}
+
 // The forward of checked arguments; the codes and scales go to xq and xs.
 int launch_forward(const void *X_bf16, const void *Wq, const float *w_scale, const void *bias_bf16, int64_t M, int64_t N, int64_t K,
                    int group, int bits, void *Y_bf16, uint8_t *xq, float *xs, hipStream_t s)
@@ -96,7 +106,10 @@ int launch_forward(const void *X_bf16, const void *Wq, const float *w_scale, con
     // In the one launch blocks write Y while others still read X: an output laid over its input takes the two.
     const uintptr_t x = reinterpret_cast<uintptr_t>(X_bf16), y = reinterpret_cast<uintptr_t>(Y_bf16);
     const bool apart = x + (uintptr_t)(M * K) * 2 <= y || y + (uintptr_t)(M * N) * 2 <= x;
-    if (M > 0 && N > 0 && apart && (convrot::gemm::forward_in_one(M, N, K) || convrot::gemm::forward_in_row_tiles(M, N, K, bits)))
+    const auto in_row_tiles = [&] {
+        return convrot::gemm::forward_in_row_tiles(M, N, K, bits) && (convrot::gemm::row_tiles_in_graph(M, N, K, group) || !captured(s));
+    };
+    if (M > 0 && N > 0 && apart && (convrot::gemm::forward_in_one(M, N, K) || in_row_tiles()))
         return from_hip(convrot::launch_forward_small(X_bf16, Wq, w_scale, bias_bf16, M, N, K, group, bits, Y_bf16, xq, xs, s));
     if (convrot::launch_rotquant(X_bf16, M, K, group, bits, xq, xs, s) != hipSuccess) return CONVROT_ERR_HIP;
     return from_hip(bits == 4 ? convrot::launch_gemm_w4a4(xq, xs, Wq, w_scale, bias_bf16, M, N, K, Y_bf16, nullptr, s)

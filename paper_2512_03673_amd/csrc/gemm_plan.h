@@ -77,18 +77,35 @@ inline RowTiles forward_row_tiles(int64_t M, int64_t N, int64_t K)
     return {(int)rows, tiles * ((N + 31) / 32) <= 256 ? 32 : tiles * ((N + 63) / 64) <= 256 ? 64 : 128};
 }
 
-// Whether a forward takes that.  One launch takes 5.1 us of the calling thread where two take 8 to 9, which is what such calls cost unless a graph
-// replays them; on the device a launch less and the rotation in every block come out about even while a block's share of W is small.  us, two
-// launches / one, called one after another: M256 x N1024 x K1024 g16 8.9 / 5.1, M389 x N437 x K1056 g4 7.8 / 6.4; replayed from a graph, 4 bits: 5.5 / 5.5 and
-// 6.1 / 6.4, M77 x N3072 x K1024 g16 5.8 / 5.2, M20 x N512 x K2048 g64 5.5 / 4.9, M60 x N1000 x K1536 g256 5.35 / 5.3, M256 x N1024 x K1024 g256 5.5 / 5.8, M1500 x N256 x
-// K1024 g64 7.2 / 6.65, M512 x N1024 x K512 g256 6.15 / 6.45; 8 bits M64 x N1024 x K1024 g64 5.7 / 5.35, M17 x N8192 x K1024 g64 6.0 / 5.2, M32 x N3072 x K2048 g64 6.5 / 7.05.
-// Past the line (a block's columns times K): M250 x N1000 x K1280 g16 5.65 / 6.4, M120 x N2048 x K2048 g256 6.4 / 7.2, M60 x N1024 x K3072 g256 5.75 / 6.25, 8 bits M256 x N2048 x K1024 g256
-// 7.3 / 8.0, M48 x N1000 x K3072 g256 6.9 / 8.0, two stretches a wavefront (it spills) M77 x N3072 x K3072 g64 8.5 / 22.
+// Whether a forward that is called (not recorded into a graph) takes that.  The line is drawn by the time of such a call, which is
+// the larger of what the calling thread and what the device needs: two launches take 7.4 us of the thread or more, one 4.5 to 5.
+// us a call through the binding, two launches / one:
+//   M256 x N1024 x K1024 g16 7.4 / 6.0, M389 x N437 x K1056 g4 7.4 / 7.2, M250 x N1000 x K1152 g16 7.5 / 7.0, M8 x N9216 x K1024 7.4 / 4.95,
+//   M1 x N32768 x K1024 8.2 / 6.9, 8 bits M17 x N8192 x K1024 g64 7.5 / 5.2, M475 x N198 x K1024 g1024 7.5 / 7.5, M880 x N178 x K1024 g1024 7.5 / 7.8
+// Over 793 shapes inside (all groups, 4 and 8 bits) one takes 0.74 of the time of two in the geometric mean and 1.04 at worst (the
+// last one above; two more than 1.00).  Past the line (a block's columns times K) 0.92, and 12 of 64 are slower:
+//   M389 x N437 x K1280 g4 7.4 / 7.4, M109 x N859 x K3232 g16 7.4 / 8.8, 8 bits M379 x N704 x K1024 g1024 7.8 / 8.4
+// (Two stretches a wavefront would spill: M77 x N3072 x K3072 g64 at 8 bits 8.5 / 22.)
 inline bool forward_in_row_tiles(int64_t M, int64_t N, int64_t K, int bits)
 {
     if (M < 1 || M > 4096 || N > 32768 || K > 4096) return false;
     const RowTiles t = forward_row_tiles(M, N, K);
     return (M + t.rows - 1) / t.rows * ((N + t.columns - 1) / t.columns) <= 256 && K * t.columns * (bits / 4) <= 144 * 1024;
+}
+
+// Whether it takes that when it is recorded into a graph.  A replay costs what the device needs, and there the launch that is saved and
+// the rotation that every block repeats come out about even: it pays for tiles of a few rows, and for long rows of a cheap
+// rotation in not too many blocks.  us, replayed, two launches / one:
+//   inside   M8 x N9216 x K1024 g16 5.9 / 4.8, M1 x N32768 x K1024 g16 8.1 / 6.9, M23 x N576 x K2048 g16 6.1 / 5.5, 8 bits M17 x N8192 x K1024 g64 6.1 / 5.2
+//   outside  M256 x N1024 x K1024 g16 5.9 / 6.0, g256 5.8 / 6.1, M389 x N437 x K1056 g4 6.6 / 7.1, M250 x N1000 x K1152 g16 6.2 / 7.0,
+//            M103 x N3648 x K128 g64 4.95 / 5.8, M596 x N448 x K256 g4 5.6 / 6.5, 8 bits M475 x N198 x K1024 g1024 6.4 / 7.5; M77 x N3072 x K1024 g16 6.4 / 5.7
+// Over 793 shapes inside forward_in_row_tiles (all groups, 4 and 8 bits): the 241 inside here take 0.89 of the time of two launches in the
+// geometric mean, 1.04 at worst (three more than 1.01); the others, which are recorded as two, would take 1.02 and 1.19, 312 more than 1.01.
+inline bool row_tiles_in_graph(int64_t M, int64_t N, int64_t K, int group)
+{
+    const RowTiles t = forward_row_tiles(M, N, K);
+    const int64_t blocks = (M + t.rows - 1) / t.rows * ((N + t.columns - 1) / t.columns);
+    return t.rows <= 6 || row_items(t.rows, K) <= (t.columns <= 64 ? 10 : 8) || (K >= 1024 && group <= 256 && blocks <= 160);
 }
 
 inline int64_t tiles_of(int64_t M, int64_t N, int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn); }

@@ -213,3 +213,25 @@ def gemm_plans(shapes):
         out = subprocess.run([exe], check=True, capture_output=True, text=True, input="\n".join(" ".join(map(str, s)) for s in shapes)).stdout.split()
     assert len(out) == 2 * len(shapes)
     return {s: (PLANS[int(out[2 * i])], PLANS[int(out[2 * i + 1])]) for i, s in enumerate(shapes)}
+
+
+def forward_rules(shapes):
+    """{(M, N, K): how a forward runs} by the same header: `one`, the one launch of a few rows; `row_tiles4` / `row_tiles8`, that of tiles of rows,
+    in a graph only if `in_graph` (at groups up to 256; `in_graph1024`); two launches otherwise"""
+    shapes = list(shapes)
+    with tempfile.TemporaryDirectory() as d:
+        src, exe = os.path.join(d, "rule.cpp"), os.path.join(d, "rule")
+        with open(src, "w") as f:
+            f.write('#include "gemm_plan.h"\n#include <cstdio>\nusing namespace convrot::gemm;\nint main() {\n  long M, N, K;\n  while (std::scanf("%ld %ld %ld", &M, &N, &K) == 3)\n'
+                    '    std::printf("%d %d %d %d %d\\n", forward_in_one(M, N, K), forward_in_row_tiles(M, N, K, 4), forward_in_row_tiles(M, N, K, 8),\n'
+                    '                K <= 4096 && row_tiles_in_graph(M, N, K, 256), K <= 4096 && row_tiles_in_graph(M, N, K, 1024));\n}\n')
+        subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, "-o", exe, src], check=True)
+        out = subprocess.run([exe], check=True, capture_output=True, text=True, input="\n".join(" ".join(map(str, s)) for s in shapes)).stdout.split()
+    assert len(out) == 5 * len(shapes)
+    return {s: dict(zip(("one", "row_tiles4", "row_tiles8", "in_graph", "in_graph1024"), (o == "1" for o in out[5 * i:5 * i + 5]))) for i, s in enumerate(shapes)}
+
+
+def two_launches(shapes, bits):
+    """The shapes whose forward takes two launches, called or captured."""
+    rules = forward_rules(shapes)
+    return [s for s in shapes if not rules[s]["one"] and not rules[s][f"row_tiles{bits}"]]

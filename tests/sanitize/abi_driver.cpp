@@ -124,6 +124,16 @@ int main()
     for (int64_t d : {8 * 1024 * 2, -(8 * 64 * 2)})
         CHECK(convlinear8bit_forward(X, A, F, nullptr, 8, 64, 1024, 16, X + d, A, convrot_workspace_bytes8(8, 1024), nullptr) == CONVROT_OK);
     CHECK(seen == "forward_small forward_small ");
+    // rows in tiles are one launch too, apart from the input and not laid over it; past both rules there are two either way
+    seen.clear();
+    CHECK(convlinear4bit_forward(A, A, F, nullptr, 400, 64, 1024, 16, Y, A, convrot_workspace_bytes(400, 1024), nullptr) == CONVROT_OK);
+    CHECK(convlinear8bit_forward(A, A, F, nullptr, 400, 64, 1024, 16, Y, A, convrot_workspace_bytes8(400, 1024), nullptr) == CONVROT_OK);
+    CHECK(convlinear4bit_forward(A, A, F, nullptr, 400, 64, 1024, 16, X + 400 * 1024 * 2 - 16, A, convrot_workspace_bytes(400, 1024), nullptr) == CONVROT_OK);
+    CHECK(seen == "forward_small forward_small rotquant gemm_w4a4 ");
+    seen.clear();
+    CHECK(convlinear4bit_forward(A, A, F, nullptr, 1200, 1000, 1024, 16, Y, A, convrot_workspace_bytes(1200, 1024), nullptr) == CONVROT_OK);
+    CHECK(convlinear8bit_forward(A, A, F, nullptr, 1200, 1000, 1024, 16, Y, A, convrot_workspace_bytes8(1200, 1024), nullptr) == CONVROT_OK);
+    CHECK(seen == "rotquant gemm_w4a4 rotquant gemm_w8a8 ");
     launches_seen = nullptr;
     std::puts("C ABI host side under sanitizers: ok");
     return 0;
