@@ -314,15 +314,28 @@ hipError_t launch_rows(const void *X, int64_t rows, int K, void *Xq, float *scal
 // Wavefronts of `rows` rows, 1024 elements each.
 inline int64_t row_waves(int64_t rows, int64_t K) { return rows * ((K + 1023) / 1024); }
 
-// The split of a row, by its length.  A few rows (up to 12 wavefronts a compute unit, rows of up to 12288 elements) are one pass of each wavefront through load,
-// arithmetic and store: a row a block, 1024 elements a wavefront (us, as more rows are split / so: [77, 3072] g16 3.1 / 2.8, [512, 2048] g256 3.75 / 3.5,
-// [256, 12288] g256 4.7 / 3.9, [1000, 3072] 3.7 / 3.45; past the line [1000, 12288] 7.6 / 8.9, [2000, 4096] at 8 bits 9.0 / 9.5).  For more rows: enough wavefronts first: with U = 1 twice as many that do half the work each, and one or two sets
-// of each; rows side by side in a wavefront as long as their digits across lanes fit (g / 64 columns), so that a store
-// instruction finds more of an output block's 64- and 32-byte row pieces adjacent, and from 2e7 elements on (4 bits) lanes that store whole chunks
-// ([12288, 3072] g16 18.0 / 17.6, g256 19.4 / 18.8, [30000, 3072] g256 42.8 / 38.7; [4608, 3072] g256 8.7 / 8.9).  Past 4096 elements a block is one row of whole
-// chunks, as few wavefronts as hold it once.  us, cold, against a kernel of 16 consecutive elements a lane with digit 2 by DPP:
+// From how many elements on lanes hold whole chunks instead of units (4 bits, rows of 1025 to 4096 elements).  us, units / whole chunks:
+//   g256                 [3906, 3072] 8.3 / 8.7, [6510, 3072] 12.4 / 12.2, [5859, 4096] 14.0 / 13.5, [9765, 4096] 21.1 / 19.8
+//   g16                  [3906, 3072] 7.95 / 8.3, [6510, 3072] 11.7 / 11.6, [9765, 2048] 11.7 / 11.6, [17090, 2048] 17.0 / 16.8
+//   g16, half-full sets  [15782, 1280] 11.5 / 12.0, [21876, 1280] 14.35 / 14.7, [26563, 1280] 16.7 / 16.8
+//   g16, four wavefronts [4932, 4096] 10.9 / 11.4, [6836, 4096] 14.0 / 14.4, [8301, 4096] 16.5 / 16.5, [9765, 4096] 18.9 / 18.7
+template <int G>
+constexpr int64_t whole_chunks_from(int K) { return G <= 16 && (K <= 1536 || K > 3072) ? 34000000 : 20000000; }
+
+// The split of a row, by its length and the number of rows.
+//
+// A few rows (up to 12 wavefronts a compute unit, rows of 1025 to 12288 elements) are one pass of each wavefront through load, arithmetic
+// and store: a row a block, 1024 elements a wavefront.  (Five, seven and nine to eleven stretches take 6, 8 and 12 wavefronts.)  us, as more rows are
+// split / so: [77, 3072] g16 3.1 / 2.8, [512, 2048] g256 3.75 / 3.5, [256, 12288] g256 4.7 / 3.9, [1000, 3072] 3.7 / 3.45.  Over 264
+// inputs of 6 to 18 wavefronts a unit 8 % less on average, up to the line 9 % (1 % more at most), past it, at 14 and 18, 7 % (2 % more at most); far past it
+// [1000, 12288], 47 a unit, 7.6 / 8.9.
+//
+// For more rows, enough wavefronts first: with U = 1 twice as many that do half the work each, and one or two sets of each; rows side by side
+// in a wavefront as long as their digits across lanes fit (g / 64 columns), so that a store instruction finds more of an output block's 64- and
+// 32-byte row pieces adjacent; from some 2e7 elements on lanes that store whole chunks (whole_chunks_from).  Past 4096 elements a block is one
+// row of whole chunks, as few wavefronts as hold it once.  us, cold, against a kernel of 16 consecutive elements a lane with digit 2 by DPP:
 //   [8000, 256] g64 5.2 -> 3.9, [8000, 512] g64 5.6 -> 4.2, [12288, 1024] g256 9.6 -> 9.0, [4608, 3072] g16 8.9 -> 8.5, g256 11.2 -> 9.8,
-//   [12288, 3072] g256 23.0 -> 22.1 (weights prepared in turn: 21.3 -> 19.9 on one box, 21.8 -> 21.8 on another), [4608, 4096] g64 13.5 -> 10.5, [4608, 12288] g16 28.4 -> 27.9, [4608, 15360] g1024 43.8 -> 40.5,
+//   [12288, 3072] g256 23.0 -> 22.1 (now 18.8), [4608, 4096] g64 13.5 -> 10.5, [4608, 12288] g16 28.4 -> 27.9, [4608, 15360] g1024 43.8 -> 40.5,
 //   8 bits [16896, 12288] g16 121 -> 103
 // and the other splits at those sizes: U = 2 [8000, 512] 5.0, [4608, 1024] g256 5.7 against 5.0; one row a wavefront [4608, 3072] g16 8.9;
 // two rows a block [4608, 12288] 28.2 to 30.5, four rows 36.3; half the wavefronts with two sets each 28.1.
@@ -346,7 +359,7 @@ hipError_t launch_g(const void *X, int64_t rows, int K, void *Xq, float *scale, 
         }
     }
     if constexpr (BITS == 4) {
-        if (K <= 4096 && rows * K >= 20000000) {
+        if (K <= 4096 && rows * K >= whole_chunks_from<G>(K)) {
             if (K <= 2048) return CONVROT_ROWS(2, 2, 2, 1);
             if (K <= 3072) return CONVROT_ROWS(2, 2, 3, 1);
             return CONVROT_ROWS(2, 2, 4, 1);

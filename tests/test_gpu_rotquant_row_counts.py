@@ -1,6 +1,7 @@
 """How a row is split over lanes and wavefronts depends on the number of rows too (few rows, many, very many): every split gives
 the codes, scales and zero padding of the few-row one, byte for byte, which test_gpu_rotquant_splits.py compares with the oracle.  Row
-counts are the first past each line of the choice (12 wavefronts of 1024 elements a compute unit; 2e7 elements at 4 bits)."""
+counts are the first past each line of the choice (12 wavefronts of 1024 elements a compute unit; at 4 bits 2e7 elements, or 3.4e7 of
+groups up to 16 in rows of up to 1536 or of more than 3072)."""
 import pytest
 import torch
 
@@ -18,7 +19,8 @@ def test_row_counts(K, bits):
     for g in (4, 16, 64, 256, 1024):
         k = -(-K // max(g, 32)) * max(g, 32)
         few = 12 * 256 // -(-k // 1024)
-        for M in [few, few + 1] + ([-(-20_000_000 // k) - 1, -(-20_000_000 // k)] if k <= 4096 and g in (16, 256, 1024) else []):
+        lines = [20_000_000] + ([34_000_000] if bits == 4 and g == 16 and (k <= 1536 or k > 3072) else [])
+        for M in [few, few + 1] + ([-(-n // k) - less for n in lines for less in (1, 0)] if k <= 4096 and g in (16, 256, 1024) else []):
             print(f"bits={bits} M={M} K={k} g={g}", flush=True)
             x = torch.randn(M, k, generator=gen, device="cuda")
             x[:, ::97] *= 30.0
