@@ -10,13 +10,14 @@ import pytest
 import torch
 
 import oracle
-from gpu_util import bf16_to_host_bits, check_output, to_dev_bf16
+from gpu_util import bf16_to_host_bits, check_output, to_dev_bf16, two_launches
 from paper_2512_03673_amd import workloads as wl
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2512_03673_amd", "csrc")
 SHAPES = [(1, 1, 32), (8, 1024, 1024), (1, 33, 96), (3, 77, 160), (8, 300, 1024), (8, 4097, 672), (7, 257, 256), (2, 4096, 4096), (4, 4096, 4096),
           (1, 4095, 16384), (1, 9216, 3072), (4, 16384, 64), (3, 1000, 5120), (5, 8192, 1024), (1, 8192, 15360)]
-TWO_LAUNCHES = [(9, 64, 256), (8, 16384, 64), (1, 16385, 64), (5, 64, 4096), (1, 64, 17408), (1, 8193, 15360), (64, 3072, 3072), (0, 64, 64)]
+# past that one launch: in tiles of rows, mostly (test_forward_row_tiles.py), and in two launches
+NOT_SO = [(9, 64, 256), (8, 16384, 64), (1, 16385, 64), (5, 64, 4096), (1, 64, 17408), (1, 8193, 15360), (64, 3072, 3072), (0, 64, 64)]
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not installed")
@@ -26,14 +27,16 @@ def test_which_shapes_take_one_launch(tmp_path):
                    '    std::printf("%d\\n", (int)convrot::gemm::forward_in_one(atol(v[i]), atol(v[i + 1]), atol(v[i + 2])));\n}\n')
     exe = str(tmp_path / "rule")
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", CSRC, "-o", exe, str(src)], check=True)
-    shapes = SHAPES + TWO_LAUNCHES[:-1] + [(2 ** 31 - 1, 2 ** 31 - 1, 65536)]
+    shapes = SHAPES + NOT_SO[:-1] + [(2 ** 31 - 1, 2 ** 31 - 1, 65536)]
     out = subprocess.run([exe] + [str(d) for s in shapes for d in s], check=True, capture_output=True, text=True).stdout.split()
     assert [int(o) for o in out] == [int(s in SHAPES) for s in shapes]
+    two = [(1, 64, 17408), (1, 8193, 15360), (64, 3072, 3072)]
+    assert two_launches(NOT_SO[:-1], 4) == two and two_launches(NOT_SO[:-1], 8) == [(5, 64, 4096)] + two
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("bits", (4, 8))
-@pytest.mark.parametrize("M,N,K", SHAPES + TWO_LAUNCHES[:2])
+@pytest.mark.parametrize("M,N,K", SHAPES + NOT_SO[:2] + [(1, 64, 17408), (64, 3072, 3072)])
 def test_one_launch_equals_two(M, N, K, bits):
     from paper_2512_03673_amd import binding as cr
     eight = "8" if bits == 8 else ""

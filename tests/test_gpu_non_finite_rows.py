@@ -1,7 +1,9 @@
 """A NaN or an infinity in a row of X or W leaves every other row as it would be without it (include/convrot.h): codes and scales of
-rotate+quantise in each split of a row, outputs of the one-launch and of the two-launch forward, bit for bit."""
+rotate+quantise in each split of a row, of few rows and of many, outputs of the one-launch forwards and of the two-launch one, bit for bit."""
 import pytest
 import torch
+
+from gpu_util import forward_rules, two_launches
 
 INF, NAN = float("inf"), float("nan")
 GROUPS = (4, 16, 64, 256, 1024)
@@ -56,7 +58,41 @@ def test_rotquant(K, bits):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("bits", (4, 8))
-@pytest.mark.parametrize("M,N,K", [(3, 100, 1024), (8, 260, 1024), (4, 5000, 3072), (3, 300, 5120), (20, 200, 3072), (300, 390, 1024)])
+@pytest.mark.parametrize("K", (1280, 2048, 3072, 4096, 5120, 8192, 12288))
+def test_rotquant_of_many_rows(K, bits):
+    """Past the lines up to which a row is a block of its own (csrc/rotquant.hip): two rows side by side in a wavefront up to K = 4096, in units
+    and (4 bits, from some 2e7 elements on) in whole chunks, single rows of whole chunks beyond.  The first and the last row, each of another half
+    of its pair, are spoiled."""
+    from paper_2512_03673_amd import binding as cr
+    size, rotquant = (cr.packed_bytes, cr.convrot_rotquant_act) if bits == 4 else (cr.packed_bytes8, cr.convrot_rotquant_act8)
+    for M in [12 * 256 // -(-K // 1024) + 1] + ([-(-20_000_000 // K), -(-34_000_000 // K)] if bits == 4 and K <= 4096 else []):
+        M += M % 2
+        x = torch.randn(M, K, generator=torch.Generator(device="cuda").manual_seed(K + bits), device="cuda").to(torch.bfloat16)
+        bad, keep = spoil(x)
+        assert not keep[0] and keep[1] and keep[M - 2] and not keep[M - 1]
+        for g in GROUPS:
+            if K % g:
+                continue
+            print(f"bits={bits} M={M} K={K} g={g}", flush=True)
+            q, s = zip(*(rotquant(v, g, Xq=torch.full((size(M, K),), 0x5A, dtype=torch.uint8, device="cuda")) for v in (x, bad)))
+            torch.cuda.synchronize()
+            assert torch.equal(s[0][keep], s[1][keep]) and same_rows(q[0], q[1], keep, bits), g
+
+
+FORWARDS = [(3, 100, 1024), (8, 260, 1024), (4, 5000, 3072), (3, 300, 5120), (20, 200, 3072), (300, 390, 1024)]
+TWO_LAUNCHES = [(20, 5000, 3072), (300, 1100, 2048), (1200, 500, 1024)]
+
+
+def test_forwards_take_each_way():
+    for bits in (4, 8):
+        rules = forward_rules(FORWARDS)
+        assert any(r["one"] for r in rules.values()) and any(r[f"row_tiles{bits}"] for r in rules.values())
+        assert two_launches(TWO_LAUNCHES, bits) == TWO_LAUNCHES
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bits", (4, 8))
+@pytest.mark.parametrize("M,N,K", FORWARDS + TWO_LAUNCHES)
 def test_forward(M, N, K, bits):
     from paper_2512_03673_amd import binding as cr
     prepare, forward = (cr.convrot_prepare_weight, cr.convlinear4bit_forward) if bits == 4 else (cr.convrot_prepare_weight8, cr.convlinear8bit_forward)

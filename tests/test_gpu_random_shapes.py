@@ -1,5 +1,6 @@
 """GPU parity on seeded random small shapes: ragged M and N around the 192-row tile edges, every K % 32 == 0
-residue of the 128-code stage, every group size that divides K, with and without a bias.  CONVROT_FUZZ_CASES in the
+residue of the 128-code stage, every group size that divides K, with and without a bias.  Nearly all of them are one launch as a forward, so
+the product is also taken by itself, and gives the same bits.  CONVROT_FUZZ_CASES in the
 environment raises the number of cases (default 24 four-bit and 12 eight-bit ones) for a longer run."""
 import os
 
@@ -36,7 +37,9 @@ def test_forward_on_random_shapes(cr):
         bias = wl.make_bias(spec) if with_bias else None
         wq, ws = cr.convrot_prepare_weight(to_dev_bf16(w), g)
         xq, xs = cr.convrot_rotquant_act(to_dev_bf16(x), g)
-        y = cr.convlinear4bit_forward(to_dev_bf16(x), wq, ws, g, bias=None if bias is None else to_dev_bf16(bias))
+        b = None if bias is None else to_dev_bf16(bias)
+        y = cr.convlinear4bit_forward(to_dev_bf16(x), wq, ws, g, bias=b)
+        y2 = cr.convrot_w4a4_gemm_dequant(xq, xs, wq, ws, K, bias=b)
         torch.cuda.synchronize()
         qxo, sxo = oracle.rotquant(x, g)
         qwo, swo = oracle.rotquant(w, g)
@@ -45,7 +48,10 @@ def test_forward_on_random_shapes(cr):
         acc = cr.convrot_w4a4_gemm_i32(xq, wq, M, N, K)
         torch.cuda.synchronize()
         assert np.array_equal(acc.cpu().numpy(), oracle.int_gemm(unpack_host(xq, M, K), unpack_host(wq, N, K))), f"case {case}"
-        check_output(bf16_to_host_bits(y), oracle.convlinear4bit(x, w, g, bias=bias), f"case {case}")
+        yo = oracle.convlinear4bit(x, w, g, bias=bias)
+        check_output(bf16_to_host_bits(y), yo, f"case {case}")
+        check_output(bf16_to_host_bits(y2), yo, f"case {case}")
+        assert torch.equal(y.view(torch.int16), y2.view(torch.int16)), f"case {case}"
 
 
 def test_forward8_on_random_shapes(cr):
@@ -63,7 +69,9 @@ def test_forward8_on_random_shapes(cr):
         bias = wl.make_bias(spec) if with_bias else None
         wq, ws = cr.convrot_prepare_weight8(to_dev_bf16(w), g)
         xq, xs = cr.convrot_rotquant_act8(to_dev_bf16(x), g)
-        y = cr.convlinear8bit_forward(to_dev_bf16(x), wq, ws, g, bias=None if bias is None else to_dev_bf16(bias))
+        b = None if bias is None else to_dev_bf16(bias)
+        y = cr.convlinear8bit_forward(to_dev_bf16(x), wq, ws, g, bias=b)
+        y2 = cr.convrot_w8a8_gemm_dequant(xq, xs, wq, ws, K, bias=b)
         acc = cr.convrot_w8a8_gemm_i32(xq, wq, M, N, K)
         torch.cuda.synchronize()
         cx, cw = unpack_host8(xq, M, K), unpack_host8(wq, N, K)
@@ -72,4 +80,7 @@ def test_forward8_on_random_shapes(cr):
             d = np.abs(c.astype(np.int16) - qo.astype(np.int16))
             assert d.max() <= 1 and (d == 0).mean() >= 0.9999, f"case {case} {what}: {int((d != 0).sum())} codes differ, max {int(d.max())}"
         assert np.array_equal(acc.cpu().numpy(), oracle.int_gemm(cx, cw)), f"case {case}"
-        check_output(bf16_to_host_bits(y), oracle.convlinear(x, w, g, bias=bias, qmax=127), f"case {case}")
+        yo = oracle.convlinear(x, w, g, bias=bias, qmax=127)
+        check_output(bf16_to_host_bits(y), yo, f"case {case}")
+        check_output(bf16_to_host_bits(y2), yo, f"case {case}")
+        assert torch.equal(y.view(torch.int16), y2.view(torch.int16)), f"case {case}"

@@ -13,7 +13,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_util import bf16_to_host_bits, check_output, gemm_plans, to_dev_bf16
+from gpu_util import bf16_to_host_bits, check_output, gemm_plans, to_dev_bf16, two_launches
 from paper_2512_03673_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -32,11 +32,21 @@ def layer(M, K, N, g, seed):
     return spec, x, w
 
 
-def test_forward_runs_on_the_given_stream(cr):
+# a forward of one launch as it is called, and one of two whatever the code width
+ONE, TWO = (300, 1024, 520), (1200, 1024, 1000)
+
+
+def test_one_and_two_launches():
+    shapes = [(M, N, K) for M, K, N in (ONE, TWO)]
+    assert two_launches(shapes, 4) == two_launches(shapes, 8) == shapes[1:]
+
+
+@pytest.mark.parametrize("M,K,N", (ONE, TWO))
+def test_forward_runs_on_the_given_stream(cr, M, K, N):
     # X is produced on a side stream by a long chain of kernels; the forward is queued behind it on the same
     # stream.  Launched anywhere else it would read X before the chain has written it (torch's side streams
     # do not synchronise with the default stream).
-    spec, x, w = layer(300, 1024, 520, 16, 11)
+    spec, x, w = layer(M, K, N, 16, 11)
     X = to_dev_bf16(x)
     wq, ws = cr.convrot_prepare_weight(to_dev_bf16(w), 16)
     y_ref = cr.convlinear4bit_forward(X, wq, ws, 16)
@@ -83,9 +93,10 @@ def test_calls_on_two_streams_do_not_disturb_each_other(cr):
         assert torch.equal(Y, y_ref)
 
 
+@pytest.mark.parametrize("M,K,N", ((520, 1024, 300), TWO))
 @pytest.mark.parametrize("bits", (4, 8))
-def test_forward_in_a_hip_graph(cr, bits):
-    spec, x, w = layer(520, 1024, 300, 16, 31 + bits)
+def test_forward_in_a_hip_graph(cr, bits, M, K, N):
+    spec, x, w = layer(M, K, N, 16, 31 + bits)
     prep, fwd, wsbytes = ((cr.convrot_prepare_weight, cr.convlinear4bit_forward, cr.workspace_bytes) if bits == 4 else
                           (cr.convrot_prepare_weight8, cr.convlinear8bit_forward, cr.workspace_bytes8))
     X = to_dev_bf16(x)

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_util import bf16_to_host_bits, check_output, to_dev_bf16
+from gpu_util import bf16_to_host_bits, check_output, to_dev_bf16, two_launches
 from paper_2512_03673_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -72,8 +72,11 @@ def test_noalloc_limit_and_errors(cr):
     cr.init()                                   # idempotent
 
 
-def test_noalloc_in_a_hip_graph(cr):
-    spec, x, w, X, wq, ws, bias = make(cr, 520, 1024, 300, 16, 77, True)
+@pytest.mark.parametrize("M,K,N", ((520, 1024, 300), (1200, 1024, 1000)))
+def test_noalloc_in_a_hip_graph(cr, M, K, N):
+    # (the larger one is two launches, the second of which reads the array)
+    assert M < 1000 or two_launches([(M, N, K)], 4)
+    spec, x, w, X, wq, ws, bias = make(cr, M, K, N, 16, 77, True)
     b = to_dev_bf16(bias)
     Y = torch.zeros((spec.M, spec.N), dtype=torch.bfloat16, device="cuda")
     cr.init()                                   # the array's address is looked up outside the capture
