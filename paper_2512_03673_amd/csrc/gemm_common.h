@@ -1,5 +1,5 @@
 // Shared pieces of the GEMM kernels of libconvrot, 4-bit and 8-bit (LDS swizzle, LDS-direct loads, which the
-// rotate+quantise kernel uses too, tile order).  gemm_tiled.h and gemm_small.h describe the method.
+// rotate+quantise kernel uses too, stores of Y).  gemm_tiled.h and gemm_small.h describe the method, gemm_plan.h the tile order.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

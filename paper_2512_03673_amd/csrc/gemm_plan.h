@@ -18,7 +18,14 @@
 // The fits are of kernels whose output went through the caches.  With every output past them the tiles' times fell together: over
 // 150 shapes (4 bits) and 130 (8 bits) of 1e9 to 6.4e11 products with operands that change from launch to launch the
 // tile taken costs 1.3 and 1.9 % more than the best, with constants fitted again to these 1.5 and 1.7 %.  (Tiles against each other;
-// the stores themselves: store_kind.  The 8-bit 128 x 192 tile is predicted with its three stages also where deep_ring gives it four.)
+// the stores themselves: store_kind.)
+//
+// No constant has been fitted again since the way to the first MFMA was halved (gemm_tiled.h) or since deep_ring gives the 4-bit 64 x 64
+// tile four stages; the 8-bit 128 x 192 tile is predicted with its three as well.  What that costs, every tile timed against the one
+// taken with operands that change: 25 products of one to four rounds (4 bits, M 2000 ... 6000, N 3072 ... 12288, K 3072) 0.5 % on average, 4 % at
+// most (M6000 x N6144, 61.1 / 58.6 with 192 x 192); 30 with deep 64 x 64 tiles among the candidates 0.1 and 1.3 %; 45 and 40 drawn ones at 4 and 8 bits
+// (M 16 ... 9000, N 64 ... 12288, K 64 ... 15360) 2.3 and 2.7 %, most of it 128 x 128 tiles of a few stages: M263 x N6954 x K384 6.3 / 4.5 with
+// 64 x 64, 8 bits M7388 x N370 x K416 7.6 / 5.6.
 #pragma once
 #include <stdint.h>
 
@@ -58,7 +65,9 @@ inline int forward_in_one_columns(int64_t N) { return N <= 16 * 256 ? 16 : N <= 
 // (M 1-16, N 64-40000, K 64-15360) the line drawn here gives 0.5 to 5 us, us two / one: M1 x N9216 x K3072 10.8 / 7.3,
 // M1 x N3072 x K12288 12.7 / 9.0, M4 x N3072 x K3072 8.7 / 6.1, M8 x N608 x K1024 6.3 / 5.2, M1 x N394 x K128 5.3 / 3.8; past it
 // M12 x N9068 x K256 5.6 / 8.7, M14 x N1933 x K1088 6.0 / 7.0, M2 x N18018 x K192 5.8 / 6.9.  (All of blocks of 16 or 32 columns, and the line still counts
-// these: it has not been drawn again for N of 8193 and more, whose blocks are fewer and wider now.  M8 x N9216 x K1024 takes two launches by it.)
+// these: it has not been drawn again for N of 8193 and more, whose blocks are fewer and wider now.)  What is past it is asked for by
+// forward_in_row_tiles, whose sixteen wavefronts take these three in one launch too, 7.4 / 4.75, 7.4 / 5.1 and 7.4 / 4.7 as called, and
+// M8 x N9216 x K1024, 7.4 / 4.95.
 inline bool forward_in_one(int64_t M, int64_t N, int64_t K)
 {
     const int64_t items = row_items(M, K), columns = N <= 4096 ? 16 : 32, blocks = (N + columns - 1) / columns;
@@ -118,7 +127,7 @@ inline int64_t tiles_of(int64_t M, int64_t N, int tm, int tn) { return ((M + tm 
 // become three, M512 x N3072 x K3072 8.2 / 8.45).  (No gain: 192 x 192 at 8 bits, 128 x 128 at 4 bits, 256 x 128 on eight wavefronts.)
 inline bool deep_ring(int64_t tiles, int64_t stages) { return tiles <= 256 && stages >= 16; }
 
-// Tile rows of a band of 256 x 256 tiles (tile_of_block, gemm_common.h), of which an XCD runs 32 at a time: 4 x 8 and 6 x 5.3 share
+// Tile rows of a band of 256 x 256 tiles (tile_of_block), of which an XCD runs 32 at a time: 4 x 8 and 6 x 5.3 share
 // operands about alike, and a last band of one to three rows shares little.  So four where they come out even or leave more rows over than
 // six do, else six.  us, bands of 4 / 6: 66 tile rows, M16896 x N3072 x K12288, 268 / 256 (8: 277); 18, M4608 x N12288 x K3072, 78.8 / 76.7 (8: 77.6);
 // 32, M8192 x N8192 x K4096, 107.8 / 110.2 (8: 112.2); 19, M4864 x N9152 x K12288, 199 / 217.  Over 23 shapes of 7, 19, 31, 43 and 55

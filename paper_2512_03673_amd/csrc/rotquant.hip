@@ -69,11 +69,16 @@ struct Split {
     static_assert((U == 1 || U == 2) && WPR <= 16 && S <= 4, "split");
 };
 
-// Whether codes are written through the L2: where a store instruction holds two rows' pieces side by side (128 bytes of an output block's A plane or
-// of two panel rows).  Left to the L2 they go to memory when the kernel ends, all at once and with nothing to do meanwhile.  us, left / written
-// through: [4608, 3072] g256 9.8 / 8.7, [12288, 3072] g256 21.4 / 19.4, 8 bits [9000, 2048] g256 14.1 / 12.4, over 63 shapes of 3000 to 30000 rows of 1280 to
-// 4096 elements 4.4 % less; with the GEMM that reads them M4608 x N12288 x K3072 at 8 bits 159.9 / 158.7.  Not the pieces of single rows, which then go to memory by themselves ([8000, 1024]
-// 5.9 / 6.5, [16896, 12288] 92 / 136), nor, at g <= 16 and 4 bits, rows of four wavefronts of U = 1 ([3000, 4096] 7.4 / 7.6).
+// Whether codes are written through the L2: where a store instruction holds two rows' pieces side by side (128 bytes of an output block's A
+// plane or of two panel rows).  Left to the L2 they go to memory when the kernel ends, all at once and with nothing to do meanwhile: of the 83 000 lines of
+// [4608, 3072] 82 800 are written back then, written through 144, and the writes to memory are the same (TCC_ALL_TC_OP_WB_WRITEBACK,
+// TCC_EA0_WRREQ).  us, left / written through:
+//   [4608, 3072] g256 9.8 / 8.7, [12288, 3072] g256 21.4 / 19.4, 8 bits [9000, 2048] g256 14.1 / 12.4; over 63 shapes of 3000 to 30000
+//   rows of 1280 to 4096 elements 4.4 % less; with the GEMM that reads them M4608 x N12288 x K3072 at 8 bits 159.9 / 158.7
+//   4 bits, g <= 16, where there is less arithmetic to do meanwhile: [12501, 1280] g16 10.9 / 10.05, [9864, 2048] g16 11.3 / 11.4, [6576, 3072]
+//   g16 11.3 / 11.6, over 24 inputs of 2048 and 3072 elements 0.9 % more, eleven whole forwards 0.4 % less
+// Not the pieces of single rows, which then go to memory by themselves ([8000, 1024] 5.9 / 6.5, [16896, 12288] 92 / 136), nor, at g <= 16 and
+// 4 bits, rows of four wavefronts of U = 1 ([3000, 4096] 7.4 / 7.6).
 template <int G, int BITS, int U, int RPW, int WPR>
 constexpr bool kThrough = RPW >= 2 && WPR >= 2 && (BITS == 8 || G >= 64 || U == 2 || WPR <= 3);
 
