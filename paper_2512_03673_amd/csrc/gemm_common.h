@@ -6,22 +6,18 @@
 
 #include <type_traits>
 
+#include "fragment_rows.h"
 #include "gemm_plan.h"
 
 namespace convrot {
 namespace gemm {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 
-constexpr int kRowBytes = 64;                 // bytes of K per row per stage: 128 4-bit codes or 64 8-bit codes
-constexpr int kSubSteps = kRowBytes / 32;     // MFMA K-steps of 32 bytes per row (one ds_read_b128 per fragment) per stage
-
-// Which of the four 16-byte slots of its LDS row a piece lands in: slot = piece ^ swz(row).
-// For any 8 consecutive rows the (row & 1, slot) pairs are distinct (32 banks), and for any 16
-// consecutive rows the (row & 3, slot) pairs are distinct (64 banks).
+// Which of the four 16-byte slots of its LDS row a piece of row 0 ... 15 of a panel lands in: slot = piece ^ swz(row) (fragment_rows.h).
 __device__ __forceinline__ int swz(int row) { return ((row >> 1) ^ (row >> 3)) & 3; }
 
 template <int N>

@@ -24,7 +24,6 @@ namespace gemm {
 
 typedef int v2i __attribute__((ext_vector_type(2)));
 typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v4f __attribute__((ext_vector_type(4)));
 
 struct Small4 {   // stage of 128 codes: half of a 3 KB block (e2m3_layout.h); quarter = one chunk of 32 codes
     struct Frag { v4i a; v2i b; };

@@ -8,8 +8,9 @@
 //
 // Data movement.  A block of WGM x WGN wavefronts owns a TM x TN tile of the output.  A K stage of the tile's operand
 // rows is kPieces contiguous kilobytes in memory, copied by LDS-direct loads (dealt evenly to the wavefronts)
-// into a ring of NS stage buffers.  A stage is two K steps; a wavefront reads the fragments of a step (32 rows each)
-// one step ahead, into the other half of a double-buffered register set, so that no MFMA waits for LDS.
+// into a ring of NS stage buffers.  A fragment is 16 rows of a whole stage and one operand of an MFMA.  A stage is two steps, in which a wavefront
+// multiplies the first and the second half of its X fragments by all of its W fragments; it holds one stage's fragments and reads each of the next one's
+// in the slots behind the last use of the one whose registers it takes, so that no MFMA waits for LDS.
 //
 // The block meets once per stage, between its two steps: by then every wavefront has read the whole of stage s into
 // registers, so the buffer can take stage s + NS, and everybody's share of stage s + 1 has landed.  With NS = 2 the
@@ -28,9 +29,13 @@
 // A wavefront issues in order, so every memory instruction gets an MFMA slot of its own (scheduling barriers pin the
 // order) instead of queueing up in a burst.
 //
-// The MFMA's row operand is the W tile and its column operand the X tile, so that a lane ends up with four
-// consecutive n for one m; the epilogue scales, rounds to bf16, transposes through LDS and writes 16 bytes per lane,
-// whole contiguous rows of the wavefront's tile, in or past the caches (store_kind).
+// MFMAs are 16 x 16, 128 codes deep at 4 bits and 64 at 8, with the X fragment as the row operand: of the forms that the chip runs at one rate this
+// takes the least power, and power is what the large products are bound by.  A register-only loop on codes like a layer's, POP/s, 32 x 32 with W / X as the row
+// operand : 16 x 16 with W / X: 4 bits, X of g = 16 (one code in seven not zero) 7.6 / 7.2 : 8.1 / 8.6, g = 64 6.7 / 6.6 : 7.4 / 7.5, g = 1024 6.4 / 6.4 : 7.2 / 7.2; 8 bits
+// 3.5 : 4.2; zeros 9.7 : 9.6 and 4.9 : 4.8.  The GEMM alone, us, 32 x 32 with W / 16 x 16 with X, operands changing: 4 bits M4608 x N12288 x K3072 77.3 / 74.7,
+// M16896 x N3072 x K12288 254 / 233, 8 bits M4608 x N12288 x K3072 136.3 / 127.4.  A lane of the result has four rows of one column; pairs of fragments share
+// their rows so that it has two neighbouring columns of each (fragment_rows.h), and the epilogue scales, rounds to bf16, transposes through LDS and
+// writes 16 bytes per lane, whole contiguous rows of the wavefront's tile, in or past the caches (store_kind).
 //
 // What bounds the large tiles is power: the chip runs as many operand bytes and multiply-adds a second as its clock lets it, and
 // the clock falls with them.  So the tile that moves the fewest bytes a product wins where its rounds are not too uneven: 256 x 256
@@ -59,10 +64,9 @@ struct Tile {
     static constexpr int NW = WGM * WGN, kThreads = 64 * NW;
     static constexpr int WM = XF * 32, WN = WF * 32;          // wavefront tile
     static constexpr int TM = WGM * WM, TN = WGN * WN, kRows = TM + TN;
-    static constexpr int NF = XF + WF;                        // fragments per wavefront and step
-    static constexpr int kMfmas = XF * WF;                    // slots of a step
-    static constexpr int kEpiPitch = WN * 2 + 16;             // bf16 row of the wavefront tile + pad
-    static constexpr int kEpiBytes = NW * 32 * kEpiPitch;
+    static constexpr int kXs = 2 * XF, kWs = 2 * WF;          // fragments (16 rows) of a stage per wavefront
+    static constexpr int kMfmas = XF * kWs;                   // slots of a step: half of the X fragments with every W fragment
+    static constexpr int kEpiBytes = NW * 32 * WN * 2;        // 32 rows of every wavefront's tile in bf16
 };
 
 template <class C, class T>
@@ -79,6 +83,18 @@ struct Stage {
     static_assert(T::NS >= 2 && T::NS <= 4 && T::kRows % 64 == 0, "ring");
     static_assert(kLds * (T::OCC * 4 / T::NW) <= 160 * 1024, "blocks per compute unit");
 };
+
+// f(0), f(1), ... f(N - 1), each with its number as a constant.
+template <class F, int... I>
+__device__ __forceinline__ void each_of(const F &f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void each(const F &f)
+{
+    each_of(f, std::make_integer_sequence<int, N>{});
+}
 
 enum class Refill { kNone, kShare, kAll };      // the loads of a stage that a step issues: its share of them, or all
 
@@ -99,8 +115,8 @@ template <class C, bool RAW, class T>
 __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, uint8_t *lds)
 {
     using St = Stage<C, T>;
-    constexpr int TM = T::TM, TN = T::TN, WM = T::WM, WN = T::WN, XF = T::XF, WF = T::WF, NF = T::NF, NW = T::NW, NS = T::NS;
-    constexpr int kMfmas = T::kMfmas, kEpiPitch = T::kEpiPitch, kLoads = St::kLoads, kMaxLoads = St::kMaxLoads;
+    constexpr int TM = T::TM, TN = T::TN, WM = T::WM, WN = T::WN, XF = T::XF, kXs = T::kXs, kWs = T::kWs, NW = T::NW, NS = T::NS;
+    constexpr int kMfmas = T::kMfmas, kLoads = St::kLoads, kMaxLoads = St::kMaxLoads;
     constexpr bool kUneven = St::kExtra != 0;
     const uint8_t *const Xq = p.Xq, *const Wq = p.Wq;
     const float *const x_scale = p.x_scale, *const w_scale = p.w_scale;
@@ -109,7 +125,7 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
     uint16_t *const Y = p.Y;
     int32_t *const acc_out = p.acc_out;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm0 = (wave % T::WGM) * WM, wn0 = (wave / T::WGM) * WN;
     const int KS = C::stages(K);   // the last one is zero-padded
 
@@ -121,7 +137,6 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
     static_assert(kGroups * kP == St::kPieces && kXGroups * C::kGroupRows == TM, "groups of a stage");
     const uint8_t *src[kMaxLoads];   // stage 0 source of each of this wavefront's loads (wavefront-uniform)
     uint32_t dst[kMaxLoads];         // its place in a stage buffer
-    const int swave = __builtin_amdgcn_readfirstlane(wave);
     const uint32_t group_bytes = (uint32_t)KS * C::kStageStride;
     auto group_source = [&](int g) {
         const bool is_x = g < kXGroups;
@@ -130,17 +145,17 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
     };
 #pragma unroll
     for (int i = 0; i < kMaxLoads; ++i) {
-        const int j = swave + NW * (i - kOwnLoads);            // past the wavefront's own groups
+        const int j = wave + NW * (i - kOwnLoads);            // past the wavefront's own groups
         const int rest = kUneven ? min(j, kRest - 1) : j;
-        const int g = i < kOwnLoads ? swave + NW * (i / kP) : kOwn * NW + rest / kP, part = i < kOwnLoads ? i % kP : rest % kP;
+        const int g = i < kOwnLoads ? wave + NW * (i / kP) : kOwn * NW + rest / kP, part = i < kOwnLoads ? i % kP : rest % kP;
         src[i] = group_source(g) + part * 1024;
         dst[i] = C::template piece_place<T::kRows>(g, part);
     }
-    const bool extra = kUneven && swave < St::kExtra;    // this wavefront has kMaxLoads loads
+    const bool extra = kUneven && wave < St::kExtra;    // this wavefront has kMaxLoads loads
     // LDS-direct loads are issued from inline assembly so that the compiler does not serialise every
     // later LDS read behind them; completion is tracked by hand with vmcnt.
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds;
-    const uint32_t lane_off = C::lane_offset(lane, wave);
+    const uint32_t lane_off = C::lane_offset(lane);
     auto load_piece = [&](auto IC, int s, uint32_t buf) {   // load i of this wavefront's share of stage s
         constexpr int i = decltype(IC)::value;
         if constexpr (i < kMaxLoads)
@@ -171,56 +186,52 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
 
     // ---- LDS -> registers
     typename C::Reader reader(lane, T::kRows, wm0, TM + wn0);
-    typename C::Op op[2][NF];   // [step parity][fragment]: 0..XF-1 X rows 32 f .., then W rows 32 (f - XF) ..
-    auto read_frag = [&](auto KSI, auto F) {      // of the step that the reader is aimed at
-        constexpr int ks = decltype(KSI)::value, f = decltype(F)::value;
-        if constexpr (f < XF) op[ks][f] = reader.template read<0, f>(lds);
-        else if constexpr (f < NF) op[ks][f] = reader.template read<1, f - XF>(lds);
-    };
+    typename C::Op xop[kXs], wop[kWs];      // of the stage; fragments f and f + 1, f even, share 32 rows (fragment_rows.h)
+    auto read_x = [&](auto F) { xop[decltype(F)::value] = reader.template read<0, decltype(F)::value>(lds); };
+    auto read_w = [&](auto F) { wop[decltype(F)::value] = reader.template read<1, decltype(F)::value>(lds); };
 
-    typename C::Acc acc[XF][WF];
+    typename C::Acc acc[kXs][kWs];
 #pragma unroll
-    for (int i = 0; i < XF; ++i)
+    for (int i = 0; i < kXs; ++i)
 #pragma unroll
-        for (int j = 0; j < WF; ++j)
+        for (int j = 0; j < kWs; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+            for (int r = 0; r < 4; ++r) acc[i][j][r] = 0;
 
-    // One step, slot by slot, in issue order.  Slot m: MFMA (i = m / WF; the X fragment stays for WF MFMAs,
-    // measured 1 % faster than the W fragment staying); with REFILL this slot's share of the LDS-direct loads of
-    // stage rs into buffer rbuf; a fragment of the next step (the other step parity; stage buffer nbuf) in each of the first
-    // slots, or two if there are more fragments than slots.
+    // Step ks of a stage, slot by slot, in issue order: X fragments XF ks ... XF ks + XF - 1 with W fragment 0, then with 1, ... (there and back, so that
+    // one operand stays from every MFMA to the next).  Slot m: MFMA; with REFILL this slot's share of the LDS-direct loads of stage rs into
+    // buffer rbuf; a fragment.  The second step reads what the next stage starts with: the first half of its X, whose registers the first step
+    // has left, and W fragment j as soon as it is done with the present one; the first step reads the last W fragment and the other half of X.  Spread over
+    // the step, behind their MFMAs: 96 stages on all-zero codes, where only cycles count, 61.1 us with the reads in the first slots, 57.4 so.
     auto slot = [&](auto MI, auto KSI, auto REFILL, int rs, uint32_t rbuf) {
-        constexpr int m = decltype(MI)::value, ks = decltype(KSI)::value, i = m / WF;
-        constexpr int j = i % 2 ? WF - 1 - m % WF : m % WF;      // there and back: one operand stays from every MFMA to the next (up to 1 %)
-        if constexpr (m < kMfmas) {
-            C::mma(acc[i][j], op[ks][XF + j], op[ks][i]);
-            if constexpr (decltype(REFILL)::value != Refill::kNone) {
-                // NS = 2: everything in the second step; otherwise its second half in the first step of the next stage
-                constexpr bool all = decltype(REFILL)::value == Refill::kAll;
-                constexpr int half = all ? 0 : NS > 2 ? kMaxLoads / 2 : kMaxLoads;
-                constexpr int first = ks == 1 ? 0 : half, count = ks == 1 ? half : kMaxLoads - half;
-                constexpr int l0 = first + m * count / kMfmas, l1 = first + (m + 1) * count / kMfmas;
-                static_assert(l1 - l0 <= 3, "loads per slot");
-                if constexpr (l0 < l1) load_piece(std::integral_constant<int, l0>{}, rs, rbuf);
-                if constexpr (l0 + 1 < l1) load_piece(std::integral_constant<int, l0 + 1>{}, rs, rbuf);
-                if constexpr (l0 + 2 < l1) load_piece(std::integral_constant<int, l0 + 2>{}, rs, rbuf);
-            }
-            constexpr int f0 = kMfmas >= NF ? m : m * NF / kMfmas, f1 = kMfmas >= NF ? m + 1 : (m + 1) * NF / kMfmas;
-            static_assert(f1 - f0 <= 2, "fragments per slot");
-            read_frag(std::integral_constant<int, 1 - ks>{}, std::integral_constant<int, f0>{});
-            if constexpr (f0 + 1 < f1) read_frag(std::integral_constant<int, 1 - ks>{}, std::integral_constant<int, f0 + 1>{});
-            __builtin_amdgcn_sched_barrier(0);
+        constexpr int m = decltype(MI)::value, ks = decltype(KSI)::value, j = m / XF;
+        constexpr int i = ks * XF + (j % 2 ? XF - 1 - m % XF : m % XF);
+        C::mma(acc[i][j], xop[i], wop[j]);
+        if constexpr (decltype(REFILL)::value != Refill::kNone) {
+            // NS = 2: everything in the second step; otherwise its second half in the first step of the next stage
+            constexpr bool all = decltype(REFILL)::value == Refill::kAll;
+            constexpr int half = all ? 0 : NS > 2 ? kMaxLoads / 2 : kMaxLoads;
+            constexpr int first = ks == 1 ? 0 : half, count = ks == 1 ? half : kMaxLoads - half;
+            constexpr int l0 = first + m * count / kMfmas, l1 = first + (m + 1) * count / kMfmas;
+            static_assert(l1 - l0 <= 3, "loads per slot");
+            if constexpr (l0 < l1) load_piece(std::integral_constant<int, l0>{}, rs, rbuf);
+            if constexpr (l0 + 1 < l1) load_piece(std::integral_constant<int, l0 + 1>{}, rs, rbuf);
+            if constexpr (l0 + 2 < l1) load_piece(std::integral_constant<int, l0 + 2>{}, rs, rbuf);
         }
-    };
-    auto step = [&](auto KSI, auto REFILL, uint32_t nbuf, int rs, uint32_t rbuf) {
         __builtin_amdgcn_sched_barrier(0);
-        reader.template aim<1 - decltype(KSI)::value>(nbuf);
-#define CONVROT_SLOT(m) slot(std::integral_constant<int, m>{}, KSI, REFILL, rs, rbuf);
-        CONVROT_SLOT(0) CONVROT_SLOT(1) CONVROT_SLOT(2) CONVROT_SLOT(3) CONVROT_SLOT(4) CONVROT_SLOT(5) CONVROT_SLOT(6) CONVROT_SLOT(7)
-        CONVROT_SLOT(8)
-#undef CONVROT_SLOT
-        static_assert(kMfmas <= 9, "slots of a step");
+        constexpr int gap = XF > 1 ? XF - 1 : 1;
+        if constexpr (ks == 1) {
+            if constexpr (m % gap == 0 && m / gap < XF) read_x(std::integral_constant<int, m / gap>{});
+            if constexpr (m > 0 && m % XF == 0) read_w(std::integral_constant<int, j - 1>{});
+        } else {
+            if constexpr (m == 0) read_w(std::integral_constant<int, kWs - 1>{});
+            if constexpr (m > 0 && (m - 1) % gap == 0 && (m - 1) / gap < XF) read_x(std::integral_constant<int, XF + (m - 1) / gap>{});
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto step = [&](auto KSI, auto REFILL, int rs, uint32_t rbuf) {
+        __builtin_amdgcn_sched_barrier(0);
+        each<kMfmas>([&](auto MI) { slot(MI, KSI, REFILL, rs, rbuf); });
     };
 
     // ---- pipeline
@@ -253,23 +264,22 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
     wait_loads_upto((late ? NS - 1 : min(KS, NS)) - 1);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    reader.template aim<0>(0);
-#define CONVROT_F(f) read_frag(K0{}, std::integral_constant<int, f>{});
-    CONVROT_F(0) CONVROT_F(1) CONVROT_F(2) CONVROT_F(3) CONVROT_F(4) CONVROT_F(5)
-#undef CONVROT_F
-    static_assert(NF <= 6, "fragments of a step");
+    each<XF>(read_x);
+    each<kWs - 1>(read_w);
 
     int s = 0;
     uint32_t buf = 0;      // stage s's buffer
     auto stage = [&](auto REST, auto REFILL, auto WAIT) {
         const uint32_t next = buf + St::kBytes == St::kRing ? 0 : buf + St::kBytes;
         const uint32_t prev = buf == 0 ? St::kRing - St::kBytes : buf - St::kBytes;
-        step(K0{}, REST, buf, s - 1 + NS, prev);      // fetches the fragments of the second step
+        step(K0{}, REST, s - 1 + NS, prev);      // fetches the other fragments of the stage
+        __builtin_amdgcn_sched_barrier(0);
+        reader.advance(next - buf);               // (here and not behind the barrier, where every wavefront would wait for it)
         __builtin_amdgcn_sched_barrier(0);
         WAIT();
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        step(K1{}, REFILL, next, s + NS, buf);        // fetches the first fragments of stage s + 1
+        step(K1{}, REFILL, s + NS, buf);         // fetches the first fragments of stage s + 1
         buf = next;
         ++s;
     };
@@ -284,86 +294,81 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
     }
     while (s < KS) stage(No{}, No{}, drain);          // (what the very last step fetches is unused)
 
-    // ---- epilogue.  Lane l, register r of a 32x32 accumulator tile: m = l % 32, n = 8 (r/4) + 4 (l/32) + r % 4.
+    // ---- epilogue.  Lane l, register r of accumulator tile (i, j): row 32 (i / 2) + row_of(4 (l / 16) + r, i % 2), column 32 (j / 2) +
+    // row_of(l % 16, j % 2) of the wavefront's.
+    uint32_t late_tid = threadIdx.x;      // (what follows from it is computed here, not held in registers through the loop)
+    keep(late_tid);
+    const int tid2 = late_tid, lane2 = tid2 & 63, quad = lane2 >> 4, col16 = lane2 & 15;
     if constexpr (RAW) {
-        const bool vec_ok = (N & 3) == 0;
 #pragma unroll
-        for (int i = 0; i < XF; ++i) {
-            const int m = m0 + wm0 + i * 32 + (lane & 31);
-            if (m >= M) continue;
+        for (int i = 0; i < kXs; ++i)
 #pragma unroll
-            for (int j = 0; j < WF; ++j) {
+            for (int r = 0; r < 4; ++r) {
+                const int m = m0 + wm0 + i / 2 * 32 + row_of(quad * 4 + r, i % 2);
+                if (m >= M) continue;
 #pragma unroll
-                for (int rb = 0; rb < 4; ++rb) {
-                    const int n = n0 + wn0 + j * 32 + rb * 8 + (lane >> 5) * 4;
-                    if (n >= N) continue;
-                    int32_t o[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = (int32_t)acc[i][j][rb * 4 + e];   // exact: a float holds an integer below 2^24
-                    int32_t *out = acc_out + (int64_t)m * N + n;
-                    if (vec_ok) {
-                        *reinterpret_cast<int4 *>(out) = make_int4(o[0], o[1], o[2], o[3]);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (n + e < N) out[e] = o[e];
-                    }
+                for (int j = 0; j < kWs; ++j) {
+                    const int n = n0 + wn0 + j / 2 * 32 + row_of(col16, j % 2);
+                    if (n < N) acc_out[(int64_t)m * N + n] = (int32_t)acc[i][j][r];   // exact: a float holds an integer below 2^24
                 }
             }
-        }
     } else {
+        // Parked so that a lane finds the scales of its four rows of an X fragment side by side, and a W fragment's columns in lane order.
         float *sx_lds = reinterpret_cast<float *>(lds + St::kScales), *sw_lds = sx_lds + TM;
-        if (tid < TM) sx_lds[tid] = my_sx;
-        if (tid < TN) {
-            sw_lds[tid] = my_sw;
-            sw_lds[TN + tid] = bf16_to_f32(my_b);
+        if (tid2 < TM) {
+            const int c = (tid2 & 31) >> 1;
+            sx_lds[(tid2 & ~31) + (c >> 2) * 8 + ((tid2 & 1) ^ crossed(c)) * 4 + (c & 3)] = my_sx;
+        }
+        if (tid2 < TN) {
+            const int c = (tid2 & 31) >> 1, at = (tid2 & ~31) + ((tid2 & 1) ^ crossed(c)) * 16 + c;
+            sw_lds[at] = my_sw;
+            sw_lds[TN + at] = bf16_to_f32(my_b);
         }
         __syncthreads();     // every wavefront has finished reading the ring; the scales are visible
-        float sxm[XF];
-#pragma unroll
-        for (int i = 0; i < XF; ++i) sxm[i] = sx_lds[wm0 + i * 32 + (lane & 31)];
-        uint8_t *stage_lds = lds + wave * (32 * kEpiPitch);      // this wavefront's 32 x WN bf16 staging tile
+        uint8_t *stage_lds = lds + wave * (32 * WN * 2);      // this wavefront's 32 x WN bf16 staging tile
+        // A lane has two neighbouring columns of a row in two accumulators, four bytes (the halves exchanged where the columns are crossed).  Rows of
+        // the staging tile need no pad: the rows that a store's two halves write lie an odd number apart, and what is read back is one straight kilobyte a pass.
+        const uint32_t crossed16 = crossed(col16) * 16;
+        uint8_t *const stage_row[2] = {stage_lds + row_of(quad * 4, 0) * (WN * 2) + col16 * 4, stage_lds + row_of(quad * 4, 1) * (WN * 2) + col16 * 4};
         // read-back: the 32 rows of WN bf16 are 32 * WN / 8 pieces of 16 bytes, dealt to the 64 lanes in order
         // (piece p = 64 pass + lane: row p / (WN / 8), columns 8 (p % (WN / 8)) ...), so every pass has all
         // lanes at work and stores whole rows of the wavefront tile back to back
         constexpr int kRowPieces = WN / 8, kRbPasses = 32 * kRowPieces / 64;
         static_assert(kRbPasses * 64 == 32 * kRowPieces, "read-back passes");
-        const int rb_row0 = lane / kRowPieces, rb_piece0 = lane % kRowPieces;   // pass 0; 64 more pieces per pass
-        // the column scales of the lane's accumulator registers, fetched once for all XF row blocks
-        float4 swv[WF][4];
+        const int rb_row0 = lane2 / kRowPieces, rb_piece0 = lane2 % kRowPieces;   // pass 0; 64 more pieces per pass
+        // the column scales and biases of the lane's accumulator registers, fetched once for all rows
+        float swv[kWs];
 #pragma unroll
-        for (int j = 0; j < WF; ++j)
-#pragma unroll
-            for (int rb = 0; rb < 4; ++rb)
-                swv[j][rb] = *reinterpret_cast<const float4 *>(sw_lds + wn0 + j * 32 + rb * 8 + (lane >> 5) * 4);
+        for (int j = 0; j < kWs; ++j) swv[j] = sw_lds[wn0 + j * 16 + col16];
         auto body = [&](auto EDGE, auto BIAS, auto KIND) {
+            float bv[kWs];
+#pragma unroll
+            for (int j = 0; j < kWs; ++j) bv[j] = decltype(BIAS)::value ? sw_lds[TN + wn0 + j * 16 + col16] : 0.0f;
 #pragma unroll
             for (int i = 0; i < XF; ++i) {
                 const int mrow = m0 + wm0 + i * 32;
 #pragma unroll
-                for (int j = 0; j < WF; ++j)
+                for (int h = 0; h < 2; ++h) {
+                    const v4f sx = *reinterpret_cast<const v4f *>(sx_lds + wm0 + i * 32 + quad * 8 + h * 4);
 #pragma unroll
-                    for (int rb = 0; rb < 4; ++rb) {
-                        const int col = j * 32 + rb * 8 + (lane >> 5) * 4;
-                        const float4 sw = swv[j][rb];
-                        const float t[4] = {(float)acc[i][j][rb * 4 + 0] * sxm[i], (float)acc[i][j][rb * 4 + 1] * sxm[i],
-                                            (float)acc[i][j][rb * 4 + 2] * sxm[i], (float)acc[i][j][rb * 4 + 3] * sxm[i]};
-                        float y[4];
-                        if constexpr (decltype(BIAS)::value) {   // explicitly fused, so that every tile shape rounds alike
-                            const float4 b = *reinterpret_cast<const float4 *>(sw_lds + TN + wn0 + col);
-                            y[0] = fmaf(t[0], sw.x, b.x); y[1] = fmaf(t[1], sw.y, b.y); y[2] = fmaf(t[2], sw.z, b.z); y[3] = fmaf(t[3], sw.w, b.w);
-                        } else {
-                            y[0] = t[0] * sw.x; y[1] = t[1] * sw.y; y[2] = t[2] * sw.z; y[3] = t[3] * sw.w;
+                    for (int j = 0; j < kWs; j += 2)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const float t[2] = {(float)acc[2 * i + h][j][r] * sx[r], (float)acc[2 * i + h][j + 1][r] * sx[r]};
+                            float y[2];
+#pragma unroll
+                            for (int e = 0; e < 2; ++e)      // explicitly fused, so that every tile shape rounds alike
+                                y[e] = decltype(BIAS)::value ? fmaf(t[e], swv[j + e], bv[j + e]) : t[e] * swv[j + e];
+                            const uint32_t two = pack_bf16x2(y[0], y[1]);
+                            *reinterpret_cast<uint32_t *>(stage_row[h] + r * 2 * (WN * 2) + j * 32) = __builtin_amdgcn_alignbit(two, two, crossed16);
                         }
-                        *reinterpret_cast<uint2 *>(stage_lds + (lane & 31) * kEpiPitch + col * 2) =
-                            make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
-                    }
+                }
                 // the same wavefront reads back row-contiguous
 #pragma unroll
                 for (int it = 0; it < kRbPasses; ++it) {
                     int piece = rb_piece0 + (it * 64) % kRowPieces, r = rb_row0 + (it * 64) / kRowPieces;
                     if ((it * 64) % kRowPieces != 0 && piece >= kRowPieces) { piece -= kRowPieces; ++r; }
-                    const v4i v = *reinterpret_cast<const v4i *>(stage_lds + r * kEpiPitch + piece * 16);
+                    const v4i v = *reinterpret_cast<const v4i *>(stage_lds + (it * 64 + lane2) * 16);
                     const int mo = mrow + r, ncol = n0 + wn0 + piece * 8;
                     uint16_t *out = Y + (int64_t)mo * N + ncol;
                     if constexpr (decltype(EDGE)::value == 0) {

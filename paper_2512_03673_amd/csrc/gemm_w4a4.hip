@@ -2,7 +2,7 @@
 // (ConvRot paper Sec. 4.3: 4-bit matrix multiplication, then dequantisation).
 //
 // gfx950 has no 4-bit integer MFMA, but every code in [-7, 7] is an FP6 (E2M3) number, and
-// v_mfma_f32_32x32x64_f8f6f4 on FP6 operands runs at twice the rate of the int8 MFMA.  Products of two
+// v_mfma_f32_16x16x128_f8f6f4 on FP6 operands runs at twice the rate of the int8 MFMA.  Products of two
 // codes (|.| <= 49) and all their partial sums (|.| <= 49 K < 2^22 for K <= 65536) are integers that
 // fp32 holds exactly, so the fp32 accumulators carry the exact integer result whatever the order of
 // the additions.  The codes arrive from the rotate+quantise kernel already as FP6 (e2m3_layout.h), six
@@ -13,7 +13,7 @@
 //
 // The operands sit in HBM as 3 KB blocks of 32 rows x 128 codes (an A plane of 32 x 64 bytes and a B plane of
 // 32 x 32 bytes, both XOR-swizzled for the fragment reads), so that a K128 stage of a tile is a list of contiguous
-// kilobytes, copied as they are.  A fragment (32 rows x 64 codes, 24 bytes per lane) is one ds_read_b128 from the A
+// kilobytes, copied as they are.  A fragment (16 rows x 128 codes, 24 bytes per lane) is one ds_read_b128 from the A
 // plane and one ds_read_b64 from the B plane and is an MFMA operand as read.  The kernel is gemm_tiled.h.
 #include "gemm_plan.h"
 #include "gemm_small.h"
@@ -28,12 +28,12 @@ namespace {
 
 typedef int v2i __attribute__((ext_vector_type(2)));
 typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
+using gemm::v4f;
 using gemm::v4i;
 
 struct Codes4 {
     typedef v8i Op;      // 6 dwords used
-    typedef v16f Acc;
+    typedef v4f Acc;
     static constexpr int kRowBytes = e2m3::kARowBytes + e2m3::kBRowBytes;     // of one row per stage
     static constexpr uint32_t kStageStride = e2m3::kBlockBytes;               // from a row's stage to its next one
 
@@ -48,49 +48,48 @@ struct Codes4 {
     {
         return part < 2 ? g * e2m3::kAPlaneBytes + part * 1024 : ROWS * e2m3::kARowBytes + g * e2m3::kBPlaneBytes;
     }
-    static __device__ __forceinline__ uint32_t lane_offset(int lane, int) { return lane * 16; }
+    static __device__ __forceinline__ uint32_t lane_offset(int lane) { return lane * 16; }
 
-    struct Reader {      // lane l holds chunk 2 ks + l / 32 of row l % 32
-        uint32_t a[2][2], b[2][2];     // [step][operand]: byte offsets of the lane's A part and B part of the wavefront's first 32 rows of X (0), W (1)
-        uint32_t at_a[2], at_b[2];     // of the step and stage that reads come from: fragments are constants further on
+    struct Reader {      // lane l holds chunk piece_of(l / 16) of row row_of(l % 16, odd) of the pair's 32
+        uint32_t a[2][2], b[2][2];     // [operand][odd fragment]: where the lane's A part and B part of the first pair's rows of X (0), W (1) are; others are constants further on
         __device__ __forceinline__ Reader(int lane, int rows, int x_row, int w_row)
         {
-            const int r = lane & 31;
+            const int c = gemm::piece_of(lane >> 4);
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                const int c = 2 * ks + (lane >> 5);
+            for (int o = 0; o < 2; ++o)
 #pragma unroll
-                for (int o = 0; o < 2; ++o) {
-                    a[ks][o] = (r + (o ? w_row : x_row)) * e2m3::kARowBytes + ((c ^ e2m3::swz_a(r)) << 4);
-                    b[ks][o] = rows * e2m3::kARowBytes + (r + (o ? w_row : x_row)) * e2m3::kBRowBytes + ((c ^ e2m3::swz_b(r)) << 3);
+                for (int odd = 0; odd < 2; ++odd) {
+                    const int r = gemm::row_of(lane & 15, odd), row = (o ? w_row : x_row) + r;
+                    a[o][odd] = row * e2m3::kARowBytes + ((c ^ e2m3::swz_a(r)) << 4);
+                    b[o][odd] = rows * e2m3::kARowBytes + row * e2m3::kBRowBytes + ((c ^ e2m3::swz_b(r)) << 3);
                 }
-            }
         }
-        template <int ks>
-        __device__ __forceinline__ void aim(uint32_t stage)
+        __device__ __forceinline__ void advance(uint32_t bytes)      // to another stage buffer
         {
 #pragma unroll
-            for (int o = 0; o < 2; ++o) {
-                at_a[o] = stage + a[ks][o];
-                at_b[o] = stage + b[ks][o];
-                gemm::keep(at_a[o]);
-                gemm::keep(at_b[o]);
-            }
+            for (int o = 0; o < 2; ++o)
+#pragma unroll
+                for (int odd = 0; odd < 2; ++odd) {
+                    a[o][odd] += bytes;
+                    b[o][odd] += bytes;
+                    gemm::keep(a[o][odd]);
+                    gemm::keep(b[o][odd]);
+                }
         }
         template <int o, int f>
         __device__ __forceinline__ Op read(const uint8_t *lds) const
         {
-            const v4i a = *reinterpret_cast<const v4i *>(lds + at_a[o] + f * e2m3::kAPlaneBytes);
-            const v2i b = *reinterpret_cast<const v2i *>(lds + at_b[o] + f * e2m3::kBPlaneBytes);
+            const v4i a = *reinterpret_cast<const v4i *>(lds + this->a[o][f % 2] + f / 2 * e2m3::kAPlaneBytes);
+            const v2i b = *reinterpret_cast<const v2i *>(lds + this->b[o][f % 2] + f / 2 * e2m3::kBPlaneBytes);
             Op v = __builtin_shufflevector(a, a, 0, 1, 2, 3, -1, -1, -1, -1);
             v[4] = b.x;
             v[5] = b.y;
             return v;
         }
     };
-    static __device__ __forceinline__ void mma(Acc &c, const Op &w, const Op &x)
+    static __device__ __forceinline__ void mma(Acc &c, const Op &x, const Op &w)
     {
-        c = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w, x, c, 2, 2, 0, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(x, w, c, 2, 2, 0, 0, 0, 0);
     }
 };
 

@@ -4,7 +4,7 @@
 //
 // A stage is 64 codes of K: the panel layout of the operands (panel_layout.h) keeps 16 rows of it in one contiguous
 // kilobyte and pads the last one with zero codes.  A 16-byte fragment read from LDS is an operand of
-// v_mfma_i32_32x32x32_i8 as it stands.  The kernel is gemm_tiled.h.
+// v_mfma_i32_16x16x64_i8 as it stands.  The kernel is gemm_tiled.h.
 #include "gemm_plan.h"
 #include "gemm_small.h"
 #include "gemm_tiled.h"
@@ -20,7 +20,7 @@ using gemm::v4i;
 
 struct Codes8 {
     typedef v4i Op;
-    typedef gemm::v16i Acc;
+    typedef v4i Acc;
     static constexpr int kRowBytes = panel::kRowBytes;
     static constexpr uint32_t kStageStride = panel::kBytes;
 
@@ -31,39 +31,38 @@ struct Codes8 {
     template <int>
     static __device__ __forceinline__ uint32_t piece_place(int g, int) { return g * panel::kBytes; }
     // Lane l fills 16-byte slot l % 4 of row l / 4 of the panel in LDS, where the swizzle keeps piece slot ^ swz(row).
-    // (A wavefront's panels are all even or all odd: swz of the tile row depends on no more than that.)
-    static __device__ __forceinline__ uint32_t lane_offset(int lane, int wave)
-    {
-        return (lane / 4) * panel::kRowBytes + ((lane % 4) ^ gemm::swz(16 * (wave & 1) + lane / 4)) * 16;
-    }
+    static __device__ __forceinline__ uint32_t lane_offset(int lane) { return (lane / 4) * panel::kRowBytes + ((lane % 4) ^ gemm::swz(lane / 4)) * 16; }
 
-    struct Reader {      // lane l holds piece 2 ks + l / 32 of row l % 32
-        uint32_t a[2][2], at[2];     // as in gemm_w4a4.hip
+    struct Reader {      // lane l holds piece piece_of(l / 16) of row row_of(l % 16, odd) of the pair's 32
+        uint32_t a[2][2];     // as in gemm_w4a4.hip
         __device__ __forceinline__ Reader(int lane, int, int x_row, int w_row)
         {
-            const int r = lane & 31;
+            const int c = gemm::piece_of(lane >> 4);
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks)
+            for (int o = 0; o < 2; ++o)
 #pragma unroll
-                for (int o = 0; o < 2; ++o)
-                    a[ks][o] = (r + (o ? w_row : x_row)) * panel::kRowBytes + (((2 * ks + (lane >> 5)) ^ gemm::swz(r)) << 4);
+                for (int odd = 0; odd < 2; ++odd) {
+                    const int r = gemm::row_of(lane & 15, odd);
+                    a[o][odd] = (r + (o ? w_row : x_row)) * panel::kRowBytes + ((c ^ gemm::swz(r & 15)) << 4);
+                }
         }
-        template <int ks>
-        __device__ __forceinline__ void aim(uint32_t stage)
+        __device__ __forceinline__ void advance(uint32_t bytes)
         {
 #pragma unroll
-            for (int o = 0; o < 2; ++o) {
-                at[o] = stage + a[ks][o];
-                gemm::keep(at[o]);
-            }
+            for (int o = 0; o < 2; ++o)
+#pragma unroll
+                for (int odd = 0; odd < 2; ++odd) {
+                    a[o][odd] += bytes;
+                    gemm::keep(a[o][odd]);
+                }
         }
         template <int o, int f>
         __device__ __forceinline__ Op read(const uint8_t *lds) const
         {
-            return *reinterpret_cast<const v4i *>(lds + at[o] + f * 32 * panel::kRowBytes);
+            return *reinterpret_cast<const v4i *>(lds + a[o][f % 2] + f / 2 * 32 * panel::kRowBytes);
         }
     };
-    static __device__ __forceinline__ void mma(Acc &c, const Op &w, const Op &x) { c = __builtin_amdgcn_mfma_i32_32x32x32_i8(w, x, c, 0, 0, 0); }
+    static __device__ __forceinline__ void mma(Acc &c, const Op &x, const Op &w) { c = __builtin_amdgcn_mfma_i32_16x16x64_i8(x, w, c, 0, 0, 0); }
 };
 
 hipError_t launch_plan(gemm::Plan plan, const gemm::Operands &o)
