@@ -265,6 +265,32 @@ inline int parts_of_last_tiles(int64_t per_xcd)
     return per_xcd < 32 || per_xcd >= 5 * 32 || rest == 0 || rest > 16 ? 1 : rest > 8 ? 2 : 4;
 }
 
+// Whether every other XCD begins with its parts instead of ending with them.  All units of a launch otherwise finish a round at once, and the rounds'
+// outputs go to memory in bursts that the next tiles wait behind; half a tile apart, one half of the chip stores while the other multiplies.
+// Long products have little to gain, and lose the operands that XCDs ask for at the same time from the same cache.  us, last / first on odd XCDs: M4608 x N12288 x K3072
+// 78.8 / 75.9, M4155 x N9216 x K1536 37.5 / 34.5, M5754 x N9152 x K2048 58.0 / 54.6; over 39 shapes of K 1024 ... 3072 4 % less (two slower, M11878 x N1664 x K3072
+// 35.8 / 37.0); M7095 x N5248 x K4096 73.8 / 72.3, but M16525 x N1216 x K3584 40.9 / 42.9, M16234 x N1472 x K4608 56.2 / 60.8, and over 34 shapes of K 3584 ... 12288
+// 1.3 % more.  With the four XCDs of one half of the chip first 80, with all of them 75.4; half a tile apart in products whose rounds come out
+// even, by parts for whole tiles, 0 to 30 % slower.
+constexpr int kPartsFirst = 1 << 8;      // (fewer than 5 * 32 tiles of an XCD are whole)
+constexpr bool parts_first(int64_t stages) { return stages <= 26; }
+
+// The work of an XCD's `turn`-th block: a tile of its range, whole or one part of it.  `how`: the tiles that are whole, and kPartsFirst.
+struct CutTurn {
+    uint32_t tile, part;
+    bool whole;
+};
+constexpr CutTurn cut_turn(uint32_t turn, uint32_t xcd, uint32_t per_xcd, uint32_t how, uint32_t parts)
+{
+    const uint32_t whole = how & (kPartsFirst - 1);
+    if (xcd & how >> 8) {
+        const uint32_t first = (per_xcd - whole) * parts;
+        turn = turn < first ? whole + turn : turn - first;
+    }
+    if (turn < whole) return {turn, 0, true};
+    return {whole + (turn - whole) / parts, (turn - whole) % parts, false};
+}
+
 template <int BITS>
 inline Plan choose(int64_t M, int64_t N, int64_t K)
 {

@@ -424,6 +424,7 @@ __global__ __launch_bounds__(T::kThreads, T::OCC) void gemm_tiled_kernel(CONVROT
 
 // Tiles of T, of which each XCD's last ones (from its `whole`-th on) are cut into `parts` of shape P: a block of T takes a
 // compute unit to itself, so a last round that few tiles share would keep most of the chip waiting for a whole tile.
+// `rows_whole`: rows of a band, and << 8 what cut_turn is told.
 template <class C, bool RAW, class T, class P>
 __global__ __launch_bounds__(T::kThreads, T::OCC) void gemm_cut_kernel(CONVROT_TILED_FIRST, int rows_whole, CONVROT_TILED_LAST)
 {
@@ -433,13 +434,13 @@ __global__ __launch_bounds__(T::kThreads, T::OCC) void gemm_cut_kernel(CONVROT_T
     __shared__ __attribute__((aligned(1024))) uint8_t lds[kLds];
     const Product p{Xq, x_scale, Wq, w_scale, bias, M, N, K, Y, acc_out, store};
     const TileOrder order{per_xcd, tiles_m, rows_whole & 0xFF, span, by_span, by_rows, by_tail};
-    const uint32_t xcd = blockIdx.x % kNumXcd, turn = blockIdx.x / kNumXcd, whole = (uint32_t)rows_whole >> 8;
-    const uint32_t part = turn < whole ? 0 : (turn - whole) % kParts, tile_turn = turn < whole ? turn : whole + (turn - whole) / kParts;
+    const uint32_t xcd = blockIdx.x % kNumXcd;
+    const CutTurn at = cut_turn(blockIdx.x / kNumXcd, xcd, (uint32_t)per_xcd, (uint32_t)rows_whole >> 8, kParts);
     int tm, tn;
-    if (!tile_of_block(order, tile_turn * kNumXcd + xcd, tm, tn) || !starts_inside(tn, T::TN, N)) return;
-    const int m0 = tm * T::TM + (int)(part % kM) * P::TM, n0 = tn * T::TN + (int)(part / kM) * P::TN;
+    if (!tile_of_block(order, at.tile * kNumXcd + xcd, tm, tn) || !starts_inside(tn, T::TN, N)) return;
+    const int m0 = tm * T::TM + (int)(at.part % kM) * P::TM, n0 = tn * T::TN + (int)(at.part / kM) * P::TN;
     if (m0 >= M || n0 >= N) return;
-    if (turn < whole) tile_product<C, RAW, T>(p, m0, n0, lds);
+    if (at.whole) tile_product<C, RAW, T>(p, m0, n0, lds);
     else tile_product<C, RAW, P>(p, m0, n0, lds);
 }
 #undef CONVROT_TILED_FIRST
@@ -476,7 +477,8 @@ hipError_t launch_cut(const Operands &o, int cut)
     if (!launchable((int64_t)tiles_m * tiles_n * (T::TM / P::TM) * (T::TN / P::TN), T::kThreads)) return hipErrorInvalidValue;
     const TileOrder t = tile_order(tiles_m, tiles_n, band_rows<T>(tiles_m));
     const int whole = t.per_xcd - cut, grid = (whole + cut * (T::TM / P::TM) * (T::TN / P::TN)) * kNumXcd;
-    auto go = [&](auto kernel) { return launch_order(kernel, o, t, t.rows | whole << 8, grid, T::kThreads); };
+    const int first = parts_first(C::stages(o.K)) ? kPartsFirst : 0;
+    auto go = [&](auto kernel) { return launch_order(kernel, o, t, t.rows | (whole | first) << 8, grid, T::kThreads); };
     return o.acc ? go(gemm_cut_kernel<C, true, T, P>) : go(gemm_cut_kernel<C, false, T, P>);
 }
 

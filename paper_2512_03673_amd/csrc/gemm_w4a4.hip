@@ -39,7 +39,7 @@ struct Codes4 {
 
     static constexpr int kGroupRows = e2m3::kRows, kGroupPieces = e2m3::kBlockBytes / 1024;
 
-    static __device__ __forceinline__ int stages(int K) { return (K + e2m3::kStageCodes - 1) / e2m3::kStageCodes; }
+    static __host__ __device__ __forceinline__ int stages(int K) { return (K + e2m3::kStageCodes - 1) / e2m3::kStageCodes; }
 
     // Where kilobyte `part` of the block of the tile's 32-row group g goes: kilobytes 0, 1 are the A plane (rows 0-15, 16-31),
     // kilobyte 2 the B plane.  A stage buffer holds the A parts of all the tile's rows, then the B parts.
