@@ -22,6 +22,10 @@ FLAGS = [
     # kernels find their first arguments in registers when they start, instead of waiting 0.3-0.6 us for a scalar load from a cold cache
     # (us: M1 x N9216 x K3072 forward 6.44 -> 6.14, M77 x N3072 x K3072 at 8 bits 10.87 -> 10.65, rotate+quantise [4608, 3072] at g = 256 10.4 -> 9.9)
     "-mllvm", "-amdgpu-kernarg-preload-count=16",
+    # pairs of float operations made into vectors are taken apart again where there are no packed ones, but their DPP operands no longer go into the
+    # instruction: 3 to 4 moves an element of the 8-bit rotate+quantise at g >= 256 (us, cold: [4608, 3072] g256 11.4 -> 10.2, g1024 12.9 -> 11.3, [4608, 12288]
+    # g256 34.2 -> 32.9; 4 bits and smaller groups the same)
+    "-fno-slp-vectorize",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
 
