@@ -124,8 +124,18 @@ inline int64_t tiles_of(int64_t M, int64_t N, int tm, int tn) { return ((M + tm 
 // stages: 4 bits, 192 x 192, M3000 x N3072 x K3072 25 / 16.3, geometric mean over 91 drawn shapes 1.35; three / four: 8 bits, 128 x 192, M300 x N12288 x
 // K12288 80 / 65, over 69 shapes 1.11; 4 bits, 64 x 64, whose stages take 0.157 us so instead of 0.214, operands from the Infinity Cache: M700 x N1000 x K2048
 // 5.7 / 5.1, M256 x N3072 x K3072 7.55 / 6.4, M1024 x N1024 x K4096 9.15 / 7.55 (six stages 5.55, 6.9, 8.0; of more than a round, where four blocks a unit
-// become three, M512 x N3072 x K3072 8.2 / 8.45).  (No gain: 192 x 192 at 8 bits, 128 x 128 at 4 bits, 256 x 128 on eight wavefronts.)
+// become three, M512 x N3072 x K3072 8.2 / 8.45).  (No gain: 192 x 192 at 8 bits, 256 x 128 on eight wavefronts.)
 inline bool deep_ring(int64_t tiles, int64_t stages) { return tiles <= 256 && stages >= 16; }
+
+// 128 x 128 tiles are eight wavefronts of 32 x 64, two on each SIMD, which wait for their LDS-direct loads and fragments in turn; four of 64 x 64 read a
+// third less from LDS, but alone on their SIMD every wait is the matrix pipe's (a stage 0.30 us, of which MFMAs take 0.11).  At 4 bits with a ring of four
+// where every tile has its unit to itself, of three else, two blocks a unit.  us, four / eight wavefronts, operands changing: 4 bits, up to 256 tiles,
+// M1619 x N1472 x K6432 16.6 / 15.3, M307 x N7296 x K5088 18.5 / 15.9, M336 x N5444 x K704 6.05 / 5.1, M424 x N6104 x K384 4.47 / 4.53; over 30 shapes 0.93,
+// 1.01 at worst; more tiles, M7771 x N916 x K128 7.25 / 6.45, M2405 x N6769 x K64 11.2 / 10.5, M16544 x N640 x K832 13.2 / 13.4, over 16 shapes 0.96.  Sixteen wavefronts of 32 x 32: 1.02.
+// 8 bits, up to 256 tiles of up to 19 stages, M702 x N4580 x K384 6.5 / 5.5, M285 x N8951 x K1184 8.3 / 7.4, M522 x N4096 x K128 4.34 / 4.36, over 16 shapes 0.95; more tiles,
+// M4990 x N1370 x K288 8.1 / 7.35, over 14 shapes 0.97; but longer products of up to 256 tiles M575 x N6336 x K1600 8.55 / 8.8, M1704 x N2304 x K2016 10.15 / 10.5,
+// M638 x N4544 x K10816 49.1 / 48.8, over 12 shapes 1.01: these keep four.
+inline bool four_wavefronts_8(int64_t tiles, int64_t stages) { return tiles <= 256 && stages >= 20; }
 
 // Tile rows of a band of 256 x 256 tiles (tile_of_block), of which an XCD runs 32 at a time: 4 x 8 and 6 x 5.3 share
 // operands about alike, and a last band of one to three rows shares little.  So four where they come out even or leave more rows over than

@@ -45,7 +45,7 @@
 // where 256 x 256 leaves 40 idle, and is slower, 72.5 against 68.6: idle units leave their power to the others.)
 //
 // Products of one round or less are bound by a lone tile's walk along K, 0.3 to 0.4 us a stage.  Tiles that otherwise share a unit two by
-// two wait for operands there and take a ring of four stages, which their lone unit has the LDS for (deep_ring); for 128 x 128 at 4 bits, 256 x 128 on
+// two wait for operands there and take a ring of four stages, which their lone unit has the LDS for (deep_ring); for 256 x 128 on
 // eight wavefronts and 192 x 192 at 8 bits a fourth stage made no difference, nor did fragments read a whole stage ahead instead of a step on any tile.
 // What is left is to spread such a product over the most units: 128 x 192, us: 4 bits M512 x N12288 x K3072 14.9 -> 13.8, M578 x N9408 x K9600 34.2 -> 31.0; 8 bits
 // M854 x N6464 x K1024 11.0 -> 10.1, M1803 x N5056 x K4992 49.2 -> 46.2.
@@ -66,6 +66,10 @@ struct Tile {
     static constexpr int TM = WGM * WM, TN = WGN * WN, kRows = TM + TN;
     static constexpr int kXs = 2 * XF, kWs = 2 * WF;          // fragments (16 rows) of a stage per wavefront
     static constexpr int kMfmas = XF * kWs;                   // slots of a step: half of the X fragments with every W fragment
+    // Two MFMAs a step take less time than a read: all of the next stage's fragments are read behind the meeting, with one wait for them.  (64 x 64 tiles alone on
+    // their unit, us, one of them read in the next step / so: M256 x N3072 x K3072 6.6 / 6.35, M804 x N1216 x K9216 13.85 / 13.15.)
+    static constexpr bool kAtOnce = kMfmas == 2;
+    static constexpr bool kSpare = kXs * kWs < 32;            // registers to spare: the last stage apart, the epilogue's addresses early
     static constexpr int kEpiBytes = NW * 32 * WN * 2;        // 32 rows of every wavefront's tile in bf16
 };
 
@@ -203,7 +207,7 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
     // buffer rbuf; a fragment.  The second step reads what the next stage starts with: the first half of its X, whose registers the first step
     // has left, and W fragment j as soon as it is done with the present one; the first step reads the last W fragment and the other half of X.  Spread over
     // the step, behind their MFMAs: 96 stages on all-zero codes, where only cycles count, 61.1 us with the reads in the first slots, 57.4 so.
-    auto slot = [&](auto MI, auto KSI, auto REFILL, int rs, uint32_t rbuf) {
+    auto slot = [&](auto MI, auto KSI, auto REFILL, auto READS, int rs, uint32_t rbuf) {
         constexpr int m = decltype(MI)::value, ks = decltype(KSI)::value, j = m / XF;
         constexpr int i = ks * XF + (j % 2 ? XF - 1 - m % XF : m % XF);
         C::mma(acc[i][j], xop[i], wop[j]);
@@ -220,7 +224,14 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
         }
         __builtin_amdgcn_sched_barrier(0);
         constexpr int gap = XF > 1 ? XF - 1 : 1;
-        if constexpr (ks == 1) {
+        if constexpr (!decltype(READS)::value) {
+        } else if constexpr (T::kAtOnce) {
+            if constexpr (ks == 1) {
+                if constexpr (m == 0) read_x(std::integral_constant<int, 0>{});
+                read_w(MI);
+                if constexpr (m == kMfmas - 1) read_x(std::integral_constant<int, 1>{});
+            }
+        } else if constexpr (ks == 1) {
             if constexpr (m % gap == 0 && m / gap < XF) read_x(std::integral_constant<int, m / gap>{});
             if constexpr (m > 0 && m % XF == 0) read_w(std::integral_constant<int, j - 1>{});
         } else {
@@ -229,9 +240,9 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
         }
         __builtin_amdgcn_sched_barrier(0);
     };
-    auto step = [&](auto KSI, auto REFILL, int rs, uint32_t rbuf) {
+    auto step = [&](auto KSI, auto REFILL, auto READS, int rs, uint32_t rbuf) {
         __builtin_amdgcn_sched_barrier(0);
-        each<kMfmas>([&](auto MI) { slot(MI, KSI, REFILL, rs, rbuf); });
+        each<kMfmas>([&](auto MI) { slot(MI, KSI, REFILL, READS, rs, rbuf); });
     };
 
     // ---- pipeline
@@ -264,22 +275,22 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
     wait_loads_upto((late ? NS - 1 : min(KS, NS)) - 1);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    each<XF>(read_x);
-    each<kWs - 1>(read_w);
+    each<T::kAtOnce ? kXs : XF>(read_x);
+    each<T::kAtOnce ? kWs : kWs - 1>(read_w);
 
     int s = 0;
     uint32_t buf = 0;      // stage s's buffer
     auto stage = [&](auto REST, auto REFILL, auto WAIT) {
         const uint32_t next = buf + St::kBytes == St::kRing ? 0 : buf + St::kBytes;
         const uint32_t prev = buf == 0 ? St::kRing - St::kBytes : buf - St::kBytes;
-        step(K0{}, REST, s - 1 + NS, prev);      // fetches the other fragments of the stage
+        step(K0{}, REST, std::true_type{}, s - 1 + NS, prev);      // fetches the other fragments of the stage
         __builtin_amdgcn_sched_barrier(0);
         reader.advance(next - buf);               // (here and not behind the barrier, where every wavefront would wait for it)
         __builtin_amdgcn_sched_barrier(0);
         WAIT();
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        step(K1{}, REFILL, s + NS, buf);         // fetches the first fragments of stage s + 1
+        step(K1{}, REFILL, std::true_type{}, s + NS, buf);         // fetches the first fragments of stage s + 1
         buf = next;
         ++s;
     };
@@ -292,12 +303,38 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
         while (s < KS - NS) stage(Yes{}, Yes{}, steady);
         stage(Yes{}, No{}, steady);
     }
-    while (s < KS) stage(No{}, No{}, drain);          // (what the very last step fetches is unused)
+    while (s < KS - T::kSpare) stage(No{}, No{}, drain);          // (what the very last step fetches is unused)
+
+    // The scales, parked so that a lane finds those of its four rows of an X fragment side by side, and a W fragment's columns in lane order.
+    float *const sx_lds = reinterpret_cast<float *>(lds + St::kScales), *const sw_lds = sx_lds + TM;
+    auto park = [&](int t) {
+        const int c = (t & 31) >> 1, half = (t & 1) ^ crossed(c);
+        if (t < TM) sx_lds[(t & ~31) + (c >> 2) * 8 + half * 4 + (c & 3)] = my_sx;
+        if (t < TN) {
+            sw_lds[(t & ~31) + half * 16 + c] = my_sw;
+            sw_lds[TN + (t & ~31) + half * 16 + c] = bf16_to_f32(my_b);
+        }
+    };
+    if constexpr (T::kSpare) {
+        // The last stage, of which nothing is read ahead.  Between its steps all loads and LDS reads of the block are over, so that is the last meeting: the ring may
+        // be written from there on, and scales that were parked before be read (with the meeting after it M5000 x N4000 x K256 13.25 us, so 13.0; where
+        // registers are short the compiler's copy of the stage spills).
+        step(K0{}, No{}, std::true_type{}, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        wait_loads(std::integral_constant<int, 0>{});
+        if constexpr (!RAW) {
+            park(tid);
+            wait_loads(std::integral_constant<int, 0>{});
+        }
+        __builtin_amdgcn_s_barrier();
+        step(K1{}, No{}, std::false_type{}, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    }
 
     // ---- epilogue.  Lane l, register r of accumulator tile (i, j): row 32 (i / 2) + row_of(4 (l / 16) + r, i % 2), column 32 (j / 2) +
     // row_of(l % 16, j % 2) of the wavefront's.
     uint32_t late_tid = threadIdx.x;      // (what follows from it is computed here, not held in registers through the loop)
-    keep(late_tid);
+    if constexpr (!T::kSpare) keep(late_tid);
     const int tid2 = late_tid, lane2 = tid2 & 63, quad = lane2 >> 4, col16 = lane2 & 15;
     if constexpr (RAW) {
 #pragma unroll
@@ -313,18 +350,10 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
                 }
             }
     } else {
-        // Parked so that a lane finds the scales of its four rows of an X fragment side by side, and a W fragment's columns in lane order.
-        float *sx_lds = reinterpret_cast<float *>(lds + St::kScales), *sw_lds = sx_lds + TM;
-        if (tid2 < TM) {
-            const int c = (tid2 & 31) >> 1;
-            sx_lds[(tid2 & ~31) + (c >> 2) * 8 + ((tid2 & 1) ^ crossed(c)) * 4 + (c & 3)] = my_sx;
+        if constexpr (!T::kSpare) {
+            park(tid2);
+            __syncthreads();     // every wavefront has finished reading the ring; the scales are visible
         }
-        if (tid2 < TN) {
-            const int c = (tid2 & 31) >> 1, at = (tid2 & ~31) + ((tid2 & 1) ^ crossed(c)) * 16 + c;
-            sw_lds[at] = my_sw;
-            sw_lds[TN + at] = bf16_to_f32(my_b);
-        }
-        __syncthreads();     // every wavefront has finished reading the ring; the scales are visible
         uint8_t *stage_lds = lds + wave * (32 * WN * 2);      // this wavefront's 32 x WN bf16 staging tile
         // A lane has two neighbouring columns of a row in two accumulators, four bytes (the halves exchanged where the columns are crossed).  Rows of
         // the staging tile need no pad: the rows that a store's two halves write lie an odd number apart, and what is read back is one straight kilobyte a pass.

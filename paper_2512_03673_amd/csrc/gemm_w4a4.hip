@@ -113,11 +113,12 @@ hipError_t launch_plan(gemm::Plan plan, const gemm::Operands &o)
         return gemm::launch_tiled<Codes4, Tile<2, 2, 3, 3, 4, 1, 8>>(o);
     if (plan == Plan::kTile64x64 && gemm::deep_ring(gemm::tiles_of(o.M, o.N, 64, 64), e2m3::stages(o.K)))
         return gemm::launch_tiled<Codes4, Tile<2, 2, 1, 1, 4, 3, 8>>(o);
+    if (plan == Plan::kTile128x128 && gemm::tiles_of(o.M, o.N, 128, 128) <= 256) return gemm::launch_tiled<Codes4, Tile<4, 2, 1, 2, 4, 2, 8>>(o);
     switch (plan) {
         case Plan::kTile192x192: return gemm::launch_tiled<Codes4, Tile<2, 2, 3, 3, 2, 2, 8>>(o);
         case Plan::kTile256x128: return gemm::launch_tiled<Codes4, Tile<2, 2, 4, 2, 2, 2, 6>>(o);
         case Plan::kTile256x128w8: return gemm::launch_tiled<Codes4, Tile<4, 2, 2, 2, 3, 2, 8>>(o);
-        case Plan::kTile128x128: return gemm::launch_tiled<Codes4, Tile<2, 2, 2, 2, 3, 2, 8>>(o);
+        case Plan::kTile128x128: return gemm::launch_tiled<Codes4, Tile<4, 2, 1, 2, 3, 4, 8>>(o);
         case Plan::kTile64x64: return gemm::launch_tiled<Codes4, Tile<2, 2, 1, 1, 3, 4, 8>>(o);
         case Plan::kSplit32x64: return gemm::launch_small<gemm::Small4, 2, 4, 8, 2>(o);
         case Plan::kSplit32x32: return gemm::launch_small<gemm::Small4, 2, 2, 4, 3>(o);

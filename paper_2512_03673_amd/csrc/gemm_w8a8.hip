@@ -71,10 +71,12 @@ hipError_t launch_plan(gemm::Plan plan, const gemm::Operands &o)
     using gemm::Tile;
     if (plan == Plan::kTile128x192 && gemm::deep_ring(gemm::tiles_of(o.M, o.N, 128, 192), panel::k_panels(o.K)))
         return gemm::launch_tiled<Codes8, Tile<2, 2, 2, 3, 4, 1, 8>>(o);
+    if (plan == Plan::kTile128x128 && gemm::four_wavefronts_8(gemm::tiles_of(o.M, o.N, 128, 128), panel::k_panels(o.K)))
+        return gemm::launch_tiled<Codes8, Tile<2, 2, 2, 2, 4, 2, 8>>(o);
     switch (plan) {
         case Plan::kTile192x192: return gemm::launch_tiled<Codes8, Tile<2, 2, 3, 3, 3, 2, 8>>(o);
         case Plan::kTile256x128: return gemm::launch_tiled<Codes8, Tile<2, 2, 4, 2, 3, 2, 6>>(o);
-        case Plan::kTile128x128: return gemm::launch_tiled<Codes8, Tile<2, 2, 2, 2, 4, 2, 8>>(o);
+        case Plan::kTile128x128: return gemm::launch_tiled<Codes8, Tile<4, 2, 1, 2, 4, 4, 8>>(o);
         case Plan::kTile64x64: return gemm::launch_tiled<Codes8, Tile<2, 2, 1, 1, 4, 4, 8>>(o);
         case Plan::kSplit32x64: return gemm::launch_small<gemm::Small8, 2, 4, 8, 2>(o);
         case Plan::kSplit32x32: return gemm::launch_small<gemm::Small8, 2, 2, 4, 3>(o);
