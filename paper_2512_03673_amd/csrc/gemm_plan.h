@@ -127,6 +127,16 @@ inline int64_t tiles_of(int64_t M, int64_t N, int tm, int tn) { return ((M + tm 
 // become three, M512 x N3072 x K3072 8.2 / 8.45).  (No gain: 192 x 192 at 8 bits, 256 x 128 on eight wavefronts.)
 inline bool deep_ring(int64_t tiles, int64_t stages) { return tiles <= 256 && stages >= 16; }
 
+// Whether a small product goes in tiles of 48 x 32 instead of 16 x 32 or 32 x 64: where these are more than a round and tiles of 48 x 32 are one (of 32 x 32, which
+// take less time in one round, it would be more than one).  What it takes then is its operand bytes, each loaded by every tile that needs it, and 48 x 32 load W in 48-row
+// steps and half the X of 32 x 64 columns a block.  us, plan's tile / 48 x 32, operands changing: 8 bits M77 x N3072 x K3072 6.3 / 5.9, K12288 18.1 / 15.7, M809 x N340 x K4704 8.85 / 7.65,
+// M123 x N2240 x K3488 7.2 / 6.4; 4 bits M359 x N960 x K12992 13.3 / 11.4, M40 x N5056 x K2336 4.75 / 4.4, M48 x N4736 x K448 4.16 / 4.14; over 19 shapes 0.93, none slower; in place of
+// 32 x 32 in one round 1.06 over 26 (M233 x N741 x K2688 4.2 / 4.6).  80 x 16 to 80 x 32, the whole of M77 at once, 1.05 to 1.25.
+inline bool rows_of_48(Plan plan, int64_t M, int64_t N)
+{
+    return (plan == Plan::kSplit16x32 || plan == Plan::kSplit32x64) && tiles_of(M, N, 32, 32) > 256 && tiles_of(M, N, 48, 32) <= 256;
+}
+
 // 128 x 128 tiles are eight wavefronts of 32 x 64, two on each SIMD, which wait for their LDS-direct loads and fragments in turn; four of 64 x 64 read a
 // third less from LDS, but alone on their SIMD every wait is the matrix pipe's (a stage 0.30 us, of which MFMAs take 0.11).  At 4 bits with a ring of four
 // where every tile has its unit to itself, of three else, two blocks a unit.  us, four / eight wavefronts, operands changing: 4 bits, up to 256 tiles,
