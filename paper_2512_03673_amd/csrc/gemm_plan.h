@@ -20,12 +20,10 @@
 // tile taken costs 1.3 and 1.9 % more than the best, with constants fitted again to these 1.5 and 1.7 %.  (Tiles against each other;
 // the stores themselves: store_kind.)
 //
-// No constant has been fitted again since the way to the first MFMA was halved (gemm_tiled.h) or since deep_ring gives the 4-bit 64 x 64
-// tile four stages; the 8-bit 128 x 192 tile is predicted with its three as well.  What that costs, every tile timed against the one
-// taken with operands that change: 25 products of one to four rounds (4 bits, M 2000 ... 6000, N 3072 ... 12288, K 3072) 0.5 % on average, 4 % at
-// most (M6000 x N6144, 61.1 / 58.6 with 192 x 192); 30 with deep 64 x 64 tiles among the candidates 0.1 and 1.3 %; 45 and 40 drawn ones at 4 and 8 bits
-// (M 16 ... 9000, N 64 ... 12288, K 64 ... 15360) 2.3 and 2.7 %, most of it 128 x 128 tiles of a few stages: M263 x N6954 x K384 6.3 / 4.5 with
-// 64 x 64, 8 bits M7388 x N370 x K416 7.6 / 5.6.
+// No constant has been fitted again since the way to the first MFMA was halved (gemm_tiled.h), since deep_ring gives the 4-bit 64 x 64
+// tile four stages, or since the MFMAs are 16 x 16; the 8-bit 128 x 192 tile is predicted with its three stages as well.  What that costs, every tile timed against
+// the one taken, operands changing, over products of 5e9 to 2e11 (M 16 ... 16000, N 64 ... 12288, K 64 ... 15360): 4 bits, 45 of them, 0.5 % on average, 9 % at most (M1406 x N11520 x
+// K352 10.2 / 9.3 with 192 x 192, M11830 x N4480 x K1312 50.9 / 48.6 with 256 x 256), 8 bits, 30, 0.6 and 11 % (M10324 x N1088 x K736 13.0 / 11.7 with 128 x 192).
 #pragma once
 #include <stdint.h>
 
@@ -366,7 +364,8 @@ inline Plan choose(int64_t M, int64_t N, int64_t K)
     };
     auto paired = [&](const Paired &c) {
         const int64_t n = tiles(c.tm, c.tn), b = (n + 255) / 256;
-        consider(c.plan, n, 256, c.fixed + c.block * (float)b + stages * (c.pair * (float)(b / 2) + c.lone * (float)(b % 2)));
+        const int threads = c.plan == Plan::kTile128x128 ? 512 : 256;
+        consider(c.plan, n, threads, c.fixed + c.block * (float)b + stages * (c.pair * (float)(b / 2) + c.lone * (float)(b % 2)));
     };
     auto small = [&](const Small &c) {
         const int64_t n = tiles(c.tm, c.tn);
