@@ -29,18 +29,18 @@ I8_MFMA_PEAK_TOPS = 5000.0    # MI355X dense int8 MFMA, published (the figure th
 
 # HBM bytes per launch of the headline shape from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (KiB per
 # dispatch), each scaled by what the same counter reads for a plain copy of known size (x2.0 and
-# x1.0); the runs are in profiles/gemm_256x256_headline_counters.md.
+# x1.0); the runs are in profiles/gemm_16x16_mfma_lds_conflicts_counters.md (GEMM) and profiles/gemm_256x256_headline_counters.md (rotate+quantise).
 # These are stored measurements, not taken live (bench.py cannot run the profiler on itself): TRAFFIC_SOURCE
 # says which build of the kernels they were taken on.
-MEASURED_TRAFFIC_BYTES = {"gemm_cut_kernel": 104482 * 1024 * 2.0 + 110713 * 1024 * 1.0,
+MEASURED_TRAFFIC_BYTES = {"gemm_cut_kernel": 108231 * 1024 * 2.0 + 110620 * 1024 * 1.0,
                           "rotquant_kernel": 13863 * 1024 * 2.0 + 10386 * 1024 * 1.0}
-TRAFFIC_SOURCE = ("rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of `python bench.py --calibrate-copy`, "
-                  "kernel sources as of commit 66d3faf; see profiles/")
+TRAFFIC_SOURCE = ("rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, GEMM: kernel sources as of commit f74c71f, "
+                  "rotate+quantise: as of commit 66d3faf; see profiles/")
 # What a register-only loop of the GEMM's MFMA sustains on this chip on operands with the workload's bit
-# statistics (8 wavefronts per compute unit, no memory traffic; 9.9 POP/s on all-zero operands): the chip lowers its
+# statistics (8 wavefronts per compute unit, no memory traffic; 9.6 POP/s on all-zero operands, 8.1 with W as the row operand): the chip lowers its
 # clock with operand activity, so this, not the nominal figure, is what a perfect kernel could reach on this data.
-MEASURED_FP6_MFMA_LOOP_TOPS = 6600.0
-MFMA_LOOP_SOURCE = "register-only v_mfma_f32_32x32x64_f8f6f4 loop on workload-like FP6 operands, on an MI355X"
+MEASURED_FP6_MFMA_LOOP_TOPS = 8600.0
+MFMA_LOOP_SOURCE = "register-only v_mfma_f32_16x16x128_f8f6f4 loop on workload-like FP6 operands, X as the row operand, on an MI355X"
 PREWARM_MS = 200.0           # load put on the device before anything is timed, whatever --warmup says
 COPY_BYTES = 512 << 20       # size of the calibration copy (--calibrate-copy)
 COLD_FOOTPRINT = 768 << 20   # kernel A, cold: bytes touched between two uses of one buffer set
