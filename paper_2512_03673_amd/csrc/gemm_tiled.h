@@ -56,7 +56,7 @@
 namespace convrot {
 namespace gemm {
 
-// WGM x WGN wavefronts of XF x WF accumulator tiles (32 x 32) each, NS stage buffers, OCC wavefronts per SIMD that the
+// WGM x WGN wavefronts of XF x WF 32 x 32 shares of the output each (2 XF x 2 WF accumulator tiles), NS stage buffers, OCC wavefronts per SIMD that the
 // registers have to leave room for, BAND tile rows per band of the XCD-aware tile order.
 template <int WGM_, int WGN_, int XF_, int WF_, int NS_, int OCC_, int BAND_>
 struct Tile {
