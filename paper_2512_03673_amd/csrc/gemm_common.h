@@ -69,6 +69,7 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b)
 // such addresses in one store, and the compiler is told no more than that.
 typedef uint32_t u32x4_row __attribute__((ext_vector_type(4), aligned(2)));
 typedef uint32_t u32x2_row __attribute__((ext_vector_type(2), aligned(2)));
+typedef int32_t i32x2_row __attribute__((ext_vector_type(2), aligned(4)));      // two accumulators of a row
 
 // Eight bf16 of a row of Y; but for kCached `out` is a multiple of 16 bytes.  (The wait state is the one that a store of more than 64 bits
 // needs before its data registers are written again, which the compiler cannot see in the asm.)
