@@ -323,15 +323,13 @@ __device__ __forceinline__ void tile_product(const Product &p, int m0, int n0, u
     if constexpr (T::kSpare) {
         // The last stage, of which nothing is read ahead.  Between its steps all loads and LDS reads of the block are over, so that is the last meeting: the ring may
         // be written from there on, and scales that were parked before be read (with the meeting after it M5000 x N4000 x K256 13.25 us, so 13.0; where
-        // registers are short the compiler's copy of the stage spills).
+        // registers are short the compiler's copy of the stage spills).  The scales are plain stores, which the fences of __syncthreads keep on their side of the
+        // meeting; what the loop's meetings hand over has been loaded by inline assembly, which they wait for by hand.
         step(K0{}, No{}, std::true_type{}, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
         wait_loads(std::integral_constant<int, 0>{});
-        if constexpr (!RAW) {
-            park(tid);
-            wait_loads(std::integral_constant<int, 0>{});
-        }
-        __builtin_amdgcn_s_barrier();
+        if constexpr (!RAW) park(tid);
+        __syncthreads();
         step(K1{}, No{}, std::false_type{}, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
     }
