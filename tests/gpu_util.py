@@ -195,6 +195,38 @@ def bf16_ulp_diff(a_bits: np.ndarray, b_bits: np.ndarray) -> np.ndarray:
     return np.abs(key(a_bits) - key(b_bits))
 
 
+def check_product(bits: int, M: int, N: int, K: int, rows=slice(None), bias: bool = False):
+    """One product of whole random codes: its accumulators against the exact integer product bit for bit, `rows` of its output against
+    the oracle's dequantisation of that, and with `bias` all of its output with a bias, within the bound of its roundings."""
+    import oracle
+    from paper_2512_03673_amd import binding as cr
+    rng = np.random.default_rng(M + N + K)
+    top = 7 if bits == 4 else 127
+    qx, qw = (rng.integers(-top, top + 1, (r, K), dtype=np.int8) for r in (M, N))
+    sx, sw = (rng.uniform(0.5, 2.0, r).astype(np.float32) for r in (M, N))
+    dev, raw, gemm = ((codes4_to_dev, cr.convrot_w4a4_gemm_i32, cr.convrot_w4a4_gemm_dequant) if bits == 4 else
+                      (codes8_to_dev, cr.convrot_w8a8_gemm_i32, cr.convrot_w8a8_gemm_dequant))
+    Xq, Wq = dev(qx), dev(qw)
+    scales = torch.from_numpy(sx).cuda(), torch.from_numpy(sw).cuda()
+    acc = raw(Xq, Wq, M, N, K)
+    y = gemm(Xq, scales[0], Wq, scales[1], K)
+    torch.cuda.synchronize()
+    t = torch.from_numpy(qx).cuda().double() @ torch.from_numpy(qw).cuda().double().T      # whole numbers below 2^53: exact in doubles
+    ref = t.round().int()
+    assert torch.equal(acc, ref)
+    at = torch.from_numpy(np.arange(M)[rows]).cuda()
+    d = bf16_ulp_diff(bf16_to_host_bits(y[at]), oracle.dequant(ref[at].cpu().numpy(), sx[rows], sw))
+    assert d.max() <= 1
+    if bias:
+        b = torch.from_numpy(rng.standard_normal(N).astype(np.float32) * 50).cuda().to(torch.bfloat16)
+        yb = gemm(Xq, scales[0], Wq, scales[1], K, bias=b)
+        torch.cuda.synchronize()
+        # one rounding to bf16 (2^-8 of the value at most) of a value that took three fp32 roundings of the product and its sum with the bias
+        t *= scales[0].double()[:, None] * scales[1].double()
+        full = t + b.double()
+        assert ((yb.double() - full).abs() <= full.abs() * (2.0 ** -8 * (1 + 2.0 ** -20)) + (t.abs() + full.abs()) * 2.0 ** -22).all()
+
+
 # ---- which tile the GEMMs take for a product: csrc/gemm_plan.h, compiled for the host and asked
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2512_03673_amd", "csrc")
 PLANS = ("192x192", "256x128", "256x128w8", "128x128", "64x64", "split32x64", "split32x32", "split16x32", "split16x16", "256x256",

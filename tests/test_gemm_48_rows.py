@@ -2,12 +2,9 @@
 import shutil
 import subprocess
 
-import numpy as np
 import pytest
-import torch
 
-import oracle
-from gpu_util import CSRC, bf16_to_host_bits, bf16_ulp_diff, codes4_to_dev, codes8_to_dev, gemm_plans
+from gpu_util import CSRC, check_product, gemm_plans
 
 # bits, M, N, K, in tiles of 48 x 32: where these are at most 256 (M 77: N 4096, M 97: N 2720) and tiles of 32 x 32 more (M 48: from N 4097 on).
 SHAPES = [(8, 77, 3072, 3072, True), (8, 77, 4096, 1056, True), (8, 77, 4097, 1056, False), (8, 96, 2723, 1280, True), (8, 97, 2723, 1280, False), (8, 40, 5056, 2336, True),
@@ -28,25 +25,5 @@ def test_rule(tmp_path):
 @pytest.mark.gpu
 @pytest.mark.parametrize("bits,M,N,K", [s[:4] for s in SHAPES])
 def test_products(bits, M, N, K):
-    from paper_2512_03673_amd import binding as cr
     print(f"bits={bits} M={M} N={N} K={K} plan {gemm_plans([(M, N, K)])[(M, N, K)][bits == 8]}", flush=True)
-    rng = np.random.default_rng(M + N + K)
-    top = 7 if bits == 4 else 127
-    qx, qw = (rng.integers(-top, top + 1, (r, K), dtype=np.int8) for r in (M, N))
-    sx, sw = (rng.uniform(0.5, 2.0, r).astype(np.float32) for r in (M, N))
-    dev = codes4_to_dev if bits == 4 else codes8_to_dev
-    Xq, Wq = dev(qx), dev(qw)
-    acc = (cr.convrot_w4a4_gemm_i32 if bits == 4 else cr.convrot_w8a8_gemm_i32)(Xq, Wq, M, N, K)
-    gemm = cr.convrot_w4a4_gemm_dequant if bits == 4 else cr.convrot_w8a8_gemm_dequant
-    scales = torch.from_numpy(sx).cuda(), torch.from_numpy(sw).cuda()
-    bias = torch.from_numpy(rng.standard_normal(N).astype(np.float32) * 50).cuda().to(torch.bfloat16)
-    y, yb = (gemm(Xq, scales[0], Wq, scales[1], K, bias=b) for b in (None, bias))
-    torch.cuda.synchronize()
-    t = torch.from_numpy(qx).cuda().double() @ torch.from_numpy(qw).cuda().double().T      # whole numbers below 2^53: exact in doubles
-    ref = t.round().int()
-    assert torch.equal(acc, ref)
-    assert bf16_ulp_diff(bf16_to_host_bits(y), oracle.dequant(ref.cpu().numpy(), sx, sw)).max() <= 1
-    # one rounding to bf16 (2^-8 of the value at most) of a value that took three fp32 roundings of the product and its sum with the bias
-    t *= scales[0].double()[:, None] * scales[1].double()
-    full = t + bias.double()
-    assert ((yb.double() - full).abs() <= full.abs() * (2.0 ** -8 * (1 + 2.0 ** -20)) + (t.abs() + full.abs()) * 2.0 ** -22).all()
+    check_product(bits, M, N, K, bias=True)
