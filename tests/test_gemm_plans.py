@@ -38,7 +38,7 @@ SHAPES = {
 @pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not installed")
 def test_no_shape_takes_a_tile_that_cannot_be_launched():
     # a HIP launch has fewer than 2^32 threads; 192 x 192 tiles of 256 threads stay below it in all of these
-    threads = {"256x128w8": 512, "256x256": 512, "split32x64": 512, "split16x32": 512, "split16x16": 1024}
+    threads = {"256x128w8": 512, "256x256": 512, "128x128": 512, "split32x64": 512, "split16x32": 512, "split16x16": 1024}
     sizes = [2 ** e + d for e in (0, 4, 6, 7, 9, 12, 16, 20, 24, 27, 28, 29, 30) for d in (0, 1)] + [2 ** 31 - 256]
     shapes = [(M, N, K) for M in sizes for N in sizes for K in (32, 128, 1024, 65536) if -(-M // 192) * -(-N // 192) * 256 < 2 ** 32 - 2048]
     assert (1, 2 ** 30, 32) in shapes and (2 ** 30, 64, 128) in shapes
