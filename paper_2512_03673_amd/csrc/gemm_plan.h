@@ -341,9 +341,11 @@ inline Plan choose(int64_t M, int64_t N, int64_t K)
     static constexpr Alone w8 = {512, 2.00f, 3.84f, 0.419f, 0.80f};                                                  // 256 x 128, 4 bits
     static constexpr Alone whole = BITS == 4 ? Alone{512, 1.10f, 5.83f, 0.606f, 0.69f} : Alone{512, 0.02f, 6.13f, 0.691f, 0.61f};     // 256 x 256
 
-    // 128 x 192, 4 bits: one round of up to 256 tiles where 256 x 128 leaves units idle.  (Its fit times 1.05: a draw goes to
-    // the tiles that it is compared with, whose fits are of more shapes.)
-    static constexpr Alone middle = {256, 1.70f, 4.55f, 0.347f, 0.98f};
+    // 128 x 192, 4 bits: one round of up to 256 tiles where 256 x 128 leaves units idle.  Six wavefronts of 64 x 64: an LDS-direct load takes longer to issue than a
+    // 16 x 16 MFMA, and of four wavefronts, one on each SIMD, every load is the matrix pipe's wait.  us, operands changing, four / six: M801 x N5440 x K2432 10.5 / 9.7,
+    // M2637 x N1728 x K4320 15.25 / 14.1, M512 x N12288 x K3072 16.3 / 15.8, M532 x N7752 x K4384 20.3 / 20.5; over 87 shapes 0.95, 1.01 at most.  (The fit is of four
+    // wavefronts, times 1.05: a draw goes to the tiles that it is compared with, whose fits are of more shapes.)
+    static constexpr Alone middle = {384, 1.70f, 4.55f, 0.347f, 0.98f};
 
     // 192 x 192, 4 bits, with a deep ring: between 128 x 192, of which such a product has more than a round, and 256 x 256, which leave units idle.
     static constexpr Alone square = {256, 1.99f, 4.53f, 0.493f, 0.532f};

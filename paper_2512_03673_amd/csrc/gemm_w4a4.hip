@@ -126,7 +126,7 @@ hipError_t launch_plan(gemm::Plan plan, const gemm::Operands &o)
         case Plan::kSplit16x32: return gemm::launch_small<gemm::Small4, 1, 2, 8, 4>(o);
         case Plan::kSplit16x16: return gemm::launch_small<gemm::Small4, 1, 1, 16, 4>(o);
         case Plan::kTile256x256: return launch_256x256(o);
-        case Plan::kTile128x192: return gemm::launch_tiled<Codes4, Tile<2, 2, 2, 3, 4, 1, 8>>(o);
+        case Plan::kTile128x192: return gemm::launch_tiled<Codes4, Tile<2, 3, 2, 2, 4, 2, 8>>(o);
         default: return hipErrorInvalidValue;
     }
 }
