@@ -285,13 +285,17 @@ inline int parts_of_last_tiles(int64_t per_xcd)
 
 // Whether every other XCD begins with its parts instead of ending with them.  All units of a launch otherwise finish a round at once, and the rounds'
 // outputs go to memory in bursts that the next tiles wait behind; half a tile apart, one half of the chip stores while the other multiplies.
-// Long products have little to gain, and lose the operands that XCDs ask for at the same time from the same cache.  us, last / first on odd XCDs: M4608 x N12288 x K3072
-// 78.8 / 75.9, M4155 x N9216 x K1536 37.5 / 34.5, M5754 x N9152 x K2048 58.0 / 54.6; over 39 shapes of K 1024 ... 3072 4 % less (two slower, M11878 x N1664 x K3072
-// 35.8 / 37.0); M7095 x N5248 x K4096 73.8 / 72.3, but M16525 x N1216 x K3584 40.9 / 42.9, M16234 x N1472 x K4608 56.2 / 60.8, and over 34 shapes of K 3584 ... 12288
-// 1.3 % more.  With the four XCDs of one half of the chip first 80, with all of them 75.4; half a tile apart in products whose rounds come out
+// Outputs left to the caches make no such bursts.  Long products have little to gain, and lose the operands that XCDs ask for at the same time from the same cache, those of
+// few columns of tiles, whose XCDs walk the same ones, before the others.  us, last / first on odd XCDs, operands changing:
+//   inside   M4608 x N12288 x K3072 78.2 / 75.5, M4155 x N9216 x K1536 38.0 / 34.1, M16659 x N1088 x K1056 18.9 / 17.8, M12452 x N1728 x K2080 27.7 / 26.1,
+//            M8854 x N2112 x K3168 31.1 / 31.2, M9469 x N3712 x K3104 54.5 / 55.3; over 84 shapes of K 1024 ... 3328 0.946, 1.015 at most
+//   narrow and of more stages  M16078 x N1280 x K2912 32.7 / 39.0, M11872 x N1792 x K2720 32.6 / 34.5, M14049 x N1280 x K2624 27.2 / 27.0; over 9 shapes 1.075
+//   rows that are not whole lines  M15579 x N2501 x K1984 57.6 / 64.5, M2230 x N10320 x K1152 26.7 / 31.2, M8087 x N2659 x K2368 44.3 / 38.0; over 95 shapes 1.010, 50 slower, 33 faster
+//   longer   M7095 x N5248 x K4096 73.8 / 72.3, but M16525 x N1216 x K3584 40.9 / 42.9; over 34 shapes of K 3584 ... 12288 1.013
+// With the four XCDs of one half of the chip first M4608 x N12288 x K3072 takes 80, with all of them 75.4; half a tile apart in products whose rounds come out
 // even, by parts for whole tiles, 0 to 30 % slower.
 constexpr int kPartsFirst = 1 << 8;      // (fewer than 5 * 32 tiles of an XCD are whole)
-constexpr bool parts_first(int64_t stages) { return stages <= 26; }
+constexpr bool parts_first(Store store, int64_t N, int64_t stages) { return store == Store::kPast && stages <= (N > 7 * 256 ? 26 : 17); }
 
 // The work of an XCD's `turn`-th block: a tile of its range, whole or one part of it.  `how`: the tiles that are whole, and kPartsFirst.
 struct CutTurn {

@@ -515,7 +515,7 @@ hipError_t launch_cut(const Operands &o, int cut)
     if (!launchable((int64_t)tiles_m * tiles_n * (T::TM / P::TM) * (T::TN / P::TN), T::kThreads)) return hipErrorInvalidValue;
     const TileOrder t = tile_order(tiles_m, tiles_n, band_rows<T>(tiles_m));
     const int whole = t.per_xcd - cut, grid = (whole + cut * (T::TM / P::TM) * (T::TN / P::TN)) * kNumXcd;
-    const int first = parts_first(C::stages(o.K)) ? kPartsFirst : 0;
+    const int first = parts_first(o.store, o.N, C::stages(o.K)) ? kPartsFirst : 0;
     auto go = [&](auto kernel) { return launch_order(kernel, o, t, t.rows | (whole | first) << 8, grid, T::kThreads); };
     return o.acc ? go(gemm_cut_kernel<C, true, T, P>) : go(gemm_cut_kernel<C, false, T, P>);
 }

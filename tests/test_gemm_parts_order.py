@@ -15,7 +15,9 @@ SOURCE = r"""
 using namespace convrot::gemm;
 int main()
 {
-    static_assert(parts_first(26) && !parts_first(27), "line");
+    constexpr Store past = Store::kPast;
+    static_assert(parts_first(past, 1793, 26) && !parts_first(past, 12288, 27) && parts_first(past, 1792, 17) && !parts_first(past, 1792, 18), "lines");
+    static_assert(!parts_first(Store::kCached, 12288, 8) && !parts_first(Store::kThrough, 12288, 8), "stores");
     for (int per = 32; per < 5 * 32; ++per) {
         const int parts = parts_of_last_tiles(per);
         if (parts == 1) continue;
@@ -49,7 +51,9 @@ def test_every_tile_or_each_of_its_parts_once(tmp_path):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,N,K", [(4100, 4600, 3328), (4100, 4600, 3360), (4360, 4870, 3328), (4360, 4870, 3360)])      # quarters, halves; 26 and 27 stages
+@pytest.mark.parametrize("M,N,K", [(4100, 4608, 3328), (4100, 4608, 3360), (4360, 4864, 3328), (4360, 4864, 3360),      # quarters, halves; 26 and 27 stages
+                                   (15888, 1216, 2176), (15888, 1216, 2208),                                            # narrow: 17 and 18
+                                   (4100, 4600, 3328), (4100, 4600, 3360), (4360, 4870, 3328), (4360, 4870, 3360)])     # rows that are not whole lines
 def test_both_orders(M, N, K):
     assert gemm_plans([(M, N, K)])[(M, N, K)][0] == "256x256" and 32 < (-(-M // 256) * -(-N // 256) + 7) // 8 <= 48
     print(f"M={M} N={N} K={K}", flush=True)
