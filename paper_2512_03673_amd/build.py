@@ -24,7 +24,7 @@ FLAGS = [
     "-mllvm", "-amdgpu-kernarg-preload-count=16",
     # pairs of float operations made into vectors are taken apart again where there are no packed ones, but their DPP operands no longer go into the
     # instruction: 3 to 4 moves an element of the 8-bit rotate+quantise at g >= 256 (us, cold: [4608, 3072] g256 11.4 -> 10.2, g1024 12.9 -> 11.3, [4608, 12288]
-    # g256 34.2 -> 32.9; 4 bits and smaller groups the same)
+    # g256 34.2 -> 32.9).  4 bits and short inputs are the same; the larger ones of 8-bit codes need fewer registers so, which rotquant.hip (kMostWaves) answers.
     "-fno-slp-vectorize",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]

@@ -82,8 +82,19 @@ struct Split {
 template <int G, int BITS, int U, int RPW, int WPR>
 constexpr bool kThrough = RPW >= 2 && WPR >= 2 && (BITS == 8 || G >= 64 || U == 2 || WPR <= 3);
 
+// Wavefronts that a SIMD has at most, by registers set aside: eight by their number, six where memory takes no more of them at once well.  At 8 bits the kernels need
+// 52 to 60 registers (73 to 75 with the SLP vectoriser, build.py, which left room for six) and rows of 4097 to 8192 elements, a block of three or four wavefronts each,
+// took up to a fifth longer with eight; at g <= 64 also rows that lie two in a block.  us, eight / six:
+//   rows of a block  [4399, 6016] g64 17.3 / 15.9 (on another box 19.6 / 16.1), [3677, 6144] g64 15.7 / 14.3, [10079, 8160] g16 43.9 / 41.5, [4608, 5120] g256 19.7 / 17.3,
+//                    g1024 21.1 / 19.9, g4 15.4 / 14.7; over 114 inputs 0.97, 1.01 at most.  Five wavefronts and more (six of [4608, 12288] g1024 36.4 / 38.9) keep eight
+//   two in a block   1025 to 4096 elements, g64, 31 inputs of 1.5e7 elements and more 0.95, 62 smaller ones 1.00 (1.01 at most), g <= 16, twelve, 0.985; but [4608, 3072]
+//                    g256 10.3 / 10.7, g1024 11.7 / 11.9
+template <int G, int BITS, int U, int RPW, int WPR>
+constexpr int kMostWaves = BITS == 8 && WPR >= 2 && WPR <= 4 && (RPW == 1 ? U == 2 : G <= 64) ? 6 : 8;
+
 template <int G, int BITS, int U, int RPW, int WPR, int S>
-__global__ __launch_bounds__((Split<U, RPW, WPR, S>::kThreads), (Split<U, RPW, WPR, S>::kOccupancy)) void rotquant_kernel(
+__global__ __launch_bounds__((Split<U, RPW, WPR, S>::kThreads))
+__attribute__((amdgpu_waves_per_eu((Split<U, RPW, WPR, S>::kOccupancy), (kMostWaves<G, BITS, U, RPW, WPR>)))) void rotquant_kernel(
     const uint16_t *__restrict__ X, int64_t rows, int K, uint8_t *__restrict__ Xq, float *__restrict__ scale)
 {
     using Sp = Split<U, RPW, WPR, S>;
