@@ -125,14 +125,21 @@ inline int64_t tiles_of(int64_t M, int64_t N, int tm, int tn) { return ((M + tm 
 // become three, M512 x N3072 x K3072 8.2 / 8.45).  (No gain: 192 x 192 at 8 bits, 256 x 128 on eight wavefronts.)
 inline bool deep_ring(int64_t tiles, int64_t stages) { return tiles <= 256 && stages >= 16; }
 
-// Whether a small product goes in tiles of 48 x 32 instead of 16 x 32 or 32 x 64: where these are more than a round and tiles of 48 x 32 are one (of 32 x 32, which
-// take less time in one round, it would be more than one).  What it takes then is its operand bytes, each loaded by every tile that needs it, and 48 x 32 load W in 48-row
-// steps and half the X of 32 x 64 columns a block.  us, plan's tile / 48 x 32, operands changing: 8 bits M77 x N3072 x K3072 6.3 / 5.9, K12288 18.1 / 15.7, M809 x N340 x K4704 8.85 / 7.65,
-// M123 x N2240 x K3488 7.2 / 6.4; 4 bits M359 x N960 x K12992 13.3 / 11.4, M40 x N5056 x K2336 4.75 / 4.4, M48 x N4736 x K448 4.16 / 4.14; over 19 shapes 0.93, none slower; in place of
-// 32 x 32 in one round 1.06 over 26 (M233 x N741 x K2688 4.2 / 4.6).  80 x 16 to 80 x 32, the whole of M77 at once, 1.05 to 1.25.
-inline bool rows_of_48(Plan plan, int64_t M, int64_t N)
+// Whether a small product goes in tiles of 48 x 32 instead of 32 x 64 or 16 x 32: where 32 x 32, which take less time in one round, would be more than a round and
+// 48 x 32 are one.  What it takes then is its operand bytes, each loaded by every tile that needs it.  Tiles of 32 x 64 are mostly one round too, of two thirds as many blocks that
+// load a fifth more rows each.  Tiles of 16 x 32 are two rounds and load W three times for twice in 48-row steps, but long chains of stages are what gains by it; in short ones, whose
+// few blocks wait for a stage's latency, more of them are better.  us, plan's tile / 48 x 32, operands changing:
+//   32 x 64  4 bits M40 x N5056 x K2336 4.75 / 4.4, M118 x N2620 x K9216 14.05 / 11.75, M48 x N4736 x K448 4.16 / 4.14; 8 bits M180 x N1664 x K15136
+//            26.1 / 22.6; over 40 shapes each 0.92 and 0.93, none slower
+//   16 x 32, inside   4 bits M104 x N2304 x K12864 17.7 / 14.7, M48 x N4920 x K8576 13.9 / 13.2; M142 x N1792 x K4320 7.2 / 5.9, over 43 shapes 0.93, none slower; 8 bits M77 x N3072 x K3072 6.3 / 5.9, N3200 x K5600 12.0 / 10.2, over 67 0.945, none slower
+//            outside  4 bits, one row of tiles, M41 x N4416 x K3872 5.8 / 5.95 (6.3 / 6.9), M34 x N4181 x K4736 7.4 / 8.0, of 35 to 39 stages as many faster by 3 %; more rows M333 x N768 x K4032 5.8 / 5.95;
+//            8 bits M76 x N2752 x K448 3.3 / 3.4, over 83 1.01, 49 slower
+// (In place of 32 x 32 in one round 1.06 over 26, M233 x N741 x K2688 4.2 / 4.6.  80 x 16 to 80 x 32, the whole of M77 at once, 1.05 to 1.25.)
+template <int BITS>
+inline bool rows_of_48(Plan plan, int64_t M, int64_t N, int64_t stages)
 {
-    return (plan == Plan::kSplit16x32 || plan == Plan::kSplit32x64) && tiles_of(M, N, 32, 32) > 256 && tiles_of(M, N, 48, 32) <= 256;
+    const bool gains = plan == Plan::kSplit32x64 || (plan == Plan::kSplit16x32 && stages >= (BITS == 8 ? 18 : M > 48 ? 34 : 40));
+    return gains && tiles_of(M, N, 32, 32) > 256 && tiles_of(M, N, 48, 32) <= 256;
 }
 
 // 128 x 128 tiles are eight wavefronts of 32 x 64, two on each SIMD, which wait for their LDS-direct loads and fragments in turn; four of 64 x 64 read a

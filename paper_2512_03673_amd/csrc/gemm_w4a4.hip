@@ -113,7 +113,7 @@ hipError_t launch_plan(gemm::Plan plan, const gemm::Operands &o)
         return gemm::launch_tiled<Codes4, Tile<2, 2, 3, 3, 4, 1, 8>>(o);
     if (plan == Plan::kTile64x64 && gemm::deep_ring(gemm::tiles_of(o.M, o.N, 64, 64), e2m3::stages(o.K)))
         return gemm::launch_tiled<Codes4, Tile<2, 2, 1, 1, 4, 3, 8>>(o);
-    if (gemm::rows_of_48(plan, o.M, o.N)) return gemm::launch_small<gemm::Small4, 3, 2, 8, 2>(o);
+    if (gemm::rows_of_48<4>(plan, o.M, o.N, e2m3::stages(o.K))) return gemm::launch_small<gemm::Small4, 3, 2, 8, 2>(o);
     if (plan == Plan::kTile128x128 && gemm::tiles_of(o.M, o.N, 128, 128) <= 256) return gemm::launch_tiled<Codes4, Tile<4, 2, 1, 2, 4, 2, 8>>(o);
     switch (plan) {
         case Plan::kTile192x192: return gemm::launch_tiled<Codes4, Tile<2, 2, 3, 3, 2, 2, 8>>(o);

@@ -71,7 +71,7 @@ hipError_t launch_plan(gemm::Plan plan, const gemm::Operands &o)
     using gemm::Tile;
     if (plan == Plan::kTile128x192 && gemm::deep_ring(gemm::tiles_of(o.M, o.N, 128, 192), panel::k_panels(o.K)))
         return gemm::launch_tiled<Codes8, Tile<2, 2, 2, 3, 4, 1, 8>>(o);
-    if (gemm::rows_of_48(plan, o.M, o.N)) return gemm::launch_small<gemm::Small8, 3, 2, 8, 2>(o);
+    if (gemm::rows_of_48<8>(plan, o.M, o.N, panel::k_panels(o.K))) return gemm::launch_small<gemm::Small8, 3, 2, 8, 2>(o);
     if (plan == Plan::kTile128x128 && gemm::four_wavefronts_8(gemm::tiles_of(o.M, o.N, 128, 128), panel::k_panels(o.K)))
         return gemm::launch_tiled<Codes8, Tile<2, 2, 2, 2, 4, 2, 8>>(o);
     switch (plan) {
