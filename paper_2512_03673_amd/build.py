@@ -13,7 +13,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libconvrot.so")
 CALLS = os.path.join(HERE, "_torch_calls.so")
-SOURCES = ("convrot_api.hip", "rotquant.hip", "gemm_w4a4.hip", "gemm_w8a8.hip", "forward_small.hip")
+SOURCES = ("convrot_api.hip", "rotquant.hip", "rotquant_lanes8.hip", "gemm_w4a4.hip", "gemm_w8a8.hip", "forward_small.hip")
+OWN_FLAGS = {"rotquant_lanes8.hip": ("-fno-slp-vectorize",)}      # the file says why
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
@@ -22,10 +23,6 @@ FLAGS = [
     # kernels find their first arguments in registers when they start, instead of waiting 0.3-0.6 us for a scalar load from a cold cache
     # (us: M1 x N9216 x K3072 forward 6.44 -> 6.14, M77 x N3072 x K3072 at 8 bits 10.87 -> 10.65, rotate+quantise [4608, 3072] at g = 256 10.4 -> 9.9)
     "-mllvm", "-amdgpu-kernarg-preload-count=16",
-    # pairs of float operations made into vectors are taken apart again where there are no packed ones, but their DPP operands no longer go into the
-    # instruction: 3 to 4 moves an element of the 8-bit rotate+quantise at g >= 256 (us, cold: [4608, 3072] g256 11.4 -> 10.2, g1024 12.9 -> 11.3, [4608, 12288]
-    # g256 34.2 -> 32.9).  4 bits and short inputs are the same; the larger ones of 8-bit codes need fewer registers so, which rotquant.hip (kMostWaves) answers.
-    "-fno-slp-vectorize",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
 
@@ -39,7 +36,7 @@ def build(verbose: bool = True, extra_flags=(), out: str = LIB) -> str:
 
     def compile_one(src: str) -> str:
         obj = os.path.join(objdir, src.replace(".hip", ".o"))
-        cmd = ["hipcc", *FLAGS, *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = ["hipcc", *FLAGS, *OWN_FLAGS.get(src, ()), *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.run(cmd, check=True)

@@ -60,7 +60,7 @@ def test_rotquant(K, bits):
 @pytest.mark.parametrize("bits", (4, 8))
 @pytest.mark.parametrize("K", (1280, 2048, 3072, 4096, 5120, 8192, 12288))
 def test_rotquant_of_many_rows(K, bits):
-    """Past the lines up to which a row is a block of its own (csrc/rotquant.hip): two rows side by side in a wavefront up to K = 4096, in units
+    """Past the lines up to which a row is a block of its own (csrc/rotquant_kernel.h): two rows side by side in a wavefront up to K = 4096, in units
     and (4 bits, from some 2e7 elements on) in whole chunks, single rows of whole chunks beyond.  The first and the last row, each of another half
     of its pair, are spoiled."""
     from paper_2512_03673_amd import binding as cr

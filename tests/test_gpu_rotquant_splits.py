@@ -46,7 +46,7 @@ def test_edges_of_the_splits(K, bits):
 @pytest.mark.parametrize("bits", (4, 8))
 @pytest.mark.parametrize("K", (1056, 2048, 3104, 4096, 6176, 10240, 12288))
 def test_splits_of_many_rows(K, bits):
-    """Past the lines of csrc/rotquant.hip (launch_g): 12 wavefronts of 1024 elements a compute unit; at 4 bits 2e7 and 3.4e7 elements.  Rows of
+    """Past the lines of csrc/rotquant_kernel.h (launch_g): 12 wavefronts of 1024 elements a compute unit; at 4 bits 2e7 and 3.4e7 elements.  Rows of
     scales from 2^-60 to 2^60, columns e^-4 to e^4 apart; the first rows, the last ones and some between against the oracle."""
     from paper_2512_03673_amd import binding as cr
     size, rotquant = (cr.packed_bytes, cr.convrot_rotquant_act) if bits == 4 else (cr.packed_bytes8, cr.convrot_rotquant_act8)
