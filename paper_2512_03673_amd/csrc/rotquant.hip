@@ -90,7 +90,7 @@ hipError_t launch_bits(const void *X, int64_t rows, int64_t K, int group, void *
         case 64: return launch_g<64, BITS>(X, rows, (int)K, Xq, scale, stream);
         default: break;
     }
-    if constexpr (BITS == 8) return launch_rotquant_lanes8(X, rows, K, group, Xq, scale, stream);
+    if constexpr (BITS == 8) return rotquant_lanes8(X, rows, K, group, Xq, scale, stream);
     else if (group == 256) return launch_g<256, BITS>(X, rows, (int)K, Xq, scale, stream);
     else if (group == 1024) return launch_g<1024, BITS>(X, rows, (int)K, Xq, scale, stream);
     return hipErrorInvalidValue;

@@ -25,6 +25,8 @@
 
 namespace convrot {
 
+namespace {
+
 // All but the last N * n of this wavefront's loads have landed (n is known where the call is inlined).
 template <int N>
 __device__ __forceinline__ void wait_loads(int n)
@@ -48,6 +50,8 @@ __device__ __forceinline__ void store8(void *out, u32x2 v)
     if constexpr (THROUGH) asm volatile("global_store_dwordx2 %0, %1, off sc1" :: "v"(out), "v"(v) : "memory");
     else *reinterpret_cast<u32x2 *>(out) = v;
 }
+
+}  // namespace
 
 // A set is what a wavefront rotates at a time: 16 U columns, U units a lane, 16 U / RPW columns of each of RPW consecutive rows.
 // A wavefront holds S sets of its rows and WPR wavefronts side by side, one block, hold the whole rows.
@@ -227,6 +231,8 @@ __attribute__((amdgpu_waves_per_eu((Split<U, RPW, WPR, S>::kOccupancy), (kMostWa
     }
 }
 
+namespace {      // (not exported: a weak definition could be taken over by another library of the process)
+
 template <int G, int BITS, int U, int RPW, int WPR, int S>
 hipError_t launch_rows(const void *X, int64_t rows, int K, void *Xq, float *scale, hipStream_t stream)
 {
@@ -318,5 +324,7 @@ hipError_t launch_g(const void *X, int64_t rows, int K, void *Xq, float *scale, 
     }
 #undef CONVROT_ROWS
 }
+
+}  // namespace
 
 }  // namespace convrot

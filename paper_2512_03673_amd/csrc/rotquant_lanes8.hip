@@ -9,7 +9,7 @@
 
 namespace convrot {
 
-hipError_t launch_rotquant_lanes8(const void *X, int64_t rows, int64_t K, int group, void *Xq, float *scale, hipStream_t stream)
+hipError_t rotquant_lanes8(const void *X, int64_t rows, int64_t K, int group, void *Xq, float *scale, hipStream_t stream)
 {
     switch (group) {
         case 256: return launch_g<256, 8>(X, rows, (int)K, Xq, scale, stream);
