@@ -13,8 +13,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libconvrot.so")
 CALLS = os.path.join(HERE, "_torch_calls.so")
-SOURCES = ("convrot_api.hip", "rotquant.hip", "rotquant_lanes8.hip", "gemm_w4a4.hip", "gemm_w8a8.hip", "forward_small.hip")
-OWN_FLAGS = {"rotquant_lanes8.hip": ("-fno-slp-vectorize",)}      # the file says why
+SOURCES = ("convrot_api.hip", "rotquant.hip", "lanes8.hip", "gemm_w4a4.hip", "gemm_w8a8.hip", "forward_small.hip")
+OWN_FLAGS = {"lanes8.hip": ("-fno-slp-vectorize",)}      # the file says why
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",

@@ -12,8 +12,6 @@ namespace convrot {
 // codes in the layout of e2m3_layout.h, bits 8: one int8 per code in the layout of panel_layout.h).
 hipError_t launch_rotquant(const void *X, int64_t rows, int64_t K, int group, int bits, void *Xq, float *scale,
                            hipStream_t stream);
-// ... of 8-bit codes and groups of 256 and 1024 (rotquant_lanes8.hip).
-hipError_t rotquant_lanes8(const void *X, int64_t rows, int64_t K, int group, void *Xq, float *scale, hipStream_t stream);
 
 // 4-bit code matrix (FP6 layout) -> int8 codes [rows, K], row-major.
 hipError_t launch_unpack_codes(const void *Xq, int64_t rows, int64_t K, int8_t *codes, hipStream_t stream);

@@ -1,4 +1,4 @@
-// Launches of the rotate+quantise kernel (rotquant_kernel.h), but for 8-bit codes of g >= 256 (rotquant_lanes8.hip); and two diagnostics, the
+// Launches of the rotate+quantise kernel (rotquant_kernel.h), but for 8-bit codes of g >= 256 (lanes8.hip); and two diagnostics, the
 // rotated rows' absmax and the codes as plain integers.
 #include "rotquant_kernel.h"
 

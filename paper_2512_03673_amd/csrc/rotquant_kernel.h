@@ -25,6 +25,9 @@
 
 namespace convrot {
 
+// The launches for 8-bit codes of g >= 256 (lanes8.hip).
+hipError_t rotquant_lanes8(const void *X, int64_t rows, int64_t K, int group, void *Xq, float *scale, hipStream_t stream);
+
 namespace {
 
 // All but the last N * n of this wavefront's loads have landed (n is known where the call is inlined).
@@ -84,7 +87,7 @@ template <int G, int BITS, int U, int RPW, int WPR>
 constexpr bool kThrough = RPW >= 2 && WPR >= 2 && (BITS == 8 || G >= 64 || U == 2 || WPR <= 3);
 
 // Wavefronts that a SIMD has at most, by registers set aside: eight by their number, six where memory takes no more of them at once well.  8-bit codes of g >= 256, built
-// without the SLP vectoriser (rotquant_lanes8.hip), need 60 registers instead of 73, and rows of 4097 to 8192 elements, a block of three or four wavefronts each, are slower with the
+// without the SLP vectoriser (lanes8.hip), need 60 registers instead of 73, and rows of 4097 to 8192 elements, a block of three or four wavefronts each, are slower with the
 // eight that then fit.  us, eight / six: [4608, 5120] g256 19.7 / 17.3, g1024 21.1 / 19.9, [3126, 7168] g256 18.1 / 16.7, over 44 inputs 0.986, 1.01 at most.  Five
 // wavefronts and more (six of [4608, 12288] g1024 36.4 / 38.9) and two rows a block ([4608, 3072] g256 10.3 / 10.7, g1024 11.7 / 11.9) keep eight.
 template <int G, int BITS, int U, int RPW, int WPR>
