@@ -21,9 +21,11 @@
 // the stores themselves: store_kind.)
 //
 // No constant has been fitted again since the way to the first MFMA was halved (gemm_tiled.h), since deep_ring gives the 4-bit 64 x 64
-// tile four stages, or since the MFMAs are 16 x 16; the 8-bit 128 x 192 tile is predicted with its three stages as well.  What that costs, every tile timed against
-// the one taken, operands changing, over products of 5e9 to 2e11 (M 16 ... 16000, N 64 ... 12288, K 64 ... 15360): 4 bits, 45 of them, 0.5 % on average, 9 % at most (M1406 x N11520 x
-// K352 10.2 / 9.3 with 192 x 192, M11830 x N4480 x K1312 50.9 / 48.6 with 256 x 256), 8 bits, 30, 0.6 and 11 % (M10324 x N1088 x K736 13.0 / 11.7 with 128 x 192).
+// tile four stages, since the MFMAs are 16 x 16, or since 128 x 128 tiles are eight wavefronts and 4-bit 128 x 192 ones six; the 8-bit 128 x 192 tile is predicted with its three
+// stages as well.  What that costs, every tile timed against the one taken, operands changing, kernels as of d223d18, over products of 5e9 to 2e11 (M 16 ... 16000, N 64 ... 12288,
+// K 64 ... 15360): 4 bits, 250 of them, 0.9 % on average, 19 % at most (M2550 x N4544 x K896 15.4 / 13.15 with 256 x 128, M771 x N4800 x K1632 9.65 / 8.2 with 128 x 192,
+// M10694 x N5683 x K352 47.9 / 43.0 with 128 x 128), 8 bits, 200, 1.8 and 24 % (M2427 x N12032 x K352 26.6 / 21.4 with 256 x 128, M13413 x N441 x K1632 22.5 / 19.0 with 128 x 128).
+// At 4 bits it is 128 x 128, whose constants are of four wavefronts, in half of the products that lose 2 % and more; at 8 bits 64 x 64 where K split is better in a third of them.
 #pragma once
 #include <stdint.h>
 
@@ -146,7 +148,8 @@ inline bool rows_of_48(Plan plan, int64_t M, int64_t N, int64_t stages)
 // third less from LDS, but alone on their SIMD every wait is the matrix pipe's (a stage 0.30 us, of which MFMAs take 0.11).  At 4 bits with a ring of four
 // where every tile has its unit to itself, of three else, two blocks a unit.  us, four / eight wavefronts, operands changing: 4 bits, up to 256 tiles,
 // M1619 x N1472 x K6432 16.6 / 15.3, M307 x N7296 x K5088 18.5 / 15.9, M336 x N5444 x K704 6.05 / 5.1, M424 x N6104 x K384 4.47 / 4.53; over 30 shapes 0.93,
-// 1.01 at worst; more tiles, M7771 x N916 x K128 7.25 / 6.45, M2405 x N6769 x K64 11.2 / 10.5, M16544 x N640 x K832 13.2 / 13.4, over 16 shapes 0.96.  Sixteen wavefronts of 32 x 32: 1.02.
+// 1.01 at worst; more tiles, M7771 x N916 x K128 7.25 / 6.45, M2405 x N6769 x K64 11.2 / 10.5, M16544 x N640 x K832 13.2 / 13.4, over 16 shapes 0.96.  Sixteen wavefronts of 32 x 32: 1.02.  (Against
+// four wavefronts on 32 x 32 MFMAs, 111 products of 257 to 600 tiles take 0.925, but M815 x N9344 x K768 9.5 / 9.75, M811 x N8256 x K544 8.1 / 8.3, M875 x N8448 x K512 8.15 / 8.35.)
 // 8 bits, up to 256 tiles of up to 19 stages, M702 x N4580 x K384 6.5 / 5.5, M285 x N8951 x K1184 8.3 / 7.4, M522 x N4096 x K128 4.34 / 4.36, over 16 shapes 0.95; more tiles,
 // M4990 x N1370 x K288 8.1 / 7.35, over 14 shapes 0.97; but longer products of up to 256 tiles M575 x N6336 x K1600 8.55 / 8.8, M1704 x N2304 x K2016 10.15 / 10.5,
 // M638 x N4544 x K10816 49.1 / 48.8, over 12 shapes 1.01: these keep four.

@@ -30,15 +30,15 @@
 // order) instead of queueing up in a burst.
 //
 // MFMAs are 16 x 16, 128 codes deep at 4 bits and 64 at 8, with the X fragment as the row operand: of the forms that the chip runs at one rate this
-// takes the least power, and power is what the large products are bound by.  A register-only loop on codes like a layer's, POP/s, 32 x 32 with W / X as the row
+// takes the least power, and the clock falls with power.  A register-only loop on codes like a layer's, POP/s, 32 x 32 with W / X as the row
 // operand : 16 x 16 with W / X: 4 bits, X of g = 16 (one code in seven not zero) 7.6 / 7.2 : 8.1 / 8.6, g = 64 6.7 / 6.6 : 7.4 / 7.5, g = 1024 6.4 / 6.4 : 7.2 / 7.2; 8 bits
 // 3.5 : 4.2; zeros 9.7 : 9.6 and 4.9 : 4.8.  The GEMM alone, us, 32 x 32 with W / 16 x 16 with X, operands changing: 4 bits M4608 x N12288 x K3072 77.3 / 74.7,
 // M16896 x N3072 x K12288 254 / 233, 8 bits M4608 x N12288 x K3072 136.3 / 127.4.  A lane of the result has four rows of one column; pairs of fragments share
 // their rows so that it has two neighbouring columns of each (fragment_rows.h), and the epilogue scales, rounds to bf16, transposes through LDS and
 // writes 16 bytes per lane, whole contiguous rows of the wavefront's tile, in or past the caches (store_kind).
 //
-// What bounds the large tiles is power: the chip runs as many operand bytes and multiply-adds a second as its clock lets it, and
-// the clock falls with them.  So the tile that moves the fewest bytes a product wins where its rounds are not too uneven: 256 x 256
+// What bounds the large tiles is power, by the clock, and waits: M4608 x N12288 x K3072 at 4 bits takes 81 to 84 us on a layer's codes and 66 on zeros, and of the former's cycles
+// the matrix pipe is busy for 47 %, at N3072 x K12288 for 53 %, at 8 bits for 68 %.  Operand bytes cost both.  So the tile that moves the fewest bytes a product wins where its rounds are not too uneven: 256 x 256
 // on eight wavefronts with a ring of three stages (150 KB, the compute unit to itself) against two 192 x 192 or 256 x 128 blocks
 // a unit, us: 4 bits M4608 x N3072 x K12288 73.1 / 71.1 -> 60.8, K3072 23.9 / 23.2 -> 20.2, N9216 70.2 / 69.7 -> 66.1; 8 bits
 // M4608 x N3072 x K12288 137.5 / 132.9 -> 126.  (A ring of two: 68.6 -> 80.6.  A 288 x 192 tile fills 256 units exactly at M4608 x N3072,

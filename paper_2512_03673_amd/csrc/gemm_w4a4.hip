@@ -7,9 +7,9 @@
 // fp32 holds exactly, so the fp32 accumulators carry the exact integer result whatever the order of
 // the additions.  The codes arrive from the rotate+quantise kernel already as FP6 (e2m3_layout.h), six
 // bits each, in the register image the MFMA wants: nothing is unpacked or widened here.  (On this
-// chip the int8 path is held back by power, not by issue: the same int8 kernel ran 98 us on all-zero
-// codes and 113-135 us on real ones, and a register-only loop sustains 2.7 POP/s of int8 MFMA against
-// 6.6 POP/s of FP6 MFMA on workload-like data; in 16 x 16 forms 4.2 against 8.6, gemm_tiled.h.)
+// chip the int8 path is held back by power, not by issue: the int8 kernel that the 4-bit layer started with ran 98 us
+// on all-zero codes and 113-135 us on real ones, and a register-only loop of 16 x 16 MFMAs sustains 4.2 POP/s of int8 against
+// 8.6 POP/s of FP6 on workload-like data, of 32 x 32 ones 3.5 against 7.6, gemm_tiled.h.)
 //
 // The operands sit in HBM as 3 KB blocks of 32 rows x 128 codes (an A plane of 32 x 64 bytes and a B plane of
 // 32 x 32 bytes, both XOR-swizzled for the fragment reads), so that a K128 stage of a tile is a list of contiguous
